@@ -1,0 +1,445 @@
+// Convolutions of any channel count on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32): the fp32 models, and
+// the bf16 layers whose channel counts are no multiple of 8 (the bf16 kernels gather 16-byte vectors of 8 channels).
+// Products and sums are fp32, as in the one-thread-per-output kernels, which stay behind CODISTILL_FORCE_SIMPLE and take
+// tensors of 2^31 elements and more.
+//
+//   fprop  y[m][n]  = sum_k im2col(x)[m][k]  * w[n][k]         m = (b,ho,wo), k = (r,s,c)
+//   dgrad  dx[m][c] = sum_k gather(dy)[m][k] * w[n][r][s][c]   m = (b,h,w),   k = (r,s,n)
+//   wgrad  dw[n][k] = sum_m dy[m][n] * im2col(x)[m][k]
+//
+// What bounds them: on these channel counts (3 to a few hundred) the launches are small or bound by the fp32 matrix rate
+// (157 TFLOP/s, a sixteenth of the bf16 one); one thread per output spent its time on one 4-byte load per multiply-add and
+// on 64-bit index divisions.  Here a tile of both operands goes through LDS, each loaded element feeds 16 to 64
+// multiply-adds, and pixels are decoded once per thread.  Measured before and after: a two-block fp32 network on 32 images
+// of 32x32, forward and backward, 2430 -> 389 us; the step of the channel-split Wide-ResNet, batch 96, whose second block
+// reads 20 channels, 62.2 -> 8.75 ms; the two-layer fp32 network's step on 8 images 725 -> 378 us.
+#include "kernels.h"
+
+namespace cd {
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// V consecutive elements as fp32
+template <typename T, int V> struct GenVec;
+template <> struct GenVec<float, 1> {
+  __device__ static void ld(const float* p, float (&v)[1]) { v[0] = *p; }
+};
+template <> struct GenVec<float, 4> {
+  __device__ static void ld(const float* p, float (&v)[4]) {
+    const float4 t = *reinterpret_cast<const float4*>(p);
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+  }
+};
+template <> struct GenVec<bf16_t, 1> {
+  __device__ static void ld(const bf16_t* p, float (&v)[1]) { v[0] = bf16_to_f32(*p); }
+};
+template <> struct GenVec<bf16_t, 4> {
+  __device__ static void ld(const bf16_t* p, float (&v)[4]) {
+    const uint2 t = *reinterpret_cast<const uint2*>(p);
+    v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xffff0000u);
+    v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xffff0000u);
+  }
+};
+
+struct GenArgs {
+  const void* src;   // fprop: x; dgrad: dy; wgrad: x
+  const void* w;     // fprop, dgrad: the filter as stored; wgrad: dy
+  const void* bias;  // fprop, nullable
+  void* out;         // fprop: y; dgrad: dx; wgrad: fp32 [splits][N][K]
+  int M, N, K;       // rows and columns of the output and the contraction (wgrad: rows = Cout, columns = K, contraction M)
+  int H, W, Cin, Ho, Wo, Cout, kh, kw, stride, pad;
+  int relu, accumulate;
+  int m_per_split, ktiles, tiles;   // wgrad
+};
+
+// MODE 0: fprop, MODE 1: dgrad.  Block = 4 waves down the rows, each 16 TM rows x 16 TN columns; 32 contraction elements
+// per step, two LDS buffers, the next step's elements travel in registers while the matrix cores work on this one.  The
+// filter is the MFMA "A" operand, so a lane's four accumulators are four consecutive channels of one pixel.  A lane reads
+// four consecutive k of its row as one 16-byte LDS load and uses them in four successive instructions: instruction j takes
+// k = 4 (lane / 16) + j from both operands.  Rows are 36 floats apart: 16 rows start in 16 different 16-byte bank groups.
+// VEC: channels per load (4 where both channel counts allow it).
+template <typename T, int MODE, int VEC, int TM, int TN>
+__global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
+  constexpr int BM = 64 * TM, BN = 16 * TN, BK = 32, P = BK + 4;
+  constexpr int KV = BK / VEC, RPP = 256 / KV, AP = BM / RPP;       // pixel rows: vectors per row, rows per pass, passes
+  constexpr int FP = MODE == 0 ? (BN + RPP - 1) / RPP : (BK + 256 / (BN / VEC) - 1) / (256 / (BN / VEC));   // filter passes
+  constexpr int CV = BN / VEC, FRPP = 256 / CV;                     // dgrad filter tile: vectors per k row, k rows per pass
+  __shared__ __attribute__((aligned(16))) float As[2][BM * P];
+  __shared__ __attribute__((aligned(16))) float Bs[2][BN * P];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  const T* __restrict__ src = static_cast<const T*>(a.src);
+  const T* __restrict__ wt = static_cast<const T*>(a.w);
+  const int CS = MODE == 0 ? a.Cin : a.Cout, HS = MODE == 0 ? a.H : a.Ho, WS = MODE == 0 ? a.W : a.Wo;
+  const int HD = MODE == 0 ? a.Ho : a.H, WD = MODE == 0 ? a.Wo : a.W;
+
+  const int kv = tid % KV, ar = tid / KV;
+  int pb[AP], ph[AP], pw[AP];   // image base row of the gathered tensor, window origin (a row past M never reads)
+#pragma unroll
+  for (int j = 0; j < AP; j++) {
+    const int m = m0 + ar + j * RPP;
+    const unsigned mm = m < a.M ? (unsigned)m : 0u;
+    const unsigned q = mm / (unsigned)WD;
+    const int x = (int)(mm - q * (unsigned)WD);
+    const unsigned b = q / (unsigned)HD;
+    const int y = (int)(q - b * (unsigned)HD);
+    pb[j] = (int)b * HS;
+    ph[j] = MODE == 0 ? y * a.stride - a.pad : y + a.pad;
+    pw[j] = MODE == 0 ? x * a.stride - a.pad : x + a.pad;
+    if (m >= a.M) ph[j] = -0x10000000;
+  }
+  float ra[AP][VEC], rb[FP][VEC];
+  auto gload = [&](int kt) {
+    {
+      const int k = kt * BK + kv * VEC;
+      const unsigned tap = (unsigned)k / (unsigned)CS;
+      const int c = k - (int)tap * CS, r = (int)(tap / (unsigned)a.kw), s = (int)tap - r * a.kw;
+#pragma unroll
+      for (int j = 0; j < AP; j++) {
+        int h, w;
+        bool ok = k < a.K;
+        if (MODE == 0) {
+          h = ph[j] + r; w = pw[j] + s;
+          ok = ok && h >= 0 && w >= 0;
+        } else {
+          h = ph[j] - r; w = pw[j] - s;
+          ok = ok && h >= 0 && w >= 0;
+          if (a.stride != 1) {
+            const int hq = h / a.stride, wq = w / a.stride;
+            ok = ok && hq * a.stride == h && wq * a.stride == w;
+            h = hq; w = wq;
+          }
+        }
+        ok = ok && h < HS && w < WS;
+#pragma unroll
+        for (int i = 0; i < VEC; i++) ra[j][i] = 0.f;
+        if (ok) GenVec<T, VEC>::ld(src + ((unsigned)((pb[j] + h) * WS + w) * (unsigned)CS + (unsigned)c), ra[j]);
+      }
+    }
+    if (MODE == 0) {   // filter rows are contiguous along k
+      const int k = kt * BK + kv * VEC;
+#pragma unroll
+      for (int j = 0; j < FP; j++) {
+        const int n = ar + j * RPP;
+#pragma unroll
+        for (int i = 0; i < VEC; i++) rb[j][i] = 0.f;
+        if (n < BN && n0 + n < a.N && k < a.K) GenVec<T, VEC>::ld(wt + ((unsigned)(n0 + n) * (unsigned)a.K + (unsigned)k), rb[j]);
+      }
+    } else {           // w[n][r][s][c]: contiguous along the output column c
+      const int c = n0 + (tid % CV) * VEC;
+#pragma unroll
+      for (int j = 0; j < FP; j++) {
+        const int kr = tid / CV + j * FRPP, k = kt * BK + kr;
+        const unsigned tap = (unsigned)k / (unsigned)CS;
+        const int n = k - (int)tap * CS;
+#pragma unroll
+        for (int i = 0; i < VEC; i++) rb[j][i] = 0.f;
+        if (kr < BK && k < a.K && c < a.N)
+          GenVec<T, VEC>::ld(wt + (((unsigned)n * (unsigned)(a.kh * a.kw) + tap) * (unsigned)a.Cin + (unsigned)c), rb[j]);
+      }
+    }
+  };
+  auto lstore = [&](int buf) {
+#pragma unroll
+    for (int j = 0; j < AP; j++)
+#pragma unroll
+      for (int i = 0; i < VEC; i++) As[buf][(ar + j * RPP) * P + kv * VEC + i] = ra[j][i];
+#pragma unroll
+    for (int j = 0; j < FP; j++) {
+      if (MODE == 0) {
+        const int n = ar + j * RPP;
+        if (n < BN) {
+#pragma unroll
+          for (int i = 0; i < VEC; i++) Bs[buf][n * P + kv * VEC + i] = rb[j][i];
+        }
+      } else {
+        const int kr = tid / CV + j * FRPP;
+        if (kr < BK) {
+#pragma unroll
+          for (int i = 0; i < VEC; i++) Bs[buf][((tid % CV) * VEC + i) * P + kr] = rb[j][i];
+        }
+      }
+    }
+  };
+  f32x4_t acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; i++)
+#pragma unroll
+    for (int j = 0; j < TM; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int fr = lane & 15, fk = (lane >> 4) * 4;
+  const int KT = (a.K + BK - 1) / BK;
+  gload(0);
+  lstore(0);
+  __syncthreads();
+  for (int kt = 0; kt < KT; kt++) {
+    const int cur = kt & 1;
+    if (kt + 1 < KT) gload(kt + 1);
+#pragma unroll
+    for (int kc = 0; kc < BK; kc += 16) {
+      f32x4_t f[TN], p[TM];
+#pragma unroll
+      for (int i = 0; i < TN; i++) f[i] = *reinterpret_cast<const f32x4_t*>(&Bs[cur][(i * 16 + fr) * P + kc + fk]);
+#pragma unroll
+      for (int j = 0; j < TM; j++) p[j] = *reinterpret_cast<const f32x4_t*>(&As[cur][((wave * TM + j) * 16 + fr) * P + kc + fk]);
+#pragma unroll
+      for (int q = 0; q < 4; q++)
+#pragma unroll
+        for (int i = 0; i < TN; i++)
+#pragma unroll
+          for (int j = 0; j < TM; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[i][q], p[j][q], acc[i][j], 0, 0, 0);
+    }
+    if (kt + 1 < KT) lstore(cur ^ 1);
+    __syncthreads();
+  }
+  T* __restrict__ out = static_cast<T*>(a.out);
+  const T* __restrict__ bias = static_cast<const T*>(a.bias);
+#pragma unroll
+  for (int j = 0; j < TM; j++) {
+    const int m = m0 + (wave * TM + j) * 16 + fr;
+    if (m >= a.M) continue;
+#pragma unroll
+    for (int i = 0; i < TN; i++) {
+      const int n = n0 + i * 16 + fk;
+      if (n >= a.N) continue;
+      T* o = out + ((unsigned)m * (unsigned)a.N + (unsigned)n);
+      const int nv = a.N - n < 4 ? a.N - n : 4;
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        v[q] = acc[i][j][q];
+        if (q < nv) {
+          if (MODE == 0 && bias) v[q] += Cvt<T>::ld(bias[n + q]);
+          if (MODE == 1 && a.accumulate) v[q] += Cvt<T>::ld(o[q]);
+          if (MODE == 0 && a.relu) v[q] = fmaxf(v[q], 0.f);
+        }
+      }
+      if ((a.N & 3) == 0) {   // four channels of a pixel at a 4-element boundary
+        if (sizeof(T) == 4) {
+          *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+          *reinterpret_cast<uint2*>(o) = make_uint2((uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16),
+                                                    (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16));
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+          if (q < nv) o[q] = Cvt<T>::st(v[q]);
+      }
+    }
+  }
+}
+
+// Weight gradient: the output is small and the contraction (pixels) long, so the four waves of a block take 16 pixels each
+// of a 64-pixel step for the whole 16 TN x 16 TK tile and are added in LDS at the end; the pixel range is split over the
+// grid, partial sums are added in a fixed order by a second kernel.  Tiles lie in LDS as in memory ([pixel][channel]); rows
+// are 16 floats apart modulo 64, so that the four pixels an instruction reads fall into different banks.
+template <typename T, int VEC, int TN, int TK>
+__global__ void __launch_bounds__(256) conv_generic_wgrad_k(GenArgs a) {
+  constexpr int BN = 16 * TN, BKK = 16 * TK, MS = 64;
+  constexpr int PN = TN == 1 ? 16 : BN + 16, PK = TK == 1 ? 16 : BKK + 16;
+  constexpr int NV = BN / VEC, KVN = BKK / VEC;
+  constexpr int DR = 256 / NV, XR = 256 / KVN;              // rows per pass
+  constexpr int DP = (MS + DR - 1) / DR, XP = (MS + XR - 1) / XR;
+  constexpr int TILE = MS * PN + MS * PK, RED = 4 * BN * BKK;
+  __shared__ __attribute__((aligned(16))) float sm[TILE > RED ? TILE : RED];
+  float* Ds = sm;
+  float* Xs = sm + MS * PN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int split = blockIdx.x / (unsigned)a.tiles, tile = blockIdx.x % (unsigned)a.tiles;
+  const int n0 = tile / a.ktiles * BN, k0 = tile % a.ktiles * BKK;
+  const int mbeg = split * a.m_per_split, mend = mbeg + a.m_per_split < a.M ? mbeg + a.m_per_split : a.M;
+  const T* __restrict__ x = static_cast<const T*>(a.src);
+  const T* __restrict__ dy = static_cast<const T*>(a.w);
+  const int dv = tid % NV, dr = tid / NV;
+  const bool dok = n0 + dv * VEC < a.N;
+  const int xv = tid % KVN, xr = tid / KVN;
+  const int k = k0 + xv * VEC;
+  const bool kok = k < a.K;
+  const int tap = kok ? k / a.Cin : 0;
+  const int kc = k - tap * a.Cin, kr = tap / a.kw, ks = tap - kr * a.kw;
+  int pb[XP], ph[XP], pw[XP];
+#pragma unroll
+  for (int j = 0; j < XP; j++) {
+    const unsigned m = (unsigned)(mbeg + xr + j * XR);
+    const unsigned q = m / (unsigned)a.Wo;
+    pw[j] = (int)(m - q * (unsigned)a.Wo);
+    pb[j] = (int)(q / (unsigned)a.Ho);
+    ph[j] = (int)(q - (unsigned)pb[j] * (unsigned)a.Ho);
+  }
+  // one step moves every row MS pixels on: whole images, then whole rows, then columns
+  const int adv_b = MS / (a.Ho * a.Wo), adv_r = MS % (a.Ho * a.Wo), adv_h = adv_r / a.Wo, adv_w = adv_r % a.Wo;
+  float rd[DP][VEC], rx[XP][VEC];
+  auto gload = [&](int ms) {   // ms: first pixel of the step
+#pragma unroll
+    for (int j = 0; j < DP; j++) {
+      const int r = dr + j * DR, m = ms + r;
+#pragma unroll
+      for (int i = 0; i < VEC; i++) rd[j][i] = 0.f;
+      if (dok && r < MS && m < mend) GenVec<T, VEC>::ld(dy + ((unsigned)m * (unsigned)a.N + (unsigned)(n0 + dv * VEC)), rd[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < XP; j++) {
+      const int r = xr + j * XR, m = ms + r;
+      const int h = ph[j] * a.stride - a.pad + kr, w = pw[j] * a.stride - a.pad + ks;
+#pragma unroll
+      for (int i = 0; i < VEC; i++) rx[j][i] = 0.f;
+      if (kok && r < MS && m < mend && (unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W)
+        GenVec<T, VEC>::ld(x + ((unsigned)((pb[j] * a.H + h) * a.W + w) * (unsigned)a.Cin + (unsigned)kc), rx[j]);
+      pw[j] += adv_w;
+      const int cw = pw[j] >= a.Wo ? 1 : 0;
+      pw[j] -= cw ? a.Wo : 0;
+      ph[j] += adv_h + cw;
+      const int ch = ph[j] >= a.Ho ? 1 : 0;
+      ph[j] -= ch ? a.Ho : 0;
+      pb[j] += adv_b + ch;
+    }
+  };
+  f32x4_t acc[TN][TK];
+#pragma unroll
+  for (int i = 0; i < TN; i++)
+#pragma unroll
+    for (int j = 0; j < TK; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int fc = lane & 15, fm = wave * 16 + (lane >> 4);
+  gload(mbeg);
+  for (int ms = mbeg; ms < mend; ms += MS) {
+#pragma unroll
+    for (int j = 0; j < DP; j++)
+      if (dr + j * DR < MS) {
+#pragma unroll
+        for (int i = 0; i < VEC; i++) Ds[(dr + j * DR) * PN + dv * VEC + i] = rd[j][i];
+      }
+#pragma unroll
+    for (int j = 0; j < XP; j++)
+      if (xr + j * XR < MS) {
+#pragma unroll
+        for (int i = 0; i < VEC; i++) Xs[(xr + j * XR) * PK + xv * VEC + i] = rx[j][i];
+      }
+    __syncthreads();
+    if (ms + MS < mend) gload(ms + MS);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      float d[TN], v[TK];
+#pragma unroll
+      for (int i = 0; i < TN; i++) d[i] = Ds[(fm + 4 * q) * PN + i * 16 + fc];
+#pragma unroll
+      for (int j = 0; j < TK; j++) v[j] = Xs[(fm + 4 * q) * PK + j * 16 + fc];
+#pragma unroll
+      for (int i = 0; i < TN; i++)
+#pragma unroll
+        for (int j = 0; j < TK; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[i], v[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+  // the four waves' sums, added in order
+#pragma unroll
+  for (int i = 0; i < TN; i++)
+#pragma unroll
+    for (int j = 0; j < TK; j++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) sm[wave * BN * BKK + (i * 16 + 4 * (lane >> 4) + q) * BKK + j * 16 + fc] = acc[i][j][q];
+  __syncthreads();
+  float* __restrict__ out = static_cast<float*>(a.out) + (int64_t)split * a.N * a.K;
+  for (int e = tid; e < BN * BKK; e += 256) {
+    const int n = n0 + e / BKK, kk = k0 + e % BKK;
+    if (n < a.N && kk < a.K)
+      out[(unsigned)n * (unsigned)a.K + (unsigned)kk] = (sm[e] + sm[BN * BKK + e]) + (sm[2 * BN * BKK + e] + sm[3 * BN * BKK + e]);
+  }
+}
+
+bool conv_generic_supported(const ConvGeom& g) {
+  // 32-bit element offsets; tap positions and window origins far from the ends of the 32-bit range
+  const int64_t lim = 1LL << 31;
+  return g.B * g.H * g.W * (int64_t)g.Cin < lim && g.M() * (int64_t)g.Cout < lim && (int64_t)g.Cout * g.kh * g.kw * g.Cin < lim &&
+         g.B * g.H * g.W < lim - 256 && g.M() < lim - 256 && g.H < (1 << 24) && g.W < (1 << 24) && g.pad >= 0 && g.stride >= 1;
+}
+
+static GenArgs gen_args(const ConvGeom& g) {
+  GenArgs a = {};
+  a.H = g.H; a.W = g.W; a.Cin = g.Cin; a.Ho = g.Ho; a.Wo = g.Wo; a.Cout = g.Cout;
+  a.kh = g.kh; a.kw = g.kw; a.stride = g.stride; a.pad = g.pad;
+  return a;
+}
+
+template <typename T, int MODE, int VEC>
+static void launch_generic(const GenArgs& a, hipStream_t s) {
+  const int tn = a.N <= 16 ? 1 : a.N <= 32 ? 2 : 4;
+  const int64_t nt = cdiv(a.N, 16 * tn);
+  // 128-row tiles once they give every compute unit two workgroups; below that 64-row tiles, twice as many
+  const bool tall = VEC == 4 && cdiv(a.M, 128) * nt >= 512;
+  const dim3 grid((unsigned)cdiv(a.M, tall ? 128 : 64), (unsigned)nt);
+  if (tall) {
+    constexpr int TM = VEC == 4 ? 2 : 1;
+    if (tn == 1) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 1>), grid, dim3(256), 0, s, a);
+    else if (tn == 2) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 2>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 4>), grid, dim3(256), 0, s, a);
+  } else {
+    if (tn == 1) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 1>), grid, dim3(256), 0, s, a);
+    else if (tn == 2) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 2>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 4>), grid, dim3(256), 0, s, a);
+  }
+}
+
+// four channels per load: both channel counts are multiples of 4 and the tensors start on a vector boundary
+static bool gen_vec4(int dtype, const ConvGeom& g, const void* p0, const void* p1) {
+  const uintptr_t mask = dtype == CD_BF16 ? 7 : 15;
+  return g.Cin % 4 == 0 && g.Cout % 4 == 0 && ((reinterpret_cast<uintptr_t>(p0) | reinterpret_cast<uintptr_t>(p1)) & mask) == 0;
+}
+
+void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
+                        hipStream_t s) {
+  GenArgs a = gen_args(g);
+  a.src = x; a.w = w; a.bias = bias; a.out = y; a.relu = relu;
+  a.M = (int)g.M(); a.N = g.Cout; a.K = g.K();
+  const bool v4 = gen_vec4(dtype, g, x, w);
+  if (dtype == CD_BF16) { if (v4) launch_generic<bf16_t, 0, 4>(a, s); else launch_generic<bf16_t, 0, 1>(a, s); }
+  else { if (v4) launch_generic<float, 0, 4>(a, s); else launch_generic<float, 0, 1>(a, s); }
+}
+
+void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, const ConvGeom& g, bool accumulate, hipStream_t s) {
+  GenArgs a = gen_args(g);
+  a.src = dy; a.w = w; a.out = dx; a.accumulate = accumulate;
+  a.M = (int)(g.B * g.H * g.W); a.N = g.Cin; a.K = g.kh * g.kw * g.Cout;
+  const bool v4 = gen_vec4(dtype, g, dy, w);
+  if (dtype == CD_BF16) { if (v4) launch_generic<bf16_t, 1, 4>(a, s); else launch_generic<bf16_t, 1, 1>(a, s); }
+  else { if (v4) launch_generic<float, 1, 4>(a, s); else launch_generic<float, 1, 1>(a, s); }
+}
+
+template <typename T>
+static void wgrad_generic_t(GenArgs a, bool v4, float* dw, float* partials, size_t partials_bytes, hipStream_t s) {
+  const int tn = a.N <= 16 ? 1 : 2, tk = v4 ? (a.K <= 32 ? 2 : 4) : 2;
+  a.ktiles = (int)cdiv(a.K, 16 * tk);
+  const int64_t tiles = cdiv(a.N, 16 * tn) * a.ktiles, nk = (int64_t)a.N * a.K;
+  // three workgroups per compute unit, but at least two 64-pixel steps each (a split costs one fp32 copy of dw)
+  int64_t splits = cdiv(768, tiles);
+  if (splits > cdiv(a.M, 128)) splits = cdiv(a.M, 128);
+  const int64_t by_mem = (int64_t)(partials_bytes / (nk * sizeof(float)));
+  if (splits > by_mem) splits = by_mem;
+  if (splits < 1) splits = 1;
+  a.m_per_split = (int)(cdiv(cdiv(a.M, splits), 64) * 64);
+  splits = cdiv(a.M, a.m_per_split);
+  a.tiles = (int)tiles;
+  a.out = splits == 1 ? dw : partials;
+  const dim3 grid((unsigned)(tiles * splits));
+  if (v4) {
+    if (tn == 1 && tk == 2) hipLaunchKernelGGL((conv_generic_wgrad_k<T, 4, 1, 2>), grid, dim3(256), 0, s, a);
+    else if (tn == 1) hipLaunchKernelGGL((conv_generic_wgrad_k<T, 4, 1, 4>), grid, dim3(256), 0, s, a);
+    else if (tk == 2) hipLaunchKernelGGL((conv_generic_wgrad_k<T, 4, 2, 2>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((conv_generic_wgrad_k<T, 4, 2, 4>), grid, dim3(256), 0, s, a);
+  } else {
+    if (tn == 1) hipLaunchKernelGGL((conv_generic_wgrad_k<T, 1, 1, 2>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((conv_generic_wgrad_k<T, 1, 2, 2>), grid, dim3(256), 0, s, a);
+  }
+  if (splits > 1) sum_splits(partials, dw, nk, (int)splits, s);
+}
+
+void conv_wgrad_generic(int dtype, const void* x, const void* dy, float* dw, const ConvGeom& g, float* partials,
+                        size_t partials_bytes, hipStream_t s) {
+  GenArgs a = gen_args(g);
+  a.src = x; a.w = dy;
+  a.M = (int)g.M(); a.N = g.Cout; a.K = g.K();
+  const bool v4 = gen_vec4(dtype, g, x, dy);
+  if (dtype == CD_BF16) wgrad_generic_t<bf16_t>(a, v4, dw, partials, partials_bytes, s);
+  else wgrad_generic_t<float>(a, v4, dw, partials, partials_bytes, s);
+}
+
+}  // namespace cd

@@ -1228,6 +1228,10 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* __restri
   if (lane == 0 && i < n) out[i] = (sm[0][ol] + sm[1][ol]) + (sm[2][ol] + sm[3][ol]);
 }
 
+void sum_splits(const float* part, float* out, int64_t n, int splits, hipStream_t s) {
+  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)cdiv(n, 64)), dim3(256), 0, s, part, out, n, splits);
+}
+
 // slices > 1: a grouped convolution cut into `slices` slices of g.Cin = g.Cout = SW channels; x and dy are the whole
 // row-major tensors with `pitch` channels per pixel and dw receives the dense per-slice gradients [slices][SW][K].
 static void wgrad_launch(const bf16_t* x, const bf16_t* dy, float* dw, const ConvGeom& g, int slices, int pitch, float* partials,
@@ -1271,8 +1275,7 @@ static void wgrad_launch(const bf16_t* x, const bf16_t* dy, float* dw, const Con
   else if (bk == 128) hipLaunchKernelGGL((wgrad_kernel<64, 128>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((wgrad_kernel<64, 64>), grid, dim3(256), 0, s, a);
   if (splits > 1)
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)cdiv(nk, 64)), dim3(256), 0, s, partials, dw, nk,
-                       (int)splits);
+    sum_splits(partials, dw, nk, (int)splits, s);
 }
 
 void conv_wgrad_mfma(const bf16_t* x, const bf16_t* dy, float* dw, const ConvGeom& g, float* partials,

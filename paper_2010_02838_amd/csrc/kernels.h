@@ -27,6 +27,18 @@ void conv_fprop_simple(int dtype, const void* x, const void* w, const void* bias
 void conv_dgrad_simple(int dtype, const void* dy, const void* w, void* dx, const ConvGeom& g, bool accumulate,
                        hipStream_t s);
 void conv_wgrad_simple(int dtype, const void* x, const void* dy, float* dw, const ConvGeom& g, hipStream_t s);
+// ---- conv_generic.hip: the same convolutions on the fp32 matrix instruction, any channel counts -------------------
+// What runs where the bf16 matrix-core kernels do not (fp32 models, channel counts that are no multiple of 8); the plain
+// kernels above remain for CODISTILL_FORCE_SIMPLE and for tensors of 2^31 elements and more.
+bool conv_generic_supported(const ConvGeom& g);
+void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
+                        hipStream_t s);
+void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, const ConvGeom& g, bool accumulate, hipStream_t s);
+// partials: scratch for the split sums (as many fp32 copies of dw as splits; without room for two the launch is not split)
+void conv_wgrad_generic(int dtype, const void* x, const void* dy, float* dw, const ConvGeom& g, float* partials,
+                        size_t partials_bytes, hipStream_t s);
+// out[i] = sum over j of part[j * n + i], in a fixed order
+void sum_splits(const float* part, float* out, int64_t n, int splits, hipStream_t s);
 void relu_bwd_inplace(int dtype, void* dy, const void* y, int64_t n, hipStream_t s);
 void colsum(int dtype, const void* a, int64_t M, int C, float* out, float* partials, hipStream_t s);
 

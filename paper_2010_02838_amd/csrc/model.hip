@@ -354,6 +354,9 @@ bool use_mfma(const cd_model* m, const ConvGeom& g) {
   return conv_mfma_supported(packed_geom(g));
 }
 
+// What the matrix-core kernels do not take runs on the fp32 matrix instruction
+bool use_generic(const ConvGeom& g) { return !force_simple() && conv_generic_supported(g); }
+
 // Whether a grouped convolution runs as sliced launches on the row-major tensors (conv_grouped_*_mfma): bf16, slices of
 // whole groups, 32-bit offsets; otherwise as dense convolutions on slice-major copies (conv_grouped.hip).
 bool grouped_sliced(const cd_model* m, const Op& o, int64_t batch) {
@@ -891,7 +894,8 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
           stat_tensor = fuse ? o.y : -1;
         } else {
           ProfScope pr(CD_K_CONV_FPROP_NARROW, c.s, 2.0 * g.M() * g.Cout * g.K(), conv_bytes(m, g));
-          conv_fprop_simple(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s);
+          if (use_generic(g)) conv_fprop_generic(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s);
+          else conv_fprop_simple(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s);
         }
         break;
       }
@@ -1300,7 +1304,8 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
             if (s2d_form(g)) s2d_unpack_dw(dw, G(o.pw), g.Cout, g.kh, gp.kh, 2 * gp.pad - g.pad, ws_);
             else if (g.Cin == 3) unpad_c8_to_c3(dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, ws_);
           } else {
-            conv_wgrad_simple(dt, in, dy, G(o.pw), g, c.s);
+            if (use_generic(g)) conv_wgrad_generic(dt, in, dy, G(o.pw), g, wpart, c.plan.partials_bytes, c.s);
+            else conv_wgrad_simple(dt, in, dy, G(o.pw), g, c.s);
           }
         }
         if (o.x != 0) {
@@ -1336,7 +1341,8 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
             if (with_sums) bn_sums[o.x] = chunks;
             if (gate) relu_done[o.x] = 1;
           } else {
-            conv_dgrad_simple(dt, dy, c.P(o.pw), dx, g, acc, c.s);
+            if (use_generic(g)) conv_dgrad_generic(dt, dy, c.P(o.pw), dx, g, acc, c.s);
+            else conv_dgrad_simple(dt, dy, c.P(o.pw), dx, g, acc, c.s);
           }
         }
         break;
