@@ -55,8 +55,9 @@ struct GenArgs {
 // MODE 0: fprop, MODE 1: dgrad.  Block = 4 waves down the rows, each 16 TM rows x 16 TN columns; 32 contraction elements
 // per step, two LDS buffers, the next step's elements travel in registers while the matrix cores work on this one.  The
 // filter is the MFMA "A" operand, so a lane's four accumulators are four consecutive channels of one pixel.  A lane reads
-// four consecutive k of its row as one 16-byte LDS load and uses them in four successive instructions: instruction j takes
-// k = 4 (lane / 16) + j from both operands.  Rows are 36 floats apart: 16 rows start in 16 different 16-byte bank groups.
+// its four k of a 16-element chunk as one 16-byte LDS load; element k of a chunk lies at place 4 (k % 4) + k / 4, so that
+// instruction j takes k = 4 j + lane / 16: the sums run over k in ascending order, tap by tap, as the definition and the
+// plain kernels add them.  Rows are 36 floats apart: 16 rows start in 16 different 16-byte bank groups.
 // VEC: channels per load (4 where both channel counts allow it).
 template <typename T, int MODE, int VEC, int TM, int TN>
 __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
@@ -89,6 +90,7 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
     if (m >= a.M) ph[j] = -0x10000000;
   }
   float ra[AP][VEC], rb[FP][VEC];
+  auto place = [](int k) { return (k & ~15) + 4 * (k & 3) + ((k >> 2) & 3); };
   auto gload = [&](int kt) {
     {
       const int k = kt * BK + kv * VEC;
@@ -143,20 +145,20 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
 #pragma unroll
     for (int j = 0; j < AP; j++)
 #pragma unroll
-      for (int i = 0; i < VEC; i++) As[buf][(ar + j * RPP) * P + kv * VEC + i] = ra[j][i];
+      for (int i = 0; i < VEC; i++) As[buf][(ar + j * RPP) * P + place(kv * VEC + i)] = ra[j][i];
 #pragma unroll
     for (int j = 0; j < FP; j++) {
       if (MODE == 0) {
         const int n = ar + j * RPP;
         if (n < BN) {
 #pragma unroll
-          for (int i = 0; i < VEC; i++) Bs[buf][n * P + kv * VEC + i] = rb[j][i];
+          for (int i = 0; i < VEC; i++) Bs[buf][n * P + place(kv * VEC + i)] = rb[j][i];
         }
       } else {
         const int kr = tid / CV + j * FRPP;
         if (kr < BK) {
 #pragma unroll
-          for (int i = 0; i < VEC; i++) Bs[buf][((tid % CV) * VEC + i) * P + kr] = rb[j][i];
+          for (int i = 0; i < VEC; i++) Bs[buf][((tid % CV) * VEC + i) * P + place(kr)] = rb[j][i];
         }
       }
     }
@@ -167,6 +169,18 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
 #pragma unroll
     for (int j = 0; j < TM; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int fr = lane & 15, fk = (lane >> 4) * 4;
+  const T* __restrict__ bias = static_cast<const T*>(a.bias);
+  if (MODE == 0 && bias) {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const int n = n0 + i * 16 + fk + q;
+        const float bv = n < a.N ? Cvt<T>::ld(bias[n]) : 0.f;
+#pragma unroll
+        for (int j = 0; j < TM; j++) acc[i][j][q] = bv;
+      }
+  }
   const int KT = (a.K + BK - 1) / BK;
   gload(0);
   lstore(0);
@@ -192,7 +206,6 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
     __syncthreads();
   }
   T* __restrict__ out = static_cast<T*>(a.out);
-  const T* __restrict__ bias = static_cast<const T*>(a.bias);
 #pragma unroll
   for (int j = 0; j < TM; j++) {
     const int m = m0 + (wave * TM + j) * 16 + fr;
@@ -208,7 +221,6 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
       for (int q = 0; q < 4; q++) {
         v[q] = acc[i][j][q];
         if (q < nv) {
-          if (MODE == 0 && bias) v[q] += Cvt<T>::ld(bias[n + q]);
           if (MODE == 1 && a.accumulate) v[q] += Cvt<T>::ld(o[q]);
           if (MODE == 0 && a.relu) v[q] = fmaxf(v[q], 0.f);
         }
