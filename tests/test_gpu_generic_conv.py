@@ -20,6 +20,9 @@ SHAPES = {
     # 7x7 stride-2 stem on odd images, 1x1 filters with and without stride
     "bottleneck": (dict(kind=2, widths=[6, 12], blocks=[1, 1], stem_width=20),
                    lambda: nets.resnet50(classes=10, widths=(6, 12), blocks=(1, 1), stem=20), 5, 37),
+    # 4100 channels into the average pool: more vectors than one block takes
+    "many_channels": (dict(kind=2, widths=[1025], blocks=[1], stem_width=4),
+                      lambda: nets.resnet50(classes=10, widths=(1025,), blocks=(1,), stem=4), 2, 16),
 }
 
 
