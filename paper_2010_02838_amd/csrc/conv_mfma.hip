@@ -21,7 +21,7 @@ namespace cd {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int BK = 32;  // contraction elements per main-loop step (one 64-byte LDS row)
+constexpr int BK = 32;  // contraction elements per main-loop step of the kernels for short contractions or few channels
 
 struct IgemmArgs {
   const bf16_t* src;  // gathered tensor [B][Hs][Ws][Cs]
@@ -135,10 +135,22 @@ __device__ inline void wait_vmem() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// LDS tiles are [row][32 elements] = 64-byte rows without padding; the 16-byte column cv of a row
-// is stored at column cv ^ ((row >> 2) & 3), which makes both the 16-byte stores (4 lanes per row)
-// and the MFMA fragment reads (16 consecutive rows, one column) bank-conflict free.
-__device__ inline int lds_off(int row, int cv) { return row * BK + ((cv ^ ((row >> 2) & 3)) << 3); }
+// the same, and until this wave's LDS reads are done; then the workgroup's barrier.  (Builtins, so that the compiler's own
+// count of outstanding LDS reads starts from zero behind it; the empty statements keep memory accesses on their side.)
+template <int N>
+__device__ inline void wait_step() {
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));   // vmcnt(N) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" : : : "memory");
+}
+
+// LDS tiles are [row][BKT elements], rows of 64 (BKT = 32) or 128 bytes without padding; the 16-byte column cv of a row
+// is stored at column cv ^ swz(row), which makes both the 16-byte stores (in lane order) and the MFMA fragment reads (16
+// consecutive rows, one column) bank-conflict free.  A thread's rows are a multiple of 32 apart and share their swz.
+template <int BKT> __device__ inline int lds_swz(int row) { return BKT == 32 ? (row >> 2) & 3 : (row >> 1) & 7; }
+template <int BKT> __device__ inline int lds_off(int row, int cv) { return row * BKT + ((cv ^ lds_swz<BKT>(row)) << 3); }
 
 // MODE 0: fprop gather, hs = hd*stride - pad + r.
 // MODE 1: dgrad gather for stride 1, hs = hd + pad - r.
@@ -162,24 +174,25 @@ __device__ inline int lds_off(int row, int cv) { return row * BK + ((cv ^ ((row 
 // EPI: 0 plain output, 1 per-column bias added, 2 bias and ReLU.  GROUP: grouped tile order (wide outputs).
 // Both are compile-time: the plain kernels pay nothing for them.
 template <int MODE, int BM, int BN, int WAVES_M, int WAVES_N, bool F32OUT = false, int STATS = 0, int NWRAP = 1,
-          bool REMAP = false, int EPI = 0, bool GROUP = false>
-__global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32) >= 8 ? 2 : 1)) igemm_kernel(IgemmArgs a) {
-  // (tiles whose accumulators take 128 registers: two waves per SIMD, i.e. two workgroups per compute unit, is what their
-  // LDS allows; the bound keeps the other registers within the 128 that leaves)
+          bool REMAP = false, int EPI = 0, bool GROUP = false, int BKT = 32, int NS = 3>
+__global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32) >= 8 ? 2 : BM == 128 && BN == 128 && NS == 3 ? 3 : 1)) igemm_kernel(IgemmArgs a) {
+  // (as many waves per SIMD, i.e. workgroups per compute unit, as the LDS allows: two for the tiles whose accumulators take 128
+  // registers, three for 128x128 tiles in three 32-wide stages; the bound keeps the other registers within what that leaves)
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int AV = BM / 64;                  // activation vectors per thread per step
-  constexpr int BV = BN >= 64 ? BN / 64 : 1;   // filter vectors per thread per step
-  constexpr int BN_PAD = BN < 64 ? 64 : BN;    // filter rows in LDS (a full 64-row store pass)
-  constexpr int NS = 3;                        // LDS stages: tile kt multiplies, kt+1 and kt+2 are in flight
-  constexpr int STAGE = (BM + BN_PAD) * BK;    // elements per stage: activation rows, then filter rows
+  constexpr int SL = BKT / 8, RPP_L = 256 / SL;  // 16-byte slots per LDS row, rows per load pass of the block
+  constexpr int AV = BM / RPP_L;                // activation vectors per thread per step
+  constexpr int BN_PAD = BN < RPP_L ? RPP_L : BN;   // filter rows in LDS (whole load passes)
+  constexpr int BV = BN_PAD / RPP_L;            // filter vectors per thread per step
+  constexpr int STAGE = (BM + BN_PAD) * BKT;    // elements per stage: activation rows, then filter rows
+  static_assert(BKT == 32 || (BKT == 64 && NWRAP == 1), "64-wide steps need at least 64 channels per tap");
   constexpr int MAIN_BYTES = NS * STAGE * 2;
   constexpr int EROWS = WM < 64 ? WM : 64;     // rows staged per epilogue pass
   constexpr int EPITCH = WN + 8;
   constexpr int EPI_BYTES = 4 * EROWS * EPITCH * 2;
   constexpr int SMEM = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
   __shared__ __attribute__((aligned(16))) char smem[SMEM];
-  bf16_t* tiles = reinterpret_cast<bf16_t*>(smem);  // [NS][BM + BN_PAD][BK]
+  // smem: [NS stages][BM + BN_PAD rows][BKT elements], later the epilogue's staging rows
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave % WAVES_M) * WM, wn0 = (wave / WAVES_M) * WN;
@@ -204,18 +217,18 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   const rsrc_words_t rwt = make_rsrc_words(a.wt, a.wt_bytes);
 
   // ---- per-thread gather state ---------------------------------------------------------------------
-  // A wave's load instruction fills 16 consecutive tile rows (64 lanes x 16 bytes, in lane order), so
-  // thread tid owns LDS slot tid & 3 of rows (tid >> 2) + 64 j; the slot holds the 16-byte column
-  // slot ^ ((row >> 2) & 3) of the tile (see lds_off), the same for all of the thread's rows.
-  const int lrow = tid >> 2;
-  const int kvec = (tid & 3) ^ ((tid >> 4) & 3);
+  // A wave's load instruction fills 64 / SL consecutive tile rows (64 lanes x 16 bytes, in lane order), so thread tid owns
+  // LDS slot tid % SL of rows tid / SL + RPP_L j; the slot holds the 16-byte column slot ^ swz(row) of the tile (see
+  // lds_off), the same for all of the thread's rows.
+  const int lrow = tid / SL;
+  const int kvec = (tid % SL) ^ lds_swz<BKT>(lrow);
   const int P = a.src_pitch ? a.src_pitch : a.Cs;   // channels per pixel of the gathered tensor
   const int cs0 = a.sliced ? n0 : 0;                // first channel this tile gathers (sliced launches)
   int rowoff[AV];                 // element offset of (image, h0, w0, first gathered channel); may be negative
   uint32_t hmask[AV], wmask[AV];  // bit r / s set: tap row r / column s reads inside the image
 #pragma unroll
   for (int j = 0; j < AV; j++) {
-    const int m = m0 + lrow + 64 * j;
+    const int m = m0 + lrow + RPP_L * j;
     const bool rowok = m < M;
     if (a.pointwise) {  // 1x1 filter, stride 1, no padding: row m of the gathered tensor, every tap inside
       hmask[j] = rowok ? 1u : 0u;
@@ -243,11 +256,13 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
     wmask[j] = wm;
     rowoff[j] = ((b * a.Hs + hh) * a.Ws + ww) * P + cs0;
   }
-  uint32_t woff[BV];  // byte offset of this thread's filter row (+ its 16-byte column), ~0 if masked
+  // byte offset of this thread's filter row (+ its 16-byte column); rows past N start beyond every buffer's end (operands
+  // are smaller than 2 GiB), so their loads give zeros at every step
+  uint32_t woff[BV];
 #pragma unroll
   for (int j = 0; j < BV; j++) {
-    const int n = n0 + lrow + 64 * j;
-    woff[j] = ((lrow + 64 * j) < BN && n < a.N) ? (uint32_t)(n * a.K + kvec * 8) * 2u : 0xffffffffu;
+    const int n = n0 + lrow + RPP_L * j;
+    woff[j] = ((lrow + RPP_L * j) < BN && n < a.N) ? (uint32_t)(n * a.K + kvec * 8) * 2u : 0x80000000u;
   }
   // position of this thread's vector in the contraction: tap (kr, ks) and channel kc
   int kc = kvec * 8, kr = 0, ks = 0;
@@ -257,66 +272,94 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
     kr = tap / a.kw;
     ks = tap - kr * a.kw;
   }
-  const int KT = (a.K + BK - 1) / BK;
+  const int KT = (a.K + BKT - 1) / BKT;
   const int tapdir = MODE == 0 ? 1 : -1;
 
-  // LDS byte address of this wave's first 16 rows of the stage-0 activation tile
-  const uint32_t lds_wave = (uint32_t)(uintptr_t)(CD_LDS char*)smem +
-                            (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6) * (16u * BK * 2u);
-  // Issues the loads of one step into the stage at byte offset stage_b.  Always issues them (a step at
-  // or beyond the end of the contraction has every vector masked, costs no memory traffic and writes
-  // zeros), so that the number of loads in flight is the same at every step, and is straight-line code.
-  auto gload = [&](uint32_t stage_b, int kt) {
-    const uint32_t kokb = kr < a.kh ? 1u : 0u;
-    const int koff = tapdir * (kr * a.Ws + ks) * P + kc;
-    const uint32_t krs = (uint32_t)kr & 31u, kss = (uint32_t)ks & 31u;
+  // LDS byte address of this wave's first rows (1024 bytes a load) of the stage-0 activation tile
+  const uint32_t lds_wave = (uint32_t)(uintptr_t)(CD_LDS char*)smem + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6) * 1024u;
+  // The byte offsets of one step's vectors (masked ones beyond the buffer), then the state of the step after it.  A step at
+  // or beyond the end of the contraction has every vector masked: its loads cost no memory traffic and write zeros, so the
+  // number of loads in flight is the same at every step.
+  uint32_t offa[AV], offb[BV];
+  constexpr int NPIECE = AV + BV + 1;
+  // piece p of the preparation of step kt: one vector's offset, or (last) the step to the next position.  Straight-line code
+  // (it sits between the MFMAs): koff, the element offset of the thread's tap and channel, is carried along, masks are or-ed in.
+  int koff = tapdir * (kr * a.Ws + ks) * P + kc;
+  const int koff_tap = tapdir * P - a.Cs, koff_row = tapdir * (a.Ws - a.kw) * P;
+  uint32_t kend = kr < a.kh ? 0u : 0xffffffffu;   // all ones beyond the end of the contraction
+  auto prep_piece = [&](int kt, int p) {
+    if (p < AV) {
+      const uint32_t okb = (hmask[p] >> ((uint32_t)kr & 31u)) & (wmask[p] >> ((uint32_t)ks & 31u)) & 1u;
+      offa[p] = ((uint32_t)(rowoff[p] + koff) * 2u) | (okb - 1u) | kend;
+    } else if (p < AV + BV) {
+      offb[p - AV] = (woff[p - AV] + (uint32_t)kt * (BKT * 2u)) | kend;
+    } else {   // NWRAP sub-steps, each crossing at most one tap boundary
 #pragma unroll
-    for (int j = 0; j < AV; j++) {
-      const uint32_t okb = (hmask[j] >> krs) & (wmask[j] >> kss) & kokb;
-      const uint32_t off = (uint32_t)(rowoff[j] + koff) * 2u;
-      load_lds16(rsrc, lds_wave + stage_b + (uint32_t)j * (64u * BK * 2u), okb ? off : 0xffffffffu);
-    }
-    const uint32_t wk = (uint32_t)kt * (BK * 2u);
-#pragma unroll
-    for (int j = 0; j < BV; j++) {
-      const uint32_t off = woff[j] + wk;
-      load_lds16(rwt, lds_wave + stage_b + (uint32_t)(BM + j * 64) * (BK * 2u),
-                 ((kokb != 0u) & (woff[j] != 0xffffffffu)) ? off : 0xffffffffu);
-    }
-    // advance to the next step: NWRAP sub-steps, each crossing at most one tap boundary
-#pragma unroll
-    for (int u = 0; u < NWRAP; u++) {
-      kc += BK / NWRAP;
-      const bool wrap = kc >= a.Cs;
-      kc -= wrap ? a.Cs : 0;
-      ks += wrap ? 1 : 0;
-      const bool wrap2 = ks == a.kw;
-      ks = wrap2 ? 0 : ks;
-      kr += wrap2 ? 1 : 0;
+      for (int u = 0; u < NWRAP; u++) {
+        kc += BKT / NWRAP;
+        koff += BKT / NWRAP;
+        const bool wrap = kc >= a.Cs;
+        kc -= wrap ? a.Cs : 0;
+        koff += wrap ? koff_tap : 0;
+        ks += wrap ? 1 : 0;
+        const bool wrap2 = ks == a.kw;
+        ks = wrap2 ? 0 : ks;
+        koff += wrap2 ? koff_row : 0;
+        kr += wrap2 ? 1 : 0;
+      }
+      kend = kr < a.kh ? 0u : 0xffffffffu;
     }
   };
+  // issues prepared load v (activation vectors, then filter vectors) into the stage at byte offset stage_b
+  auto issue = [&](uint32_t stage_b, int v) {
+    if (v < AV) load_lds16(rsrc, lds_wave + stage_b + (uint32_t)v * (RPP_L * BKT * 2u), offa[v]);
+    else load_lds16(rwt, lds_wave + stage_b + (uint32_t)(BM + (v - AV) * RPP_L) * (BKT * 2u), offb[v - AV]);
+  };
 
-  // STATS 2: what the epilogue reads besides the tile itself (the BatchNorm's input and its ReLU bits at this lane's
-  // output vectors) is requested now and arrives during the main loop.  (Vector memory operations retire in order:
-  // the main loop's first wait also waits for these, and the compiler's own waits for them can only be too strict.)
+  // STATS 2: what the epilogue reads besides the tile itself.  The BatchNorm's input at this lane's output vectors is requested
+  // now and arrives during the main loop (vector memory operations retire in order: the main loop's first wait also waits for
+  // these, and the compiler's own waits for them can only be too strict); its ReLU bits, a byte per vector, follow behind the
+  // loop: sixteen registers through the loop would spill (128x256) or cost the third workgroup per compute unit (128x128).
   constexpr int BS_LPR = WN / 8, BS_RPP = 64 / BS_LPR, BS_EROWS = WM < 64 ? WM : 64;
   constexpr int BS_NV = STATS == 2 ? (WM / BS_EROWS) * (BS_EROWS / BS_RPP) : 1;
   uint4 bs_x[BS_NV];
   uint32_t bs_bits[BS_NV];
+  auto bs_index = [&](int v, bool& ok) {   // element index of vector v in an [M][N] tensor
+    const int pass = v / (BS_EROWS / BS_RPP), pp = v % (BS_EROWS / BS_RPP);
+    const int m = m0 + wm0 + pass * BS_EROWS + pp * BS_RPP + lane / BS_LPR, n = n0 + wn0 + (lane % BS_LPR) * 8;
+    ok = m < M && n < a.N;
+    return (unsigned)m * (unsigned)a.N + (unsigned)n;
+  };
   if (STATS == 2) {
-    const int er_ = lane / BS_LPR, n = n0 + wn0 + (lane % BS_LPR) * 8;
 #pragma unroll
     for (int v = 0; v < BS_NV; v++) {
-      const int pass = v / (BS_EROWS / BS_RPP), pp = v % (BS_EROWS / BS_RPP);
-      const int m = m0 + wm0 + pass * BS_EROWS + pp * BS_RPP + er_;
+      bool ok;
+      const unsigned idx = bs_index(v, ok);
       bs_x[v] = make_uint4(0, 0, 0, 0);
-      bs_bits[v] = 0u;
-      if (m < M && n < a.N) {
-        const unsigned idx = (unsigned)m * (unsigned)a.N + (unsigned)n;
-        bs_x[v] = *reinterpret_cast<const uint4*>(a.bn_x + idx);
-        bs_bits[v] = a.bn_mask ? a.bn_mask[idx >> 3] : 0xffu;
-      }
+      if (ok) bs_x[v] = *reinterpret_cast<const uint4*>(a.bn_x + idx);
     }
+  }
+  // EPI: the bias of this lane's channels, requested here so that its latency passes under the main loop (read behind it, element
+  // by element, it cost 3 us a tile: 8192 x 2048 x 512 26 us, now 23).  Register v of tile i belongs to channel
+  // n0 + wn0 + 32 i + 8 (v / 4) + 4 (lane / 32) + v % 4: four consecutive channels at a time, on 8-byte boundaries.
+  uint2 bias4[EPI >= 1 ? TN : 1][4];
+  if (EPI >= 1) {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const int n = n0 + wn0 + i * 32 + 8 * g + 4 * (lane >> 5);
+        bias4[i][g] = make_uint2(0u, 0u);
+        if (n + 3 < a.N) {
+          bias4[i][g] = *reinterpret_cast<const uint2*>(a.bias + n);
+        } else {   // the last columns of an output whose width is no multiple of four
+          uint32_t e[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int q = 0; q < 4; q++)
+            if (n + q < a.N) e[q] = a.bias[n + q];
+          bias4[i][g] = make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16));
+        }
+      }
   }
   f32x16_t acc[TN][TM];
 #pragma unroll
@@ -327,55 +370,90 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
 
   const int frow = lane & 31, fcv = lane >> 5;
-  bf16x8_t wf[2][TN], xf[2][TM];  // [k16 half][tile]
-  auto read_frags = [&](uint32_t stage_e) {
+  // Main loop: NS stages rotate, tile kt lies in stage kt % NS.  A step is KK sub-steps of 16; the fragments of the next
+  // sub-step are read from LDS while the matrix cores work on the current one, across the step boundary too: before the
+  // last sub-step of tile kt the waves wait for their own loads of tile kt+1 (all but the newest NS - 2 tiles') and for
+  // their LDS reads of tile kt, and meet at the step's only barrier, which publishes tile kt+1 and frees the stage of tile
+  // kt; the loads of tile kt+NS go there.  Their offsets were computed in the shadow of the earlier sub-steps' MFMAs.
+  // (Not for the 128-accumulator tiles that also hold the backward sums' operands through the loop: no registers are left for
+  // a second fragment buffer, they read a sub-step's fragments and use them.)
+  constexpr bool AHEAD = !(STATS == 2 && TN * TM >= 8);
+  constexpr int KK = BKT / 16, TT = TN * TM, FB = AHEAD ? 2 : 1;
+  bf16x8_t wf[FB][TN], xf[FB][TM];  // [buffer][tile]
+  // byte offset of this lane's fragment of sub-step kk inside a tile row block (swz depends on the lane's row only: tile
+  // rows are multiples of 32 apart)
+  uint32_t fcol[KK];
 #pragma unroll
-    for (int kk = 0; kk < 2; kk++) {
+  for (int kk = 0; kk < KK; kk++) fcol[kk] = (uint32_t)(frow * BKT + (((kk * 2 + fcv) ^ lds_swz<BKT>(frow)) << 3)) * 2u;
+  const uint32_t xbase = (uint32_t)(wm0 * BKT) * 2u, wbase = (uint32_t)((BM + wn0) * BKT) * 2u;
+  auto read_frags = [&](int buf, uint32_t stage_b, int kk) {
+    const char* xp = smem + (stage_b + xbase + fcol[kk]);
+    const char* wp = smem + (stage_b + wbase + fcol[kk]);
 #pragma unroll
-      for (int i = 0; i < TN; i++)
-        wf[kk][i] = *reinterpret_cast<const bf16x8_t*>(tiles + stage_e + BM * BK + lds_off(wn0 + i * 32 + frow, kk * 2 + fcv));
+    for (int i = 0; i < TN; i++) wf[buf][i] = *reinterpret_cast<const bf16x8_t*>(wp + i * 32 * BKT * 2);
 #pragma unroll
-      for (int j = 0; j < TM; j++)
-        xf[kk][j] = *reinterpret_cast<const bf16x8_t*>(tiles + stage_e + lds_off(wm0 + j * 32 + frow, kk * 2 + fcv));
-    }
+    for (int j = 0; j < TM; j++) xf[buf][j] = *reinterpret_cast<const bf16x8_t*>(xp + j * 32 * BKT * 2);
   };
-  auto mfma_step = [&]() {
+  uint32_t cur = 0, nxt = STAGE * 2u;  // byte offsets
 #pragma unroll
-    for (int kk = 0; kk < 2; kk++)
+  for (int t = 0; t < NS; t++) {
 #pragma unroll
-      for (int i = 0; i < TN; i++)
+    for (int p = 0; p < NPIECE; p++) prep_piece(t, p);
 #pragma unroll
-        for (int j = 0; j < TM; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk][i], xf[kk][j], acc[i][j], 0, 0, 0);
-  };
-  // Three stages rotate: at step kt the stage `cur` holds tile kt, `nxt` receives tile kt+1 (loads issued
-  // one step ago) and `fre` (read last at step kt-1) receives tile kt+2.  One barrier per step: it
-  // publishes tile kt (every wave has waited for its own loads of it) and retires the reads of tile kt-1.
-  uint32_t cur = 0, nxt = STAGE, fre = 2 * STAGE;  // element offsets
-  gload(cur * 2u, 0);
-  gload(nxt * 2u, 1);
+    for (int v = 0; v < AV + BV; v++) issue(t * STAGE * 2u, v);
+  }
+  wait_step<(NS - 1) * (AV + BV)>();
+  if (AHEAD) read_frags(0, cur, 0);
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));   // lgkmcnt(0): with the scalar loads, so that none is waited for inside
   for (int kt = 0; kt < KT; kt++) {
-    wait_vmem<AV + BV>();   // all but the newest step's loads have landed
-    __syncthreads();
-    gload(fre * 2u, kt + 2);
-    read_frags(cur);
-    mfma_step();
-    const uint32_t t = cur; cur = nxt; nxt = fre; fre = t;
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++) {
+      if (!AHEAD) read_frags(0, cur, kk);
+      if (kk == KK - 1) wait_step<(NS - 2) * (AV + BV)>();
+      if (AHEAD) read_frags((kk + 1) & (FB - 1), kk == KK - 1 ? nxt : cur, (kk + 1) % KK);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < TT; i++) {
+        acc[i / TM][i % TM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & (FB - 1)][i / TM], xf[kk & (FB - 1)][i % TM],
+                                                                      acc[i / TM][i % TM], 0, 0, 0);
+        // in the MFMA's shadow: a share of the next offsets, in the last sub-step of the loads
+        if (kk < KK - 1) {
+          constexpr int SLOTS = (KK - 1) * TT;
+          const int slot = kk * TT + i;
+#pragma unroll
+          for (int p = 0; p < NPIECE; p++)
+            if (p * SLOTS / NPIECE == slot) prep_piece(kt + NS, p);
+        } else {
+#pragma unroll
+          for (int v = 0; v < AV + BV; v++)
+            if (v * TT / (AV + BV) == i) issue(cur, v);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    cur = nxt;
+    nxt = nxt + STAGE * 2u == NS * STAGE * 2u ? 0 : nxt + STAGE * 2u;
+  }
+  if (STATS == 2) {
+#pragma unroll
+    for (int v = 0; v < BS_NV; v++) {
+      bool ok;
+      const unsigned idx = bs_index(v, ok);
+      bs_bits[v] = 0u;
+      if (ok) bs_bits[v] = a.bn_mask ? a.bn_mask[idx >> 3] : 0xffu;
+    }
   }
   wait_vmem<0>();  // the masked loads past the end still write (zeros) into the stages the epilogue reuses
 
   // accumulator layout: lane holds pixel column (lane % 32); register v holds channel
   // 8*(v/4) + 4*(lane/32) + v%4 of the 32x32 tile
-  // per-column bias: register v of tile i belongs to channel n0 + wn0 + 32 i + 8 (v / 4) + 4 (lane / 32) + v % 4
   if (EPI >= 1) {
 #pragma unroll
     for (int i = 0; i < TN; i++)
 #pragma unroll
       for (int g = 0; g < 4; g++) {
-        const int n = n0 + wn0 + i * 32 + 8 * g + 4 * (lane >> 5);
-        float bv[4];
-#pragma unroll
-        for (int q = 0; q < 4; q++) bv[q] = n + q < a.N ? bf16_to_f32(a.bias[n + q]) : 0.f;
+        const float bv[4] = {__uint_as_float(bias4[i][g].x << 16), __uint_as_float(bias4[i][g].x & 0xffff0000u),
+                             __uint_as_float(bias4[i][g].y << 16), __uint_as_float(bias4[i][g].y & 0xffff0000u)};
 #pragma unroll
         for (int j = 0; j < TM; j++)
 #pragma unroll
@@ -593,78 +671,100 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   }
 }
 
-// Output tile of the wide-output kernels (N > 64): 128x128 (three workgroups per compute unit, 768 at a
-// time), 256x128 or 128x256 (two per compute unit, 512 at a time).  Measured on the layer shapes of
-// ResNet-50 at batch 256:
-//  - a short contraction leaves a tile little more than its prologue and epilogue, and the larger
-//    tiles halve those per output element: 128x256, which also reads the activations once per 256
-//    columns and stores 512-byte row segments, wins up to K = 1024; with very short contractions
-//    onto many columns (K <= 128, N >= 512) 256x128 wins instead;
-//  - otherwise the taller tile pays only when its last round of workgroups is clearly fuller.
-enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2 };
-static int igemm_tile(int64_t M, int N, int K) {
+// Output tile of the wide-output kernels (N > 64), and how their main loop is fed.
+//
+// What a workgroup's step costs (128x128 tile, 64 contraction elements, cycles at 2.4 GHz; 16 MFMAs a wave take 620 alone): the loads
+// from L2 into LDS move 31 B per cycle and compute unit in 64-byte row segments and 52 in 128-byte ones (a line at a time is
+// looked up), so 64-wide steps feed the matrix cores where 32-wide ones cannot: 530 against 315 cycles per 16 KB.  A
+// workgroup alone on its compute unit takes 1200 cycles a step, two together 860 each.
+//  - one workgroup per compute unit or less (at most 256): four stages of 64-wide steps (128 KB), loads three steps ahead;
+//  - otherwise two stages (64 KB, two workgroups per unit);
+//  - many tiles of a short contraction (more than 1024, K <= 512) live on their prologues and epilogues overlapping: three
+//    workgroups per unit with 32-wide steps (200704 x 128 x 512: 45 us, 51 with two).
+// Before (32-wide steps in three stages for all, fragments read and used in the same step; random operands): 12544 x 512 x
+// 4608 76 -> 67 us, 6144 x 640 x 5760 63 -> 52, 8192 x 512 x 2048 28 -> 23, 200704 x 128 x 1152 83 -> 76; the large layers of
+// ResNet-50 at batch 256 are bound by memory and by the clock under full matrix load and gain 1 to 3 %.
+//
+// Tiles, measured with random operands that come from memory (constant ones leave the matrix cores a higher clock), on the
+// layer shapes of ResNet-50 at batch 256 and 50, Wide-ResNet at 96 and the Transformer (us):
+//  - more than 256 tiles of 128x128: 128x256 up to K = 1024 (a short contraction leaves a tile little more than its
+//    prologue and epilogue; 200704 x 512 x 128 93 -> 81, 50176 x 256 x 1024 50 -> 46, 8192 x 1536 x 512 28 -> 25; 12544 x 512 x
+//    2048 42 either way), 256x128 where its rounds of 512 workgroups are no emptier (50176 x 256 x 2304 80 -> 76: the clock
+//    follows the power, and a larger tile moves fewer bytes per product);
+//  - where 128x128 tiles do not fill the 256 compute units, or fill them unevenly, 128x64 and 64x64 tiles do: the cost of
+//    a tile shape is the number of workgroups on the busiest unit times what one costs there (128x64 0.7 of a 128x128
+//    one, 64x64 half), but no less than what one takes alone (1.4, 1.08 and 0.75): 2450 x 512 x 4608 (80 tiles of 128x128)
+//    49 -> 26 on 312 of 64x64, 24576 x 320 x 2880 74 -> 66 on 128x64 (five columns of 64 instead of three of 128).
+enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2, TILE_NARROW = 3, TILE_SMALL = 4 };
+static int igemm_tile(int64_t M, int N, int K, bool small_tiles) {
   if (N <= 64) return TILE_SQUARE;
   if (g_tune_tile == 2) return TILE_SQUARE;
   if (g_tune_tile == 3) return TILE_TALL;
   if (g_tune_tile == 4) return N % 256 == 0 ? TILE_WIDE : TILE_SQUARE;
-  if (K <= 128 && N >= 512) return TILE_TALL;
-  if (N % 256 == 0 && K <= 1024) return TILE_WIDE;
-  const int64_t t128 = cdiv(M, 128) * cdiv(N, 128), t256 = cdiv(M, 256) * cdiv(N, 128);
-  const double e128 = (double)t128 / (double)(cdiv(t128, 768) * 768), e256 = (double)t256 / (double)(cdiv(t256, 512) * 512);
-  return e256 > 1.2 * e128 ? TILE_TALL : TILE_SQUARE;
+  if (g_tune_tile == 5) return TILE_NARROW;
+  if (g_tune_tile == 6) return TILE_SMALL;
+  const int64_t t128 = cdiv(M, 128) * cdiv(N, 128);
+  if (t128 > 256 && N % 256 == 0 && K <= 1024) return TILE_WIDE;
+  const double square = std::max(1.4, (double)cdiv(t128, 256));
+  double narrow = 1e30, small = 1e30;
+  if (small_tiles) {   // (their kernels take 64-wide steps)
+    narrow = std::max(1.08, (K <= 1024 ? 0.68 : 0.72) * (double)cdiv(cdiv(M, 128) * cdiv(N, 64), 256));
+    small = std::max(0.75, 0.5 * (double)cdiv(cdiv(M, 64) * cdiv(N, 64), 256));
+  }
+  if (t128 > 256) {
+    if (narrow < 0.97 * square) return TILE_NARROW;
+    const int64_t t256 = cdiv(M, 256) * cdiv(N, 128);
+    const double e128 = (double)t128 / (double)(cdiv(t128, 512) * 512), e256 = (double)t256 / (double)(cdiv(t256, 512) * 512);
+    return t128 > 512 && e256 >= e128 ? TILE_TALL : TILE_SQUARE;
+  }
+  return small < narrow && small < square ? TILE_SMALL : narrow < square ? TILE_NARROW : TILE_SQUARE;
 }
 int conv_fprop_tile_class(const ConvGeom& g, bool bias) {
+  (void)bias;
   if (g.Cout <= 64) return 2;
-  if (g.Cin < BK || bias) return 0;
-  const int t = igemm_tile(g.M(), g.Cout, (int)g.K());
+  if (g.Cin < BK) return 0;
+  const int t = igemm_tile(g.M(), g.Cout, (int)g.K(), g.Cin >= 64);
   return t == TILE_SQUARE ? 0 : (t == TILE_WIDE ? 1 : 2);
 }
 
-// returns the number of m-tiles (= statistics chunks when STATS)
+template <int MODE, int BM, int BN, int WM, int WN, int STATS, int NWRAP, bool REMAP, int EPI, int BKT, int NS>
+static int launch_tile(IgemmArgs& a, hipStream_t s) {
+  a.ntiles = (int)cdiv(a.N, BN);
+  const int mt = (int)cdiv(a.M, BM);
+  hipLaunchKernelGGL((igemm_kernel<MODE, BM, BN, WM, WN, false, STATS, NWRAP, REMAP, EPI, false, BKT, NS>),
+                     dim3((unsigned)((int64_t)mt * a.ntiles)), dim3(256), 0, s, a);
+  return mt;
+}
+
+// returns the number of m-tiles (= statistics chunks when STATS; 64-row tiles occur below 256 tiles of 128x128 only, so that
+// there are never more than cdiv(M, 128) + 257 chunks)
 template <int MODE, int STATS, int NWRAP, bool REMAP, int EPI>
 static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
   a.pointwise = (a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.pad_w == 0 && a.Hs == a.Hd &&
                  a.Ws == a.Wd) ? 1 : 0;
   a.group_m = 1;
-  const int tile = (NWRAP == 1 && !REMAP && EPI == 0 && !a.sliced) ? igemm_tile(a.M, a.N, a.K) : TILE_SQUARE;
-  if (tile == TILE_TALL) {
-    a.ntiles = (int)cdiv(a.N, 128);
-    const int mt = (int)cdiv(a.M, 256);
-    hipLaunchKernelGGL((igemm_kernel<MODE, 256, 128, 2, 2, false, STATS, 1, false>),
-                       dim3((unsigned)((int64_t)mt * a.ntiles)), dim3(256), 0, s, a);
-    return mt;
-  }
-  if (tile == TILE_WIDE) {
-    a.ntiles = a.N / 256;
-    const int mt = (int)cdiv(a.M, 128);
-    hipLaunchKernelGGL((igemm_kernel<MODE, 128, 256, 2, 2, false, STATS, 1, false>),
-                       dim3((unsigned)((int64_t)mt * a.ntiles)), dim3(256), 0, s, a);
-    return mt;
-  }
-  if (a.N > 64 && g_tune_tile != 1 && !a.sliced) {
-    a.ntiles = (int)cdiv(a.N, 128);
-    const int mt = (int)cdiv(a.M, 128);
-    hipLaunchKernelGGL((igemm_kernel<MODE, 128, 128, 2, 2, false, STATS, NWRAP, REMAP, EPI>),
-                       dim3((unsigned)((int64_t)mt * a.ntiles)), dim3(256), 0, s, a);
-    return mt;
-  }
   if (a.sliced) {   // grouped convolution: one column tile per slice of Cs = 32 or 64 channels
-    a.ntiles = a.N / a.Cs;
-    const int mt = (int)cdiv(a.M, 256);
-    const dim3 grid((unsigned)((int64_t)mt * a.ntiles));
-    if (a.Cs == 64) hipLaunchKernelGGL((igemm_kernel<MODE, 256, 64, 4, 1, false, STATS, NWRAP, REMAP, EPI>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((igemm_kernel<MODE, 256, 32, 4, 1, false, STATS, NWRAP, REMAP, EPI>), grid, dim3(256), 0, s, a);
-    return mt;
+    if (a.Cs == 64) return launch_tile<MODE, 256, 64, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
+    return launch_tile<MODE, 256, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
   }
-  a.ntiles = (int)cdiv(a.N, 64);
-  const int mt = (int)cdiv(a.M, 256);
-  if (a.N > 32)
-    hipLaunchKernelGGL((igemm_kernel<MODE, 256, 64, 4, 1, false, STATS, NWRAP, REMAP, EPI>),
-                       dim3((unsigned)((int64_t)mt * a.ntiles)), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((igemm_kernel<MODE, 256, 32, 4, 1, false, STATS, NWRAP, REMAP, EPI>), dim3((unsigned)mt), dim3(256),
-                       0, s, a);
-  return mt;
+  if (a.N <= 32) return launch_tile<MODE, 256, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
+  if (a.N <= 64 || g_tune_tile == 1) return launch_tile<MODE, 256, 64, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
+  if constexpr (NWRAP == 1) {
+    const bool w64 = a.Cs >= 64;
+    const int tile = igemm_tile(a.M, a.N, a.K, w64);
+    if constexpr (!REMAP) {
+      if (EPI == 0 && tile == TILE_TALL) return launch_tile<MODE, 256, 128, 2, 2, STATS, 1, false, EPI, 32, 3>(a, s);
+      if (tile == TILE_WIDE) return launch_tile<MODE, 128, 256, 2, 2, STATS, 1, false, EPI, 32, 3>(a, s);
+    }
+    if (w64) {
+      if (tile == TILE_SMALL) return launch_tile<MODE, 64, 64, 2, 2, STATS, 1, REMAP, EPI, 64, 4>(a, s);
+      if (tile == TILE_NARROW) return launch_tile<MODE, 128, 64, 2, 2, STATS, 1, REMAP, EPI, 64, 3>(a, s);
+      const int64_t wgs = cdiv(a.M, 128) * cdiv(a.N, 128);
+      if (wgs <= 256) return launch_tile<MODE, 128, 128, 2, 2, STATS, 1, REMAP, EPI, 64, 4>(a, s);
+      if (wgs <= 1024 || a.K > 512) return launch_tile<MODE, 128, 128, 2, 2, STATS, 1, REMAP, EPI, 64, 2>(a, s);
+    }
+  }
+  return launch_tile<MODE, 128, 128, 2, 2, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
 }
 template <int MODE, int STATS, bool REMAP = false, int EPI = 0>
 static int launch_igemm(IgemmArgs a, hipStream_t s) {
@@ -679,6 +779,13 @@ bool conv_mfma_supported(const ConvGeom& g) {
          (int64_t)g.Cout * g.K() * 2 < lim;
 }
 
+template <int BM, int BN, int EPI, bool GROUP, int BKT, int NS>
+static void launch_linear(IgemmArgs a, hipStream_t s) {
+  a.ntiles = (int)cdiv(a.N, BN);
+  hipLaunchKernelGGL((igemm_kernel<0, BM, BN, 2, 2, true, 0, 1, false, EPI, GROUP, BKT, NS>),
+                     dim3((unsigned)(cdiv(a.M, BM) * a.ntiles)), dim3(256), 0, s, a);
+}
+
 void linear_fwd_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, float* y, int64_t B, int F, int C,
                      hipStream_t s) {
   IgemmArgs a;
@@ -691,16 +798,22 @@ void linear_fwd_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, float
   a.group_m = 8;
   a.src_bytes = (uint32_t)(B * (int64_t)F * 2);
   a.wt_bytes = (uint32_t)((int64_t)C * F * 2);
-  a.ntiles = (int)cdiv(C, 128);
-  const dim3 grid((unsigned)(cdiv(B, 128) * a.ntiles));
-  // a filter matrix beyond an L2's 4 MiB under a wide output: grouped tile order
+  // a filter matrix beyond an L2's 4 MiB under a wide output: grouped tile order, with a short contraction on 256x128 tiles
+  // (8192 x 32768 x 512 inside a training step: 471 us on 128x128 tiles, 459 so; non-temporal stores of the logits, faster when
+  // the launch is repeated alone, 368 us, cost it 70 us there)
   const bool group = (int64_t)C * F * 2 > (4 << 20) && C >= 2048;
-  if (group) {
-    if (bias) hipLaunchKernelGGL((igemm_kernel<0, 128, 128, 2, 2, true, false, 1, false, 1, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((igemm_kernel<0, 128, 128, 2, 2, true, false, 1, false, 0, true>), grid, dim3(256), 0, s, a);
+  const int tile = igemm_tile(B, C, F, F >= 64);
+  if (group && F <= 512 && cdiv(B, 256) * cdiv(C, 128) >= 512) {
+    a.group_m = 4;
+    if (bias) launch_linear<256, 128, 1, true, 32, 3>(a, s); else launch_linear<256, 128, 0, true, 32, 3>(a, s);
+  } else if (group && F >= 64) {
+    if (bias) launch_linear<128, 128, 1, true, 64, 2>(a, s); else launch_linear<128, 128, 0, true, 64, 2>(a, s);
+  } else if (tile == TILE_SMALL) {   // few rows or few classes: as igemm_tile says (256 x 1000 x 2048 18 -> 11 us)
+    if (bias) launch_linear<64, 64, 1, false, 64, 4>(a, s); else launch_linear<64, 64, 0, false, 64, 4>(a, s);
+  } else if (F >= 64) {
+    if (bias) launch_linear<128, 128, 1, false, 64, 2>(a, s); else launch_linear<128, 128, 0, false, 64, 2>(a, s);
   } else {
-    if (bias) hipLaunchKernelGGL((igemm_kernel<0, 128, 128, 2, 2, true, false, 1, false, 1, false>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((igemm_kernel<0, 128, 128, 2, 2, true, false, 1, false, 0, false>), grid, dim3(256), 0, s, a);
+    if (bias) launch_linear<128, 128, 1, false, 32, 3>(a, s); else launch_linear<128, 128, 0, false, 32, 3>(a, s);
   }
 }
 

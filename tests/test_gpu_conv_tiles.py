@@ -1,0 +1,41 @@
+"""The tile shapes and step widths the matrix-core convolutions choose between, each at a size that selects it, layer by layer
+against the oracle: ragged rows and columns, contractions that are no multiple of a step, forward, data gradient (with the
+BatchNorm sums in the epilogue, and in parity classes for stride 2), bias and ReLU epilogues."""
+import pytest
+
+from oracle import nets
+
+from gpu_util import Case
+from test_gpu_step import check_layers
+from test_gpu_transformer_head import head_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    # 64x64 tiles: 2800 and 700 rows, 72 and 200 columns, contractions of 648 and 1800; stride 2 in between
+    "small": (dict(kind=1, widths=[72, 200], blocks=[1, 1], stem_width=72), lambda: nets.resnet20(widths=(72, 200), blocks=(1, 1)), 7, 20),
+    # 200 tiles of 128x128: 64-wide steps in four stages (3x3), 128x64 tiles (1x1 into 128 columns)
+    "alone": (dict(kind=2, widths=[128], blocks=[1], stem_width=64),
+              lambda: nets.resnet50(classes=10, widths=(128,), blocks=(1,), stem=64), 100, 64),
+    # 300 tiles of 128x128, a contraction of 1152: 64-wide steps in two stages
+    "two_stages": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), lambda: nets.resnet20(widths=(128,), blocks=(1,)), 150, 16),
+    # 320 columns: five 128x64 tiles instead of three of 128x128
+    "uneven_columns": (dict(kind=1, widths=[320], blocks=[1], stem_width=320), lambda: nets.resnet20(widths=(320,), blocks=(1,)), 96, 16),
+    # 520 tiles: 256x128
+    "tall": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), lambda: nets.resnet20(widths=(128,), blocks=(1,)), 260, 16),
+}
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_tile_shapes_bf16_layers(name):
+    kw, mk, batch, res = SHAPES[name]
+    c = Case(kw, mk(), "bf16", batch, res, 10)
+    check_layers(c, c.gpu())
+
+
+@pytest.mark.parametrize("shape", [(2100, 512, 2048, 264),    # 128x256 tiles with bias and ReLU, 64x64 with bias
+                                   (70, 72, 200, 1000),       # few rows: 64x64 tiles, fp32 logits too
+                                   (8200, 64, 128, 4104)])    # 64-wide steps with a single step; ragged logits
+def test_dense_layer_tiles_bf16_layers(shape):
+    c = head_case("bf16", *shape)
+    check_layers(c, c.gpu())
