@@ -143,7 +143,8 @@ int conv_dgrad_mfma(const bf16_t* dy, const bf16_t* w, bf16_t* wt, bf16_t* dx, c
                     const bf16_t* relu_out = nullptr, const BnBackwardSums* bn = nullptr, bool wt_ready = false);
 // The filter re-layouts of many data gradients in one launch (a backward pass needs one per convolution, each a few
 // microseconds of work behind a launch of its own otherwise).  A job writes wt[c][jh][jw][n] = w[n][r0 + rstep jh][s0 + rstep jw][c]
-// for c < cin, jh < th, jw < tw, n < cout; first = the number of elements of the jobs in front of it.
+// for c < cin, jh < th, jw < tw, n < cout (channel counts multiples of 8, 16-byte aligned pointers); first = the number of tiles
+// of the jobs in front of it.
 struct WeightLayoutJob { const bf16_t* w; bf16_t* wt; int cout, kh, kw, cin, th, tw, r0, s0, rstep; int64_t first; };
 // appends the jobs that conv_dgrad_mfma's own re-layout of this convolution consists of (same places inside wt)
 void conv_dgrad_layout_jobs(const bf16_t* w, bf16_t* wt, const ConvGeom& g, std::vector<WeightLayoutJob>& jobs);
@@ -178,8 +179,6 @@ void s2d_pack_w(const bf16_t* w, bf16_t* ws, int cout, int k, int ks, int shift,
 void s2d_unpack_dw(const float* dws, float* dw, int cout, int k, int ks, int shift, hipStream_t s);
 // fp32 [n][8] -> [n][3]
 void unpad_c8_to_c3(const float* in, float* out, int64_t n, hipStream_t s);
-// w[Cout][taps][Cin] -> wt[Cin][taps][Cout]
-void transpose_weight(const bf16_t* w, bf16_t* wt, int cout, int taps, int cin, hipStream_t s);
 
 // ---- conv_grouped.hip: a grouped convolution (Cin = Cout = C) as dense convolutions on channel slices ----
 // slices of grouped_slice_width(C) channels (C itself up to 128, else 128), each a whole number of groups
