@@ -45,6 +45,17 @@ def test_transformer_padded_sentences_bf16_layers(name):
     assert np.all(got["dz"][c.y < 0] == 0)
 
 
+@pytest.mark.parametrize("Ts,Tt,d", [(1, 1, 128), (32, 33, 64), (31, 64, 128), (65, 96, 128), (128, 129, 64), (129, 32, 128),
+                                     (257, 160, 128)])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_attention_tile_edges_bf16_layers(Ts, Tt, d, ragged):
+    """Matrix-core attention (head dimensions 32 and 64) at the edges of its 32-row tiles, 64-row chunks and 128-row stages,
+    one below, at and one above each; causal, cross and full attention, padded keys or none."""
+    ref = nets.transformer(2, Ts, Tt, d=d, heads=2, d_ff=64, vocab=64, enc_layers=1, dec_layers=1)
+    c = Case(dict(kind=4, widths=[d, 64, 2], blocks=[1, 1]), ref, "bf16", 2, 0, 64, jitter=0.1, tokens=(Ts, Tt), ragged=ragged)
+    check_layers(c, c.gpu(alpha=0.5, label_smoothing=0.1))
+
+
 def make_packed(name, multiple=16, slack_sentences=3):
     """The ragged batch of make(name, ragged=True), handed to the library without its padding."""
     S, Ts, Tt, d, heads, ff, vocab, ne, nd = CASES[name]
