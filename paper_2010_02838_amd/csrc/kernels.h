@@ -58,6 +58,9 @@ void bn_stats(int dtype, const void* x, const void* gamma, const void* beta, int
 void bn_running_update(const float* stats, float* running, int64_t M, int C, float momentum, hipStream_t s);
 void bn_stats_from_running(int dtype, const float* running, const void* gamma, const void* beta, float* stats, int C,
                            hipStream_t s);
+// bn_apply_running: the elementwise pass with the running averages [mean | var]; stats (4 C floats) may be written.
+void bn_apply_running(int dtype, const void* x, const void* res, bool relu, void* y, int64_t M, int C, const float* running,
+                      const void* gamma, const void* beta, float* stats, uint8_t* relu_mask, hipStream_t s);
 void bn_apply(int dtype, const void* x, const void* res, bool relu, void* y, int64_t M, int C, const float* stats,
               uint8_t* relu_mask, hipStream_t s);
 // bn_apply with ReLU followed by a 3x3 stride-2 pad-1 max-pool, in one pass: y [B][H/2][W/2][C] is the pooled

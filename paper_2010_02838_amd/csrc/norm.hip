@@ -298,12 +298,32 @@ __global__ void __launch_bounds__(1024) col_fold_k(const float* __restrict__ par
   out[(int64_t)blockIdx.y * stat_pitch(C) + C + c] = s1;
 }
 
+// scale and shift of channel c from the running averages [mean[C] | var[C]]; returns 1 / standard deviation
+template <typename T>
+__device__ inline float running_scale_shift(const float* __restrict__ running, const T* __restrict__ gamma,
+                                            const T* __restrict__ beta, int C, int c, float* scale, float* shift) {
+  const float mean = running[c], istd = 1.f / sqrtf(running[C + c] + kBnEps);
+  *scale = Cvt<T>::ld(gamma[c]) * istd;
+  *shift = Cvt<T>::ld(beta[c]) - mean * *scale;
+  return istd;
+}
+
 // mask (VEC 8 only, nullable): receives one byte per vector, bit k = (y[k] > 0), for the backward pass
-template <typename T, int VEC, bool FIXC>
+// RUN (with FIXC, C <= kRunChannels): stats is [mean[C] | var[C]], the running averages, and a block computes the scale and
+// shift of all channels itself, once, into LDS.
+constexpr int kRunChannels = 2048;   // what 256 threads of 8 channels touch; 16 KB of LDS
+template <typename T, int VEC, bool FIXC, bool RUN>
 __global__ void __launch_bounds__(256) bn_apply_k(const T* __restrict__ x, const T* __restrict__ res, T* __restrict__ y,
                                                   const float* __restrict__ stats, int relu, int64_t nvec, int C,
-                                                  uint8_t* __restrict__ mask) {
+                                                  uint8_t* __restrict__ mask, const T* __restrict__ gamma,
+                                                  const T* __restrict__ beta) {
+  static_assert(FIXC || !RUN, "a thread that changes channels reads them from stats");
+  __shared__ __attribute__((aligned(16))) float ss[RUN ? 2 * kRunChannels : 4];
   const int vc = C / VEC;
+  if (RUN) {
+    for (int c = threadIdx.x; c < C; c += 256) running_scale_shift(stats, gamma, beta, C, c, ss + c, ss + kRunChannels + c);
+    __syncthreads();
+  }
   const int64_t stride = (int64_t)gridDim.x * 256;
   // last rows first: the producing convolution wrote them most recently, so they are the part of x
   // that the caches still hold
@@ -312,7 +332,10 @@ __global__ void __launch_bounds__(256) bn_apply_k(const T* __restrict__ x, const
   if (FIXC) {
     const int c0 = (int)(i0 % vc) * VEC;
 #pragma unroll
-    for (int k = 0; k < VEC; k++) { sc[k] = stats[2 * C + c0 + k]; sh[k] = stats[3 * C + c0 + k]; }
+    for (int k = 0; k < VEC; k++) {
+      sc[k] = RUN ? ss[c0 + k] : stats[2 * C + c0 + k];
+      sh[k] = RUN ? ss[kRunChannels + c0 + k] : stats[3 * C + c0 + k];
+    }
   }
   for (int64_t ib = i0; ib < nvec; ib += stride * kEltUnroll) {
     typename Vec<T, VEC>::Raw ra[kEltUnroll], rr[kEltUnroll];
@@ -678,8 +701,8 @@ static void bn_apply_t(const T* x, const T* res, bool relu, T* y, int64_t M, int
   bool fixc;
   const unsigned blocks = elt_grid(nvec, C / vec, kEltUnroll, &fixc);
 #define CD_BN_APPLY(VV, FC) \
-  hipLaunchKernelGGL((bn_apply_k<T, VV, FC>), dim3(blocks), dim3(256), 0, s, x, res, y, stats, (int)relu, nvec, C, \
-                     relu ? mask : (uint8_t*)nullptr)
+  hipLaunchKernelGGL((bn_apply_k<T, VV, FC, false>), dim3(blocks), dim3(256), 0, s, x, res, y, stats, (int)relu, nvec, C, \
+                     relu ? mask : (uint8_t*)nullptr, (const T*)nullptr, (const T*)nullptr)
   if (vec > 1) { if (fixc) CD_BN_APPLY(V, true); else CD_BN_APPLY(V, false); }
   else { if (fixc) CD_BN_APPLY(1, true); else CD_BN_APPLY(1, false); }
 #undef CD_BN_APPLY
@@ -705,7 +728,8 @@ static void bn_backward_t(const T* dy, const T* y, const T* x, const T* gamma, c
     src = scratch;
   }
   hipLaunchKernelGGL((col_finalize_k<T, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
-                     src, chunks, M, C, gamma, (const T*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
+                     src, chunks, M, C,
+                     gamma, (const T*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
   const int64_t nvec = M * C / vec;
   bool fixc;
   const unsigned blocks = elt_grid(nvec, C / vec, 2, &fixc);
@@ -724,7 +748,8 @@ static void colsum_t(const T* a, int64_t M, int C, float* out, float* partials, 
   ReducePlan p = vec > 1 ? launch_reduce<T, V, 2>(a, nullptr, nullptr, nullptr, false, M, C, partials, s)
                          : launch_reduce<T, 1, 2>(a, nullptr, nullptr, nullptr, false, M, C, partials, s);
   hipLaunchKernelGGL((col_finalize_k<T, 2>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
-                     partials, p.chunks, M, C, (const T*)nullptr, (const T*)nullptr, (float*)nullptr, out, (float*)nullptr, (float*)nullptr);
+                     partials, p.chunks, M, C,
+                     (const T*)nullptr, (const T*)nullptr, (float*)nullptr, out, (float*)nullptr, (float*)nullptr);
 }
 
 // ---- running averages (evaluation mode) ----------------------------------------------------------
@@ -746,12 +771,12 @@ __global__ void __launch_bounds__(256) bn_stats_from_running_k(const float* __re
                                                                const T* __restrict__ beta, float* __restrict__ stats, int C) {
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c >= C) return;
-  const float mean = running[c], istd = 1.f / sqrtf(running[C + c] + kBnEps);
-  const float scale = Cvt<T>::ld(gamma[c]) * istd;
-  stats[c] = mean;
+  float scale, shift;
+  const float istd = running_scale_shift(running, gamma, beta, C, c, &scale, &shift);
+  stats[c] = running[c];
   stats[C + c] = istd;
   stats[2 * C + c] = scale;
-  stats[3 * C + c] = Cvt<T>::ld(beta[c]) - mean * scale;
+  stats[3 * C + c] = shift;
 }
 
 void bn_running_update(const float* stats, float* running, int64_t M, int C, float momentum, hipStream_t s) {
@@ -767,6 +792,38 @@ void bn_stats_from_running(int dtype, const float* running, const void* gamma, c
   else
     hipLaunchKernelGGL(bn_stats_from_running_k<float>, dim3((unsigned)cdiv(C, 256)), dim3(256), 0, s, running,
                        (const float*)gamma, (const float*)beta, stats, C);
+}
+
+// The elementwise pass with the running averages.  Where a thread keeps its channels (channel vectors per row divide the grid
+// stride, which elt_grid arranges for all but the largest launches) it needs no statistics kernel in front of it: that launch
+// took 4.5 us per layer, as long as many of the passes behind it.
+template <typename T>
+static void bn_apply_running_t(const T* x, const T* res, bool relu, T* y, int64_t M, int C, const float* running,
+                               const T* gamma, const T* beta, float* stats, uint8_t* mask, hipStream_t s) {
+  const int vec = pick_vec<T>(C, x, res, y, nullptr);
+  constexpr int V = sizeof(T) == 2 ? 8 : 4;
+  const int64_t nvec = M * C / vec;
+  bool fixc;
+  const unsigned blocks = elt_grid(nvec, C / vec, kEltUnroll, &fixc);
+  if (!fixc || C > kRunChannels) {
+    hipLaunchKernelGGL(bn_stats_from_running_k<T>, dim3((unsigned)cdiv(C, 256)), dim3(256), 0, s, running, gamma, beta, stats, C);
+    bn_apply_t<T>(x, res, relu, y, M, C, stats, mask, s);
+    return;
+  }
+#define CD_BN_RUN(VV) \
+  hipLaunchKernelGGL((bn_apply_k<T, VV, true, true>), dim3(blocks), dim3(256), 0, s, x, res, y, running, (int)relu, nvec, C, \
+                     relu ? mask : (uint8_t*)nullptr, gamma, beta)
+  if (vec > 1) CD_BN_RUN(V); else CD_BN_RUN(1);
+#undef CD_BN_RUN
+}
+void bn_apply_running(int dtype, const void* x, const void* res, bool relu, void* y, int64_t M, int C, const float* running,
+                      const void* gamma, const void* beta, float* stats, uint8_t* relu_mask, hipStream_t s) {
+  if (dtype == CD_BF16)
+    bn_apply_running_t<bf16_t>((const bf16_t*)x, (const bf16_t*)res, relu, (bf16_t*)y, M, C, running, (const bf16_t*)gamma,
+                               (const bf16_t*)beta, stats, relu_mask, s);
+  else
+    bn_apply_running_t<float>((const float*)x, (const float*)res, relu, (float*)y, M, C, running, (const float*)gamma,
+                              (const float*)beta, stats, relu_mask, s);
 }
 
 void bn_stats(int dtype, const void* x, const void* gamma, const void* beta, int64_t M, int C, float* stats,
@@ -795,7 +852,8 @@ void bn_relu_pool_backward(const bf16_t* dpool, const uint8_t* argmax, const bf1
   hipLaunchKernelGGL(bn_pool_bwd_reduce_k, dim3(p.chunks, p.cgroups), dim3(256), 0, s, dpool, argmax, x, stats, relu_mask, B,
                      H, W, C, partials);
   hipLaunchKernelGGL((col_finalize_k<bf16_t, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
-                     partials, p.chunks, M, C, gamma, (const bf16_t*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
+                     partials, p.chunks, M, C,
+                     gamma, (const bf16_t*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
   hipLaunchKernelGGL(bn_pool_bwd_apply_k, dim3((unsigned)cdiv(M * (C / 8), 256)), dim3(256), 0, s, dpool, argmax, x, coef,
                      relu_mask, dx, B, H, W, C);
 }

@@ -631,6 +631,40 @@ def test_batchnorm_running_averages_and_evaluation_mode(name, dtype_name):
     assert torch.equal(run_ref, before)                # an evaluation pass leaves the averages alone
 
 
+@pytest.mark.parametrize("kind,width,batch,res,dtype_name", [
+    (1, 20, 3, 9, "bf16"),      # channels no multiple of 8: one at a time
+    (1, 24, 5, 7, "bf16"),      # three vectors a row, 256 threads no multiple of them
+    (2, 512, 2, 8, "bf16"),     # 2048 channels, the most whose scales a block holds
+    (2, 520, 2, 8, "bf16"),     # 2080: the statistics kernel runs in front
+    (1, 18, 3, 6, "f32"),
+])
+def test_evaluation_mode_channel_counts(kind, width, batch, res, dtype_name):
+    """The evaluation-mode BatchNorm at the channel counts where its form changes."""
+    import torch
+    from paper_2010_02838_amd.runner import pack_flat, to_device
+    mk = nets.resnet20 if kind == 1 else nets.resnet50
+    kw = dict(widths=(width,), blocks=(1,))
+    ref = mk(**kw) if kind == 1 else mk(classes=10, stem=64, **kw)
+    c = Case(dict(kind=kind, widths=[width], blocks=[1], stem_width=width if kind == 1 else 64), ref, dtype_name, batch, res, 10)
+    B, model, dev = c.B, c.model, "cuda:0"
+    names = [n for n, _, _, _ in ref.params]
+    lib_order = [names[o["param_w"]] for o in model.graph(batch)[0] if o["kind"] == "bn"]
+    ref_order = [o["gamma"] for o in ref.ops if o["op"] == "bn"]
+    P32, rng = c.per_tensor(c.th), np.random.default_rng(7)
+    avg = {n: [rng.normal(0, 0.5, P32[n].shape[0]).astype(np.float32), rng.uniform(0.5, 2, P32[n].shape[0]).astype(np.float32)]
+           for n in ref_order}
+    run = torch.from_numpy(np.concatenate([np.concatenate(avg[n]) for n in lib_order])).to(dev)
+    ws = torch.empty(model.workspace_bytes(batch, False), dtype=torch.uint8, device=dev)
+    logits = torch.empty(batch, 10, device=dev)
+    B.codistill_forward(model, to_device(pack_flat(model, c.th), model.torch_dtype), to_device(c.x, model.torch_dtype), ws,
+                        logits, False, B.CD_BN_RUNNING, run)
+    torch.cuda.synchronize()
+    P = c.per_tensor(c.th.astype(np.float64))
+    z, _ = nets.forward(ref, P, c.x.astype(np.float64), running=[[a.astype(np.float64) for a in avg[n]] for n in ref_order],
+                        bn_eval=True)
+    assert rel(logits.cpu().numpy(), z) <= (1e-4 if dtype_name == "f32" else 3e-2)   # as in the test above
+
+
 # ------------------------------------------------------------------- environment switches
 def test_serial_switch_is_bit_identical(monkeypatch):
     """CODISTILL_SERIAL=1 keeps the weight gradients on the caller's stream: same kernels, same fixed-order
