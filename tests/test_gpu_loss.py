@@ -59,6 +59,35 @@ def test_loss_parity_shapes(rows, cols, mode):
     check(z, [zp], t, 0.5, 0.0, mode)
 
 
+@pytest.mark.parametrize("cols", [1, 2, 3, 5, 255, 257, 1023, 1025, 4095, 4097, 8191, 8193, 10007, 16381, 16385, 32766, 32767, 32769])
+@pytest.mark.parametrize("mode,peers", [("mse", 0), ("mse", 1), ("mse", 3), ("kl", 1), ("mse_centered_rows", 1)])
+def test_ragged_rows(cols, mode, peers):
+    """Column counts that are no multiple of 4, around the widths at which the row kernels change: rows start at any element,
+    the last vector is partial; not in place and in place, an ignored row in between (its neighbours stay whole)."""
+    rows = 5
+    z = synth.logits(rows, cols, 3.0, seed=cols)
+    ps = [synth.logits(rows, cols, 3.0, seed=cols + 1 + j) for j in range(peers)]
+    t = synth.labels(rows, cols, seed=7)
+    t[2] = -1
+    if cols <= 3:
+        # The row's loss is lse - (1 - eps) z_t - eps mean(z): terms of size |z| that cancel (wholly, for one column, where the
+        # exact loss is 0), each rounded once, so its error is bounded by a few 2^-24 |z| and not by a multiple of itself.
+        # The KL term cancels likewise (its terms are log-sum-exps).  Gradients are bounded by 1 / rows and each is formed
+        # from a handful of roundings of exponentials and of differences of logits (up to 2 alpha |z - z'| times 2^-24).
+        (tot, task, dist), dz_ref = oracle_loss(z, ps, t, 0.5, 0.1, MODES[mode][2], MODES[mode][3])
+        l, status, dz = run_gpu(z, ps, t, 0.5, 0.1, mode)
+        size = max(np.abs(a).max() for a in [z] + ps) + 2.0
+        assert status == 0 and np.all(dz[2] == 0)
+        for got, want in zip(l, (tot, task, dist)):
+            assert abs(got - want) <= TOL * abs(want) + 16 * 2.0 ** -24 * size, (got, want)
+        assert np.abs(dz - dz_ref).max() <= 16 * 2.0 ** -24 * size
+        return
+    _, dz = check(z, ps, t, 0.5, 0.1, mode)
+    assert np.all(dz[2] == 0)
+    _, dz2 = check(z, ps, t, 0.5, 0.1, mode, inplace=True)
+    assert np.array_equal(dz, dz2)
+
+
 @pytest.mark.parametrize("mode", ["mse", "mse_rows", "kl", "mse_centered", "mse_centered_rows"])
 @pytest.mark.parametrize("eps", [0.0, 0.1])
 def test_loss_parity_modes(mode, eps):
