@@ -7,10 +7,10 @@ Workload: two ResNet-50 (bf16 compute, fp32 master weights), batch 256 of
 224x224x3 images ~ N(0,1), 1000 uniform classes, alpha = 1.
 
 Prints ONE JSON line.  `roofline` is for the kernel that takes the most time of the step,
-bn_apply_k<bf16,8,true> (the elementwise pass of every BatchNorm forward, both models):
+bn_apply_k<bf16,8,true,false> (the elementwise pass of every BatchNorm forward, both models):
 HBM-bound, algorithmic bytes (input, residual, output and ReLU bit mask, each once) over
 the HIP-event time of its launches.  `roofline_conv` is the same for the convolution kernel
-that takes the most time, igemm_kernel<0,128,256,2,2,false,1,1,false,0,false> (bf16 MFMA
+that takes the most time, igemm_kernel<0,128,256,2,2,false,1,1,false,0,false,32,3> (bf16 MFMA
 implicit GEMM, forward, 128x256 tiles): its arithmetic intensity decides which roof bounds
 it, and its fraction of the MFMA peak is given either way.  Both are measured in a second
 pass of the same steps with the library's per-launch event timer (events on the launch
@@ -34,8 +34,8 @@ PEAK_HBM_GBS = 8000.0
 # this script, FETCH_SIZE then WRITE_SIZE, each scaled by what the same counter read for the 1 GiB copy of
 # --copy-calibration).  Valid only for the kernels the counters were taken on: set to None when one changes.
 TRAFFIC_SOURCE = "profiles/resnet50_bs256_step_hbm_counters.md"
-ROOFLINE_TRAFFIC_BYTES = 260.2e6        # bn_apply_k<bf16,8,true>: FETCH_SIZE 76166.7 KiB x 2.000 + WRITE_SIZE 101792.6 KiB x 1.000
-ROOFLINE_CONV_TRAFFIC_BYTES = 221.0e6   # igemm_kernel<0,128,256,...>: FETCH_SIZE 40974.9 KiB x 2.000 + WRITE_SIZE 133859.5 KiB x 1.000
+ROOFLINE_TRAFFIC_BYTES = 260.2e6        # bn_apply_k<bf16,8,true,false>: FETCH_SIZE 76167.4 KiB x 2.000 + WRITE_SIZE 101792.6 KiB x 1.000
+ROOFLINE_CONV_TRAFFIC_BYTES = 228.2e6   # igemm_kernel<0,128,256,...>: FETCH_SIZE 39095.4 KiB x 2.000 + WRITE_SIZE 144691.6 KiB x 1.000
 # Matrix-pipe busy share of that convolution kernel from hardware counters (SQ_VALU_MFMA_BUSY_CYCLES over
 # GRBM_GUI_ACTIVE x 1024 SIMDs, mean over its dispatches); None when the kernel changes.
 MFMA_COUNTER_SOURCE = "profiles/resnet50_bs256_step_mfma_counters.md"
@@ -188,7 +188,7 @@ def transformer_head(args, B, synth, StepRunner, pack_flat, to_device, torch, de
                    "distillation": "mse_logits"},
         "loss": [float(v) for v in loss[:3]],
         "roofline": dict(roofline_of(lin["flops"], lin["bytes"], lin["ms"], lin["launches"],
-                                     "igemm_kernel<0,128,128,2,2,true,0,1,false> (vocabulary projection, fp32 logits)",
+                                     "igemm_kernel<0,256,128,2,2,true,0,1,false,0,true,32,3> (vocabulary projection, fp32 logits)",
                                      None), launches_per_step=lin["launches"] / psteps),
         "kernel_class_ms_per_step": {k: round(v["ms"] / psteps, 4) for k, v in prof.items()},
         "hbm_kernels": hbm,
@@ -446,12 +446,12 @@ def main():
     bn = prof["bn_apply"]
     ev_us = B.profile_event_overhead()
     roofline = roofline_of(bn["flops"], bn["bytes"], bn["ms"], bn["launches"],
-                           "bn_apply_k<bf16,8,true> (BatchNorm forward: normalise, add the residual, ReLU, bit mask)",
+                           "bn_apply_k<bf16,8,true,false> (BatchNorm forward: normalise, add the residual, ReLU, bit mask)",
                            ROOFLINE_TRAFFIC_BYTES if default_pair else None, ev_us)
     roofline["launches_per_step"] = bn["launches"] / psteps
     cw = prof["conv_fprop_wide"]
     roofline_conv = roofline_of(cw["flops"], cw["bytes"], cw["ms"], cw["launches"],
-                                "igemm_kernel<0,128,256,2,2,false,1,1,false,0,false> (bf16 implicit-GEMM conv fprop on "
+                                "igemm_kernel<0,128,256,2,2,false,1,1,false,0,false,32,3> (bf16 implicit-GEMM conv fprop on "
                                 "128x256 tiles, BatchNorm column sums in the epilogue)", ROOFLINE_CONV_TRAFFIC_BYTES if default_pair else None,
                                 ev_us)
     roofline_conv["launches_per_step"] = cw["launches"] / psteps

@@ -8,8 +8,8 @@
 //
 // fprop and dgrad share one kernel: both operands are contiguous along the contraction index, so
 // a lane's 8-element MFMA operand is one 16-byte load.  Block = 4 waves; buffer loads write global
-// memory straight into LDS (three stages of unpadded, XOR-swizzled 64-byte rows: conflict-free
-// 16-byte reads) -> MFMA; the fp32 tile is rounded to bf16, transposed through LDS and written as
+// memory straight into LDS (two to four stages of unpadded, XOR-swizzled 64- or 128-byte rows:
+// conflict-free 16-byte reads) -> MFMA; the fp32 tile is rounded to bf16, transposed through LDS and written as
 // full 16-byte vectors along the channels.  The MFMA "A" operand is the filter tile and "B" the
 // activation tile, so that a lane's 16 accumulators run along the output channels of one pixel.
 #include "kernels.h"
@@ -157,10 +157,11 @@ template <int BKT> __device__ inline int lds_off(int row, int cv) { return row *
 // (The dgrad of a stride-2 convolution is run as four MODE 0 problems, one per parity of the output
 // pixel; see conv_dgrad_mfma.)
 //
-// Main loop: one barrier per 32-wide step.  At step kt the waves wait for their own loads of tile kt
-// (issued two steps earlier), meet at the barrier, issue the loads of tile kt+2 into the stage that
-// tile kt-1 occupied, read the fragments of tile kt and multiply.  The loads are inline assembly: the
-// compiler does not track them, so it cannot serialise them against the LDS reads.
+// Main loop: one barrier per step of BKT contraction elements, NS stages in LDS.  At step kt the waves wait for
+// their own loads of tile kt (issued NS - 1 steps earlier), meet at the barrier, issue the loads of tile kt+NS-1
+// into the stage that tile kt-1 occupied, read the fragments of tile kt and multiply; the fragments of the next
+// sub-step are read while the matrix cores work on the current one, except where their registers would spill.
+// The loads are inline assembly: the compiler does not track them, so it cannot serialise them against the LDS reads.
 // F32OUT: the output is fp32 [M][N] (dense layers that produce logits); like the bf16 output it is
 // transposed through LDS so that a store instruction writes whole 256-byte row segments.
 // STATS 1: the epilogue also emits, per m-tile, the column sums and sums of squares of the bf16 values
