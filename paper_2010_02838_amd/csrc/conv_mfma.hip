@@ -692,19 +692,28 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
 //    prologue and epilogue; 200704 x 512 x 128 93 -> 81, 50176 x 256 x 1024 50 -> 46, 8192 x 1536 x 512 28 -> 25; 12544 x 512 x
 //    2048 42 either way), 256x128 where its rounds of 512 workgroups are no emptier (50176 x 256 x 2304 80 -> 76: the clock
 //    follows the power, and a larger tile moves fewer bytes per product);
+//  - launches that also take a BatchNorm's column sums choose by rows first: a tile is one fp32 partial sum, and where 256 rows
+//    went into one in place of 128 (or the other way) the batch statistics and all roundings behind them moved.  They keep 256x128
+//    for K <= 128 onto N >= 512 and where its last round is 1.2 times fuller, otherwise 128 rows;
 //  - where 128x128 tiles do not fill the 256 compute units, or fill them unevenly, 128x64 and 64x64 tiles do: the cost of
 //    a tile shape is the number of workgroups on the busiest unit times what one costs there (128x64 0.7 of a 128x128
 //    one, 64x64 half), but no less than what one takes alone (1.4, 1.08 and 0.75): 2450 x 512 x 4608 (80 tiles of 128x128)
 //    49 -> 26 on 312 of 64x64, 24576 x 320 x 2880 74 -> 66 on 128x64 (five columns of 64 instead of three of 128).
 enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2, TILE_NARROW = 3, TILE_SMALL = 4 };
-static int igemm_tile(int64_t M, int N, int K, bool small_tiles) {
+static int igemm_tile(int64_t M, int N, int K, bool small_tiles, bool sums) {
   if (N <= 64) return TILE_SQUARE;
   if (g_tune_tile == 2) return TILE_SQUARE;
   if (g_tune_tile == 3) return TILE_TALL;
   if (g_tune_tile == 4) return N % 256 == 0 ? TILE_WIDE : TILE_SQUARE;
   if (g_tune_tile == 5) return TILE_NARROW;
   if (g_tune_tile == 6) return TILE_SMALL;
-  const int64_t t128 = cdiv(M, 128) * cdiv(N, 128);
+  const int64_t t128 = cdiv(M, 128) * cdiv(N, 128), t256 = cdiv(M, 256) * cdiv(N, 128);
+  if (sums && t128 > 256) {
+    if (K <= 128 && N >= 512) return TILE_TALL;
+    if (N % 256 == 0 && K <= 1024) return TILE_WIDE;
+    const double e128 = (double)t128 / (double)(cdiv(t128, 768) * 768), e256 = (double)t256 / (double)(cdiv(t256, 512) * 512);
+    if (e256 > 1.2 * e128) return TILE_TALL;
+  }
   if (t128 > 256 && N % 256 == 0 && K <= 1024) return TILE_WIDE;
   const double square = std::max(1.4, (double)cdiv(t128, 256));
   double narrow = 1e30, small = 1e30;
@@ -714,17 +723,16 @@ static int igemm_tile(int64_t M, int N, int K, bool small_tiles) {
   }
   if (t128 > 256) {
     if (narrow < 0.97 * square) return TILE_NARROW;
-    const int64_t t256 = cdiv(M, 256) * cdiv(N, 128);
+    if (sums) return TILE_SQUARE;
     const double e128 = (double)t128 / (double)(cdiv(t128, 512) * 512), e256 = (double)t256 / (double)(cdiv(t256, 512) * 512);
     return t128 > 512 && e256 >= e128 ? TILE_TALL : TILE_SQUARE;
   }
   return small < narrow && small < square ? TILE_SMALL : narrow < square ? TILE_NARROW : TILE_SQUARE;
 }
 int conv_fprop_tile_class(const ConvGeom& g, bool bias) {
-  (void)bias;
   if (g.Cout <= 64) return 2;
   if (g.Cin < BK) return 0;
-  const int t = igemm_tile(g.M(), g.Cout, (int)g.K(), g.Cin >= 64);
+  const int t = igemm_tile(g.M(), g.Cout, (int)g.K(), g.Cin >= 64, !bias);
   return t == TILE_SQUARE ? 0 : (t == TILE_WIDE ? 1 : 2);
 }
 
@@ -752,7 +760,7 @@ static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
   if (a.N <= 64 || g_tune_tile == 1) return launch_tile<MODE, 256, 64, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
   if constexpr (NWRAP == 1) {
     const bool w64 = a.Cs >= 64;
-    const int tile = igemm_tile(a.M, a.N, a.K, w64);
+    const int tile = igemm_tile(a.M, a.N, a.K, w64, STATS != 0);
     if constexpr (!REMAP) {
       if (EPI == 0 && tile == TILE_TALL) return launch_tile<MODE, 256, 128, 2, 2, STATS, 1, false, EPI, 32, 3>(a, s);
       if (tile == TILE_WIDE) return launch_tile<MODE, 128, 256, 2, 2, STATS, 1, false, EPI, 32, 3>(a, s);
@@ -803,7 +811,7 @@ void linear_fwd_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, float
   // (8192 x 32768 x 512 inside a training step: 471 us on 128x128 tiles, 459 so; non-temporal stores of the logits, faster when
   // the launch is repeated alone, 368 us, cost it 70 us there)
   const bool group = (int64_t)C * F * 2 > (4 << 20) && C >= 2048;
-  const int tile = igemm_tile(B, C, F, F >= 64);
+  const int tile = igemm_tile(B, C, F, F >= 64, false);
   if (group && F <= 512 && cdiv(B, 256) * cdiv(C, 128) >= 512) {
     a.group_m = 4;
     if (bias) launch_linear<256, 128, 1, true, 32, 3>(a, s); else launch_linear<256, 128, 0, true, 32, 3>(a, s);
