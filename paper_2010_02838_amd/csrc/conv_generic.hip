@@ -14,6 +14,7 @@
 // of 32x32, forward and backward, 2430 -> 389 us; the step of the channel-split Wide-ResNet, batch 96, whose second block
 // reads 20 channels, 62.2 -> 8.75 ms; the two-layer fp32 network's step on 8 images 725 -> 378 us.
 #include "kernels.h"
+#include "conv_rules.h"
 
 namespace cd {
 
@@ -259,7 +260,7 @@ __global__ void __launch_bounds__(256) conv_generic_wgrad_k(GenArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int split = blockIdx.x / (unsigned)a.tiles, tile = blockIdx.x % (unsigned)a.tiles;
   const int n0 = tile / a.ktiles * BN, k0 = tile % a.ktiles * BKK;
-  const int mbeg = split * a.m_per_split, mend = mbeg + a.m_per_split < a.M ? mbeg + a.m_per_split : a.M;
+  const int mbeg = split * a.m_per_split, mend = generic_split_end(a.M, mbeg, a.m_per_split);
   const T* __restrict__ x = static_cast<const T*>(a.src);
   const T* __restrict__ dy = static_cast<const T*>(a.w);
   const int dv = tid % NV, dr = tid / NV;
@@ -418,17 +419,11 @@ void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, cons
 
 template <typename T>
 static void wgrad_generic_t(GenArgs a, bool v4, float* dw, float* partials, size_t partials_bytes, hipStream_t s) {
-  const int tn = a.N <= 16 ? 1 : 2, tk = v4 ? (a.K <= 32 ? 2 : 4) : 2;
-  a.ktiles = (int)cdiv(a.K, 16 * tk);
-  const int64_t tiles = cdiv(a.N, 16 * tn) * a.ktiles, nk = (int64_t)a.N * a.K;
-  // three workgroups per compute unit, but at least two 64-pixel steps each (a split costs one fp32 copy of dw)
-  int64_t splits = cdiv(768, tiles);
-  if (splits > cdiv(a.M, 128)) splits = cdiv(a.M, 128);
-  const int64_t by_mem = (int64_t)(partials_bytes / (nk * sizeof(float)));
-  if (splits > by_mem) splits = by_mem;
-  if (splits < 1) splits = 1;
-  a.m_per_split = (int)(cdiv(cdiv(a.M, splits), 64) * 64);
-  splits = cdiv(a.M, a.m_per_split);
+  const GenericWgradPlan p = generic_wgrad_plan(a.M, a.N, a.K, v4, partials_bytes);
+  const int tn = p.tn, tk = p.tk;
+  const int64_t tiles = p.tiles, splits = p.splits, nk = (int64_t)a.N * a.K;
+  a.ktiles = (int)p.ktiles;
+  a.m_per_split = p.m_per_split;
   a.tiles = (int)tiles;
   a.out = splits == 1 ? dw : partials;
   const dim3 grid((unsigned)(tiles * splits));

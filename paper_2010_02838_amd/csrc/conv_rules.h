@@ -1,0 +1,41 @@
+// Host rules of the convolution launches, in plain integers: no HIP header is needed, so that they can be compiled and
+// checked on a machine without a GPU.  (constexpr functions are callable from device code.)
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+namespace cd {
+
+// ---- weight gradient of conv_generic.hip: a 16 tn x 16 tk tile of dw per block, the pixel range cut into splits ----
+struct GenericWgradPlan {
+  int tn, tk;              // 16-wide tiles of output channels and of (tap, input channel) per block
+  int64_t ktiles, tiles;   // tiles along the contraction side of dw, tiles altogether
+  int64_t splits;
+  int m_per_split;         // pixels per split, a multiple of the 64 a step takes
+};
+
+// M pixels, N output channels, K = taps x input channels; v4: four channels per load
+inline GenericWgradPlan generic_wgrad_plan(int64_t M, int N, int K, bool v4, size_t partials_bytes) {
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  GenericWgradPlan p;
+  p.tn = N <= 16 ? 1 : 2;
+  p.tk = v4 ? (K <= 32 ? 2 : 4) : 2;
+  p.ktiles = up(K, 16 * p.tk);
+  p.tiles = up(N, 16 * p.tn) * p.ktiles;
+  // three workgroups per compute unit, but at least two 64-pixel steps each (a split costs one fp32 copy of dw)
+  p.splits = up(768, p.tiles);
+  if (p.splits > up(M, 128)) p.splits = up(M, 128);
+  const int64_t by_mem = (int64_t)(partials_bytes / ((size_t)N * K * sizeof(float)));
+  if (p.splits > by_mem) p.splits = by_mem;
+  if (p.splits < 1) p.splits = 1;
+  p.m_per_split = (int)(up(up(M, p.splits), 64) * 64);
+  p.splits = up(M, p.m_per_split);
+  return p;
+}
+// first pixel behind the split that starts at mbeg < M (the splits overshoot M by up to 64 pixels each: mbeg + m_per_split need
+// not fit 32 bits)
+constexpr int generic_split_end(int M, int mbeg, int m_per_split) {
+  return M - mbeg > m_per_split ? mbeg + m_per_split : M;
+}
+
+}  // namespace cd
