@@ -1,7 +1,7 @@
 // Convolutions of any channel count on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32): the fp32 models, and
 // the bf16 layers whose channel counts are no multiple of 8 (the bf16 kernels gather 16-byte vectors of 8 channels).
 // Products and sums are fp32, as in the one-thread-per-output kernels, which stay behind CODISTILL_FORCE_SIMPLE and take
-// tensors of 2^31 elements and more.
+// tensors of 2^31 elements or 2^30 pixels and more.
 //
 //   fprop  y[m][n]  = sum_k im2col(x)[m][k]  * w[n][k]         m = (b,ho,wo), k = (r,s,c)
 //   dgrad  dx[m][c] = sum_k gather(dy)[m][k] * w[n][r][s][c]   m = (b,h,w),   k = (r,s,n)
@@ -360,10 +360,7 @@ __global__ void __launch_bounds__(256) conv_generic_wgrad_k(GenArgs a) {
 }
 
 bool conv_generic_supported(const ConvGeom& g) {
-  // 32-bit element offsets; tap positions and window origins far from the ends of the 32-bit range
-  const int64_t lim = 1LL << 31;
-  return g.B * g.H * g.W * (int64_t)g.Cin < lim && g.M() * (int64_t)g.Cout < lim && (int64_t)g.Cout * g.kh * g.kw * g.Cin < lim &&
-         g.B * g.H * g.W < lim - 256 && g.M() < lim - 256 && g.H < (1 << 24) && g.W < (1 << 24) && g.pad >= 0 && g.stride >= 1;
+  return generic_conv_fits(g.B, g.H, g.W, g.Cin, g.Ho, g.Wo, g.Cout, g.kh, g.kw, g.stride, g.pad);
 }
 
 static GenArgs gen_args(const ConvGeom& g) {

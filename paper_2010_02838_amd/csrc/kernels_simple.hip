@@ -1,6 +1,6 @@
 // Plain layer kernels: one thread per output element, fp32 arithmetic, fp32 or bf16 storage.
 // They define the layers for any shape.  Pooling and the small layers around the convolutions run on them; the
-// convolutions themselves only with CODISTILL_FORCE_SIMPLE or for tensors of 2^31 elements and more.
+// convolutions themselves only with CODISTILL_FORCE_SIMPLE or for tensors of 2^31 elements or 2^30 pixels and more.
 #include "kernels.h"
 
 namespace cd {

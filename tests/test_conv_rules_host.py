@@ -41,3 +41,42 @@ def test_generic_weight_gradient_splits_take_every_row_once(split_rows, M, N, K,
     splits, end, whole = split_rows(M, N, K, v4, scratch)
     assert end == M and whole
     assert splits == 1 or splits * N * K * 4 <= scratch
+
+
+@pytest.fixture(scope="module")
+def generic_fits(tmp_path_factory):
+    """whether conv_generic.hip takes a convolution, and the threads along x and blocks along y its launches would have at most"""
+    run = compiled(tmp_path_factory.mktemp("fits"), """
+int main(int, char** v) {
+  long long a[11];
+  for (int i = 0; i < 11; i++) a[i] = atoll(v[1 + i]);
+  const long long M = a[0] * a[4] * a[5], Min = a[0] * a[1] * a[2], K = a[7] * a[8] * a[3];
+  const bool ok = generic_conv_fits(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10]);
+  long long x = ((M > Min ? M : Min) + 63) / 64, y = ((a[3] > a[6] ? a[3] : a[6]) + 63) / 64;
+  if (ok) {
+    const GenericWgradPlan p = generic_wgrad_plan(M, (int)a[6], (int)K, false, 128u << 20);
+    if (p.tiles * p.splits > x) x = p.tiles * p.splits;
+  }
+  printf("%d %lld %lld", (int)ok, x * 256, y);
+}
+""")
+    return lambda *a: tuple(int(t) for t in run(*a).split())
+
+
+@pytest.mark.parametrize("geom,fits", [
+    ((32, 32, 32, 16, 32, 32, 16, 3, 3, 1, 1), True),
+    ((256, 2048, 2047, 1, 2048, 2047, 1, 3, 3, 1, 1), True),         # 1073217536 pixels
+    ((1073741760, 1, 1, 1, 1, 1, 1, 1, 1, 1, 0), True),              # the most
+    ((1073741761, 1, 1, 1, 1, 1, 1, 1, 1, 1, 0), False),
+    ((133, 4096, 3942, 1, 4096, 3942, 1, 3, 3, 1, 1), False),        # 2147475456 pixels: 2^33 threads of 64-pixel tiles
+    ((133, 4096, 3942, 1, 2048, 1971, 1, 3, 3, 2, 1), False),        # the same number in the data gradient alone
+    ((1, 1, 1, 1, 1, 1, 4194240, 1, 1, 1, 0), True),
+    ((1, 1, 1, 1, 1, 1, 4194241, 1, 1, 1, 0), False),                # 65536 column tiles
+    ((1, 1, 1, 4194240, 1, 1, 1, 7, 7, 1, 3), True),
+    ((2, 8, 8, 4000000, 8, 8, 1, 13, 13, 1, 6), False),              # 21 M tiles of the weight gradient
+])
+def test_generic_convolutions_stay_within_the_launch_limits(generic_fits, geom, fits):
+    ok, threads, blocks_y = generic_fits(*geom)
+    assert ok == fits
+    if ok:
+        assert threads < 2 ** 32 and blocks_y <= 65535
