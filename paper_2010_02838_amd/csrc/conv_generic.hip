@@ -53,6 +53,56 @@ struct GenArgs {
   int m_per_split, ktiles, tiles;   // wgrad
 };
 
+// One output element from its definition: taps outside the image (and, in a strided data gradient, between the strides) take
+// no part.  The matrix kernels multiply zeros there instead, which is the same unless the other factor is infinite or NaN
+// (0 * inf = NaN): an element that comes out as NaN is computed again here.  A NaN that belongs there is found at its first
+// product, so that a diverged network costs little.
+template <typename T, int MODE> __device__ inline float gen_element(const GenArgs& a, int m, int n) {
+  const T* __restrict__ src = static_cast<const T*>(a.src);
+  const T* __restrict__ wt = static_cast<const T*>(a.w);
+  const int HD = MODE == 0 ? a.Ho : a.H, WD = MODE == 0 ? a.Wo : a.W;
+  const int HS = MODE == 0 ? a.H : a.Ho, WS = MODE == 0 ? a.W : a.Wo, CS = MODE == 0 ? a.Cin : a.Cout;
+  const int q = m / WD, x = m - q * WD, b = q / HD, y = q - b * HD;
+  float acc = MODE == 0 && a.bias ? Cvt<T>::ld(static_cast<const T*>(a.bias)[n]) : 0.f;
+  for (int r = 0; r < a.kh; r++) {
+    int h = MODE == 0 ? y * a.stride - a.pad + r : y + a.pad - r;
+    if (h < 0 || (MODE == 1 && h % a.stride)) continue;
+    if (MODE == 1) h /= a.stride;
+    if (h >= HS) continue;
+    for (int s = 0; s < a.kw; s++) {
+      int w = MODE == 0 ? x * a.stride - a.pad + s : x + a.pad - s;
+      if (w < 0 || (MODE == 1 && w % a.stride)) continue;
+      if (MODE == 1) w /= a.stride;
+      if (w >= WS) continue;
+      const T* p = src + (unsigned)((b * HS + h) * WS + w) * (unsigned)CS;
+      const unsigned tap = (unsigned)(r * a.kw + s);
+      for (int c = 0; c < CS; c++) {
+        const unsigned at = MODE == 0 ? (unsigned)n * (unsigned)a.K + tap * (unsigned)CS + (unsigned)c
+                                      : ((unsigned)c * (unsigned)(a.kh * a.kw) + tap) * (unsigned)a.Cin + (unsigned)n;
+        acc += Cvt<T>::ld(p[c]) * Cvt<T>::ld(wt[at]);
+        if (acc != acc) return acc;
+      }
+    }
+  }
+  return acc;
+}
+// the same for element (n, k) of a weight gradient over the pixels [mbeg, mend)
+template <typename T> __device__ inline float gen_wgrad_element(const GenArgs& a, int n, int k, int mbeg, int mend) {
+  const T* __restrict__ x = static_cast<const T*>(a.src);
+  const T* __restrict__ dy = static_cast<const T*>(a.w);
+  const int tap = k / a.Cin, c = k - tap * a.Cin, r = tap / a.kw, s = tap - r * a.kw;
+  float acc = 0.f;
+  for (int m = mbeg; m < mend; m++) {
+    const int q = m / a.Wo, b = q / a.Ho;
+    const int h = (q - b * a.Ho) * a.stride - a.pad + r, w = (m - q * a.Wo) * a.stride - a.pad + s;
+    if ((unsigned)h >= (unsigned)a.H || (unsigned)w >= (unsigned)a.W) continue;
+    acc += Cvt<T>::ld(dy[(unsigned)m * (unsigned)a.N + (unsigned)n]) *
+           Cvt<T>::ld(x[(unsigned)((b * a.H + h) * a.W + w) * (unsigned)a.Cin + (unsigned)c]);
+    if (acc != acc) return acc;
+  }
+  return acc;
+}
+
 // MODE 0: fprop, MODE 1: dgrad.  Block = 4 waves down the rows, each 16 TM rows x 16 TN columns; 32 contraction elements
 // per step, two LDS buffers, the next step's elements travel in registers while the matrix cores work on this one.  The
 // filter is the MFMA "A" operand, so a lane's four accumulators are four consecutive channels of one pixel.  A lane reads
@@ -207,6 +257,24 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
     __syncthreads();
   }
   T* __restrict__ out = static_cast<T*>(a.out);
+  static_assert(TM * TN * 4 <= 32, "one bit per element of a lane");
+  uint32_t again = 0;   // elements that are NaN (they count as zero until the end): bit 4 (TN j + i) + q
+  float odd = 0.f;      // becomes NaN if one is, or is infinite
+#pragma unroll
+  for (int i = 0; i < TN; i++)
+#pragma unroll
+    for (int j = 0; j < TM; j++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) odd = fmaf(acc[i][j][q], 0.f, odd);
+  if (__builtin_expect(__any(odd != odd), 0)) {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int j = 0; j < TM; j++)
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+          if (acc[i][j][q] != acc[i][j][q]) { again |= 1u << (4 * (TN * j + i) + q); acc[i][j][q] = 0.f; }
+  }
 #pragma unroll
   for (int j = 0; j < TM; j++) {
     const int m = m0 + (wave * TM + j) * 16 + fr;
@@ -238,6 +306,19 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
         for (int q = 0; q < 4; q++)
           if (q < nv) o[q] = Cvt<T>::st(v[q]);
       }
+    }
+  }
+  if (__builtin_expect(__any(again != 0), 0)) {
+    while (again) {
+      const int e = __ffs(again) - 1;
+      again &= again - 1;
+      const int m = m0 + (wave * TM + e / (4 * TN)) * 16 + fr, n = n0 + e / 4 % TN * 16 + fk + e % 4;
+      if (m >= a.M || n >= a.N) continue;
+      float v = gen_element<T, MODE>(a, m, n);
+      T* o = out + ((unsigned)m * (unsigned)a.N + (unsigned)n);
+      if (MODE == 1 && a.accumulate) v += Cvt<T>::ld(*o);
+      if (MODE == 0 && a.relu) v = fmaxf(v, 0.f);
+      *o = Cvt<T>::st(v);
     }
   }
 }
@@ -352,10 +433,23 @@ __global__ void __launch_bounds__(256) conv_generic_wgrad_k(GenArgs a) {
       for (int q = 0; q < 4; q++) sm[wave * BN * BKK + (i * 16 + 4 * (lane >> 4) + q) * BKK + j * 16 + fc] = acc[i][j][q];
   __syncthreads();
   float* __restrict__ out = static_cast<float*>(a.out) + (int64_t)split * a.N * a.K;
+  bool again = false;
   for (int e = tid; e < BN * BKK; e += 256) {
     const int n = n0 + e / BKK, kk = k0 + e % BKK;
-    if (n < a.N && kk < a.K)
-      out[(unsigned)n * (unsigned)a.K + (unsigned)kk] = (sm[e] + sm[BN * BKK + e]) + (sm[2 * BN * BKK + e] + sm[3 * BN * BKK + e]);
+    if (n < a.N && kk < a.K) {
+      const float t = (sm[e] + sm[BN * BKK + e]) + (sm[2 * BN * BKK + e] + sm[3 * BN * BKK + e]);
+      out[(unsigned)n * (unsigned)a.K + (unsigned)kk] = t;
+      again = again || t != t;
+    }
+  }
+  if (__builtin_expect(__any(again), 0)) {
+#pragma unroll 1
+    for (int e = tid; e < BN * BKK; e += 256) {
+      const int n = n0 + e / BKK, kk = k0 + e % BKK;
+      if (n >= a.N || kk >= a.K) continue;
+      float* o = out + ((unsigned)n * (unsigned)a.K + (unsigned)kk);
+      if (*o != *o) *o = gen_wgrad_element<T>(a, n, kk, mbeg, mend);
+    }
   }
 }
 

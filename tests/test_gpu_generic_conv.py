@@ -1,9 +1,12 @@
 """Convolutions on the fp32 matrix instruction (any channel count, fp32 and bf16 storage), layer by layer against the oracle."""
+import numpy as np
 import pytest
 
 from oracle import nets
+from paper_2010_02838_amd import synth
+from paper_2010_02838_amd.runner import pack_flat, to_device
 
-from gpu_util import Case
+from gpu_util import Case, rel
 from test_gpu_step import check_layers
 
 pytestmark = pytest.mark.gpu
@@ -32,3 +35,107 @@ def test_generic_convolutions_layers(name, dtype):
     kw, mk, batch, res = SHAPES[name]
     c = Case(kw, mk(), dtype, batch, res, 10)
     check_layers(c, c.gpu())
+
+
+def _both_forms(monkeypatch, run):
+    """run() on the fp32 matrix instruction and on the plain kernels, which leave out what lies outside the image"""
+    a = run()
+    monkeypatch.setenv("CODISTILL_FORCE_SIMPLE", "1")
+    b = run()
+    monkeypatch.delenv("CODISTILL_FORCE_SIMPLE")
+    return zip(a, b)
+
+
+def _same(got, want, tol, what):
+    """NaN and infinities at the same places, the finite values alike; there are finite and infinite or NaN ones at all"""
+    finite = np.isfinite(want)
+    assert finite.any() and not finite.all(), what
+    assert np.array_equal(np.isnan(got), np.isnan(want)), (what, int(np.isnan(got).sum()), int(np.isnan(want).sum()))
+    assert np.array_equal(got[~finite & ~np.isnan(want)], want[~finite & ~np.isnan(want)]), what
+    assert rel(got[finite], want[finite]) <= tol, (what, rel(got[finite], want[finite]))
+
+
+class _Net:
+    """A network, its inputs and its finite parameters; pass_() runs forward and, given dz, backward with other parameters."""
+
+    def __init__(self, dtype, batch, h, w, **kw):
+        import torch
+        from paper_2010_02838_amd import binding as B
+        self.B, self.batch = B, batch
+        self.m = B.Model(B.arch_preset(kw.pop("kind"), in_h=h, in_w=w, classes=10, **kw), B.CD_BF16 if dtype == "bf16" else B.CD_F32)
+        self.flat = pack_flat(self.m, synth.he_init(self.m.param_table(), 1, 0.1))
+        self.x = to_device(synth.images(batch, h, w, 3, seed=0), self.m.torch_dtype)
+        self.ops, self.tensors = self.m.graph(batch)
+        self.ws = torch.zeros(self.m.workspace_bytes(batch, True), dtype=torch.uint8, device="cuda:0")
+
+    def param(self, flat, idx):
+        q = self.m.params[idx]
+        return flat[q["offset"]:q["offset"] + q["size"]].reshape(q["shape"])
+
+    def pass_(self, forward, backward=None, dz=None):
+        import torch
+        dev = lambda a: to_device(a, self.m.torch_dtype)  # noqa: E731
+        self.B.codistill_forward(self.m, dev(forward), self.x, self.ws, torch.empty(self.batch, 10, device="cuda:0"), True)
+        if dz is None:
+            return None
+        grads = torch.zeros(self.m.n_elements, device="cuda:0")
+        self.B.codistill_backward(self.m, dev(forward if backward is None else backward), self.x, self.ws, torch.from_numpy(dz).to("cuda:0"), grads)
+        return grads.cpu().numpy()
+
+    def read(self, t, key):
+        import torch
+        t = self.tensors[t]
+        n, at = self.batch * t["h"] * t["w"] * t["c"], t[key]
+        size = 2 if self.m.torch_dtype == torch.bfloat16 else 4
+        return self.ws[at:at + size * n].view(self.m.torch_dtype).double().cpu().numpy().reshape(self.batch, t["h"], t["w"], t["c"])
+
+
+@pytest.mark.parametrize("dtype,tol", [("f32", 1e-6), ("bf16", 1e-2)])
+@pytest.mark.parametrize("widths", [(4, 8), (5, 3), (20, 68)])
+def test_infinite_filter_elements_do_not_reach_past_the_border(monkeypatch, dtype, tol, widths):
+    """Forward: where the tap of an infinite filter element lies outside the image the output stays finite."""
+    c = _Net(dtype, 3, 9, 9, kind=0, widths=list(widths))
+    first, second = [o for o in c.ops if o["kind"] == "conv"]
+    w = c.flat.copy()
+    c.param(w, first["param_w"])[0, 2, 2, 1] = np.inf    # the tap below and to the right
+    c.param(w, second["param_w"])[1, 0, 1, 0] = -np.inf  # the tap above, on a channel that is infinite itself
+
+    def run():
+        c.pass_(w)
+        return [c.read(first["y"], "act_offset"), c.read(second["y"], "act_offset")]
+    for k, (a, b) in enumerate(_both_forms(monkeypatch, run)):
+        if k == 0:
+            assert np.isfinite(b[:, -1]).all() and np.isfinite(b[:, :, -1]).all() and not np.isfinite(b[:, :-1, :-1, 0]).all()
+        _same(a, b, tol, "activation %d" % k)
+
+
+@pytest.mark.parametrize("dtype,tol", [("f32", 1e-5), ("bf16", 1e-2)])
+@pytest.mark.parametrize("hw", [(1, 1), (2, 1), (1, 5)])
+def test_infinite_gradients_stay_with_the_taps_that_see_them(monkeypatch, dtype, tol, hw):
+    """Weight gradients: taps that lie outside the image at every pixel keep their zero however large dy is."""
+    c = _Net(dtype, 40, hw[0], hw[1], kind=0, widths=[5, 12])
+    dz = np.random.default_rng(2).standard_normal((40, 10)).astype(np.float32)
+    dz[7, 3] = np.inf
+    for a, b in _both_forms(monkeypatch, lambda: [c.param(c.pass_(c.flat, dz=dz), o["param_w"]) for o in c.ops if o["kind"] == "conv"]):
+        for r, s in ((0, 0), (0, 2), (2, 0), (2, 2)):    # the corner taps see no image of one row or one column
+            assert np.all(b[:, r, s] == 0)
+        _same(a, b, tol, "weight gradient")
+
+
+@pytest.mark.parametrize("dtype,tol", [("f32", 1e-5), ("bf16", 2e-2)])
+@pytest.mark.parametrize("widths", [(4, 12), (5, 33)])
+def test_infinite_filter_elements_in_a_strided_data_gradient(monkeypatch, dtype, tol, widths):
+    """Data gradient of a stride-2 3x3 convolution and of the stride-2 1x1 convolution beside it (accumulated): pixels
+    between the strides do not see an infinite filter element, and what was there already stays."""
+    c = _Net(dtype, 3, 9, 9, kind=1, widths=list(widths), blocks=[1, 1], stem_width=widths[0])
+    dz = np.random.default_rng(2).standard_normal((3, 10)).astype(np.float32) / 30
+    strided = [o for o in c.ops if o["kind"] == "conv" and o["stride"] == 2]
+    assert len(strided) == 2 and strided[0]["x"] == strided[1]["x"]
+    w = c.flat.copy()
+    c.param(w, [o for o in strided if o["k"] == 3][0]["param_w"])[0, 0, 1, 1] = np.inf
+
+    def run():
+        c.pass_(c.flat, w, dz)
+        return [c.read(strided[0]["x"], "grad_offset")]
+    for a, b in _both_forms(monkeypatch, run):
+        _same(a, b, tol, "input gradient")
