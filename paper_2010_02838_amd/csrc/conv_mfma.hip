@@ -756,7 +756,14 @@ static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
     if (a.Cs == 64) return launch_tile<MODE, 256, 64, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
     return launch_tile<MODE, 256, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
   }
-  if (a.N <= 32) return launch_tile<MODE, 256, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
+  if (a.N <= 32) {
+    // few channels, few steps (3 to 9): with more workgroups than two per compute unit, two stages (40 KB, three workgroups per
+    // unit, one tile of loads less in front of the first step) against three stages: evaluation of ResNet-20 at
+    // batch 8000 (8192000 x 16 x 144 and smaller) 5024 -> 4154 us a pass (4880 before fragments were read ahead), training step at batch 2048
+    // 5195 -> 4639; with two workgroups or fewer the third stage hides latency (ResNet-20 step at batch 128 1147 against 1161)
+    if (cdiv(a.M, 256) > 512) return launch_tile<MODE, 256, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 2>(a, s);
+    return launch_tile<MODE, 256, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
+  }
   if (a.N <= 64 || g_tune_tile == 1) return launch_tile<MODE, 256, 64, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
   if constexpr (NWRAP == 1) {
     const bool w64 = a.Cs >= 64;

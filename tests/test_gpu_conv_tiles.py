@@ -21,6 +21,9 @@ SHAPES = {
     "two_stages": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), lambda: nets.resnet20(widths=(128,), blocks=(1,)), 150, 16),
     # 320 columns: five 128x64 tiles instead of three of 128x128
     "uneven_columns": (dict(kind=1, widths=[320], blocks=[1], stem_width=320), lambda: nets.resnet20(widths=(320,), blocks=(1,)), 96, 16),
+    # 537 tiles of 256x32, the last one ragged: two stages; three and five steps of 8 and 16 channels, nine of 32
+    "narrow_16": (dict(kind=1, widths=[16], blocks=[1], stem_width=16), lambda: nets.resnet20(widths=(16,), blocks=(1,)), 143, 31),
+    "narrow_32": (dict(kind=1, widths=[32], blocks=[1], stem_width=32), lambda: nets.resnet20(widths=(32,), blocks=(1,)), 143, 31),
     # 520 tiles: 256x128
     "tall": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), lambda: nets.resnet20(widths=(128,), blocks=(1,)), 260, 16),
 }
