@@ -88,6 +88,25 @@ def test_ragged_rows(cols, mode, peers):
     assert np.array_equal(dz, dz2)
 
 
+@pytest.mark.parametrize("cols", [5, 1023, 10007, 32767])
+@pytest.mark.parametrize("mode,peers", [("mse", 0), ("mse", 1), ("mse", 3), ("kl", 1), ("mse_centered_rows", 1)])
+def test_ragged_ignored_rows_are_left_out(cols, mode, peers):
+    """Most rows ignored, whatever they hold (NaN, infinities): zero gradients, nothing of them in the loss."""
+    rows = 9
+    z = synth.logits(rows, cols, 3.0, seed=cols)
+    ps = [synth.logits(rows, cols, 3.0, seed=cols + 1 + j) for j in range(peers)]
+    t = synth.labels(rows, cols, seed=7)
+    skip = np.array([0, 1, 2, 4, 5, 7, 8])
+    t[skip] = -1
+    for inplace in (False, True):
+        _, clean = check(z, ps, t, 0.5, 0.1, mode, inplace=inplace)
+        bad = [a.copy() for a in [z] + ps]
+        for k, a in enumerate(bad):
+            a[skip[k::2]] = (np.nan, np.inf, -np.inf)[k % 3]
+        l, status, dz = run_gpu(bad[0], bad[1:], t, 0.5, 0.1, mode)
+        assert status == 0 and np.isfinite(l).all() and np.array_equal(dz, clean) and np.all(dz[skip] == 0)
+
+
 @pytest.mark.parametrize("mode", ["mse", "mse_rows", "kl", "mse_centered", "mse_centered_rows"])
 @pytest.mark.parametrize("eps", [0.0, 0.1])
 def test_loss_parity_modes(mode, eps):
