@@ -20,6 +20,12 @@ inline bool generic_conv_fits(int64_t B, int64_t H, int64_t W, int64_t Cin, int6
          H < (1 << 24) && W < (1 << 24) && pad >= 0 && stride >= 1;
 }
 
+// Whether a weight gradient goes to conv_generic.hip.  A handful of weights over few pixels is one launch of the plain kernel,
+// a block per weight, all of them resident (1024: four a compute unit); here it is a split launch and its reduction.  Both
+// gradients of the two-layer network, 1 and 1 channels (9 and 27 weights): 1024 pixels 11.2 us plain, 18.9 here; 2048 15.7 and 23.8;
+// 4096 23.1 and 22.1.
+inline bool generic_wgrad_pays(int64_t M, int64_t weights) { return M > 2048 || weights > 1024; }
+
 // ---- weight gradient of conv_generic.hip: a 16 tn x 16 tk tile of dw per block, the pixel range cut into splits ----
 struct GenericWgradPlan {
   int tn, tk;              // 16-wide tiles of output channels and of (tap, input channel) per block
@@ -36,8 +42,10 @@ inline GenericWgradPlan generic_wgrad_plan(int64_t M, int N, int K, bool v4, siz
   p.tk = v4 ? (K <= 32 ? 2 : 4) : 2;
   p.ktiles = up(K, 16 * p.tk);
   p.tiles = up(N, 16 * p.tn) * p.ktiles;
-  // three workgroups per compute unit, but at least two 64-pixel steps each (a split costs one fp32 copy of dw)
-  p.splits = up(768, p.tiles);
+  // three workgroups per compute unit, but at least two 64-pixel steps each (a split costs one fp32 copy of dw), and no splits
+  // of four steps or fewer, where the reduction's launch takes longer (16 and 32 channels, 256 pixels: both gradients 23.7 us
+  // split, 17.4 not; 512 pixels 23.7 and 26.1)
+  p.splits = M <= 256 ? 1 : up(768, p.tiles);
   if (p.splits > up(M, 128)) p.splits = up(M, 128);
   const int64_t by_mem = (int64_t)(partials_bytes / ((size_t)N * K * sizeof(float)));
   if (p.splits > by_mem) p.splits = by_mem;

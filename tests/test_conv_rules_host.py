@@ -34,13 +34,13 @@ int main(int, char** v) {
     return lambda *a: tuple(int(t) for t in run(*a).split())
 
 
-@pytest.mark.parametrize("M", [1, 63, 64, 65, 127, 128, 129, 4097, 98304, 2 ** 24 + 1, 2 ** 30 - 63, 2147475456, 2 ** 31 - 49151, 2 ** 31 - 257])
+@pytest.mark.parametrize("M", [1, 63, 64, 65, 127, 128, 129, 256, 257, 4097, 98304, 2 ** 24 + 1, 2 ** 30 - 63, 2147475456, 2 ** 31 - 49151, 2 ** 31 - 257])
 @pytest.mark.parametrize("N,K,v4", [(1, 9, 0), (1, 27, 0), (16, 144, 1), (33, 45, 0), (320, 180, 1), (4100, 1025, 0)])
 @pytest.mark.parametrize("scratch", [128 << 20, 1 << 10])
 def test_generic_weight_gradient_splits_take_every_row_once(split_rows, M, N, K, v4, scratch):
     splits, end, whole = split_rows(M, N, K, v4, scratch)
     assert end == M and whole
-    assert splits == 1 or splits * N * K * 4 <= scratch
+    assert splits == 1 or (M > 256 and splits * N * K * 4 <= scratch)
 
 
 @pytest.fixture(scope="module")

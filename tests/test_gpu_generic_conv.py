@@ -17,6 +17,8 @@ SHAPES = {
                   66, 32),
     # one channel per load: odd channel counts, ragged tiles in every dimension
     "scalar": (dict(kind=1, widths=[5, 33], blocks=[1, 1], stem_width=5), lambda: nets.resnet20(widths=(5, 33), blocks=(1, 1)), 3, 13),
+    # the same over more pixels (2197): few weights leave the plain weight gradient for the tiled one
+    "scalar_rows": (dict(kind=1, widths=[5, 33], blocks=[1, 1], stem_width=5), lambda: nets.resnet20(widths=(5, 33), blocks=(1, 1)), 13, 13),
     # more than 64 columns and a contraction of many taps; fewer pixels than one step of the weight gradient
     "columns": (dict(kind=1, widths=[68, 132], blocks=[1, 1], stem_width=68), lambda: nets.resnet20(widths=(68, 132), blocks=(1, 1)),
                 1, 7),
@@ -113,8 +115,8 @@ def test_infinite_filter_elements_do_not_reach_past_the_border(monkeypatch, dtyp
 @pytest.mark.parametrize("hw", [(1, 1), (2, 1), (1, 5)])
 def test_infinite_gradients_stay_with_the_taps_that_see_them(monkeypatch, dtype, tol, hw):
     """Weight gradients: taps that lie outside the image at every pixel keep their zero however large dy is."""
-    c = _Net(dtype, 40, hw[0], hw[1], kind=0, widths=[5, 12])
-    dz = np.random.default_rng(2).standard_normal((40, 10)).astype(np.float32)
+    c = _Net(dtype, 2100, hw[0], hw[1], kind=0, widths=[5, 12])
+    dz = np.random.default_rng(2).standard_normal((2100, 10)).astype(np.float32)
     dz[7, 3] = np.inf
     for a, b in _both_forms(monkeypatch, lambda: [c.param(c.pass_(c.flat, dz=dz), o["param_w"]) for o in c.ops if o["kind"] == "conv"]):
         for r, s in ((0, 0), (0, 2), (2, 0), (2, 2)):    # the corner taps see no image of one row or one column
