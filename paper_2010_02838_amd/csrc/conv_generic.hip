@@ -466,10 +466,9 @@ static GenArgs gen_args(const ConvGeom& g) {
 
 template <typename T, int MODE, int VEC>
 static void launch_generic(const GenArgs& a, hipStream_t s) {
-  const int tn = a.N <= 16 ? 1 : a.N <= 32 ? 2 : 4;
+  const int tn = generic_column_tiles(a.N);
   const int64_t nt = cdiv(a.N, 16 * tn);
-  // 128-row tiles once they give every compute unit two workgroups; below that 64-row tiles, twice as many
-  const bool tall = VEC == 4 && cdiv(a.M, 128) * nt >= 512;
+  const bool tall = generic_tall_tiles(a.M, a.N, VEC == 4);
   const dim3 grid((unsigned)cdiv(a.M, tall ? 128 : 64), (unsigned)nt);
   if (tall) {
     constexpr int TM = VEC == 4 ? 2 : 1;

@@ -13,6 +13,7 @@
 // full 16-byte vectors along the channels.  The MFMA "A" operand is the filter tile and "B" the
 // activation tile, so that a lane's 16 accumulators run along the output channels of one pixel.
 #include "kernels.h"
+#include "conv_rules.h"
 #include <algorithm>
 
 namespace cd {
@@ -685,21 +686,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
 // Before (32-wide steps in three stages for all, fragments read and used in the same step; random operands): 12544 x 512 x
 // 4608 76 -> 67 us, 6144 x 640 x 5760 63 -> 52, 8192 x 512 x 2048 28 -> 23, 200704 x 128 x 1152 83 -> 76; the large layers of
 // ResNet-50 at batch 256 are bound by memory and by the clock under full matrix load and gain 1 to 3 %.
-//
-// Tiles, measured with random operands that come from memory (constant ones leave the matrix cores a higher clock), on the
-// layer shapes of ResNet-50 at batch 256 and 50, Wide-ResNet at 96 and the Transformer (us):
-//  - more than 256 tiles of 128x128: 128x256 up to K = 1024 (a short contraction leaves a tile little more than its
-//    prologue and epilogue; 200704 x 512 x 128 93 -> 81, 50176 x 256 x 1024 50 -> 46, 8192 x 1536 x 512 28 -> 25; 12544 x 512 x
-//    2048 42 either way), 256x128 where its rounds of 512 workgroups are no emptier (50176 x 256 x 2304 80 -> 76: the clock
-//    follows the power, and a larger tile moves fewer bytes per product);
-//  - launches that also take a BatchNorm's column sums choose by rows first: a tile is one fp32 partial sum, and where 256 rows
-//    went into one in place of 128 (or the other way) the batch statistics and all roundings behind them moved.  They keep 256x128
-//    for K <= 128 onto N >= 512 and where its last round is 1.2 times fuller, otherwise 128 rows;
-//  - where 128x128 tiles do not fill the 256 compute units, or fill them unevenly, 128x64 and 64x64 tiles do: the cost of
-//    a tile shape is the number of workgroups on the busiest unit times what one costs there (128x64 0.7 of a 128x128
-//    one, 64x64 half), but no less than what one takes alone (1.4, 1.08 and 0.75): 2450 x 512 x 4608 (80 tiles of 128x128)
-//    49 -> 26 on 312 of 64x64, 24576 x 320 x 2880 74 -> 66 on 128x64 (five columns of 64 instead of three of 128).
-enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2, TILE_NARROW = 3, TILE_SMALL = 4 };
+// (Which tile: conv_tile_rule in conv_rules.h.)
 static int igemm_tile(int64_t M, int N, int K, bool small_tiles, bool sums) {
   if (N <= 64) return TILE_SQUARE;
   if (g_tune_tile == 2) return TILE_SQUARE;
@@ -707,27 +694,7 @@ static int igemm_tile(int64_t M, int N, int K, bool small_tiles, bool sums) {
   if (g_tune_tile == 4) return N % 256 == 0 ? TILE_WIDE : TILE_SQUARE;
   if (g_tune_tile == 5) return TILE_NARROW;
   if (g_tune_tile == 6) return TILE_SMALL;
-  const int64_t t128 = cdiv(M, 128) * cdiv(N, 128), t256 = cdiv(M, 256) * cdiv(N, 128);
-  if (sums && t128 > 256) {
-    if (K <= 128 && N >= 512) return TILE_TALL;
-    if (N % 256 == 0 && K <= 1024) return TILE_WIDE;
-    const double e128 = (double)t128 / (double)(cdiv(t128, 768) * 768), e256 = (double)t256 / (double)(cdiv(t256, 512) * 512);
-    if (e256 > 1.2 * e128) return TILE_TALL;
-  }
-  if (t128 > 256 && N % 256 == 0 && K <= 1024) return TILE_WIDE;
-  const double square = std::max(1.4, (double)cdiv(t128, 256));
-  double narrow = 1e30, small = 1e30;
-  if (small_tiles) {   // (their kernels take 64-wide steps)
-    narrow = std::max(1.08, (K <= 1024 ? 0.68 : 0.72) * (double)cdiv(cdiv(M, 128) * cdiv(N, 64), 256));
-    small = std::max(0.75, 0.5 * (double)cdiv(cdiv(M, 64) * cdiv(N, 64), 256));
-  }
-  if (t128 > 256) {
-    if (narrow < 0.97 * square) return TILE_NARROW;
-    if (sums) return TILE_SQUARE;
-    const double e128 = (double)t128 / (double)(cdiv(t128, 512) * 512), e256 = (double)t256 / (double)(cdiv(t256, 512) * 512);
-    return t128 > 512 && e256 >= e128 ? TILE_TALL : TILE_SQUARE;
-  }
-  return small < narrow && small < square ? TILE_SMALL : narrow < square ? TILE_NARROW : TILE_SQUARE;
+  return conv_tile_rule(M, N, K, small_tiles, sums);
 }
 int conv_fprop_tile_class(const ConvGeom& g, bool bias) {
   if (g.Cout <= 64) return 2;

@@ -3,8 +3,52 @@
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
+#include <algorithm>
 
 namespace cd {
+
+// ---- output tile of the matrix-core convolutions (conv_mfma.hip) ------------------------------------------------------------
+// Tiles, measured with random operands that come from memory (constant ones leave the matrix cores a higher clock), on the
+// layer shapes of ResNet-50 at batch 256 and 50, Wide-ResNet at 96 and the Transformer (us):
+//  - more than 256 tiles of 128x128: 128x256 up to K = 1024 (a short contraction leaves a tile little more than its
+//    prologue and epilogue; 200704 x 512 x 128 93 -> 81, 50176 x 256 x 1024 50 -> 46, 8192 x 1536 x 512 28 -> 25; 12544 x 512 x
+//    2048 42 either way), 256x128 where its rounds of 512 workgroups are no emptier (50176 x 256 x 2304 80 -> 76: the clock
+//    follows the power, and a larger tile moves fewer bytes per product);
+//  - of those, launches that also take a BatchNorm's column sums choose by rows first: a tile is one fp32 partial sum, and where
+//    256 rows went into one in place of 128 (or the other way) the batch statistics and all roundings behind them moved.  They
+//    keep 256x128 for K <= 128 onto N >= 512 and where its last round is 1.2 times fuller, otherwise 128 rows.  (With 256
+//    tiles or fewer they choose like the others: a 64-row tile halves the rows of a partial sum, so the statistics of small
+//    batches did move when these tiles came.)
+//  - where 128x128 tiles do not fill the 256 compute units, or fill them unevenly, 128x64 and 64x64 tiles do: the cost of
+//    a tile shape is the number of workgroups on the busiest unit times what one costs there (128x64 0.7 of a 128x128
+//    one, 64x64 half), but no less than what one takes alone (1.4, 1.08 and 0.75): 2450 x 512 x 4608 (80 tiles of 128x128)
+//    49 -> 26 on 312 of 64x64, 24576 x 320 x 2880 74 -> 66 on 128x64 (five columns of 64 instead of three of 128).
+enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2, TILE_NARROW = 3, TILE_SMALL = 4 };   // 128x128 256x128 128x256 128x64 64x64
+// M rows, N > 64 columns, contraction K; small_tiles: the 64-wide steps that the last two need fit; sums: takes column sums
+inline int conv_tile_rule(int64_t M, int N, int K, bool small_tiles, bool sums) {
+  auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const int64_t t128 = cdiv(M, 128) * cdiv(N, 128), t256 = cdiv(M, 256) * cdiv(N, 128);
+  if (sums && t128 > 256) {
+    if (K <= 128 && N >= 512) return TILE_TALL;
+    if (N % 256 == 0 && K <= 1024) return TILE_WIDE;
+    const double e128 = (double)t128 / (double)(cdiv(t128, 768) * 768), e256 = (double)t256 / (double)(cdiv(t256, 512) * 512);
+    if (e256 > 1.2 * e128) return TILE_TALL;
+  }
+  if (t128 > 256 && N % 256 == 0 && K <= 1024) return TILE_WIDE;
+  const double square = std::max(1.4, (double)cdiv(t128, 256));
+  double narrow = 1e30, small = 1e30;
+  if (small_tiles) {   // (their kernels take 64-wide steps)
+    narrow = std::max(1.08, (K <= 1024 ? 0.68 : 0.72) * (double)cdiv(cdiv(M, 128) * cdiv(N, 64), 256));
+    small = std::max(0.75, 0.5 * (double)cdiv(cdiv(M, 64) * cdiv(N, 64), 256));
+  }
+  if (t128 > 256) {
+    if (narrow < 0.97 * square) return TILE_NARROW;
+    if (sums) return TILE_SQUARE;
+    const double e128 = (double)t128 / (double)(cdiv(t128, 512) * 512), e256 = (double)t256 / (double)(cdiv(t256, 512) * 512);
+    return t128 > 512 && e256 >= e128 ? TILE_TALL : TILE_SQUARE;
+  }
+  return small < narrow && small < square ? TILE_SMALL : narrow < square ? TILE_NARROW : TILE_SQUARE;
+}
 
 // ---- what conv_generic.hip takes ----------------------------------------------------------------------------------------
 // 32-bit element offsets, and launches within the runtime's limits: fewer than 2^32 threads along x (256 for each 64 pixels,
@@ -18,6 +62,14 @@ inline bool generic_conv_fits(int64_t B, int64_t H, int64_t W, int64_t Cin, int6
   return in <= rows && out <= rows && Cin <= channels && Cout <= channels && in * Cin < lim && out * Cout < lim &&
          Cout * kh * kw * Cin < lim && ((Cout + 15) / 16) * ((kh * kw * Cin + 31) / 32) + 768 <= blocks &&
          H < (1 << 24) && W < (1 << 24) && pad >= 0 && stride >= 1;
+}
+
+// Forward and data gradient there: 16-column tiles side by side in a block, and whether its rows are 128 instead of 64: once
+// 128-row tiles give every compute unit two workgroups (below that twice as many of 64 rows), with four channels per load.
+inline int generic_column_tiles(int N) { return N <= 16 ? 1 : N <= 32 ? 2 : 4; }
+inline bool generic_tall_tiles(int64_t M, int N, bool v4) {
+  const int64_t bn = 16 * generic_column_tiles(N);
+  return v4 && (M + 127) / 128 * ((N + bn - 1) / bn) >= 512;
 }
 
 // Whether a weight gradient goes to conv_generic.hip.  A handful of weights over few pixels is one launch of the plain kernel,

@@ -80,3 +80,49 @@ def test_generic_convolutions_stay_within_the_launch_limits(generic_fits, geom, 
     assert ok == fits
     if ok:
         assert threads < 2 ** 32 and blocks_y <= 65535
+
+
+SQUARE, TALL, WIDE, NARROW, SMALL = range(5)
+
+
+@pytest.fixture(scope="module")
+def tile(tmp_path_factory):
+    run = compiled(tmp_path_factory.mktemp("tile"),
+                   "int main(int, char** v) { printf(\"%d\", conv_tile_rule(atoll(v[1]), atoi(v[2]), atoi(v[3]), atoi(v[4]) != 0, atoi(v[5]) != 0)); }")
+    return lambda *a: int(run(*a))
+
+
+@pytest.fixture(scope="module")
+def generic_tile(tmp_path_factory):
+    run = compiled(tmp_path_factory.mktemp("generic"),
+                   "int main(int, char** v) { const int n = atoi(v[2]); printf(\"%d %d\", generic_column_tiles(n), "
+                   "(int)generic_tall_tiles(atoll(v[1]), n, atoi(v[3]) != 0)); }")
+    return lambda *a: tuple(int(x) for x in run(*a).split())
+
+
+@pytest.mark.parametrize("shape,want", [
+    # (rows, columns, contraction, 64 channels or more per tap, column sums): the launches that test_gpu_conv_tiles.py is for
+    ((2800, 72, 648, 1, 1), SMALL), ((700, 200, 648, 1, 1), SMALL), ((700, 200, 1800, 1, 1), SMALL),   # "small"
+    ((25600, 128, 1152, 1, 1), SQUARE), ((25600, 128, 64, 1, 1), NARROW),                              # "alone"
+    ((38400, 128, 1152, 1, 1), SQUARE),                                                                # "two_stages"
+    ((24576, 320, 2880, 1, 1), NARROW),                                                                # "uneven_columns"
+    ((66560, 128, 1152, 1, 1), SQUARE),                                                                # "rows_per_sum"
+    ((66759, 128, 1152, 1, 0), TALL),                                                                  # tall tiles, no sums
+    ((2100, 2048, 512, 1, 0), WIDE), ((2100, 512, 2048, 1, 0), SMALL),                                 # dense layers
+    ((70, 200, 72, 1, 0), SMALL), ((8200, 128, 64, 1, 0), SMALL), ((8200, 4104, 128, 1, 0), SQUARE),
+    # and of ResNet-50 at batch 256, with the sums
+    ((802816, 256, 64, 1, 1), WIDE), ((200704, 512, 128, 1, 1), TALL), ((200704, 512, 256, 1, 1), WIDE), ((50176, 256, 1024, 1, 1), WIDE),
+    ((50176, 256, 2304, 1, 1), TALL),
+])
+def test_tile_of_a_convolution(tile, shape, want):
+    assert tile(*shape) == want
+
+
+@pytest.mark.parametrize("rows,cols,vec4,want", [
+    (66309, 12, 1, (1, 1)), (66309, 20, 1, (2, 1)), (66309, 36, 1, (4, 1)), (33635, 68, 1, (4, 1)),   # test_gpu_generic_conv.py
+    (17664, 20, 1, (2, 0)), (66309, 12, 0, (1, 0)), (65408, 16, 1, (1, 0)), (65409, 16, 1, (1, 1)),
+])
+def test_tile_of_a_generic_convolution(generic_tile, rows, cols, vec4, want):
+    assert generic_tile(rows, cols, vec4) == want
+    if want[1] and rows > 66000:
+        assert rows % 128

@@ -12,9 +12,14 @@ from test_gpu_step import check_layers
 pytestmark = pytest.mark.gpu
 
 SHAPES = {
-    # four channels per load, one and two column tiles of 16, 128-row tiles with a ragged last one (66 * 32 * 32 rows)
+    # four channels per load; 66309 rows: 519 tiles of 128 rows, the last one ragged; 12 columns (one tile of 16), and 20 behind
+    # the stride, on 64-row tiles
     "vec4_tall": (dict(kind=1, widths=[12, 20], blocks=[1, 1], stem_width=12), lambda: nets.resnet20(widths=(12, 20), blocks=(1, 1)),
-                  66, 32),
+                  69, 31),
+    # the same 128-row tiles with two and with four 16-column tiles side by side, and with two such blocks of columns (33635 rows)
+    "vec4_tall_20": (dict(kind=1, widths=[20], blocks=[1], stem_width=20), lambda: nets.resnet20(widths=(20,), blocks=(1,)), 69, 31),
+    "vec4_tall_36": (dict(kind=1, widths=[36], blocks=[1], stem_width=36), lambda: nets.resnet20(widths=(36,), blocks=(1,)), 69, 31),
+    "vec4_tall_68": (dict(kind=1, widths=[68], blocks=[1], stem_width=68), lambda: nets.resnet20(widths=(68,), blocks=(1,)), 35, 31),
     # one channel per load: odd channel counts, ragged tiles in every dimension
     "scalar": (dict(kind=1, widths=[5, 33], blocks=[1, 1], stem_width=5), lambda: nets.resnet20(widths=(5, 33), blocks=(1, 1)), 3, 13),
     # the same over more pixels (2197): few weights leave the plain weight gradient for the tiled one
