@@ -712,8 +712,7 @@ static int launch_tile(IgemmArgs& a, hipStream_t s) {
   return mt;
 }
 
-// returns the number of m-tiles (= statistics chunks when STATS; 64-row tiles occur below 256 tiles of 128x128 only, so that
-// there are never more than cdiv(M, 128) + 257 chunks)
+// returns the number of m-tiles (= statistics chunks when STATS; conv_stat_chunks_max bounds it)
 template <int MODE, int STATS, int NWRAP, bool REMAP, int EPI>
 static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
   a.pointwise = (a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.pad_w == 0 && a.Hs == a.Hd &&

@@ -50,6 +50,14 @@ inline int conv_tile_rule(int64_t M, int N, int K, bool small_tiles, bool sums) 
   return small < narrow && small < square ? TILE_SMALL : narrow < square ? TILE_NARROW : TILE_SQUARE;
 }
 
+// Row tiles, i.e. partial sums, of a launch over M rows that takes column sums, at the most: 64-row tiles are chosen only where
+// there are at most 256 tiles of 128x128.
+inline int64_t conv_stat_chunks_max(int64_t M) { return M <= 256 * 128 ? (M + 63) / 64 : (M + 127) / 128; }
+// room for them and for the 32 rows they are folded into, each of `pitch` floats (stat_pitch)
+inline bool conv_sums_fit(int64_t M, int64_t pitch, size_t bytes) {
+  return (size_t)(conv_stat_chunks_max(M) + 32) * pitch * sizeof(float) <= bytes;
+}
+
 // ---- what conv_generic.hip takes ----------------------------------------------------------------------------------------
 // 32-bit element offsets, and launches within the runtime's limits: fewer than 2^32 threads along x (256 for each 64 pixels,
 // input or output, and for each tile of a weight gradient, at the least 16 x 32 elements), 65535 blocks along y (64 channels

@@ -122,8 +122,7 @@ namespace cd {
 bool conv_mfma_supported(const ConvGeom& g);
 // y[M][Cout] = im2col(x)[M][K] * w[Cout][K]^T.  With stat_partials the kernel also writes per-tile
 // column sums and sums of squares, [chunks][stat_pitch(Cout)] fp32, and returns the number of chunks
-// (one per row tile: needs (M/128 + 258) * stat_pitch(Cout) floats at most, the tiles of 64 rows being chosen for few rows
-// only); see bn_stats.
+// (one per row tile, conv_stat_chunks_max(M) at most: conv_sums_fit says whether they fit); see bn_stats.
 // bias (nullable, [Cout] bf16) is added and, with relu, the result clamped at zero before rounding.
 int conv_fprop_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, bool relu, bf16_t* y, const ConvGeom& g,
                     float* stat_partials, hipStream_t s);

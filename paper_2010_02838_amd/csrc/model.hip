@@ -829,7 +829,7 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
           // BatchNorm that follows gets its column sums from the epilogue like behind a dense convolution
           const bool fuse = bn_mode == CD_BN_BATCH_STATS && oi + 1 < m->ops.size() && m->ops[oi + 1].kind == OP_BN &&
                             m->ops[oi + 1].x == o.y &&
-                            (size_t)(g.M() / 128 + 1 + 32) * stat_pitch(g.Cout) * sizeof(float) <= c.plan.partials_bytes;
+                            conv_sums_fit(g.M(), stat_pitch(g.Cout), c.plan.partials_bytes);
           ProfScope pr(CD_K_CONV_FPROP_NARROW, c.s, 2.0 * g.M() * g.Cout * (double)g.kh * g.kw * grouped_mfma_slice(g.Cin, o.groups),
                        conv_bytes(m, g));
           stat_chunks = conv_grouped_fprop_mfma(static_cast<const bf16_t*>(in), static_cast<const bf16_t*>(c.P(o.pw)),
@@ -889,7 +889,7 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
           // a BatchNorm that follows directly gets its column sums from the convolution's epilogue
           const bool fuse = bn_mode == CD_BN_BATCH_STATS && o.pb < 0 && oi + 1 < m->ops.size() &&
                             m->ops[oi + 1].kind == OP_BN && m->ops[oi + 1].x == o.y &&
-                            (size_t)(g.M() / 128 + 1 + 32) * stat_pitch(g.Cout) * sizeof(float) <= c.plan.partials_bytes;
+                            conv_sums_fit(g.M(), stat_pitch(g.Cout), c.plan.partials_bytes);
           stat_chunks = conv_fprop_mfma(src, w, static_cast<const bf16_t*>(c.P(o.pb)), o.relu, static_cast<bf16_t*>(out), gp,
                                         fuse ? c.partials() : nullptr, c.s);
           stat_tensor = fuse ? o.y : -1;
@@ -1329,7 +1329,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
             bool with_sums = false;
             if (pi == (int)i - 1 && m->ops[pi].kind == OP_BN && g.stride == 1 && !separate_bn_reduction() &&
                 !pool_fused(m, pi) && m->ops[pi].x != 0 && (!m->ops[pi].relu || c.plan.aux[pi] != 0) &&
-                (size_t)(batch * g.H * g.W / 128 + 1 + 32) * stat_pitch(g.Cin) * sizeof(float) <= c.plan.partials_bytes) {
+                conv_sums_fit(batch * g.H * g.W, stat_pitch(g.Cin), c.plan.partials_bytes)) {
               const Op& b = m->ops[pi];
               sums.x = static_cast<const bf16_t*>(c.act(b.x));
               sums.mask = b.relu ? reinterpret_cast<const uint8_t*>(c.ws + c.plan.aux[pi]) : nullptr;

@@ -126,3 +126,32 @@ def test_tile_of_a_generic_convolution(generic_tile, rows, cols, vec4, want):
     assert generic_tile(rows, cols, vec4) == want
     if want[1] and rows > 66000:
         assert rows % 128
+
+
+def test_partial_sums_fit_where_the_check_says_so(tmp_path):
+    """Over row, column and contraction counts: the row tiles of a launch with column sums are at most conv_stat_chunks_max, and an
+    area of exactly that many rows and the 32 fold rows is accepted, a float less is not."""
+    run = compiled(tmp_path, """
+int main() {
+  const long long Ms[] = {1, 63, 64, 65, 128, 129, 2450, 8192, 12544, 16320, 16384, 16385, 24576, 32704, 32767, 32768, 32769, 32832, 50176, 65536, 200704, 802816, 3211264};
+  const int Ns[] = {65, 72, 128, 129, 256, 320, 512, 640, 1024, 2048, 4096}, Ks[] = {64, 128, 256, 576, 1024, 2304, 4608, 36864}, rows[] = {128, 256, 128, 128, 64};
+  long long worst = 0;
+  for (long long M : Ms)
+    for (int N : Ns) {
+      const long long pitch = 2 * N + 64;
+      const size_t need = (size_t)(conv_stat_chunks_max(M) + 32) * pitch * 4;
+      if (!conv_sums_fit(M, pitch, need) || conv_sums_fit(M, pitch, need - 4)) { printf("check %lld %d", M, N); return 0; }
+      for (int K : Ks)
+        for (int w64 = 0; w64 < 2; w64++) {
+          const int r = rows[conv_tile_rule(M, N, K, w64 != 0, true)];
+          const long long chunks = (M + r - 1) / r;
+          if (chunks > conv_stat_chunks_max(M)) { printf("%lld %d %d: %lld chunks", M, N, K, chunks); return 0; }
+          if (chunks - (M / 128 + 1) > worst) worst = chunks - (M / 128 + 1);
+        }
+    }
+  printf("ok %lld", worst);
+}
+""")
+    out = run().split()
+    assert out[0] == "ok"
+    assert int(out[1]) > 32     # more than 128-row tiles and the fold rows' room would have held
