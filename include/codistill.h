@@ -373,13 +373,14 @@ int codistill_tensor_info(const cd_model* m, int64_t batch, int64_t idx, cd_act_
 /* ---- measurement aid -------------------------------------------------------------------- */
 /* kernel classes for the built-in timer */
 enum {
-  CD_K_CONV_FPROP = 0,        /* bf16 MFMA fprop launches on 128x128 tiles (one kernel symbol) */
+  CD_K_CONV_FPROP = 0,        /* bf16 MFMA fprop launches on 128x128 tiles */
   CD_K_CONV_DGRAD = 1, CD_K_CONV_WGRAD = 2,
   CD_K_NORM = 3,              /* normalisation launches other than CD_K_BN_APPLY */
   CD_K_GLUE = 4, CD_K_LINEAR = 5, CD_K_LOSS = 6, CD_K_SGD = 7,
   CD_K_CONV_FPROP_NARROW = 8, /* every other fprop launch (other tile shapes, plain kernels) */
   CD_K_BN_APPLY = 9,          /* BatchNorm forward: the elementwise normalise (+ residual, ReLU) kernel alone */
-  CD_K_CONV_FPROP_WIDE = 10,  /* bf16 MFMA fprop launches on 128x256 tiles (one kernel symbol) */
+  CD_K_CONV_FPROP_WIDE = 10,  /* bf16 MFMA fprop launches on 128x256 tiles (in training one kernel symbol,
+                                 in evaluation, without the column sums, another) */
   CD_K_ATTN = 11,             /* attention forward and backward launches */
   CD_K_COUNT = 12
 };

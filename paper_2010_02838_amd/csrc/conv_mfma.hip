@@ -696,11 +696,11 @@ static int igemm_tile(int64_t M, int N, int K, bool small_tiles, bool sums) {
   if (g_tune_tile == 6) return TILE_SMALL;
   return conv_tile_rule(M, N, K, small_tiles, sums);
 }
-int conv_fprop_tile_class(const ConvGeom& g, bool bias) {
+int conv_fprop_tile_class(const ConvGeom& g, bool bias, bool sums) {
   if (g.Cout <= 64) return 2;
   if (g.Cin < BK) return 0;
-  const int t = igemm_tile(g.M(), g.Cout, (int)g.K(), g.Cin >= 64, !bias);
-  return t == TILE_SQUARE ? 0 : (t == TILE_WIDE ? 1 : 2);
+  const int t = igemm_tile(g.M(), g.Cout, (int)g.K(), g.Cin >= 64, sums);
+  return t == TILE_SQUARE || (t == TILE_TALL && bias) ? 0 : (t == TILE_WIDE ? 1 : 2);   // (no 256x128 kernel with a bias)
 }
 
 template <int MODE, int BM, int BN, int WM, int WN, int STATS, int NWRAP, bool REMAP, int EPI, int BKT, int NS>

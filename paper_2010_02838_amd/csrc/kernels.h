@@ -126,8 +126,8 @@ bool conv_mfma_supported(const ConvGeom& g);
 // bias (nullable, [Cout] bf16) is added and, with relu, the result clamped at zero before rounding.
 int conv_fprop_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, bool relu, bf16_t* y, const ConvGeom& g,
                     float* stat_partials, hipStream_t s);
-// which kernel conv_fprop_mfma runs this shape with: 0 the 128x128 tiles, 1 the 128x256 tiles, 2 any other
-int conv_fprop_tile_class(const ConvGeom& g, bool bias);
+// which tiles conv_fprop_mfma runs this shape on, with a bias or with stat_partials (sums): 0 128x128, 1 128x256, 2 any other
+int conv_fprop_tile_class(const ConvGeom& g, bool bias, bool sums);
 // dx[B*H*W][Cin] (+)= gather(dy)[.][taps*Cout] * wt[Cin][taps*Cout]^T.  w is the filter as stored; wt is
 // scratch of at least Cout*K + 32 elements that receives its re-laid-out copy (or copies, per parity
 // class, for stride 2).  addend (nullable; stride 1 and accumulate == false only): dx = product + addend,

@@ -882,14 +882,14 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
             src = c.xpack();
             w = c.wpack();
           }
-          const int tc = conv_fprop_tile_class(g, o.pb >= 0);
-          ProfScope pr(tc == 0 ? CD_K_CONV_FPROP : (tc == 1 ? CD_K_CONV_FPROP_WIDE : CD_K_CONV_FPROP_NARROW), c.s,
-                       2.0 * g.M() * g.Cout * g.K(),
-                       conv_bytes(m, g));
           // a BatchNorm that follows directly gets its column sums from the convolution's epilogue
           const bool fuse = bn_mode == CD_BN_BATCH_STATS && o.pb < 0 && oi + 1 < m->ops.size() &&
                             m->ops[oi + 1].kind == OP_BN && m->ops[oi + 1].x == o.y &&
                             conv_sums_fit(g.M(), stat_pitch(g.Cout), c.plan.partials_bytes);
+          const int tc = conv_fprop_tile_class(g, o.pb >= 0, fuse);
+          ProfScope pr(tc == 0 ? CD_K_CONV_FPROP : (tc == 1 ? CD_K_CONV_FPROP_WIDE : CD_K_CONV_FPROP_NARROW), c.s,
+                       2.0 * g.M() * g.Cout * g.K(),
+                       conv_bytes(m, g));
           stat_chunks = conv_fprop_mfma(src, w, static_cast<const bf16_t*>(c.P(o.pb)), o.relu, static_cast<bf16_t*>(out), gp,
                                         fuse ? c.partials() : nullptr, c.s);
           stat_tensor = fuse ? o.y : -1;

@@ -110,6 +110,7 @@ def generic_tile(tmp_path_factory):
     ((66759, 128, 1152, 1, 0), TALL),                                                                  # tall tiles, no sums
     ((2100, 2048, 512, 1, 0), WIDE), ((2100, 512, 2048, 1, 0), SMALL),                                 # dense layers
     ((70, 200, 72, 1, 0), SMALL), ((8200, 128, 64, 1, 0), SMALL), ((8200, 4104, 128, 1, 0), SQUARE),
+    ((10240, 512, 64, 1, 1), TALL), ((10240, 512, 128, 1, 1), TALL), ((10240, 512, 64, 1, 0), WIDE), ((10240, 512, 128, 1, 0), WIDE),  # timer classes
     # and of ResNet-50 at batch 256, with the sums
     ((802816, 256, 64, 1, 1), WIDE), ((200704, 512, 128, 1, 1), TALL), ((200704, 512, 256, 1, 1), WIDE), ((50176, 256, 1024, 1, 1), WIDE),
     ((50176, 256, 2304, 1, 1), TALL),

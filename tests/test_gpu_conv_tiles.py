@@ -67,3 +67,31 @@ def test_tall_tiles_without_column_sums(monkeypatch):
 def test_dense_layer_tiles_bf16_layers(shape):
     c = head_case("bf16", *shape)
     check_layers(c, c.gpu())
+
+
+def _timer_classes(m, batch, res, evaluation):
+    """launches per class of the built-in timer in one forward pass"""
+    from paper_2010_02838_amd import binding as B
+    dev = "cuda:0"
+    x = torch.randn(batch, res, res, 3, device=dev).to(m.torch_dtype)
+    run = torch.ones(m.bn_running_elements(), device=dev)
+    B.profile_reset()
+    B.profile_enable(True)
+    try:
+        B.codistill_forward(m, torch.zeros(m.n_elements, dtype=m.torch_dtype, device=dev), x,
+                            torch.empty(m.workspace_bytes(batch, False), dtype=torch.uint8, device=dev), torch.empty(batch, 10, device=dev), False,
+                            B.CD_BN_RUNNING if evaluation else B.CD_BN_BATCH_STATS, run)
+        torch.cuda.synchronize()
+        return {k: v["launches"] for k, v in B.profile_collect().items()}
+    finally:
+        B.profile_enable(False)
+        B.profile_reset()
+
+
+def test_timer_class_of_a_convolution_is_that_of_its_tiles():
+    """10240 rows: the 1x1 convolutions onto 512 columns (contractions of 64 and 128) take 256x128 tiles with the column sums and
+    128x256 ones without; every other convolution has 64 or 128 columns."""
+    from paper_2010_02838_amd import binding as B
+    m = B.Model(B.arch_preset(2, in_h=64, in_w=64, classes=10, widths=[128], blocks=[1], stem_width=64), B.CD_BF16)
+    assert _timer_classes(m, 40, 64, evaluation=False)["conv_fprop_wide"] == 0
+    assert _timer_classes(m, 40, 64, evaluation=True)["conv_fprop_wide"] == 2
