@@ -907,9 +907,11 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
         const void* res = o.res >= 0 ? c.act(o.res) : nullptr;
         float* running = bn_running ? bn_running + 2 * m->bn_off[o.bn_slot] : nullptr;   // this op's [mean | var]
         const bool pooled = pool_fused(m, (int)oi);
-        if (bn_mode == CD_BN_RUNNING) {   // (only the fused max-pool wants the statistics as such)
-          ProfScope pr(CD_K_NORM, c.s, 0, 0.0);
-          if (pooled) bn_stats_from_running(dt, running, c.P(o.pw), c.P(o.pb), c.stats(o), tx.c, c.s);
+        if (bn_mode == CD_BN_RUNNING) {
+          if (pooled) {   // (only the fused max-pool wants the statistics as such)
+            ProfScope pr(CD_K_NORM, c.s, 0, 0.0);
+            bn_stats_from_running(dt, running, c.P(o.pw), c.P(o.pb), c.stats(o), tx.c, c.s);
+          }
         } else {
           ProfScope pr(CD_K_NORM, c.s, 0, fused ? 0.0 : (double)M * tx.c * m->esize());
           bn_stats(dt, in, c.P(o.pw), c.P(o.pb), M, tx.c, c.stats(o), c.partials(), fused ? stat_chunks : 0,

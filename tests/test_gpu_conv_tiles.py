@@ -95,3 +95,14 @@ def test_timer_class_of_a_convolution_is_that_of_its_tiles():
     m = B.Model(B.arch_preset(2, in_h=64, in_w=64, classes=10, widths=[128], blocks=[1], stem_width=64), B.CD_BF16)
     assert _timer_classes(m, 40, 64, evaluation=False)["conv_fprop_wide"] == 0
     assert _timer_classes(m, 40, 64, evaluation=True)["conv_fprop_wide"] == 2
+
+
+def test_timer_counts_only_launches_that_are_made():
+    """Evaluation: one normalisation pass per BatchNorm, none in front of it; the one that also computes the max-pool has two
+    (statistics, then both in one pass)."""
+    from paper_2010_02838_amd import binding as B
+    m = B.Model(B.arch_preset(2, in_h=64, in_w=64, classes=10, widths=[128], blocks=[1], stem_width=64), B.CD_BF16)
+    bn = [o for o in m.graph(4)[0] if o["kind"] == "bn"]
+    n = _timer_classes(m, 4, 64, evaluation=True)
+    assert n["bn_apply"] == len(bn) - 1 and sum(o["fused_pool"] for o in bn) == 1
+    assert n["norm"] == 2
