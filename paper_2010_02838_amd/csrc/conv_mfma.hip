@@ -148,20 +148,18 @@ __device__ inline void wait_step() {
 }
 
 // LDS tiles are [row][BKT elements], rows of 64 (BKT = 32) or 128 bytes without padding; the 16-byte column cv of a row
-// is stored at column cv ^ swz(row), which makes both the 16-byte stores (in lane order) and the MFMA fragment reads (16
-// consecutive rows, one column) bank-conflict free.  A thread's rows are a multiple of 32 apart and share their swz.
+// is stored at column cv ^ swz(row) (element row * BKT + 8 (cv ^ swz(row))), which makes both the 16-byte stores (in lane
+// order) and the MFMA fragment reads (16 consecutive rows, one column) bank-conflict free.  A thread's rows are a multiple of 32
+// apart and share their swz.
 template <int BKT> __device__ inline int lds_swz(int row) { return BKT == 32 ? (row >> 2) & 3 : (row >> 1) & 7; }
-template <int BKT> __device__ inline int lds_off(int row, int cv) { return row * BKT + ((cv ^ lds_swz<BKT>(row)) << 3); }
 
 // MODE 0: fprop gather, hs = hd*stride - pad + r.
 // MODE 1: dgrad gather for stride 1, hs = hd + pad - r.
 // (The dgrad of a stride-2 convolution is run as four MODE 0 problems, one per parity of the output
 // pixel; see conv_dgrad_mfma.)
 //
-// Main loop: one barrier per step of BKT contraction elements, NS stages in LDS.  At step kt the waves wait for
-// their own loads of tile kt (issued NS - 1 steps earlier), meet at the barrier, issue the loads of tile kt+NS-1
-// into the stage that tile kt-1 occupied, read the fragments of tile kt and multiply; the fragments of the next
-// sub-step are read while the matrix cores work on the current one, except where their registers would spill.
+// Main loop: one barrier per step of BKT contraction elements, NS stages in LDS, the loads NS - 1 steps ahead of their use, the
+// fragments of the next sub-step read while the matrix cores work on the current one; what a step waits for stands at the loop.
 // The loads are inline assembly: the compiler does not track them, so it cannot serialise them against the LDS reads.
 // F32OUT: the output is fp32 [M][N] (dense layers that produce logits); like the bf16 output it is
 // transposed through LDS so that a store instruction writes whole 256-byte row segments.
@@ -221,7 +219,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   // ---- per-thread gather state ---------------------------------------------------------------------
   // A wave's load instruction fills 64 / SL consecutive tile rows (64 lanes x 16 bytes, in lane order), so thread tid owns
   // LDS slot tid % SL of rows tid / SL + RPP_L j; the slot holds the 16-byte column slot ^ swz(row) of the tile (see
-  // lds_off), the same for all of the thread's rows.
+  // lds_swz), the same for all of the thread's rows.
   const int lrow = tid / SL;
   const int kvec = (tid % SL) ^ lds_swz<BKT>(lrow);
   const int P = a.src_pitch ? a.src_pitch : a.Cs;   // channels per pixel of the gathered tensor
@@ -322,6 +320,8 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   // now and arrives during the main loop (vector memory operations retire in order: the main loop's first wait also waits for
   // these, and the compiler's own waits for them can only be too strict); its ReLU bits, a byte per vector, follow behind the
   // loop: sixteen registers through the loop would spill (128x256) or cost the third workgroup per compute unit (128x128).
+  // (The input's vectors leave the two 128-accumulator tiles short of 6 (256x128) and 2 (128x256) registers: those are stored to
+  // scratch memory in front of the loop and loaded behind it.)
   constexpr int BS_LPR = WN / 8, BS_RPP = 64 / BS_LPR, BS_EROWS = WM < 64 ? WM : 64;
   constexpr int BS_NV = STATS == 2 ? (WM / BS_EROWS) * (BS_EROWS / BS_RPP) : 1;
   uint4 bs_x[BS_NV];

@@ -61,8 +61,8 @@ inline bool conv_sums_fit(int64_t M, int64_t pitch, size_t bytes) {
 // ---- what conv_generic.hip takes ----------------------------------------------------------------------------------------
 // 32-bit element offsets, and launches within the runtime's limits: fewer than 2^32 threads along x (256 for each 64 pixels,
 // input or output, and for each tile of a weight gradient, at the least 16 x 32 elements), 65535 blocks along y (64 channels
-// each).  (The runtime refused a launch of 2^32 threads, but took one of 2^33 - 2^15,
-// whose count does not fit 32 bits, without an error.)  Beyond that the plain kernels run, one thread per element with 64-bit offsets.
+// each).  (The runtime refused a launch of 2^32 threads, but took one of 2^33 - 2^15, whose count does not fit 32 bits, without
+// an error.)  Beyond that the plain kernels run, one thread per element with 64-bit offsets.
 inline bool generic_conv_fits(int64_t B, int64_t H, int64_t W, int64_t Cin, int64_t Ho, int64_t Wo, int64_t Cout, int64_t kh,
                               int64_t kw, int64_t stride, int64_t pad) {
   const int64_t lim = 1LL << 31, blocks = (1LL << 24) - 1, rows = 64 * blocks, channels = 64 * 65535LL;

@@ -29,7 +29,8 @@ void conv_dgrad_simple(int dtype, const void* dy, const void* w, void* dx, const
 void conv_wgrad_simple(int dtype, const void* x, const void* dy, float* dw, const ConvGeom& g, hipStream_t s);
 // ---- conv_generic.hip: the same convolutions on the fp32 matrix instruction, any channel counts -------------------
 // What runs where the bf16 matrix-core kernels do not (fp32 models, channel counts that are no multiple of 8); the plain
-// kernels above remain for CODISTILL_FORCE_SIMPLE and for tensors of 2^31 elements or 2^30 pixels and more (generic_conv_fits).
+// kernels above remain for CODISTILL_FORCE_SIMPLE, for tensors of 2^31 elements or 2^30 pixels and more (generic_conv_fits) and
+// for weight gradients of few weights over few pixels (generic_wgrad_pays).
 bool conv_generic_supported(const ConvGeom& g);
 void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
                         hipStream_t s);

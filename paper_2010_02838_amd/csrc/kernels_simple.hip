@@ -1,6 +1,7 @@
 // Plain layer kernels: one thread per output element, fp32 arithmetic, fp32 or bf16 storage.
-// They define the layers for any shape.  Pooling and the small layers around the convolutions run on them; the
-// convolutions themselves only with CODISTILL_FORCE_SIMPLE or for tensors of 2^31 elements or 2^30 pixels and more.
+// They define the layers for any shape.  Pooling and the small layers around the convolutions run on them; of the
+// convolutions the weight gradients of few weights over few pixels (generic_wgrad_pays), and all with CODISTILL_FORCE_SIMPLE or
+// for tensors of 2^31 elements or 2^30 pixels and more.
 #include "kernels.h"
 
 namespace cd {
@@ -348,7 +349,7 @@ void maxpool_bwd(int dtype, const void* x, const void* dy, const uint8_t* argmax
 // Global average pool.  A block owns one sample and up to BLOCK vectors of V channels; the rows of the image are dealt to the
 // BLOCK / vectors row groups, several loads in flight per thread, and the groups are added in LDS in a fixed order.  (One
 // thread per channel with a serial loop over the pixels left the chip idle: 8 samples of 32x32x32 fp32 took 227 us, one
-// load latency per pixel; now 7 us.)
+// load latency per pixel; now 5 us.)
 template <typename T, int V, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) gap_fwd_k(const T* __restrict__ x, T* __restrict__ y, int HW, int C) {
   __shared__ float sm[BLOCK * V];

@@ -796,7 +796,8 @@ void bn_stats_from_running(int dtype, const float* running, const void* gamma, c
 
 // The elementwise pass with the running averages.  Where a thread keeps its channels (channel vectors per row divide the grid
 // stride, which elt_grid arranges for all but the largest launches) it needs no statistics kernel in front of it: that launch
-// took 4.5 us per layer, as long as many of the passes behind it.
+// took 4.5 us per layer, as long as many of the passes behind it; the channels' constants cost every block a little instead.
+// Evaluation of ResNet-50, with the launches and so: batch 1 619 -> 585 us, 50 1747 -> 1715, 256 and 512 no difference.
 template <typename T>
 static void bn_apply_running_t(const T* x, const T* res, bool relu, T* y, int64_t M, int C, const float* running,
                                const T* gamma, const T* beta, float* stats, uint8_t* mask, hipStream_t s) {
