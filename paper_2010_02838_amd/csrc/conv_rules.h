@@ -1,4 +1,4 @@
-// Host rules of the convolution launches, in plain integers: no HIP header is needed, so that they can be compiled and
+// Host rules of the convolution and dense-layer launches, in plain integers: no HIP header is needed, so that they can be compiled and
 // checked on a machine without a GPU.  (constexpr functions are callable from device code.)
 #pragma once
 #include <stddef.h>
@@ -118,6 +118,17 @@ inline GenericWgradPlan generic_wgrad_plan(int64_t M, int N, int K, bool v4, siz
 // not fit 32 bits)
 constexpr int generic_split_end(int M, int mbeg, int m_per_split) {
   return M - mbeg > m_per_split ? mbeg + m_per_split : M;
+}
+
+// ---- weight gradient of a dense layer (kernels_simple.hip) -----------------------------------------------------------------
+// A block per 64 of the F + 1 columns and 4 classes, the column tiles of 4 classes side by side (they read the same part of dy:
+// 20000 classes of 512 columns over 256 rows 922 us so, 1388 with the classes side by side), as many classes along x as a
+// launch of fewer than 2^32 threads has room for, the rest along y.
+struct LinearDwGrid { int64_t x, y; };
+inline LinearDwGrid linear_dw_grid(int F, int C) {
+  const int64_t tiles = ((int64_t)F + 64) / 64, groups = ((int64_t)C + 3) / 4, most = std::max<int64_t>(1, (1 << 22) / tiles);
+  const int64_t per = std::min(groups, most);
+  return {tiles * per, (groups + per - 1) / per};
 }
 
 }  // namespace cd

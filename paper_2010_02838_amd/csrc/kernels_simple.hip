@@ -3,6 +3,7 @@
 // convolutions the weight gradients of few weights over few pixels (generic_wgrad_pays), and all with CODISTILL_FORCE_SIMPLE or
 // for tensors of 2^31 elements or 2^30 pixels and more.
 #include "kernels.h"
+#include "conv_rules.h"
 
 namespace cd {
 
@@ -470,8 +471,9 @@ __global__ void __launch_bounds__(256) linear_dw_k(const float* __restrict__ dy,
                                                    int C) {
   __shared__ float sm[4][4][64];
   const int fl = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const unsigned ft = (unsigned)(F + 64) / 64u;   // 64-column tiles of the F + 1 columns
-  const int f = (int)(blockIdx.x % ft) * 64 + fl, c0 = (int)(blockIdx.x / ft) * 4;
+  const unsigned ft = (unsigned)(F + 64) / 64u;   // 64-column tiles of the F + 1 columns (linear_dw_grid)
+  const int f = (int)(blockIdx.x % ft) * 64 + fl, c0 = (int)(blockIdx.y * (gridDim.x / ft) + blockIdx.x / ft) * 4;
+  if (c0 >= C) return;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   if (f <= F) {
 #pragma unroll 4
@@ -500,7 +502,8 @@ void linear_bwd(int dtype, const void* x, const void* w, const float* dy, void* 
                 float* db, int64_t B, int F, int C, hipStream_t s) {
   CD_DISPATCH_T(dtype, {
     hipLaunchKernelGGL(linear_dx_k<T>, grid1d(B * F), dim3(256), 0, s, dy, (const T*)w, (T*)dx, (int)accumulate, B, F, C);
-    hipLaunchKernelGGL(linear_dw_k<T>, dim3((unsigned)(cdiv(F + 1, 64) * cdiv(C, 4))), dim3(256), 0, s, dy, (const T*)x, dw, db, B, F, C);
+    const LinearDwGrid g = linear_dw_grid(F, C);
+    hipLaunchKernelGGL(linear_dw_k<T>, dim3((unsigned)g.x, (unsigned)g.y), dim3(256), 0, s, dy, (const T*)x, dw, db, B, F, C);
   });
 }
 

@@ -1311,8 +1311,10 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
             if (s2d_form(g)) s2d_unpack_dw(dw, G(o.pw), g.Cout, g.kh, gp.kh, 2 * gp.pad - g.pad, ws_);
             else if (g.Cin == 3) unpad_c8_to_c3(dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, ws_);
           } else {
-            if (use_generic(g) && generic_wgrad_pays(g.M(), (int64_t)g.Cout * g.K())) conv_wgrad_generic(dt, in, dy, G(o.pw), g, wpart, c.plan.partials_bytes, c.s);
-            else conv_wgrad_simple(dt, in, dy, G(o.pw), g, c.s);
+            if (use_generic(g) && generic_wgrad_pays(g.M(), (int64_t)g.Cout * g.K()))
+              conv_wgrad_generic(dt, in, dy, G(o.pw), g, wpart, c.plan.partials_bytes, c.s);
+            else
+              conv_wgrad_simple(dt, in, dy, G(o.pw), g, c.s);
           }
         }
         if (o.x != 0) {

@@ -156,3 +156,13 @@ int main() {
     out = run().split()
     assert out[0] == "ok"
     assert int(out[1]) > 32     # more than 128-row tiles and the fold rows' room would have held
+
+
+@pytest.mark.parametrize("F,C", [(1, 1), (63, 5), (64, 1000), (2048, 1000), (192, 1 << 24), (254, 1 << 24), (16000, 1 << 18)])
+def test_dense_weight_gradient_stays_within_the_launch_limits(tmp_path, F, C):
+    """The most classes that a model takes (2^24) and inputs for which a thread per weight is a launch of fewer than 2^32 threads."""
+    x, y = (int(v) for v in compiled(tmp_path, "int main(int, char** v) { const LinearDwGrid g = linear_dw_grid(atoi(v[1]), atoi(v[2])); "
+                                     "printf(\"%lld %lld\", (long long)g.x, (long long)g.y); }")(F, C).split())
+    tiles, groups = -(-(F + 1) // 64), -(-C // 4)
+    assert x * 256 < 2 ** 32 and y <= 65535 and x % tiles == 0
+    assert (y - 1) * (x // tiles) < groups <= y * (x // tiles)    # the last row of blocks is wanted, and the last class has a block
