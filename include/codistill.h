@@ -211,7 +211,8 @@ int codistill_workspace_bytes(const cd_model* m, int64_t batch, int save_for_bac
  *                      0: keep nothing (peer model; its logits are constants)
  *   bn_mode     CD_BN_BATCH_STATS: every BatchNorm uses the statistics of this batch (training; also what the stale
  *               peer's forward pass uses).  CD_BN_RUNNING: evaluation mode, the running averages in bn_running are
- *               used instead (save_for_backward must be 0)
+ *               used instead (save_for_backward must be 0).  A convolution then applies the BatchNorm behind it as it
+ *               stores (its own output is not written); with the built-in timer on that is a launch of its own
  *   bn_running  NULL, or device fp32 [codistill_bn_running_elements(m)]: per BatchNorm op, in graph order, its
  *               running mean [C] then running variance [C] (the caller initialises them to 0 and 1).  With
  *               CD_BN_BATCH_STATS and a non-NULL pointer the pass also updates them: 0.9 old + 0.1 batch value,

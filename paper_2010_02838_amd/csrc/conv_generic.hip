@@ -15,6 +15,7 @@
 // reads 20 channels, 62.2 -> 8.75 ms; the two-layer fp32 network's step on 8 images 725 -> 378 us.
 #include "kernels.h"
 #include "conv_rules.h"
+#include <type_traits>
 
 namespace cd {
 
@@ -52,6 +53,14 @@ struct GenArgs {
   int relu, accumulate;
   int m_per_split, ktiles, tiles;   // wgrad
 };
+struct GenNormArgs : GenArgs { EvalNorm norm; };   // fprop with the evaluation-mode BatchNorm that follows
+
+// an element of the output behind that BatchNorm, from the convolution's result and the residual's element
+template <typename T> __device__ inline float gen_norm(const GenNormArgs& a, float v, float scale, float shift, float res) {
+  v = fmaf(Cvt<T>::ld(Cvt<T>::st(v)), scale, shift);
+  v = a.norm.res ? v + res : v;
+  return a.norm.relu ? fmaxf(v, 0.f) : v;
+}
 
 // One output element from its definition: taps outside the image (and, in a strided data gradient, between the strides) take
 // no part.  The matrix kernels multiply zeros there instead, which is the same unless the other factor is infinite or NaN
@@ -109,9 +118,10 @@ template <typename T> __device__ inline float gen_wgrad_element(const GenArgs& a
 // its four k of a 16-element chunk as one 16-byte LDS load; element k of a chunk lies at place 4 (k % 4) + k / 4, so that
 // instruction j takes k = 4 j + lane / 16: the sums run over k in ascending order, tap by tap, as the definition and the
 // plain kernels add them.  Rows are 36 floats apart: 16 rows start in 16 different 16-byte bank groups.
-// VEC: channels per load (4 where both channel counts allow it).
-template <typename T, int MODE, int VEC, int TM, int TN>
-__global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
+// VEC: channels per load (4 where both channel counts allow it).  NORM (fprop): the evaluation-mode BatchNorm behind it is applied
+// to the values as they are stored.
+template <typename T, int MODE, int VEC, int TM, int TN, bool NORM>
+__global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, GenNormArgs, GenArgs> a) {
   constexpr int BM = 64 * TM, BN = 16 * TN, BK = 32, P = BK + 4;
   constexpr int KV = BK / VEC, RPP = 256 / KV, AP = BM / RPP;       // pixel rows: vectors per row, rows per pass, passes
   constexpr int FP = MODE == 0 ? (BN + RPP - 1) / RPP : (BK + 256 / (BN / VEC) - 1) / (256 / (BN / VEC));   // filter passes
@@ -275,6 +285,18 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
         for (int q = 0; q < 4; q++)
           if (acc[i][j][q] != acc[i][j][q]) { again |= 1u << (4 * (TN * j + i) + q); acc[i][j][q] = 0.f; }
   }
+  float nsc[NORM ? TN : 1][4], nsh[NORM ? TN : 1][4];   // scale and shift of this lane's channels
+  if constexpr (NORM) {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const int n = n0 + i * 16 + fk + q;
+        if (n < a.N)
+          running_scale_shift(a.norm.running, static_cast<const T*>(a.norm.gamma), static_cast<const T*>(a.norm.beta), a.N, n,
+                              &nsc[i][q], &nsh[i][q]);
+      }
+  }
 #pragma unroll
   for (int j = 0; j < TM; j++) {
     const int m = m0 + (wave * TM + j) * 16 + fr;
@@ -293,6 +315,17 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
           if (MODE == 1 && a.accumulate) v[q] += Cvt<T>::ld(o[q]);
           if (MODE == 0 && a.relu) v[q] = fmaxf(v[q], 0.f);
         }
+      }
+      if constexpr (NORM) {   // (all four, straight: inside the condition above the compiler mixed up the lanes' values)
+        float r[4] = {0.f, 0.f, 0.f, 0.f};
+        if (a.norm.res) {
+          const T* p = static_cast<const T*>(a.norm.res) + ((unsigned)m * (unsigned)a.N + (unsigned)n);
+#pragma unroll
+          for (int q = 0; q < 4; q++)
+            if (q < nv) r[q] = Cvt<T>::ld(p[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q++) v[q] = gen_norm<T>(a, v[q], nsc[i][q], nsh[i][q], r[q]);
       }
       if ((a.N & 3) == 0) {   // four channels of a pixel at a 4-element boundary
         if (sizeof(T) == 4) {
@@ -318,6 +351,12 @@ __global__ void __launch_bounds__(256) conv_generic_k(GenArgs a) {
       T* o = out + ((unsigned)m * (unsigned)a.N + (unsigned)n);
       if (MODE == 1 && a.accumulate) v += Cvt<T>::ld(*o);
       if (MODE == 0 && a.relu) v = fmaxf(v, 0.f);
+      if constexpr (NORM) {
+        float sc, sh;
+        running_scale_shift(a.norm.running, static_cast<const T*>(a.norm.gamma), static_cast<const T*>(a.norm.beta), a.N, n, &sc, &sh);
+        const float r = a.norm.res ? Cvt<T>::ld(static_cast<const T*>(a.norm.res)[(unsigned)m * (unsigned)a.N + (unsigned)n]) : 0.f;
+        v = gen_norm<T>(a, v, sc, sh, r);
+      }
       *o = Cvt<T>::st(v);
     }
   }
@@ -464,21 +503,21 @@ static GenArgs gen_args(const ConvGeom& g) {
   return a;
 }
 
-template <typename T, int MODE, int VEC>
-static void launch_generic(const GenArgs& a, hipStream_t s) {
+template <typename T, int MODE, int VEC, bool NORM>
+static void launch_generic(const std::conditional_t<NORM, GenNormArgs, GenArgs>& a, hipStream_t s) {
   const int tn = generic_column_tiles(a.N);
   const int64_t nt = cdiv(a.N, 16 * tn);
   const bool tall = generic_tall_tiles(a.M, a.N, VEC == 4);
   const dim3 grid((unsigned)cdiv(a.M, tall ? 128 : 64), (unsigned)nt);
   if (tall) {
     constexpr int TM = VEC == 4 ? 2 : 1;
-    if (tn == 1) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 1>), grid, dim3(256), 0, s, a);
-    else if (tn == 2) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 2>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 4>), grid, dim3(256), 0, s, a);
+    if (tn == 1) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 1, NORM>), grid, dim3(256), 0, s, a);
+    else if (tn == 2) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 2, NORM>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, TM, 4, NORM>), grid, dim3(256), 0, s, a);
   } else {
-    if (tn == 1) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 1>), grid, dim3(256), 0, s, a);
-    else if (tn == 2) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 2>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 4>), grid, dim3(256), 0, s, a);
+    if (tn == 1) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 1, NORM>), grid, dim3(256), 0, s, a);
+    else if (tn == 2) hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 2, NORM>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((conv_generic_k<T, MODE, VEC, 1, 4, NORM>), grid, dim3(256), 0, s, a);
   }
 }
 
@@ -488,14 +527,23 @@ static bool gen_vec4(int dtype, const ConvGeom& g, const void* p0, const void* p
   return g.Cin % 4 == 0 && g.Cout % 4 == 0 && ((reinterpret_cast<uintptr_t>(p0) | reinterpret_cast<uintptr_t>(p1)) & mask) == 0;
 }
 
+template <typename T, bool NORM>
+static void fprop_generic_t(const std::conditional_t<NORM, GenNormArgs, GenArgs>& a, bool v4, hipStream_t s) {
+  if (v4) launch_generic<T, 0, 4, NORM>(a, s); else launch_generic<T, 0, 1, NORM>(a, s);
+}
+
 void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
-                        hipStream_t s) {
-  GenArgs a = gen_args(g);
+                        hipStream_t s, const EvalNorm* norm) {
+  GenNormArgs a = {gen_args(g), {}};
   a.src = x; a.w = w; a.bias = bias; a.out = y; a.relu = relu;
   a.M = (int)g.M(); a.N = g.Cout; a.K = g.K();
   const bool v4 = gen_vec4(dtype, g, x, w);
-  if (dtype == CD_BF16) { if (v4) launch_generic<bf16_t, 0, 4>(a, s); else launch_generic<bf16_t, 0, 1>(a, s); }
-  else { if (v4) launch_generic<float, 0, 4>(a, s); else launch_generic<float, 0, 1>(a, s); }
+  if (norm) {
+    a.norm = *norm;
+    if (dtype == CD_BF16) fprop_generic_t<bf16_t, true>(a, v4, s); else fprop_generic_t<float, true>(a, v4, s);
+  } else {
+    if (dtype == CD_BF16) fprop_generic_t<bf16_t, false>(a, v4, s); else fprop_generic_t<float, false>(a, v4, s);
+  }
 }
 
 void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, const ConvGeom& g, bool accumulate, hipStream_t s) {
@@ -503,8 +551,8 @@ void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, cons
   a.src = dy; a.w = w; a.out = dx; a.accumulate = accumulate;
   a.M = (int)(g.B * g.H * g.W); a.N = g.Cin; a.K = g.kh * g.kw * g.Cout;
   const bool v4 = gen_vec4(dtype, g, dy, w);
-  if (dtype == CD_BF16) { if (v4) launch_generic<bf16_t, 1, 4>(a, s); else launch_generic<bf16_t, 1, 1>(a, s); }
-  else { if (v4) launch_generic<float, 1, 4>(a, s); else launch_generic<float, 1, 1>(a, s); }
+  if (dtype == CD_BF16) { if (v4) launch_generic<bf16_t, 1, 4, false>(a, s); else launch_generic<bf16_t, 1, 1, false>(a, s); }
+  else { if (v4) launch_generic<float, 1, 4, false>(a, s); else launch_generic<float, 1, 1, false>(a, s); }
 }
 
 template <typename T>

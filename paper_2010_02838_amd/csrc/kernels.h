@@ -21,6 +21,20 @@ constexpr size_t kPartialsBytes = 128u << 20;  // reduction / split-K partials i
 // would send every chunk's writes to the same memory channel.
 __host__ __device__ inline int64_t stat_pitch(int C) { return 2 * (int64_t)C + 64; }
 
+// Scale and shift of channel c from the running averages [mean[C] | var[C]]; returns 1 / standard deviation.
+template <typename T>
+__device__ inline float running_scale_shift(const float* __restrict__ running, const T* __restrict__ gamma,
+                                            const T* __restrict__ beta, int C, int c, float* scale, float* shift) {
+  const float mean = running[c], istd = 1.f / sqrtf(running[C + c] + kBnEps);
+  *scale = Cvt<T>::ld(gamma[c]) * istd;
+  *shift = fmaf(-mean, *scale, Cvt<T>::ld(beta[c]));
+  return istd;
+}
+// The evaluation-mode BatchNorm behind a convolution, applied by the convolution as it stores: y = relu?(scale * c + shift (+ res))
+// with c the convolution's result as the model's dtype holds it, so that the values are those of a normalisation pass of its own.
+// running: [mean[C] | var[C]]; gamma, beta [C] and res (nullable) [M][C] in the model's dtype.
+struct EvalNorm { const float* running; const void* gamma; const void* beta; const void* res; bool relu; };
+
 // ---- plain kernels: any shape, fp32 or bf16 storage, fp32 arithmetic ------------------------------
 void conv_fprop_simple(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g,
                        bool relu, hipStream_t s);
@@ -33,7 +47,7 @@ void conv_wgrad_simple(int dtype, const void* x, const void* dy, float* dw, cons
 // for weight gradients of few weights over few pixels (generic_wgrad_pays).
 bool conv_generic_supported(const ConvGeom& g);
 void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
-                        hipStream_t s);
+                        hipStream_t s, const EvalNorm* norm = nullptr);
 void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, const ConvGeom& g, bool accumulate, hipStream_t s);
 // partials: scratch for the split sums (as many fp32 copies of dw as splits; without room for two the launch is not split)
 void conv_wgrad_generic(int dtype, const void* x, const void* dy, float* dw, const ConvGeom& g, float* partials,
@@ -125,8 +139,9 @@ bool conv_mfma_supported(const ConvGeom& g);
 // column sums and sums of squares, [chunks][stat_pitch(Cout)] fp32, and returns the number of chunks
 // (one per row tile, conv_stat_chunks_max(M) at most: conv_sums_fit says whether they fit); see bn_stats.
 // bias (nullable, [Cout] bf16) is added and, with relu, the result clamped at zero before rounding.
+// norm (nullable; without bias and stat_partials only): y is the normalised tensor instead.
 int conv_fprop_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, bool relu, bf16_t* y, const ConvGeom& g,
-                    float* stat_partials, hipStream_t s);
+                    float* stat_partials, hipStream_t s, const EvalNorm* norm = nullptr);
 // which tiles conv_fprop_mfma runs this shape on, with a bias or with stat_partials (sums): 0 128x128, 1 128x256, 2 any other
 int conv_fprop_tile_class(const ConvGeom& g, bool bias, bool sums);
 // dx[B*H*W][Cin] (+)= gather(dy)[.][taps*Cout] * wt[Cin][taps*Cout]^T.  w is the filter as stored; wt is
@@ -164,7 +179,8 @@ void conv_wgrad_mfma(const bf16_t* x, const bf16_t* dy, float* dw, const ConvGeo
 // its per-slice form, at least C * kh * kw * 64 + 64 elements (fp32 elements for the weight gradient's dwd).
 int grouped_mfma_slice(int C, int groups);
 int conv_grouped_fprop_mfma(const bf16_t* x, const bf16_t* w, bf16_t* wd, bf16_t* y, const ConvGeom& g, int groups,
-                            float* stat_partials, hipStream_t s);   // returns the number of statistics chunks
+                            float* stat_partials, hipStream_t s,
+                            const EvalNorm* norm = nullptr);   // returns the number of statistics chunks
 void conv_grouped_dgrad_mfma(const bf16_t* dy, const bf16_t* w, bf16_t* wd, bf16_t* dx, const ConvGeom& g, int groups,
                              bool accumulate, hipStream_t s);
 void conv_grouped_wgrad_mfma(const bf16_t* x, const bf16_t* dy, float* dwd, float* dw, const ConvGeom& g, int groups,

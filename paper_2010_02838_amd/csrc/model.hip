@@ -816,6 +816,24 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
     sentence_tables(tok + m->arch.in_h, c.positions() + m->arch.in_h, m->arch.in_w, m->arch.max_sentences, c.table(1), c.s);
   }
   int stat_chunks = 0, stat_tensor = -1;  // statistics a convolution left in the partials area for its BatchNorm
+  // Evaluation: the BatchNorm right behind a convolution, the tensor's only reader, is applied by the convolution as it stores; the
+  // convolution's own output is then not written.  (With the per-launch timer on they stay two launches, so that each class's time
+  // is its own.)
+  const bool norm_in_conv = bn_mode == CD_BN_RUNNING && !timer_enabled();
+  auto eval_norm = [&](size_t oi, EvalNorm* n) {
+    const int y = m->ops[oi].y;
+    if (!norm_in_conv || oi + 1 >= m->ops.size() || m->ops[oi].pb >= 0 || m->ops[oi].relu) return false;
+    const Op& b = m->ops[oi + 1];
+    if (b.kind != OP_BN || b.x != y || b.res == y || pool_fused(m, (int)oi + 1)) return false;
+    for (size_t j = oi + 2; j < m->ops.size(); j++)
+      if (m->ops[j].x == y || m->ops[j].res == y) return false;
+    n->running = bn_running + 2 * m->bn_off[b.bn_slot];
+    n->gamma = c.P(b.pw);
+    n->beta = c.P(b.pb);
+    n->res = b.res >= 0 ? c.act(b.res) : nullptr;
+    n->relu = b.relu;
+    return true;
+  };
   for (size_t oi = 0; oi < m->ops.size(); oi++) {
     const Op& o = m->ops[oi];
     const void* in = o.x == 0 ? x : c.act(o.x);
@@ -824,6 +842,7 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
     switch (o.kind) {
       case OP_CONV: {
         ConvGeom g = conv_geom(m, o, batch);
+        EvalNorm norm;
         if (grouped_sliced(m, o, batch)) {
           // grouped, in place on the row-major tensors: one launch whose column tiles are slices of whole groups; the
           // BatchNorm that follows gets its column sums from the epilogue like behind a dense convolution
@@ -832,10 +851,13 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
                             conv_sums_fit(g.M(), stat_pitch(g.Cout), c.plan.partials_bytes);
           ProfScope pr(CD_K_CONV_FPROP_NARROW, c.s, 2.0 * g.M() * g.Cout * (double)g.kh * g.kw * grouped_mfma_slice(g.Cin, o.groups),
                        conv_bytes(m, g));
+          const bool normed = eval_norm(oi, &norm);
+          if (normed) out = c.act(m->ops[oi + 1].y);
           stat_chunks = conv_grouped_fprop_mfma(static_cast<const bf16_t*>(in), static_cast<const bf16_t*>(c.P(o.pw)),
                                                 reinterpret_cast<bf16_t*>(c.ws + c.plan.gw), static_cast<bf16_t*>(out), g, o.groups,
-                                                fuse ? c.partials() : nullptr, c.s);
+                                                fuse ? c.partials() : nullptr, c.s, normed ? &norm : nullptr);
           stat_tensor = fuse ? o.y : -1;
+          if (normed) oi++;
           break;
         }
         if (o.groups > 1) {
@@ -890,13 +912,20 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
           ProfScope pr(tc == 0 ? CD_K_CONV_FPROP : (tc == 1 ? CD_K_CONV_FPROP_WIDE : CD_K_CONV_FPROP_NARROW), c.s,
                        2.0 * g.M() * g.Cout * g.K(),
                        conv_bytes(m, g));
+          const bool normed = eval_norm(oi, &norm);
+          if (normed) out = c.act(m->ops[oi + 1].y);
           stat_chunks = conv_fprop_mfma(src, w, static_cast<const bf16_t*>(c.P(o.pb)), o.relu, static_cast<bf16_t*>(out), gp,
-                                        fuse ? c.partials() : nullptr, c.s);
+                                        fuse ? c.partials() : nullptr, c.s, normed ? &norm : nullptr);
           stat_tensor = fuse ? o.y : -1;
+          if (normed) oi++;
         } else {
           ProfScope pr(CD_K_CONV_FPROP_NARROW, c.s, 2.0 * g.M() * g.Cout * g.K(), conv_bytes(m, g));
-          if (use_generic(g)) conv_fprop_generic(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s);
-          else conv_fprop_simple(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s);
+          if (use_generic(g)) {
+            const bool normed = eval_norm(oi, &norm);
+            if (normed) out = c.act(m->ops[oi + 1].y);
+            conv_fprop_generic(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s, normed ? &norm : nullptr);
+            if (normed) oi++;
+          } else conv_fprop_simple(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s);
         }
         break;
       }

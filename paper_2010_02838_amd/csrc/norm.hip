@@ -298,16 +298,6 @@ __global__ void __launch_bounds__(1024) col_fold_k(const float* __restrict__ par
   out[(int64_t)blockIdx.y * stat_pitch(C) + C + c] = s1;
 }
 
-// scale and shift of channel c from the running averages [mean[C] | var[C]]; returns 1 / standard deviation
-template <typename T>
-__device__ inline float running_scale_shift(const float* __restrict__ running, const T* __restrict__ gamma,
-                                            const T* __restrict__ beta, int C, int c, float* scale, float* shift) {
-  const float mean = running[c], istd = 1.f / sqrtf(running[C + c] + kBnEps);
-  *scale = Cvt<T>::ld(gamma[c]) * istd;
-  *shift = Cvt<T>::ld(beta[c]) - mean * *scale;
-  return istd;
-}
-
 // mask (VEC 8 only, nullable): receives one byte per vector, bit k = (y[k] > 0), for the backward pass
 // RUN (with FIXC, C <= kRunChannels): stats is [mean[C] | var[C]], the running averages, and a block computes the scale and
 // shift of all channels itself, once, into LDS.
@@ -362,7 +352,7 @@ __global__ void __launch_bounds__(256) bn_apply_k(const T* __restrict__ x, const
         uint32_t bits = 0;
 #pragma unroll
         for (int k = 0; k < VEC; k++) {
-          float v = a[k] * sc[k] + sh[k];
+          float v = fmaf(a[k], sc[k], sh[k]);   // (written out: the convolutions that apply a BatchNorm give the same bits)
           if (res) v += r[k];
           a[k] = relu ? fmaxf(v, 0.f) : v;
           bits |= (a[k] > 0.f ? 1u : 0u) << k;

@@ -106,3 +106,44 @@ def test_timer_counts_only_launches_that_are_made():
     n = _timer_classes(m, 4, 64, evaluation=True)
     assert n["bn_apply"] == len(bn) - 1 and sum(o["fused_pool"] for o in bn) == 1
     assert n["norm"] == 2
+
+
+EVAL_SHAPES = {   # architecture, batch, resolution: the tiles, column counts and dtypes an evaluation-mode convolution can take
+    "small_tiles": (dict(kind=2, widths=[72], blocks=[2], stem_width=64), "bf16", 3, 40),            # 288 columns, 300 rows
+    "narrow_columns": (dict(kind=1, widths=[16, 40], blocks=[1, 1], stem_width=16), "bf16", 143, 31),  # 32- and 64-column tiles
+    "wide_and_tall": (dict(kind=2, widths=[128], blocks=[1], stem_width=64), "bf16", 130, 65),         # 128x256; odd image: no fused pool
+    "tall": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), "bf16", 231, 17),                 # 256x128
+    "grouped": (dict(kind=5, widths=[128, 256], out_widths=[128, 256], blocks=[2, 1], stem_width=64, groups=32), "bf16", 5, 48),
+    "odd_channels": (dict(kind=1, widths=[18, 22], blocks=[1, 1], stem_width=18), "bf16", 7, 13),
+    "f32": (dict(kind=1, widths=[16, 33], blocks=[1, 1], stem_width=16), "f32", 5, 15),
+    "few_rows": (dict(kind=1, widths=[8, 8, 8, 8], blocks=[1, 1, 1, 1], stem_width=8), "bf16", 1, 8),
+}
+
+
+@pytest.mark.parametrize("name", list(EVAL_SHAPES))
+def test_evaluation_norm_inside_the_convolution(name):
+    """Evaluation applies a BatchNorm as the convolution in front of it stores; with the per-launch timer on it is a pass of its
+    own.  Same arithmetic on the same rounded values: the logits agree bit for bit."""
+    from paper_2010_02838_amd import binding as B
+    kw, dtype, batch, res = EVAL_SHAPES[name]
+    m = B.Model(B.arch_preset(kw["kind"], in_h=res, in_w=res, classes=10, **{k: v for k, v in kw.items() if k != "kind"}),
+                B.CD_F32 if dtype == "f32" else B.CD_BF16)
+    g = torch.Generator().manual_seed(3)
+    params = (torch.randn(m.n_elements, generator=g) * 0.1).to("cuda:0", m.torch_dtype)
+    x = torch.randn(batch, res, res, 3, generator=g).to("cuda:0", m.torch_dtype)
+    run = (torch.rand(m.bn_running_elements(), generator=g) + 0.5).to("cuda:0")
+    ws = torch.empty(m.workspace_bytes(batch, False), dtype=torch.uint8, device="cuda:0")
+    z = [torch.empty(batch, 10, device="cuda:0") for _ in range(2)]
+    B.codistill_forward(m, params, x, ws, z[0], False, B.CD_BN_RUNNING, run)
+    torch.cuda.synchronize()
+    B.profile_reset()
+    B.profile_enable(True)
+    try:
+        B.codistill_forward(m, params, x, ws, z[1], False, B.CD_BN_RUNNING, run)
+        torch.cuda.synchronize()
+        assert B.profile_collect()["bn_apply"]["launches"] > 0
+    finally:
+        B.profile_enable(False)
+        B.profile_reset()
+    assert bool(torch.isfinite(z[0]).all()) and float(z[0].std()) > 0
+    assert torch.equal(z[0], z[1])
