@@ -20,7 +20,8 @@
  *   - Calls only enqueue work (`stream` is a hipStream_t passed as void*; NULL is
  *     the default stream) and never synchronise the host.  Everything is enqueued
  *     on the caller's stream, with one exception: codistill_backward forks the
- *     weight gradients of the convolutions onto a second stream that the library
+ *     weight gradients of the convolutions (several layers to a launch, with
+ *     their bias gradients) onto a second stream that the library
  *     creates on first use (default priority, one per process) and joins it back
  *     with an event before it returns, so the caller's stream still orders the
  *     whole call.  CODISTILL_SERIAL=1 in the environment, or the built-in timer,

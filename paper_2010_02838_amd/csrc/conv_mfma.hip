@@ -1187,114 +1187,143 @@ void conv_grouped_dgrad_mfma(const bf16_t* dy, const bf16_t* w, bf16_t* wd, bf16
 // (ds_read_b64_tr_b16): in every group of 16 lanes, lane i receives element (i & 3) of the four
 // 8-byte chunks addressed by lanes (i >> 2), 4 + (i >> 2), 8 + (i >> 2), 12 + (i >> 2).  Pointing
 // chunk 4e+q at pixel e, channels 4q..4q+3 therefore hands lane i four consecutive pixels of channel
-// i, which is the MFMA operand layout.  The pixel range is split over blockIdx.y; partial sums are
-// written per split and added by a second kernel in a fixed order.
-struct WgradArgs {
-  const bf16_t* x;   // [B][H][W][Cin]
-  const bf16_t* dy;  // [M][N]
-  float* out;        // [splits][N][K]
-  int64_t M, m_per_split;
+// i, which is the MFMA operand layout.
+//
+// A launch takes the weight gradients of several layers: a tile of any of them is a workgroup.  One layer of a Transformer or of
+// a late ResNet stage has 16 to 144 tiles, which fill the chip only if its pixels are cut into many splits, and each split is
+// an fp32 copy of dw to be written and added up again; side by side the layers fill it with few splits or none.  (The rule: wgrad_plan in
+// conv_rules.h.)  Splits are added by a second kernel in a fixed order.
+// One encoder layer (8192 tokens, 512 columns, 2048 inside): its four layers one after the other 146 us with registers in front of the
+// LDS and two stages, 114 with this loop, 69 in one launch, 78 with the bias gradients (41 launch by launch before); 32768 x 512 over 8192 rows
+// 363 -> 308, 256 x 2304 over 50176 99 -> 90.  More stages or 64-pixel steps cost workgroups per compute unit and were no faster.
+//
+// Main loop: as igemm_kernel's, steps of 32 pixels, NS stages in LDS filled by direct loads NS - 1 steps ahead, one barrier a
+// step, the fragments of the next 16 pixels read while the matrix cores work.
+struct WgradJob {
+  const bf16_t* x;    // [B][H][W][Cin]
+  const bf16_t* dy;   // [M][N]
+  float* out;         // [splits][slices][N][K]
+  double* bias_part;  // column sums of dy, the bias gradient: [splits][N] (more than one split) or null
+  float* bias_out;    // [N] (one split) or null
+  int M, m_per_split;
   int N, K;
-  int H, W, Cin, Ho, Wo, kh, kw, stride, pad;
-  int ktiles, tiles;  // tiles along K; tiles of dw in all
+  int H, W, Cin, Ho, Wo, kw, stride, pad;
+  int ktiles, tiles_per_slice, tiles;   // tiles along K; of a slice of dw; of dw in all
+  // Grouped convolutions (sliced launches): independent problems, slice s taking channels [s * N, (s + 1) * N) of
+  // dy and [s * Cin, (s + 1) * Cin) of x, both row-major with `pitch` channels per pixel (N = Cin = the slice width).
+  // An ordinary convolution: one slice, x_pitch = Cin, dy_pitch = N.
+  int slices, x_pitch, dy_pitch;
   uint32_t x_bytes, dy_bytes;
-  // Grouped convolutions (sliced launches): `slices` independent problems, slice s taking channels [s * N, (s + 1) * N) of
-  // dy and [s * Cin, (s + 1) * Cin) of x, both row-major with `pitch` channels per pixel (N = Cin = the slice width);
-  // out is [splits][slices][N][K].  An ordinary convolution: slices = 1, x_pitch = Cin, dy_pitch = N.
-  int slices = 1, tiles_per_slice = 0, x_pitch = 0, dy_pitch = 0;
+  uint32_t first;     // workgroups of the jobs in front of this one
 };
+template <int NJ> struct WgradBatch { WgradJob j[NJ]; int n; };
 
-constexpr int WG_MS = 32;  // pixels per main-loop step
+constexpr int WG_MS = 32;   // pixels per main-loop step
 
-template <int BN, int BKK>
-__global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
-  constexpr int PN = BN + 32, PK = BKK + 32;   // pitches (elements): rows 16 banks apart, conflict-free reads
+// PW: 1x1 filters, stride 1, no padding: row m of x belongs to row m of dy
+template <int BN, int BKK, bool PW, int NJ>
+__global__ void __launch_bounds__(256) wgrad_kernel(WgradBatch<NJ> batch) {
+  constexpr int NS = kWgradStages;
   constexpr int NVR = BN / 8, KVR = BKK / 8;   // 16-byte vectors per tile row
   constexpr int DV = WG_MS * NVR / 256, XV = WG_MS * KVR / 256;  // vectors per thread per step
   constexpr int DROWS = 256 / NVR, XROWS = 256 / KVR;
   constexpr int WNT = BN / 2, WKT = BKK / 2;   // wave tile (2 x 2 waves)
-  constexpr int TN = WNT / 32, TK = WKT / 32;
-  __shared__ __attribute__((aligned(16))) bf16_t Dy[2][WG_MS][PN];
-  __shared__ __attribute__((aligned(16))) bf16_t Xs[2][WG_MS][PK];
+  constexpr int TN = WNT / 32, TK = WKT / 32, TT = TN * TK, KK = WG_MS / 16;
+  constexpr uint32_t DY_BYTES = WG_MS * BN * 2, STAGE_BYTES = DY_BYTES + WG_MS * BKK * 2;
+  static_assert(NS * STAGE_BYTES >= 2 * BN * 8, "the bias sums of two waves fit");
+  __shared__ __attribute__((aligned(16))) char smem[NS * STAGE_BYTES];   // stage: [32 pixels][BN] of dy, [32 pixels][BKK] of x
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wn0 = (wave & 1) * WNT, wk0 = (wave >> 1) * WKT;
-  // One-dimensional grid of tiles x splits, renumbered per XCD: the tiles of one pixel range (they
+  // One-dimensional grid of jobs x splits x tiles, renumbered per XCD: the tiles of one pixel range (they
   // read the same rows of dy, and the same rows of x up to the filter's reach) run side by side on
   // one XCD and share those rows in its L2 instead of each fetching them from memory.
-  const unsigned wg = xcd_remap(blockIdx.x, gridDim.x);
+  const unsigned bid = xcd_remap(blockIdx.x, gridDim.x);
+  int jn = 0;
+  if (NJ > 1)
+    while (jn + 1 < batch.n && batch.j[jn + 1].first <= bid) jn++;
+  const WgradJob& a = batch.j[jn];
+  const unsigned wg = bid - a.first;
   const unsigned split = wg / (unsigned)a.tiles, tile_all = wg - split * (unsigned)a.tiles;
   const unsigned sl = tile_all / (unsigned)a.tiles_per_slice, tile = tile_all - sl * (unsigned)a.tiles_per_slice;
   const int n0 = (int)(tile / (unsigned)a.ktiles) * BN, k0 = (int)(tile % (unsigned)a.ktiles) * BKK;
   const int dyc0 = (int)sl * a.N, xc0 = (int)sl * a.Cin;   // first channel of this slice in dy and in x
   // pixel and element indices fit 32 bits: every operand is smaller than 2 GiB (conv_mfma_supported)
-  const int M = (int)a.M;
-  const int mbeg = (int)split * (int)a.m_per_split;
-  const int mend = mbeg + (int)a.m_per_split < M ? mbeg + (int)a.m_per_split : M;
-  const __amdgpu_buffer_rsrc_t rx_src = make_rsrc(a.x, a.x_bytes);
-  const __amdgpu_buffer_rsrc_t rdy = make_rsrc(a.dy, a.dy_bytes);
+  const int M = a.M;
+  const int mbeg = (int)split * a.m_per_split;
+  const int mend = M - mbeg > a.m_per_split ? mbeg + a.m_per_split : M;
+  const rsrc_words_t rx = make_rsrc_words(a.x, a.x_bytes), rdy = make_rsrc_words(a.dy, a.dy_bytes);
 
-  // dy loader: fixed channel vector, DV rows; doff = byte offset of (row, channel vector) at step 0
-  const int dnv = tid % NVR, drow = tid / NVR;
-  const bool dnok = n0 + dnv * 8 < a.N;
-  int dm[DV];
-  uint32_t doff[DV];
-#pragma unroll
-  for (int j = 0; j < DV; j++) {
-    dm[j] = mbeg + drow + DROWS * j;
-    doff[j] = ((uint32_t)dm[j] * (uint32_t)a.dy_pitch + (uint32_t)(dyc0 + n0 + dnv * 8)) * 2u;
-  }
-  const uint32_t dstep = (uint32_t)WG_MS * (uint32_t)a.dy_pitch * 2u;
-  // x loader: fixed (tap, channel) vector, XV rows, pixel coordinates advanced incrementally
-  const int xkv = tid % KVR, xrow = tid / KVR;
-  const int k = k0 + xkv * 8;
-  const bool kok = k < a.K;
-  const int tap = kok ? k / a.Cin : 0;
-  const int kc = k - tap * a.Cin, kr = tap / a.kw, ks = tap - (tap / a.kw) * a.kw;
-  int xm[XV], pb[XV], ph[XV], pw[XV];
-#pragma unroll
-  for (int j = 0; j < XV; j++) {
-    const unsigned m = (unsigned)(mbeg + xrow + XROWS * j);
-    const unsigned q = m / (unsigned)a.Wo;
-    xm[j] = (int)m;
-    pw[j] = (int)(m - q * (unsigned)a.Wo);
-    pb[j] = (int)(q / (unsigned)a.Ho);
-    ph[j] = (int)(q - (unsigned)pb[j] * (unsigned)a.Ho);
-  }
-  // one step moves every row WG_MS pixels on: whole images, then whole rows, then columns
-  const int adv_b = WG_MS / (a.Ho * a.Wo), adv_r = WG_MS % (a.Ho * a.Wo);
-  const int adv_h = adv_r / a.Wo, adv_w = adv_r % a.Wo;
-
-  // Loads are unconditional (masked vectors read nothing) so that the compiler can count the loads in
-  // flight, and the address update is straight-line code (selects, no loops); see igemm_kernel.
-  uint4 rd[2][DV], rx[2][XV];
-  auto gload = [&](uint4* rd, uint4* rx) {
-#pragma unroll
-    for (int j = 0; j < DV; j++) {
-      rd[j] = buf_load16(rdy, (dnok && dm[j] < mend) ? doff[j] : 0xffffffffu);
-      dm[j] += WG_MS;
-      doff[j] += dstep;
-    }
+  // ---- loads: thread tid owns LDS slot tid % NVR (16 bytes) of the tile rows tid / NVR + DROWS j.  The 16-byte column cv of a
+  // row lies in slot cv ^ swz(row): a transpose load's four rows of 32 bytes, and the neighbouring 32 bytes that the next
+  // sixteen lanes read, then fall into different banks.  A thread's rows are a multiple of 16 apart and share their swz.
+  auto swz = [](int row, int vr) { return vr == 16 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); };
+  const int drow = tid / NVR, dcv = (tid % NVR) ^ swz(drow, NVR);
+  const uint32_t dnot = n0 + dcv * 8 < a.N ? 0u : 0xffffffffu;   // or-ed into an offset: beyond every buffer, reads zeros
+  int dm = mbeg + drow;                                          // row of vector 0 in the step at hand
+  uint32_t doff = ((uint32_t)dm * (uint32_t)a.dy_pitch + (uint32_t)(dyc0 + n0 + dcv * 8)) * 2u;
+  const uint32_t dstep = (uint32_t)WG_MS * (uint32_t)a.dy_pitch * 2u, drstep = (uint32_t)DROWS * (uint32_t)a.dy_pitch * 2u;
+  const int xrow = tid / KVR, xcv = (tid % KVR) ^ swz(xrow, KVR);
+  const int k = k0 + xcv * 8;
+  const uint32_t xnot = k < a.K ? 0u : 0xffffffffu;
+  int xm = mbeg + xrow;
+  // PW: byte offset of vector 0.  Otherwise: the tap and channel of this thread's column, and each row's pixel
+  uint32_t xoff = ((uint32_t)xm * (uint32_t)a.x_pitch + (uint32_t)(xc0 + k)) * 2u;
+  const uint32_t xstep = (uint32_t)WG_MS * (uint32_t)a.x_pitch * 2u, xrstep = (uint32_t)XROWS * (uint32_t)a.x_pitch * 2u;
+  const int tap = PW || xnot ? 0 : k / a.Cin;
+  const int kc = k - tap * a.Cin, kr = PW ? 0 : tap / a.kw, ks = tap - kr * (PW ? 0 : a.kw);
+  int pb[PW ? 1 : XV], ph[PW ? 1 : XV], pw[PW ? 1 : XV];
+  int adv_b = 0, adv_h = 0, adv_w = 0;
+  if (!PW) {
 #pragma unroll
     for (int j = 0; j < XV; j++) {
-      const int hi = ph[j] * a.stride - a.pad + kr, wi = pw[j] * a.stride - a.pad + ks;
-      const bool ok = kok && xm[j] < mend && (unsigned)hi < (unsigned)a.H && (unsigned)wi < (unsigned)a.W;
-      rx[j] = buf_load16(rx_src, ok ? (uint32_t)(((pb[j] * a.H + hi) * a.W + wi) * a.x_pitch + xc0 + kc) * 2u : 0xffffffffu);
-      xm[j] += WG_MS;
-      pw[j] += adv_w;
-      const int cw = pw[j] >= a.Wo ? 1 : 0;
-      pw[j] -= cw ? a.Wo : 0;
-      ph[j] += adv_h + cw;
-      const int ch = ph[j] >= a.Ho ? 1 : 0;
-      ph[j] -= ch ? a.Ho : 0;
-      pb[j] += adv_b + ch;
+      const unsigned m = (unsigned)(xm + XROWS * j);
+      const unsigned q = m / (unsigned)a.Wo;
+      pw[j] = (int)(m - q * (unsigned)a.Wo);
+      pb[j] = (int)(q / (unsigned)a.Ho);
+      ph[j] = (int)(q - (unsigned)pb[j] * (unsigned)a.Ho);
+    }
+    // one step moves every row WG_MS pixels on: whole images, then whole rows, then columns
+    adv_b = WG_MS / (a.Ho * a.Wo);
+    const int adv_r = WG_MS % (a.Ho * a.Wo);
+    adv_h = adv_r / a.Wo;
+    adv_w = adv_r % a.Wo;
+  }
+  uint32_t offd[DV], offx[XV];
+  constexpr int NPIECE = DV + XV + 1;
+  // piece p of the preparation of the step at hand: one vector's offset (rows past the split's end are masked in both operands),
+  // or (last) the move to the next step; straight-line code between the MFMAs
+  auto prep_piece = [&](int p) {
+    if (p < DV) {
+      offd[p] = (doff + (uint32_t)p * drstep) | dnot | (dm + DROWS * p < mend ? 0u : 0xffffffffu);
+    } else if (p < DV + XV) {
+      const int j = p - DV;
+      const uint32_t out = xnot | (xm + XROWS * j < mend ? 0u : 0xffffffffu);
+      if (PW) {
+        offx[j] = (xoff + (uint32_t)j * xrstep) | out;
+      } else {
+        const int hi = ph[j] * a.stride - a.pad + kr, wi = pw[j] * a.stride - a.pad + ks;
+        const bool ok = (unsigned)hi < (unsigned)a.H && (unsigned)wi < (unsigned)a.W;
+        offx[j] = ((uint32_t)(((pb[j] * a.H + hi) * a.W + wi) * a.x_pitch + xc0 + kc) * 2u) | out | (ok ? 0u : 0xffffffffu);
+        pw[j] += adv_w;
+        const int cw = pw[j] >= a.Wo ? 1 : 0;
+        pw[j] -= cw ? a.Wo : 0;
+        ph[j] += adv_h + cw;
+        const int ch = ph[j] >= a.Ho ? 1 : 0;
+        ph[j] -= ch ? a.Ho : 0;
+        pb[j] += adv_b + ch;
+      }
+    } else {
+      dm += WG_MS;
+      doff += dstep;
+      xm += WG_MS;
+      xoff += xstep;
     }
   };
-  auto lstore = [&](const uint4* rd, const uint4* rx, int buf) {
-#pragma unroll
-    for (int j = 0; j < DV; j++) *reinterpret_cast<uint4*>(&Dy[buf][drow + DROWS * j][dnv * 8]) = rd[j];
-#pragma unroll
-    for (int j = 0; j < XV; j++) *reinterpret_cast<uint4*>(&Xs[buf][xrow + XROWS * j][xkv * 8]) = rx[j];
+  const uint32_t lds_wave = (uint32_t)(uintptr_t)(CD_LDS char*)smem + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6) * 1024u;
+  auto issue = [&](uint32_t stage_b, int v) {
+    if (v < DV) load_lds16(rdy, lds_wave + stage_b + (uint32_t)v * 4096u, offd[v]);
+    else load_lds16(rx, lds_wave + stage_b + DY_BYTES + (uint32_t)(v - DV) * 4096u, offx[v - DV]);
   };
 
   f32x16_t acc[TN][TK];
@@ -1305,78 +1334,89 @@ __global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
 
-  // transpose-load addressing of this lane inside a 16-pixel x 32-channel fragment
+  // transpose-load addressing of this lane inside a 16-pixel x 32-channel fragment (the second load: four pixels on, same swz)
   const int grp = lane >> 4, li = lane & 15;
-  const int tr_m = 8 * (grp >> 1) + (li >> 2);      // pixel row (second load: +4)
+  const int tr_m = 8 * (grp >> 1) + (li >> 2);      // pixel row
   const int tr_c = 16 * (grp & 1) + 4 * (li & 3);   // first of the 4 channels this lane points at
+  // byte offset of channel c of row m in a tile of vr vectors a row
+  auto at = [&](int m, int c, int vr) { return (uint32_t)((m * vr + ((c >> 3) ^ swz(m, vr))) * 16 + (c & 7) * 2); };
+  uint32_t fd[TN], fx[TK];
+#pragma unroll
+  for (int i = 0; i < TN; i++) fd[i] = at(tr_m, wn0 + i * 32 + tr_c, NVR);
+#pragma unroll
+  for (int j = 0; j < TK; j++) fx[j] = DY_BYTES + at(tr_m, wk0 + j * 32 + tr_c, KVR);
+  bf16x8_t df[2][TN], xf[2][TK];  // [buffer][tile]
+  auto read_tr = [&](uint32_t b, int pitch) {
+    const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((CD_LDS bf16x4_t*)(smem + b));
+    const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((CD_LDS bf16x4_t*)(smem + b + 4 * pitch));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  auto read_frags = [&](int buf, uint32_t stage_b, int kk) {
+#pragma unroll
+    for (int i = 0; i < TN; i++) df[buf][i] = read_tr(stage_b + fd[i] + (uint32_t)(kk * 16 * BN * 2), BN * 2);
+#pragma unroll
+    for (int j = 0; j < TK; j++) xf[buf][j] = read_tr(stage_b + fx[j] + (uint32_t)(kk * 16 * BKK * 2), BKK * 2);
+  };
+  // The bias gradient: the workgroups of the first tile column add up the dy fragments that pass through their registers, the
+  // two waves of a channel block alternate sub-steps.  A lane holds eight pixels of one channel: their sum is fp32, the sums'
+  // sum fp64.
+  const bool bias = k0 == 0 && (a.bias_part || a.bias_out);
+  const int uwave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double bsum[TN];
+#pragma unroll
+  for (int i = 0; i < TN; i++) bsum[i] = 0.0;
+  float bhalf = 0.f;
+  auto add_bias = [&](const bf16x8_t& f, int half, double& s) {   // four pixels at a time: the shadow of one MFMA
+    const uint4 u = __builtin_bit_cast(uint4, f);
+    const uint32_t w0 = half ? u.z : u.x, w1 = half ? u.w : u.y;
+    const float t = (__uint_as_float(w0 << 16) + __uint_as_float(w0 & 0xffff0000u)) +
+                    (__uint_as_float(w1 << 16) + __uint_as_float(w1 & 0xffff0000u));
+    if (half) s += (double)(bhalf + t); else bhalf = t;
+  };
 
-  bf16x8_t df[2][2][TN], xf[2][2][TK];  // [fragment set][16-pixel half][tile]
-  auto read_frags = [&](bf16x8_t (&df)[2][TN], bf16x8_t (&xf)[2][TK], int buf) {
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-#pragma unroll
-      for (int i = 0; i < TN; i++) {
-        const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-            (CD_LDS bf16x4_t*)(&Dy[buf][h * 16 + tr_m][wn0 + i * 32 + tr_c]));
-        const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-            (CD_LDS bf16x4_t*)(&Dy[buf][h * 16 + tr_m + 4][wn0 + i * 32 + tr_c]));
-        df[h][i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-#pragma unroll
-      for (int j = 0; j < TK; j++) {
-        const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-            (CD_LDS bf16x4_t*)(&Xs[buf][h * 16 + tr_m][wk0 + j * 32 + tr_c]));
-        const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-            (CD_LDS bf16x4_t*)(&Xs[buf][h * 16 + tr_m + 4][wk0 + j * 32 + tr_c]));
-        xf[h][j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-    }
-  };
-  auto mfma_step = [&](const bf16x8_t (&df)[2][TN], const bf16x8_t (&xf)[2][TK]) {
-#pragma unroll
-    for (int h = 0; h < 2; h++)
-#pragma unroll
-      for (int i = 0; i < TN; i++)
-#pragma unroll
-        for (int j = 0; j < TK; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(df[h][i], xf[h][j], acc[i][j], 0, 0, 0);
-  };
-
-  // same software pipeline as igemm_kernel: store tile st+1, load tile st+3, MFMAs of tile st, barrier,
-  // fragments of tile st+1
-  auto interleave = [&]() {
-    constexpr int NMFMA = 2 * TN * TK, NREAD = 4 * (TN + TK), NWRITE = DV + XV;
-#pragma unroll
-    for (int i = 0; i < NMFMA; i++) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                  // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, (NREAD + NMFMA - 1) / NMFMA, 0);        // DS read
-      __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);                                  // VALU
-      if (i < NWRITE) {
-        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                                // DS write
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                // VMEM read
-      }
-    }
-  };
   const int steps = (mend - mbeg + WG_MS - 1) / WG_MS;
-  gload(rd[0], rx[0]);
-  gload(rd[1], rx[1]);
-  lstore(rd[0], rx[0], 0);
-  gload(rd[0], rx[0]);
-  __syncthreads();
-  read_frags(df[0], xf[0], 0);
-  for (int st = 0; st < steps; st += 2) {
-    lstore(rd[1], rx[1], 1);
-    gload(rd[1], rx[1]);
-    mfma_step(df[0], xf[0]);
-    interleave();
-    __syncthreads();
-    read_frags(df[1], xf[1], 1);
-    lstore(rd[0], rx[0], 0);
-    gload(rd[0], rx[0]);
-    mfma_step(df[1], xf[1]);
-    interleave();
-    __syncthreads();
-    read_frags(df[0], xf[0], 0);
+  uint32_t cur = 0, nxt = STAGE_BYTES;
+#pragma unroll
+  for (int t = 0; t < NS; t++) {
+#pragma unroll
+    for (int p = 0; p < NPIECE; p++) prep_piece(p);
+#pragma unroll
+    for (int v = 0; v < DV + XV; v++) issue((uint32_t)t * STAGE_BYTES, v);
+  }
+  wait_step<(NS - 1) * (DV + XV)>();
+  read_frags(0, cur, 0);
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));   // lgkmcnt(0): with the scalar loads, so that none is waited for inside
+  for (int st = 0; st < steps; st++) {
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++) {
+      if (kk == KK - 1) wait_step<(NS - 2) * (DV + XV)>();
+      read_frags((kk + 1) & 1, kk == KK - 1 ? nxt : cur, (kk + 1) % KK);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < TT; i++) {
+        acc[i / TK][i % TK] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(df[kk & 1][i / TK], xf[kk & 1][i % TK], acc[i / TK][i % TK],
+                                                                      0, 0, 0);
+        if (kk < KK - 1) {
+          constexpr int SLOTS = (KK - 1) * TT;
+          const int slot = kk * TT + i;
+#pragma unroll
+          for (int p = 0; p < NPIECE; p++)
+            if (p * SLOTS / NPIECE == slot) prep_piece(p);
+        } else {
+#pragma unroll
+          for (int v = 0; v < DV + XV; v++)
+            if (v * TT / (DV + XV) == i) issue(cur, v);
+        }
+        if (bias && (uwave >> 1) == (kk & 1)) {
+#pragma unroll
+          for (int h = 0; h < 2 * TN; h++)
+            if (h * TT / (2 * TN) == i) add_bias(df[kk & 1][h >> 1], h & 1, bsum[h >> 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    cur = nxt;
+    nxt = nxt + STAGE_BYTES == NS * STAGE_BYTES ? 0u : nxt + STAGE_BYTES;
   }
 
   float* out = a.out + ((int64_t)split * a.slices + sl) * a.N * a.K;   // N*K*4 bytes < 2^33: 32-bit element offsets inside
@@ -1391,6 +1431,22 @@ __global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a) {
         if (n < a.N && kk < a.K) out[(uint32_t)n * (uint32_t)a.K + (uint32_t)kk] = acc[i][j][v];
       }
     }
+  wait_vmem<0>();   // the masked loads past the end still write (zeros) into the stages
+  if (bias) {       // uniform over the workgroup
+    __syncthreads();
+    double* red = reinterpret_cast<double*>(smem);   // [wave >> 1][BN]
+#pragma unroll
+    for (int i = 0; i < TN; i++) {
+      const double s = bsum[i] + __shfl_xor(bsum[i], 32, 64);
+      if (lane < 32) red[(wave >> 1) * BN + wn0 + i * 32 + lane] = s;
+    }
+    __syncthreads();
+    if (tid < BN && n0 + tid < a.N) {
+      const double s = red[tid] + red[BN + tid];
+      if (a.bias_part) a.bias_part[(int64_t)split * a.N + n0 + tid] = s;
+      else a.bias_out[n0 + tid] = (float)s;
+    }
+  }
 }
 
 // 64 outputs x 4 split lanes per block; every lane adds every 4th split, fixed-order combine in LDS
@@ -1413,55 +1469,150 @@ void sum_splits(const float* part, float* out, int64_t n, int splits, hipStream_
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)cdiv(n, 64)), dim3(256), 0, s, part, out, n, splits);
 }
 
-// slices > 1: a grouped convolution cut into `slices` slices of g.Cin = g.Cout = SW channels; x and dy are the whole
-// row-major tensors with `pitch` channels per pixel and dw receives the dense per-slice gradients [slices][SW][K].
-static void wgrad_launch(const bf16_t* x, const bf16_t* dy, float* dw, const ConvGeom& g, int slices, int pitch, float* partials,
-                         size_t partials_bytes, hipStream_t s) {
-  WgradArgs a;
-  a.x = x; a.dy = dy;
-  a.M = g.M(); a.N = g.Cout; a.K = g.K();
-  a.H = g.H; a.W = g.W; a.Cin = g.Cin; a.Ho = g.Ho; a.Wo = g.Wo;
-  a.kh = g.kh; a.kw = g.kw; a.stride = g.stride; a.pad = g.pad;
-  a.slices = slices;
-  a.x_pitch = slices > 1 ? pitch : g.Cin;
-  a.dy_pitch = slices > 1 ? pitch : g.Cout;
-  a.x_bytes = (uint32_t)(g.B * g.H * g.W * (int64_t)a.x_pitch * 2);
-  a.dy_bytes = (uint32_t)(g.M() * (int64_t)a.dy_pitch * 2);
-  const int bn = a.N > 64 ? 128 : 64, bk = a.K > 64 ? 128 : 64;
-  const int ntiles = (int)cdiv(a.N, bn);
-  a.ktiles = (int)cdiv(a.K, bk);
-  a.tiles_per_slice = ntiles * a.ktiles;
-  const int64_t tiles = (int64_t)a.tiles_per_slice * slices;
-  const int64_t nk = (int64_t)a.N * a.K * slices;
-  // Workgroups to aim for (measured on the layer shapes of ResNet-50 at batch 256).  Every split writes
-  // an fp32 copy of dw, so 1x1 filters with small N*K/(N+K) (few flops per byte of dy and x: the launch
-  // is bound by memory traffic whatever the split) run one long workgroup per compute unit; the other
-  // 1x1 launches take two, gathers over several taps four.
-  int64_t target = 1024;
-  if (a.kh * a.kw == 1) target = (double)a.N * a.K / ((double)a.N + a.K) < 150.0 ? 256 : 512;
-  if (g_tune_co > 0) target = g_tune_co;
-  int64_t splits = cdiv(target, tiles);
-  const int64_t max_by_m = cdiv(a.M, 4 * WG_MS);
-  if (splits > max_by_m) splits = max_by_m;
-  const int64_t max_by_mem = (int64_t)(partials_bytes / (nk * sizeof(float)));
-  if (splits > max_by_mem) splits = max_by_mem;
-  if (splits < 1) splits = 1;
-  a.m_per_split = cdiv(cdiv(a.M, splits), WG_MS) * WG_MS;
-  splits = cdiv(a.M, a.m_per_split);
-  a.out = splits == 1 ? dw : partials;
-  a.tiles = (int)tiles;
-  dim3 grid((unsigned)(tiles * splits));
-  if (bn == 128 && bk == 128) hipLaunchKernelGGL((wgrad_kernel<128, 128>), grid, dim3(256), 0, s, a);
-  else if (bn == 128) hipLaunchKernelGGL((wgrad_kernel<128, 64>), grid, dim3(256), 0, s, a);
-  else if (bk == 128) hipLaunchKernelGGL((wgrad_kernel<64, 128>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((wgrad_kernel<64, 64>), grid, dim3(256), 0, s, a);
-  if (splits > 1)
-    sum_splits(partials, dw, nk, (int)splits, s);
+// The splits of a batch: 256 outputs (four a thread) x 4 split lanes per block, in the order of wgrad_reduce_kernel; behind a job's
+// outputs a block per 256 channels adds the bias sums.
+struct WgradSum { const float* part; float* out; const double* bias_part; float* bias_out; uint32_t n4; int splits, N; uint32_t first, bias_first; };
+template <int NJ> struct WgradSums { WgradSum j[NJ]; int n; };
+template <int NJ>
+__global__ void __launch_bounds__(256) wgrad_sum_kernel(WgradSums<NJ> b) {
+  __shared__ float4 sm[4][64];
+  int k = 0;
+  if (NJ > 1)
+    while (k + 1 < b.n && b.j[k + 1].first <= blockIdx.x) k++;
+  const WgradSum& q = b.j[k];
+  if (blockIdx.x >= q.bias_first) {
+    const int c = (int)(blockIdx.x - q.bias_first) * 256 + (int)threadIdx.x;
+    if (c >= q.N) return;
+    double s = 0.0;
+    for (int j = 0; j < q.splits; j++) s += q.bias_part[(int64_t)j * q.N + c];
+    q.bias_out[c] = (float)s;
+    return;
+  }
+  const int ol = threadIdx.x & 63, lane = threadIdx.x >> 6;
+  const uint32_t i = (blockIdx.x - q.first) * 64u + (uint32_t)ol;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (i < q.n4) {
+    const float4* p = reinterpret_cast<const float4*>(q.part) + i;
+#pragma unroll 4
+    for (int j = lane; j < q.splits; j += 4) {
+      const float4 v = p[(int64_t)j * q.n4];
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+  }
+  sm[lane][ol] = s;
+  __syncthreads();
+  if (lane == 0 && i < q.n4) {
+    const float4 t0 = sm[0][ol], t1 = sm[1][ol], t2 = sm[2][ol], t3 = sm[3][ol];
+    reinterpret_cast<float4*>(q.out)[i] = make_float4((t0.x + t1.x) + (t2.x + t3.x), (t0.y + t1.y) + (t2.y + t3.y),
+                                                      (t0.z + t1.z) + (t2.z + t3.z), (t0.w + t1.w) + (t2.w + t3.w));
+  }
+}
+
+template <int BN, int BKK, bool PW>
+static void launch_wgrad(const WgradJob* jobs, int n, unsigned blocks, hipStream_t s) {
+  if (n == 1) {
+    WgradBatch<1> b;
+    b.j[0] = jobs[0]; b.n = 1;
+    hipLaunchKernelGGL((wgrad_kernel<BN, BKK, PW, 1>), dim3(blocks), dim3(256), 0, s, b);
+  } else {
+    WgradBatch<kWgradJobs> b;
+    for (int k = 0; k < n; k++) b.j[k] = jobs[k];
+    b.n = n;
+    hipLaunchKernelGGL((wgrad_kernel<BN, BKK, PW, kWgradJobs>), dim3(blocks), dim3(256), 0, s, b);
+  }
+}
+
+WgradShape conv_wgrad_shape(const ConvGeom& g, int slices) {
+  WgradShape h;
+  h.M = g.M(); h.N = g.Cout; h.K = g.K(); h.slices = slices;
+  h.taps = g.kh * g.kw;
+  h.pointwise = g.kh == 1 && g.kw == 1 && g.stride == 1 && g.pad == 0;
+  return h;
+}
+
+// p[0 .. n): problems of one tile class (WgradShape::tile_class), at most kWgradJobs
+static void wgrad_run(const WgradProblem* p, int n, int pitch, float* partials, size_t partials_bytes, hipStream_t s) {
+  WgradJob jobs[kWgradJobs];
+  WgradShape shapes[kWgradJobs];
+  WgradSplit plan[kWgradJobs];
+  for (int k = 0; k < n; k++) {
+    shapes[k] = conv_wgrad_shape(p[k].g, p[k].slices);
+    shapes[k].bias = p[k].db != nullptr;
+  }
+  wgrad_plan(shapes, n, partials_bytes, g_tune_co, plan);
+  WgradSums<kWgradJobs> sums;
+  sums.n = 0;
+  unsigned blocks = 0, sum_blocks = 0;
+  char* room = reinterpret_cast<char*>(partials);
+  for (int k = 0; k < n; k++) {
+    const ConvGeom& g = p[k].g;
+    const WgradShape& h = shapes[k];
+    WgradJob& a = jobs[k];
+    a.x = p[k].x; a.dy = p[k].dy;
+    a.M = (int)h.M; a.N = h.N; a.K = h.K;
+    a.H = g.H; a.W = g.W; a.Cin = g.Cin; a.Ho = g.Ho; a.Wo = g.Wo; a.kw = g.kw; a.stride = g.stride; a.pad = g.pad;
+    a.slices = h.slices;
+    a.x_pitch = h.slices > 1 ? pitch : g.Cin;
+    a.dy_pitch = h.slices > 1 ? pitch : g.Cout;
+    a.x_bytes = (uint32_t)(g.B * g.H * g.W * (int64_t)a.x_pitch * 2);
+    a.dy_bytes = (uint32_t)(h.M * (int64_t)a.dy_pitch * 2);
+    a.ktiles = (int)cdiv(h.K, h.bk());
+    a.tiles_per_slice = (int)(h.tiles() / h.slices);
+    a.tiles = (int)h.tiles();
+    a.m_per_split = (int)plan[k].m_per_split;
+    a.first = blocks;
+    a.out = p[k].dw;
+    a.bias_part = nullptr;
+    a.bias_out = p[k].db;
+    const int splits = (int)plan[k].splits;
+    blocks += (unsigned)(h.tiles() * splits);
+    if (splits > 1) {
+      a.out = reinterpret_cast<float*>(room);
+      room += align_up((size_t)(h.weights() * splits) * sizeof(float), 256);
+      WgradSum& q = sums.j[sums.n++];
+      q.part = a.out; q.out = p[k].dw; q.n4 = (uint32_t)(h.weights() / 4); q.splits = splits; q.N = h.N;
+      q.first = sum_blocks;
+      sum_blocks += (unsigned)cdiv(q.n4, 64);
+      q.bias_first = sum_blocks;
+      q.bias_part = nullptr; q.bias_out = p[k].db;
+      if (p[k].db) {
+        a.bias_part = reinterpret_cast<double*>(room);
+        room += align_up((size_t)h.N * splits * sizeof(double), 256);
+        a.bias_out = nullptr;
+        q.bias_part = a.bias_part;
+        sum_blocks += (unsigned)cdiv(h.N, 256);
+      } else {
+        q.bias_first = 0xffffffffu;
+      }
+    }
+  }
+  switch (shapes[0].tile_class()) {
+    case 0: launch_wgrad<64, 64, false>(jobs, n, blocks, s); break;
+    case 1: launch_wgrad<64, 64, true>(jobs, n, blocks, s); break;
+    case 2: launch_wgrad<64, 128, false>(jobs, n, blocks, s); break;
+    case 3: launch_wgrad<64, 128, true>(jobs, n, blocks, s); break;
+    case 4: launch_wgrad<128, 64, false>(jobs, n, blocks, s); break;
+    case 5: launch_wgrad<128, 64, true>(jobs, n, blocks, s); break;
+    case 6: launch_wgrad<128, 128, false>(jobs, n, blocks, s); break;
+    default: launch_wgrad<128, 128, true>(jobs, n, blocks, s); break;
+  }
+  if (sums.n == 1) {
+    WgradSums<1> one;
+    one.j[0] = sums.j[0]; one.n = 1;
+    hipLaunchKernelGGL(wgrad_sum_kernel<1>, dim3(sum_blocks), dim3(256), 0, s, one);
+  } else if (sums.n > 1) {
+    hipLaunchKernelGGL(wgrad_sum_kernel<kWgradJobs>, dim3(sum_blocks), dim3(256), 0, s, sums);
+  }
+}
+
+void conv_wgrad_batch(const WgradProblem* p, int n, float* partials, size_t partials_bytes, hipStream_t s) {
+  for (int k = 0; k < n; k += kWgradJobs) wgrad_run(p + k, std::min(n - k, kWgradJobs), 0, partials, partials_bytes, s);
 }
 
 void conv_wgrad_mfma(const bf16_t* x, const bf16_t* dy, float* dw, const ConvGeom& g, float* partials,
                      size_t partials_bytes, hipStream_t s) {
-  wgrad_launch(x, dy, dw, g, 1, 0, partials, partials_bytes, s);
+  const WgradProblem p = {x, dy, dw, nullptr, g, 1};
+  wgrad_run(&p, 1, 0, partials, partials_bytes, s);
 }
 
 // dw [C][taps][cg] fp32 of a grouped convolution: dense per-slice gradients dwd [C / SW][SW][taps][SW] (scratch) by the
@@ -1481,7 +1632,8 @@ void conv_grouped_wgrad_mfma(const bf16_t* x, const bf16_t* dy, float* dwd, floa
   const int C = g.Cin, cg = C / groups, SW = grouped_mfma_slice(C, groups), taps = g.kh * g.kw;
   ConvGeom gs = g;
   gs.Cin = gs.Cout = SW;
-  wgrad_launch(x, dy, dwd, gs, C / SW, C, partials, partials_bytes, s);
+  const WgradProblem p = {x, dy, dwd, nullptr, gs, C / SW};   // C / SW independent problems on slices of the row-major tensors
+  wgrad_run(&p, 1, C, partials, partials_bytes, s);
   const int64_t n = (int64_t)C * taps * cg;
   hipLaunchKernelGGL(extract_sliced_dw_k, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, dwd, dw, C, taps, cg, SW);
 }

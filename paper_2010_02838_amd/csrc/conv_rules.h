@@ -58,6 +58,83 @@ inline bool conv_sums_fit(int64_t M, int64_t pitch, size_t bytes) {
   return (size_t)(conv_stat_chunks_max(M) + 32) * pitch * sizeof(float) <= bytes;
 }
 
+// ---- weight gradients of the matrix-core path (conv_mfma.hip) -----------------------------------------------------------------
+constexpr int kWgradJobs = 16;     // layers in a launch: their table travels in the kernel arguments
+constexpr int kWgradStages = 3;
+constexpr int kWgradBlocks = 512;  // workgroups a launch of several layers aims for: two a compute unit
+struct WgradShape {
+  int64_t M;      // pixels (rows)
+  int N, K;       // dw [N][K], per slice
+  int taps, slices;
+  bool pointwise, bias;
+  int bn() const { return N > 64 ? 128 : 64; }
+  int bk() const { return K > 64 ? 128 : 64; }
+  int tile_class() const { return (bn() == 128 ? 4 : 0) + (bk() == 128 ? 2 : 0) + (pointwise ? 1 : 0); }
+  int64_t tiles() const { return (int64_t)((N + bn() - 1) / bn()) * ((K + bk() - 1) / bk()) * slices; }
+  int64_t steps() const { return (M + 31) / 32; }
+  int64_t weights() const { return (int64_t)N * K * slices; }
+  // bytes of partial sums, each part on a 256-byte boundary
+  int64_t partials(int64_t splits) const {
+    return splits < 2 ? 0 : (weights() * splits * 4 + 255) / 256 * 256 + (bias ? (N * splits * 8 + 255) / 256 * 256 : 0);
+  }
+};
+struct WgradSplit { int64_t splits, m_per_split; };   // m_per_split: a multiple of the 32 pixels of a step
+
+// How many splits the pixels of n layers (one tile class) in one launch are cut into.  tune > 0: workgroups to aim for instead.
+inline void wgrad_plan(const WgradShape* s, int n, size_t partials_bytes, int tune, WgradSplit* out) {
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  auto cut = [&](const WgradShape& h, int64_t splits) {
+    WgradSplit r;
+    splits = std::max<int64_t>(1, std::min(splits, up(h.M, 4 * 32)));
+    r.m_per_split = up(up(h.M, splits), 32) * 32;
+    r.splits = up(h.M, r.m_per_split);
+    return r;
+  };
+  if (n == 1) {
+    // A layer by itself (measured on the layer shapes of ResNet-50 at batch 256).  Every split writes
+    // an fp32 copy of dw, so 1x1 filters with small N*K/(N+K) (few flops per byte of dy and x: the launch
+    // is bound by memory traffic whatever the split) run one long workgroup per compute unit; the other
+    // 1x1 launches take two, gathers over several taps four.
+    const WgradShape& h = s[0];
+    int64_t target = 1024;
+    if (h.taps == 1) target = (double)h.N * h.K / ((double)h.N + h.K) < 150.0 ? 256 : 512;
+    if (tune > 0) target = tune;
+    int64_t splits = up(target, h.tiles());
+    out[0] = cut(h, splits);
+    while (out[0].splits > 1 && h.partials(out[0].splits) > (int64_t)partials_bytes) out[0] = cut(h, out[0].splits - 1);
+    return;
+  }
+  // Several layers: as many steps to a workgroup as give the launch kWgradBlocks of them, the same for every layer, so that they end
+  // together; one split each where the tiles alone are that many.
+  int64_t work = 0;
+  for (int k = 0; k < n; k++) work += s[k].tiles() * s[k].steps();
+  const int64_t target = tune > 0 ? tune : kWgradBlocks;
+  for (int64_t per = std::max<int64_t>(4, up(work, target));; per += std::max<int64_t>(1, per / 16)) {
+    int64_t blocks = 0, bytes = 0;
+    bool whole = true;
+    for (int k = 0; k < n; k++) {
+      out[k] = cut(s[k], up(s[k].steps(), per));
+      blocks += s[k].tiles() * out[k].splits;
+      bytes += s[k].partials(out[k].splits);
+      whole = whole && out[k].splits == 1;
+    }
+    if (whole || (blocks <= target && bytes <= (int64_t)partials_bytes)) return;
+  }
+}
+// Whether a layer by itself loses little: its splits' partial sums, written and read again, are a small part of what its operands move.
+inline bool wgrad_alone(const WgradShape& h, int64_t operand_bytes) {
+  WgradSplit r;
+  wgrad_plan(&h, 1, ~(size_t)0 >> 1, 0, &r);
+  return r.splits == 1 || 4 * (2 * h.partials(r.splits)) <= operand_bytes;
+}
+// Whether the layers collected so far are a launch: tiles enough without a split, or enough work for every compute unit to be busy
+// some 20 us (96 steps in each of 512 workgroups), or as much as the pass still has to collect and worth a launch: launches run beside
+// the data gradients of the layers in front, and what is launched last runs beside nothing.
+inline bool wgrad_batch_full(int64_t tiles, int64_t work, int jobs, int64_t work_left) {
+  return jobs >= kWgradJobs || tiles >= kWgradBlocks || work >= (int64_t)kWgradBlocks * 96 ||
+         (work >= work_left && work >= (int64_t)kWgradBlocks * 16);
+}
+
 // ---- what conv_generic.hip takes ----------------------------------------------------------------------------------------
 // 32-bit element offsets, and launches within the runtime's limits: fewer than 2^32 threads along x (256 for each 64 pixels,
 // input or output, and for each tile of a weight gradient, at the least 16 x 32 elements), 65535 blocks along y (64 channels

@@ -1075,7 +1075,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
   hipStream_t side = nullptr;
   if (!timer_enabled() && !force_serial()) {
     side_lock.lock();
-    int convs = 0;
+    int convs = 16;   // (a launch per convolution and tile class at the most)
     for (const Op& o : m->ops) convs += o.kind == OP_CONV ? 1 : 0;
     side = side_stream();
     if (side && !side_event(convs)) side = nullptr;
@@ -1096,7 +1096,36 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     }
   }
   int forks = 0;
+  // The weight gradients of the matrix-core convolutions wait here, by tile class, until they are a launch (wgrad_batch_full): each
+  // needs its dy and its input only, which nothing after this point of the pass writes to.  They have a partials area of their own.
+  struct PendingWgrads { std::vector<WgradProblem> p; int64_t tiles = 0, work = 0, work_left = 0; double flops = 0, bytes = 0; };
+  PendingWgrads pending[8];
+  auto operand_bytes = [](const ConvGeom& g) { return 2 * (g.B * g.H * g.W * (int64_t)g.Cin + g.M() * (int64_t)g.Cout); };
+  auto waits = [&](const ConvGeom& g, const WgradShape& h) { return g.Cin > 16 && !wgrad_alone(h, operand_bytes(g)); };   // (not a packed stem)
+  for (size_t i = (size_t)m->first_trainable_op; i < m->ops.size(); i++) {
+    if (m->ops[i].kind != OP_CONV || grouped_sliced(m, m->ops[i], batch) || m->ops[i].groups > 1) continue;
+    const ConvGeom g = conv_geom(m, m->ops[i], batch), gp = packed_geom(g);
+    const WgradShape h = conv_wgrad_shape(gp, 1);
+    if (use_mfma(m, g) && waits(gp, h)) pending[h.tile_class()].work_left += h.tiles() * h.steps();
+  }
   int late_rc = CD_OK;   // a launch-time failure of the fork / join machinery: reported after the join was attempted
+  hipStream_t wgrad_stream = side ? side : c.s;
+  auto run_wgrads = [&](PendingWgrads& q) {
+    if (q.p.empty()) return;
+    if (side) {
+      hipEvent_t ev = side_event(forks);
+      if (!ev || hipEventRecord(ev, c.s) != hipSuccess || hipStreamWaitEvent(side, ev, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        late_rc = set_error(CD_ERR_HIP, "backward: could not fork onto the weight-gradient stream (event record / wait failed)");
+      }
+      forks++;
+    }
+    ProfScope pr(CD_K_CONV_WGRAD, wgrad_stream, q.flops, q.bytes);
+    conv_wgrad_batch(q.p.data(), (int)q.p.size(), c.partials_side(), c.plan.partials_bytes, wgrad_stream);
+    q.p.clear();
+    q.tiles = q.work = 0;
+    q.flops = q.bytes = 0.0;
+  };
   std::vector<char> written(m->tensors.size(), 0);
   // gradients of residual inputs that are handed on as "dy and a bit mask" instead of being written
   // (see residual_grad_route)
@@ -1312,39 +1341,36 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
           relu_bwd_inplace(dt, dy, c.act(o.y), g.M() * g.Cout, c.s);
         }
         const bool mf = use_mfma(m, g);
-        {
-          hipStream_t ws_ = c.s;
-          float* wpart = c.partials();
-          if (mf && side) {
-            hipEvent_t ev = side_event(forks);
-            if (ev && hipEventRecord(ev, c.s) == hipSuccess && hipStreamWaitEvent(side, ev, 0) == hipSuccess) {
-              ws_ = side;
-              wpart = c.partials_side();
-              forks++;
-            }
+        if (mf) {   // (the bias gradient, column sums of dy, comes with the weight gradient)
+          const ConvGeom gp = packed_geom(g);
+          WgradProblem w = {static_cast<const bf16_t*>(in), static_cast<const bf16_t*>(dy), G(o.pw), o.pb >= 0 ? G(o.pb) : nullptr, gp, 1};
+          if (g.Cin == 3) {  // the forward pass left the re-laid-out image in xpack
+            w.x = c.xpack();
+            w.dw = reinterpret_cast<float*>(c.wpack());
           }
-          if (o.pb >= 0) {  // the bias gradient reads dy only, like the weight gradient: same stream, same partials area
-            ProfScope pr(CD_K_GLUE, ws_, 0, (double)g.M() * g.Cout * m->esize());
-            colsum(dt, dy, g.M(), g.Cout, G(o.pb), wpart, ws_);
+          const WgradShape h = conv_wgrad_shape(gp, 1);
+          PendingWgrads one;
+          const bool wait = waits(gp, h);
+          PendingWgrads& q = wait ? pending[h.tile_class()] : one;
+          q.p.push_back(w);
+          q.tiles += h.tiles();
+          q.work += h.tiles() * h.steps();
+          q.flops += 2.0 * g.M() * g.Cout * g.K();
+          q.bytes += conv_bytes(m, g) + 2.0 * g.Cout * g.K();
+          if (wait) q.work_left -= h.tiles() * h.steps();
+          if (!wait || wgrad_batch_full(q.tiles, q.work, (int)q.p.size(), q.work_left)) run_wgrads(q);
+          if (s2d_form(g)) s2d_unpack_dw(w.dw, G(o.pw), g.Cout, g.kh, gp.kh, 2 * gp.pad - g.pad, wgrad_stream);
+          else if (g.Cin == 3) unpad_c8_to_c3(w.dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, wgrad_stream);
+        } else {
+          if (o.pb >= 0) {
+            ProfScope pr(CD_K_GLUE, c.s, 0, (double)g.M() * g.Cout * m->esize());
+            colsum(dt, dy, g.M(), g.Cout, G(o.pb), c.partials(), c.s);
           }
-          ProfScope pr(CD_K_CONV_WGRAD, ws_, 2.0 * g.M() * g.Cout * g.K(), conv_bytes(m, g) + 2.0 * g.Cout * g.K());
-          if (mf) {
-            const ConvGeom gp = packed_geom(g);
-            const bf16_t* src = static_cast<const bf16_t*>(in);
-            float* dw = G(o.pw);
-            if (g.Cin == 3) {  // the forward pass left the re-laid-out image in xpack
-              src = c.xpack();
-              dw = reinterpret_cast<float*>(c.wpack());
-            }
-            conv_wgrad_mfma(src, static_cast<const bf16_t*>(dy), dw, gp, wpart, c.plan.partials_bytes, ws_);
-            if (s2d_form(g)) s2d_unpack_dw(dw, G(o.pw), g.Cout, g.kh, gp.kh, 2 * gp.pad - g.pad, ws_);
-            else if (g.Cin == 3) unpad_c8_to_c3(dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, ws_);
-          } else {
-            if (use_generic(g) && generic_wgrad_pays(g.M(), (int64_t)g.Cout * g.K()))
-              conv_wgrad_generic(dt, in, dy, G(o.pw), g, wpart, c.plan.partials_bytes, c.s);
-            else
-              conv_wgrad_simple(dt, in, dy, G(o.pw), g, c.s);
-          }
+          ProfScope pr(CD_K_CONV_WGRAD, c.s, 2.0 * g.M() * g.Cout * g.K(), conv_bytes(m, g) + 2.0 * g.Cout * g.K());
+          if (use_generic(g) && generic_wgrad_pays(g.M(), (int64_t)g.Cout * g.K()))
+            conv_wgrad_generic(dt, in, dy, G(o.pw), g, c.partials(), c.plan.partials_bytes, c.s);
+          else
+            conv_wgrad_simple(dt, in, dy, G(o.pw), g, c.s);
         }
         if (o.x != 0) {
           ProfScope pr(CD_K_CONV_DGRAD, c.s, 2.0 * g.M() * g.Cout * g.K(), conv_bytes(m, g));
@@ -1388,6 +1414,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     }
     if (o.x != 0) written[o.x] = 1;
   }
+  for (PendingWgrads& q : pending) run_wgrads(q);
   if (forks > 0) {  // join: the caller's stream continues after the last weight gradient
     hipEvent_t ev = side_event(forks);
     if (!ev || hipEventRecord(ev, side) != hipSuccess || hipStreamWaitEvent(c.s, ev, 0) != hipSuccess) {

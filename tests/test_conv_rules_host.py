@@ -166,3 +166,51 @@ def test_dense_weight_gradient_stays_within_the_launch_limits(tmp_path, F, C):
     tiles, groups = -(-(F + 1) // 64), -(-C // 4)
     assert x * 256 < 2 ** 32 and y <= 65535 and x % tiles == 0
     assert (y - 1) * (x // tiles) < groups <= y * (x // tiles)    # the last row of blocks is wanted, and the last class has a block
+
+
+@pytest.fixture(scope="module")
+def wgrad_splits(tmp_path_factory):
+    """per layer: splits, where the rows that the splits take one after the other end, whether each is whole 32-row steps; then the
+    launch's workgroups and the bytes of its partial sums.  arguments: scratch bytes, then M N K pointwise bias per layer"""
+    run = compiled(tmp_path_factory.mktemp("wgrad"), """
+int main(int c, char** v) {
+  const int n = (c - 2) / 5;
+  WgradShape s[16]; WgradSplit r[16];
+  for (int k = 0; k < n; k++) {
+    char** a = v + 2 + 5 * k;
+    s[k].M = atoll(a[0]); s[k].N = atoi(a[1]); s[k].K = atoi(a[2]); s[k].pointwise = atoi(a[3]); s[k].bias = atoi(a[4]);
+    s[k].taps = s[k].pointwise ? 1 : 9; s[k].slices = 1;
+  }
+  wgrad_plan(s, n, (size_t)atoll(v[1]), 0, r);
+  long long blocks = 0, bytes = 0;
+  for (int k = 0; k < n; k++) {
+    long long at = 0, i;
+    for (i = 0; i < r[k].splits; i++) {   // the kernel's 32-bit arithmetic
+      const int M = (int)s[k].M, mbeg = (int)i * (int)r[k].m_per_split;
+      const int mend = M - mbeg > (int)r[k].m_per_split ? mbeg + (int)r[k].m_per_split : M;
+      if (mbeg != at || mend <= mbeg) break;
+      at = mend;
+    }
+    printf("%lld %lld %d ", (long long)r[k].splits, at, r[k].m_per_split % 32 == 0);
+    blocks += s[k].tiles() * r[k].splits; bytes += s[k].partials(r[k].splits);
+  }
+  printf("%lld %lld", blocks, bytes);
+}
+""")
+    return lambda *a: [int(t) for t in run(*a).split()]
+
+
+@pytest.mark.parametrize("scratch", [128 << 20, 1 << 20])
+@pytest.mark.parametrize("layers", [[(1, 8, 8, 1, 0)], [(134217727, 8, 8, 1, 0)], [(8192, 512, 512, 1, 1)], [(8192, 32768, 512, 1, 0)], [(802816, 64, 576, 0, 0)],
+                                    [(8192, 512, 512, 1, 1), (8192, 1536, 512, 1, 1), (8192, 2048, 512, 1, 1), (8192, 512, 2048, 1, 1)],
+                                    [(31, 128, 1152, 0, 0)] * 16, [(75, 72, 648, 0, 0), (27, 80, 720, 0, 0), (50176, 256, 2304, 0, 0)],
+                                    [(12544, 512, 4608, 0, 0)] * 5])
+def test_weight_gradient_splits_take_every_row_once(wgrad_splits, layers, scratch):
+    got = wgrad_splits(scratch, *[v for l in layers for v in l])
+    blocks, bytes_ = got[-2:]
+    splits = got[0:-2:3]
+    for k, l in enumerate(layers):
+        assert got[3 * k + 1] == l[0] and got[3 * k + 2] == 1
+    assert bytes_ <= scratch
+    if len(layers) > 1:   # a launch of several layers stays within two workgroups a compute unit where it splits at all
+        assert blocks <= 512 or all(s == 1 for s in splits)

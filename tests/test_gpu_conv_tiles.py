@@ -27,6 +27,11 @@ SHAPES = {
     # 537 tiles of 256x32, the last one ragged: two stages; three and five steps of 8 and 16 channels, nine of 32
     "narrow_16": (dict(kind=1, widths=[16], blocks=[1], stem_width=16), lambda: nets.resnet20(widths=(16,), blocks=(1,)), 143, 31),
     "narrow_32": (dict(kind=1, widths=[32], blocks=[1], stem_width=32), lambda: nets.resnet20(widths=(32,), blocks=(1,)), 143, 31),
+    # weight gradients of several layers in a launch: 21 of one tile class (more than a launch takes), 75 and 27 pixels (no whole steps)
+    "many_layers": (dict(kind=1, widths=[72, 80], blocks=[5, 5], stem_width=72), lambda: nets.resnet20(widths=(72, 80), blocks=(5, 5)), 3, 5),
+    # 16 and 4 pixels: less than a step; 64-column and 64-row tiles beside 128 (bottleneck: 1x1 and 3x3, stride 2, a shortcut each)
+    "few_pixels": (dict(kind=2, widths=[24, 72], blocks=[2, 2], stem_width=64),
+                   lambda: nets.resnet50(classes=10, widths=(24, 72), blocks=(2, 2), stem=64), 1, 16),
     # 520 tiles with column sums: 128x128 still (without the sums 256x128: the test below)
     "rows_per_sum": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), lambda: nets.resnet20(widths=(128,), blocks=(1,)), 260, 16),
 }
