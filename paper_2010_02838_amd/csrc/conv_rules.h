@@ -197,6 +197,32 @@ constexpr int generic_split_end(int M, int mbeg, int m_per_split) {
   return M - mbeg > m_per_split ? mbeg + m_per_split : M;
 }
 
+// ---- elementwise passes of the BatchNorms (norm.hip) --------------------------------------------------------------------------
+// Channels are cut into groups of at most 64, a block takes one of them for all of its rows.
+constexpr int kFoldChunks = 32;   // chunks that long lists of partial sums are folded into
+// Small tensors' blocks add up the partial sums of their channels themselves, 64 KB at the most, 16 loads a thread.  ResNet-20 at
+// batch 128 (0.5 to 4 MB): 240 -> 178 launches, 1330 -> 1192 us a step (1214 with up to 32 KB); a two-block fp32 network (2 MB) 318 -> 309.
+// Larger ones lose: 2048 blocks of several trips in ResNet-50 at batch 256, the sums folded to 16 KB for each: forward passes 41 -> 53 us,
+// backward 58 -> 74, against 10 us of separate kernels; Wide-ResNet's 16 to 31 MB 9 -> 15, against 5.
+constexpr int kSumBytes = 64 << 10;
+struct BnGroups { int gc, groups; };
+inline BnGroups bn_groups(int C, int vec) {
+  BnGroups g;
+  const int n = (C + 63) / 64, each = (C + n - 1) / n;
+  g.gc = (each + vec - 1) / vec * vec;
+  g.groups = (C + g.gc - 1) / g.gc;
+  return g;
+}
+constexpr int64_t kSumTensor = 8 << 20;
+inline bool bn_own_sums(int64_t M, int C, int esize, BnGroups g, int chunks) {
+  return (int64_t)chunks * g.gc * 8 <= kSumBytes && M * C * esize <= kSumTensor;
+}
+// blocks over M rows: a trip of `unroll` rows a thread
+inline int64_t bn_blocks(int64_t M, BnGroups g, int vec, int unroll) {
+  const int64_t rows = (int64_t)(256 / (g.gc / vec)) * unroll;
+  return (M + rows - 1) / rows * g.groups;
+}
+
 // ---- weight gradient of a dense layer (kernels_simple.hip) -----------------------------------------------------------------
 // A block per 64 of the F + 1 columns and 4 classes, the column tiles of 4 classes side by side (they read the same part of dy:
 // 20000 classes of 512 columns over 256 rows 922 us so, 1388 with the classes side by side), as many classes along x as a

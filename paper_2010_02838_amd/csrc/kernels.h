@@ -62,10 +62,12 @@ void colsum(int dtype, const void* a, int64_t M, int C, float* out, float* parti
 // relu_mask (nullable; bf16 with C % 8 == 0 only): M*C/8 bytes, bit k of byte i = (y[8i + k] > 0).  The
 // forward pass writes it, the backward pass reads it instead of y (an eighth of a byte per element
 // instead of two bytes, in both of its passes).
-// Two steps.  bn_stats: the batch statistics of x into stats; with pre_chunks > 0 the column sums are
-// already in partials ([pre_chunks][stat_pitch(C)], from the producing convolution; scratch: room for
-// 32 * stat_pitch(C) floats behind them), with pre_chunks == 0 x is reduced first (partials is scratch).
-// bn_apply: the elementwise pass with those statistics.
+// pre_chunks > 0: the column sums of x are already in partials ([pre_chunks][stat_pitch(C)], from the producing convolution, with
+// room for 32 * stat_pitch(C) floats behind them); pre_chunks == 0: x is reduced first (partials is scratch).
+// running (nullable): the running averages, updated with momentum 0.1.
+void bn_forward(int dtype, const void* x, const void* res, bool relu, void* y, const void* gamma, const void* beta, int64_t M, int C,
+                float* stats, float* partials, int pre_chunks, uint8_t* relu_mask, float* running, hipStream_t s);
+// The statistics alone, into stats (in front of bn_relu_pool); scratch: the room behind the sums.
 void bn_stats(int dtype, const void* x, const void* gamma, const void* beta, int64_t M, int C, float* stats,
               float* partials, int pre_chunks, float* scratch, hipStream_t s);
 // Running averages [mean[C] | var[C]] (fp32) for the evaluation mode: updated from the statistics of a training-mode
@@ -76,11 +78,9 @@ void bn_stats_from_running(int dtype, const float* running, const void* gamma, c
 // bn_apply_running: the elementwise pass with the running averages [mean | var]; stats (4 C floats) may be written.
 void bn_apply_running(int dtype, const void* x, const void* res, bool relu, void* y, int64_t M, int C, const float* running,
                       const void* gamma, const void* beta, float* stats, uint8_t* relu_mask, hipStream_t s);
-void bn_apply(int dtype, const void* x, const void* res, bool relu, void* y, int64_t M, int C, const float* stats,
-              uint8_t* relu_mask, hipStream_t s);
-// bn_apply with ReLU followed by a 3x3 stride-2 pad-1 max-pool, in one pass: y [B][H/2][W/2][C] is the pooled
+// The normalisation with ReLU followed by a 3x3 stride-2 pad-1 max-pool, in one pass: y [B][H/2][W/2][C] is the pooled
 // tensor, the normalised one is not written.  bf16, C % 8 == 0, even H and W, 16-byte aligned pointers.
-// argmax (nullable): as maxpool_fwd writes it; relu_mask (nullable): as bn_apply writes it.
+// argmax (nullable): as maxpool_fwd writes it; relu_mask (nullable): as bn_forward writes it.
 void bn_relu_pool(const bf16_t* x, const float* stats, bf16_t* y, uint8_t* argmax, uint8_t* relu_mask, int64_t B, int H,
                   int W, int C, hipStream_t s);
 // Its backward pass: dpool [B][H/2][W/2][C] is the gradient of the pooled tensor, argmax and relu_mask what the

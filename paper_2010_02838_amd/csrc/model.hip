@@ -936,30 +936,29 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
         const void* res = o.res >= 0 ? c.act(o.res) : nullptr;
         float* running = bn_running ? bn_running + 2 * m->bn_off[o.bn_slot] : nullptr;   // this op's [mean | var]
         const bool pooled = pool_fused(m, (int)oi);
-        if (bn_mode == CD_BN_RUNNING) {
-          if (pooled) {   // (only the fused max-pool wants the statistics as such)
-            ProfScope pr(CD_K_NORM, c.s, 0, 0.0);
-            bn_stats_from_running(dt, running, c.P(o.pw), c.P(o.pb), c.stats(o), tx.c, c.s);
-          }
-        } else {
-          ProfScope pr(CD_K_NORM, c.s, 0, fused ? 0.0 : (double)M * tx.c * m->esize());
-          bn_stats(dt, in, c.P(o.pw), c.P(o.pb), M, tx.c, c.stats(o), c.partials(), fused ? stat_chunks : 0,
-                   fused ? c.partials() + (size_t)stat_chunks * stat_pitch(tx.c) : nullptr, c.s);
-          if (running) bn_running_update(c.stats(o), running, M, tx.c, 0.1f, c.s);
-        }
         if (pooled) {   // the next op, a max-pool, is computed here; `out` stays unwritten
           const Op& q = m->ops[oi + 1];
+          {
+            ProfScope pr(CD_K_NORM, c.s, 0, fused || bn_mode == CD_BN_RUNNING ? 0.0 : (double)M * tx.c * m->esize());
+            if (bn_mode == CD_BN_RUNNING) {
+              bn_stats_from_running(dt, running, c.P(o.pw), c.P(o.pb), c.stats(o), tx.c, c.s);
+            } else {
+              bn_stats(dt, in, c.P(o.pw), c.P(o.pb), M, tx.c, c.stats(o), c.partials(), fused ? stat_chunks : 0,
+                       fused ? c.partials() + (size_t)stat_chunks * stat_pitch(tx.c) : nullptr, c.s);
+              if (running) bn_running_update(c.stats(o), running, M, tx.c, 0.1f, c.s);
+            }
+          }
           ProfScope pr(CD_K_NORM, c.s, 0, (double)M * tx.c * (m->esize() * 1.25 + (mask ? 0.125 : 0.0) + (c.plan.aux[oi + 1] ? 0.25 : 0.0)));
           bn_relu_pool(static_cast<const bf16_t*>(in), c.stats(o), static_cast<bf16_t*>(c.act(q.y)),
                        c.plan.aux[oi + 1] ? reinterpret_cast<uint8_t*>(c.ws + c.plan.aux[oi + 1]) : nullptr, mask, batch, tx.h,
                        tx.w, tx.c, c.s);
-        } else {
+        } else if (bn_mode == CD_BN_RUNNING) {
           ProfScope pr(CD_K_BN_APPLY, c.s, 0,
                        (double)M * tx.c * (m->esize() * (2 + (res ? 1 : 0)) + (o.relu && mask ? 0.125 : 0.0)));
-          if (bn_mode == CD_BN_RUNNING)
-            bn_apply_running(dt, in, res, o.relu, out, M, tx.c, running, c.P(o.pw), c.P(o.pb), c.stats(o), mask, c.s);
-          else
-            bn_apply(dt, in, res, o.relu, out, M, tx.c, c.stats(o), mask, c.s);
+          bn_apply_running(dt, in, res, o.relu, out, M, tx.c, running, c.P(o.pw), c.P(o.pb), c.stats(o), mask, c.s);
+        } else {
+          bn_forward(dt, in, res, o.relu, out, c.P(o.pw), c.P(o.pb), M, tx.c, c.stats(o), c.partials(), fused ? stat_chunks : 0, mask,
+                     running, c.s);
         }
         stat_tensor = -1;
         break;

@@ -8,6 +8,7 @@
 // load stays coalesced.  Partial sums per row chunk go to a scratch array and a second, tiny
 // kernel adds them in a fixed order (deterministic, no atomics).
 #include "kernels.h"
+#include "conv_rules.h"
 
 namespace cd {
 
@@ -73,6 +74,39 @@ template <> struct Vec<bf16_t, 8> {
     *reinterpret_cast<uint4*>(p) = make_uint4(u[0], u[1], u[2], u[3]);
   }
 };
+
+// The end of a block's column sums: [rpi rows][vcb * VEC columns] of the threads' sums in s0 and s1 (LDS) are added down the rows and stored at
+// columns c0 ... of a partial row.  Few columns: all threads share the rows (one thread per vector walked up to 256 of them
+// alone; with the blocks of reduce_plan 32768 x 16 fp32, MODE 1, 8.8 -> 4.3 us, 131072 x 16 bf16 19.9 -> 5.8).
+template <int VEC>
+__device__ inline void block_column_sums(float* s0, float* s1, int vcb, int rpi, int c0, int C, float* __restrict__ out) {
+  const int cols = vcb * VEC;
+  __syncthreads();
+  if (cols < 256) {
+    const int L = 256 / cols, col = threadIdx.x % cols, lane = threadIdx.x / cols;
+    float t0 = 0.f, t1 = 0.f;
+    if (lane < L)
+      for (int j = lane; j < rpi; j += L) { t0 += s0[j * cols + col]; t1 += s1[j * cols + col]; }
+    __syncthreads();
+    if (lane < L) { s0[threadIdx.x] = t0; s1[threadIdx.x] = t1; }
+    __syncthreads();
+    if ((int)threadIdx.x >= cols) return;
+    for (int l = 1; l < L; l++) { t0 += s0[l * cols + col]; t1 += s1[l * cols + col]; }
+    out[c0 + col] = t0;
+    out[C + c0 + col] = t1;
+    return;
+  }
+  if ((int)threadIdx.x < vcb) {
+#pragma unroll
+    for (int k = 0; k < VEC; k++) {
+      const int col = (int)threadIdx.x * VEC + k;
+      float t0 = 0.f, t1 = 0.f;
+      for (int j = 0; j < rpi; j++) { t0 += s0[j * cols + col]; t1 += s1[j * cols + col]; }
+      out[c0 + col] = t0;
+      out[C + c0 + col] = t1;
+    }
+  }
+}
 
 // MODE 0: sums of x and x^2.  MODE 1: sums of dz and dz*xhat with dz = dy * (relu ? y > 0 : 1).
 // MODE 2: sum of a0.  partials: [chunks][stat_pitch(C)].
@@ -182,19 +216,7 @@ __global__ void __launch_bounds__(256) col_reduce_k(const T* __restrict__ a0, co
 #pragma unroll
     for (int k = 0; k < VEC; k++) { sm[0][threadIdx.x * VEC + k] = s0[k]; sm[1][threadIdx.x * VEC + k] = s1[k]; }
   }
-  __syncthreads();
-  if ((int)threadIdx.x < vcb) {
-#pragma unroll
-    for (int k = 0; k < VEC; k++) {
-      float t0 = 0.f, t1 = 0.f;
-      for (int j = 0; j < rpi; j++) {
-        t0 += sm[0][(j * vcb + tx) * VEC + k];
-        t1 += sm[1][(j * vcb + tx) * VEC + k];
-      }
-      partials[(int64_t)blockIdx.x * stat_pitch(C) + c0 + k] = t0;
-      partials[(int64_t)blockIdx.x * stat_pitch(C) + C + c0 + k] = t1;
-    }
-  }
+  block_column_sums<VEC>(sm[0], sm[1], vcb, rpi, v0 * VEC, C, partials + (int64_t)blockIdx.x * stat_pitch(C));
 }
 
 // FIN 0: BatchNorm statistics.  FIN 1: BatchNorm backward sums.  FIN 2: plain column sum.
@@ -364,6 +386,209 @@ __global__ void __launch_bounds__(256) bn_apply_k(const T* __restrict__ x, const
   }
 }
 
+// ---- elementwise passes that finish the column sums themselves -----------------------------------------------------------
+// A block owns a group of up to 64 channels (the same for all of its rows) and adds that group's partial sums, at most kSumBytes of
+// them, while its first rows are on their way; a kernel for that in front of every pass was 2 to 5 us and a launch each (two where there
+// are more than 256 chunks), as long as the pass itself.  (Which tensors: bn_own_sums in conv_rules.h.)
+//
+// Totals of channels c0 .. c0 + gc of the partial sums [chunks][pitch] into sm: [2][64] doubles at the front.  Every thread adds
+// four neighbouring columns of every L-th chunk, eight loads in flight; the L = 512 / gc partial totals of a column are added in order.
+__device__ inline void group_totals(const float* __restrict__ part, int chunks, int C, int c0, int gc, double* sm) {
+  const int64_t pitch = stat_pitch(C);
+  const int cols4 = gc / 2, L = 256 / cols4;   // 16-byte columns: gc / 4 of the first sums, gc / 4 of the second
+  const int col = threadIdx.x % cols4, lane = threadIdx.x / cols4;
+  double t[4] = {0.0, 0.0, 0.0, 0.0};
+  if (lane < L) {
+    const float* p = part + (col < gc / 4 ? c0 + 4 * col : C + c0 + 4 * (col - gc / 4));
+    for (int j = lane; j < chunks; j += L * kFinalizeLoads) {
+      float4 v[kFinalizeLoads];
+#pragma unroll
+      for (int u = 0; u < kFinalizeLoads; u++) {   // (loads past the last chunk re-read a real one, count as zero)
+        const bool in = j + u * L < chunks;
+        v[u] = *reinterpret_cast<const float4*>(p + (int64_t)(in ? j + u * L : j) * pitch);
+        if (!in) v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+#pragma unroll
+      for (int u = 0; u < kFinalizeLoads; u++) { t[0] += (double)v[u].x; t[1] += (double)v[u].y; t[2] += (double)v[u].z; t[3] += (double)v[u].w; }
+    }
+    // column-major over the lanes: [lane][2 gc]
+    double* o = sm + lane * 2 * gc + 4 * col;
+    o[0] = t[0]; o[1] = t[1]; o[2] = t[2]; o[3] = t[3];
+  }
+  __syncthreads();
+  double s = 0.0;
+  if ((int)threadIdx.x < 2 * gc)
+    for (int l = 0; l < L; l++) s += sm[l * 2 * gc + threadIdx.x];
+  __syncthreads();
+  if ((int)threadIdx.x < 2 * gc) sm[(int)threadIdx.x < gc ? threadIdx.x : 64 + threadIdx.x - gc] = s;
+  __syncthreads();
+}
+
+// The block's share of an elementwise pass: group of channels and rows.  Consecutive logical blocks (the groups of the same
+// rows) run on one XCD, so that a row's pieces, and the bytes of its bit mask, meet in one L2; last rows first: what was written
+// or read most recently is what the caches still hold.
+struct GroupRows { int c0, gc; int64_t r0, rstride; bool first; int off; };   // off: this thread's first channel in the group, -1: idle
+template <int VEC>
+__device__ inline GroupRows group_rows(int C, int gc, int groups) {
+  const unsigned xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3, per = gridDim.x >> 3, rem = gridDim.x & 7u;
+  const unsigned id = xcd * per + (xcd < rem ? xcd : rem) + idx;
+  const int g = (int)(id % (unsigned)groups), rb = (int)(id / (unsigned)groups), nrb = (int)(gridDim.x / (unsigned)groups);
+  GroupRows q;
+  q.c0 = g * gc;
+  q.gc = C - q.c0 < gc ? C - q.c0 : gc;
+  const int vpr = q.gc / VEC, rpi = 256 / vpr, ty = threadIdx.x / vpr;
+  q.off = ty < rpi ? (int)(threadIdx.x % vpr) * VEC : -1;
+  q.r0 = (int64_t)(nrb - 1 - rb) * rpi + ty;
+  q.rstride = (int64_t)nrb * rpi;
+  q.first = rb == 0;
+  return q;
+}
+
+// forward: batch statistics from the sums and y = relu?(scale * x + shift (+ res)); the first block of each group leaves the
+// statistics in stats for the backward pass
+template <typename T, int VEC>
+__global__ void __launch_bounds__(256) bn_sums_apply_k(const T* __restrict__ x, const T* __restrict__ res, T* __restrict__ y,
+                                                       const float* __restrict__ part, int chunks, int64_t M, int C, int gc_max,
+                                                       int groups, const T* __restrict__ gamma, const T* __restrict__ beta,
+                                                       float* __restrict__ stats, int relu, uint8_t* __restrict__ mask) {
+  __shared__ __attribute__((aligned(16))) double sm[1024];
+  __shared__ float ss[2][64];
+  const GroupRows q = group_rows<VEC>(C, gc_max, groups);
+  // the first trip's rows are requested before the sums are added up
+  const int64_t c = q.c0 + (q.off < 0 ? 0 : q.off), end = q.off < 0 ? 0 : M;
+  typename Vec<T, VEC>::Raw ra[kEltUnroll], rr[kEltUnroll];
+  auto request = [&](int64_t rb) {
+#pragma unroll
+    for (int u = 0; u < kEltUnroll; u++) {
+      const int64_t r = rb + u * q.rstride;
+      if (r < end) {
+        ra[u] = Vec<T, VEC>::ldraw_nt(x + r * C + c);
+        if (res) rr[u] = Vec<T, VEC>::ldraw_nt(res + r * C + c);
+      }
+    }
+  };
+  request(q.r0);
+  group_totals(part, chunks, C, q.c0, q.gc, sm);
+  if ((int)threadIdx.x < q.gc) {
+    const int c = q.c0 + threadIdx.x;
+    const double mean = sm[threadIdx.x] / (double)M;
+    double var = sm[64 + threadIdx.x] / (double)M - mean * mean;
+    if (var < 0.0) var = 0.0;
+    const float istd = (float)(1.0 / sqrt(var + (double)kBnEps));
+    const float scale = Cvt<T>::ld(gamma[c]) * istd, shift = Cvt<T>::ld(beta[c]) - (float)mean * scale;
+    ss[0][threadIdx.x] = scale;
+    ss[1][threadIdx.x] = shift;
+    if (q.first) { stats[c] = (float)mean; stats[C + c] = istd; stats[2 * C + c] = scale; stats[3 * C + c] = shift; }
+  }
+  __syncthreads();
+  if (q.off < 0) return;
+  float sc[VEC], sh[VEC];
+#pragma unroll
+  for (int k = 0; k < VEC; k++) { sc[k] = ss[0][q.off + k]; sh[k] = ss[1][q.off + k]; }
+  for (int64_t rb = q.r0; rb < M; rb += q.rstride * kEltUnroll) {
+    if (rb != q.r0) request(rb);
+#pragma unroll
+    for (int u = 0; u < kEltUnroll; u++) {
+      const int64_t r = rb + u * q.rstride;
+      if (r < M) {
+        float a[VEC], e[VEC];
+        Vec<T, VEC>::unpack(ra[u], a);
+        if (res) Vec<T, VEC>::unpack(rr[u], e);
+        uint32_t bits = 0;
+#pragma unroll
+        for (int k = 0; k < VEC; k++) {
+          float v = fmaf(a[k], sc[k], sh[k]);
+          if (res) v += e[k];
+          a[k] = relu ? fmaxf(v, 0.f) : v;
+          bits |= (a[k] > 0.f ? 1u : 0u) << k;
+        }
+        Vec<T, VEC>::st(y + r * C + c, a);
+        if (VEC == 8 && mask) mask[(r * C + c) >> 3] = (uint8_t)bits;
+      }
+    }
+  }
+}
+
+// backward: dgamma, dbeta and the coefficients from the sums of dz and dz * xhat, and dx = c1 dz + c2 x + c3 (+ the residual's copy of dz)
+template <typename T, int VEC>
+__global__ void __launch_bounds__(256) bn_sums_bwd_k(const T* __restrict__ dy, const T* __restrict__ y, const T* __restrict__ x,
+                                                     const float* __restrict__ part, int chunks, int64_t M, int C, int gc_max,
+                                                     int groups, const T* __restrict__ gamma, const float* __restrict__ stats,
+                                                     float* __restrict__ dgamma, float* __restrict__ dbeta, int relu,
+                                                     T* __restrict__ dx, int acc_dx, T* __restrict__ dres, int acc_dres,
+                                                     const uint8_t* __restrict__ mask) {
+  constexpr int U = 2;
+  __shared__ __attribute__((aligned(16))) double sm[1024];
+  __shared__ float cc[3][64];
+  const GroupRows q = group_rows<VEC>(C, gc_max, groups);
+  const bool use_mask = VEC == 8 && mask != nullptr;
+  const int64_t c = q.c0 + (q.off < 0 ? 0 : q.off), end = q.off < 0 ? 0 : M;
+  typename Vec<T, VEC>::Raw rdz[U], rxv[U], ryv[U], rpdx[U], rpdr[U];
+  uint32_t bits[U];
+  auto request = [&](int64_t rb) {   // as in bn_sums_apply_k
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int64_t r = rb + u * q.rstride, i = r * C + c;
+      if (r < end) {
+        rdz[u] = Vec<T, VEC>::ldraw(dy + i);
+        rxv[u] = Vec<T, VEC>::ldraw(x + i);
+        if (relu) {
+          if (use_mask) bits[u] = mask[i >> 3];
+          else ryv[u] = Vec<T, VEC>::ldraw(y + i);
+        }
+        if (acc_dx) rpdx[u] = Vec<T, VEC>::ldraw(dx + i);
+        if (dres && acc_dres) rpdr[u] = Vec<T, VEC>::ldraw(dres + i);
+      }
+    }
+  };
+  request(q.r0);
+  group_totals(part, chunks, C, q.c0, q.gc, sm);
+  if ((int)threadIdx.x < q.gc) {
+    const int c = q.c0 + threadIdx.x;
+    const float mean = stats[c], istd = stats[C + c];
+    const float db = (float)sm[threadIdx.x], dg = (float)sm[64 + threadIdx.x];
+    const float c1 = Cvt<T>::ld(gamma[c]) * istd, c2 = -c1 * istd * dg / (float)M;
+    cc[0][threadIdx.x] = c1;
+    cc[1][threadIdx.x] = c2;
+    cc[2][threadIdx.x] = -c1 * db / (float)M - c2 * mean;
+    if (q.first) { dgamma[c] = dg; dbeta[c] = db; }
+  }
+  __syncthreads();
+  if (q.off < 0) return;
+  float c1[VEC], c2[VEC], c3[VEC];
+#pragma unroll
+  for (int k = 0; k < VEC; k++) { c1[k] = cc[0][q.off + k]; c2[k] = cc[1][q.off + k]; c3[k] = cc[2][q.off + k]; }
+  for (int64_t rb = q.r0; rb < M; rb += q.rstride * U) {
+    if (rb != q.r0) request(rb);
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int64_t r = rb + u * q.rstride, i = r * C + c;
+      if (r < M) {
+        float dz[VEC], xv[VEC], yv[VEC], pdx[VEC], pdr[VEC], o[VEC];
+        Vec<T, VEC>::unpack(rdz[u], dz);
+        Vec<T, VEC>::unpack(rxv[u], xv);
+        if (relu && !use_mask) Vec<T, VEC>::unpack(ryv[u], yv);
+        if (acc_dx) Vec<T, VEC>::unpack(rpdx[u], pdx);
+        if (dres && acc_dres) Vec<T, VEC>::unpack(rpdr[u], pdr);
+#pragma unroll
+        for (int k = 0; k < VEC; k++) {
+          if (relu) dz[k] = (use_mask ? ((bits[u] >> k) & 1u) != 0u : yv[k] > 0.f) ? dz[k] : 0.f;
+          o[k] = c1[k] * dz[k] + c2[k] * xv[k] + c3[k];
+          if (acc_dx) o[k] += pdx[k];
+        }
+        Vec<T, VEC>::st(dx + i, o);
+        if (dres) {
+          if (acc_dres) {
+#pragma unroll
+            for (int k = 0; k < VEC; k++) dz[k] += pdr[k];
+          }
+          Vec<T, VEC>::st(dres + i, dz);
+        }
+      }
+    }
+  }
+}
+
 // BatchNorm apply + ReLU + 3x3 stride-2 pad-1 max-pool in one pass (bf16, C % 8 == 0, even H and W): the
 // normalised tensor is never written.  One thread per pooled 8-channel vector; the window's values are
 // normalised on the fly (each input is read by 2.25 windows on average, from cache).  argmax
@@ -500,19 +725,7 @@ __global__ void __launch_bounds__(256) bn_pool_bwd_reduce_k(const bf16_t* __rest
 #pragma unroll
     for (int k = 0; k < 8; k++) { sm[0][threadIdx.x * 8 + k] = s0[k]; sm[1][threadIdx.x * 8 + k] = s1[k]; }
   }
-  __syncthreads();
-  if ((int)threadIdx.x < vcb) {
-#pragma unroll
-    for (int k = 0; k < 8; k++) {
-      float t0 = 0.f, t1 = 0.f;
-      for (int j = 0; j < rpi; j++) {
-        t0 += sm[0][(j * vcb + tx) * 8 + k];
-        t1 += sm[1][(j * vcb + tx) * 8 + k];
-      }
-      partials[(int64_t)blockIdx.x * stat_pitch(C) + c0 + k] = t0;
-      partials[(int64_t)blockIdx.x * stat_pitch(C) + C + c0 + k] = t1;
-    }
-  }
+  block_column_sums<8>(sm[0], sm[1], vcb, rpi, v0 * 8, C, partials + (int64_t)blockIdx.x * stat_pitch(C));
 }
 
 // dx = c1 * dz + c2 * x + c3 with the coefficients col_finalize_k<., 1> left in coef
@@ -626,7 +839,7 @@ static unsigned elt_grid(int64_t nvec, int vc, int unroll, bool* fixc) {
 
 // How the rows are cut into chunks; the same rule sizes the launch and bounds the partials.
 struct ReducePlan { int chunks; int64_t rows_per_chunk; int cgroups; };
-static ReducePlan reduce_plan(int64_t M, int C, int vec) {
+static ReducePlan reduce_plan(int64_t M, int C, int vec, int in_flight) {
   ReducePlan p;
   const int vc = C / vec;
   p.cgroups = (int)cdiv(vc, 256);
@@ -637,7 +850,9 @@ static ReducePlan reduce_plan(int64_t M, int C, int vec) {
   if (target > cap) target = cap;
   if (target < 1) target = 1;
   int64_t rpc = cdiv(M, target);
-  const int64_t min_rows = (int64_t)rpi * 8;              // at least a few iterations per block
+  // at least a few iterations per block; where that leaves compute units without a block, the rows a thread has in flight at a time
+  int64_t min_rows = (int64_t)rpi * 8;
+  if (cdiv(M, min_rows) * p.cgroups < 512) min_rows = (int64_t)rpi * in_flight;
   if (rpc < min_rows) rpc = min_rows;
   p.rows_per_chunk = rpc;
   p.chunks = (int)cdiv(M, rpc);
@@ -653,10 +868,19 @@ template <typename T> static int pick_vec(int C, const void* p0, const void* p1,
 template <typename T, int VEC, int MODE>
 static ReducePlan launch_reduce(const T* a0, const T* a1, const T* a2, const float* stats, bool relu, int64_t M, int C,
                                 float* partials, hipStream_t s, const uint8_t* mask = nullptr) {
-  ReducePlan p = reduce_plan(M, C, VEC);
+  ReducePlan p = reduce_plan(M, C, VEC, MODE == 1 ? 2 : 4);
   hipLaunchKernelGGL((col_reduce_k<T, VEC, MODE>), dim3(p.chunks, p.cgroups), dim3(256), 0, s, a0, a1, a2, stats,
                      (int)relu, M, C, p.rows_per_chunk, partials, mask);
   return p;
+}
+
+// Where the column sums of M rows lie, and in how many chunks: from the convolution in front (pre_chunks > 0, in partials), or reduced here.
+struct ColSums { const float* part; int chunks; };
+// Folds them into kFoldChunks in scratch where they are more than `most`
+static ColSums fold_sums(ColSums q, int C, int most, float* scratch, hipStream_t s) {
+  if (q.chunks <= most) return q;
+  hipLaunchKernelGGL(col_fold_k, dim3((unsigned)cdiv(C, 64), kFoldChunks), dim3(1024), 0, s, q.part, q.chunks, C, scratch);
+  return {scratch, kFoldChunks};
 }
 
 // Batch statistics -> stats.  pre_chunks > 0: the column sums are already in partials (written by the
@@ -666,19 +890,14 @@ static void bn_stats_t(const T* x, const T* gamma, const T* beta, int64_t M, int
                        int pre_chunks, float* scratch, hipStream_t s) {
   const int vec = pick_vec<T>(C, x, nullptr, nullptr, nullptr);
   constexpr int V = sizeof(T) == 2 ? 8 : 4;
-  int chunks = pre_chunks;
-  const float* src = partials;
-  if (pre_chunks == 0) {
-    ReducePlan p = vec > 1 ? launch_reduce<T, V, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)
-                           : launch_reduce<T, 1, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s);
-    chunks = p.chunks;
-  } else if (pre_chunks > 256) {
-    hipLaunchKernelGGL(col_fold_k, dim3((unsigned)cdiv(C, 64), 32), dim3(1024), 0, s, partials, pre_chunks, C, scratch);
-    chunks = 32;
-    src = scratch;
-  }
+  ColSums q = {partials, pre_chunks};
+  if (pre_chunks == 0)
+    q.chunks = (vec > 1 ? launch_reduce<T, V, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)
+                        : launch_reduce<T, 1, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)).chunks;
+  else
+    q = fold_sums(q, C, 256, scratch, s);
   hipLaunchKernelGGL((col_finalize_k<T, 0>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
-                     src, chunks, M, C, gamma, beta, stats, (float*)nullptr, (float*)nullptr, (float*)nullptr);
+                     q.part, q.chunks, M, C, gamma, beta, stats, (float*)nullptr, (float*)nullptr, (float*)nullptr);
 }
 
 // y = relu?(scale * x + shift (+ res)) with the scale and shift that bn_stats_t left in stats
@@ -699,26 +918,54 @@ static void bn_apply_t(const T* x, const T* res, bool relu, T* y, int64_t M, int
 }
 
 template <typename T>
+static void bn_forward_t(const T* x, const T* res, bool relu, T* y, const T* gamma, const T* beta, int64_t M, int C, float* stats,
+                         float* partials, int pre_chunks, uint8_t* mask, float* running, hipStream_t s) {
+  constexpr int V = sizeof(T) == 2 ? 8 : 4;
+  const bool vec = pick_vec<T>(C, x, res, y, partials) > 1;
+  const double bytes = (double)M * C * (sizeof(T) * (2 + (res ? 1 : 0)) + (relu && mask ? 0.125 : 0.0));
+  const BnGroups g = bn_groups(C, V);
+  int chunks = pre_chunks;
+  const bool own_sums = vec && bn_own_sums(M, C, sizeof(T), g, pre_chunks ? pre_chunks : reduce_plan(M, C, V, 4).chunks);
+  if (!own_sums || pre_chunks == 0) {
+    ProfScope pr(CD_K_NORM, s, 0, pre_chunks ? 0.0 : (double)M * C * sizeof(T));
+    if (own_sums) chunks = launch_reduce<T, V, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s).chunks;
+    else bn_stats_t<T>(x, gamma, beta, M, C, stats, partials, pre_chunks, partials + (size_t)pre_chunks * stat_pitch(C), s);
+  }
+  {
+    ProfScope pr(CD_K_BN_APPLY, s, 0, bytes);
+    if (own_sums)
+      hipLaunchKernelGGL((bn_sums_apply_k<T, V>), dim3((unsigned)bn_blocks(M, g, V, kEltUnroll)), dim3(256), 0, s, x, res, y,
+                         partials, chunks, M, C, g.gc, g.groups, gamma, beta, stats, (int)relu, relu ? mask : (uint8_t*)nullptr);
+    else
+      bn_apply_t<T>(x, res, relu, y, M, C, stats, mask, s);
+  }
+  if (running) {
+    ProfScope pr(CD_K_NORM, s, 0, 0.0);
+    bn_running_update(stats, running, M, C, 0.1f, s);
+  }
+}
+
+template <typename T>
 static void bn_backward_t(const T* dy, const T* y, const T* x, const T* gamma, const float* stats, bool relu, T* dx,
                           bool acc_dx, T* dres, bool acc_dres, float* dgamma, float* dbeta, float* coef,
                           float* partials, const uint8_t* mask, int64_t M, int C, hipStream_t s, int pre_chunks) {
   int vec = pick_vec<T>(C, dy, y, x, dx);
   if (!aligned16(dres)) vec = 1;
   constexpr int V = sizeof(T) == 2 ? 8 : 4;
-  int chunks = pre_chunks;
-  const float* src = partials;
-  if (pre_chunks == 0) {
-    ReducePlan p = vec > 1 ? launch_reduce<T, V, 1>(dy, y, x, stats, relu, M, C, partials, s, mask)
-                           : launch_reduce<T, 1, 1>(dy, y, x, stats, relu, M, C, partials, s);
-    chunks = p.chunks;
-  } else if (pre_chunks > 256) {   // the sums came per row tile of the data gradient that wrote dy: fold them first
-    float* scratch = partials + (size_t)pre_chunks * stat_pitch(C);
-    hipLaunchKernelGGL(col_fold_k, dim3((unsigned)cdiv(C, 64), 32), dim3(1024), 0, s, partials, pre_chunks, C, scratch);
-    chunks = 32;
-    src = scratch;
+  ColSums q = {partials, pre_chunks};   // (pre_chunks > 0: the sums came per row tile of the data gradient that wrote dy)
+  if (pre_chunks == 0)
+    q.chunks = (vec > 1 ? launch_reduce<T, V, 1>(dy, y, x, stats, relu, M, C, partials, s, mask)
+                        : launch_reduce<T, 1, 1>(dy, y, x, stats, relu, M, C, partials, s)).chunks;
+  const BnGroups g = bn_groups(C, V);
+  if (vec > 1 && aligned16(partials) && bn_own_sums(M, C, sizeof(T), g, q.chunks)) {
+    hipLaunchKernelGGL((bn_sums_bwd_k<T, V>), dim3((unsigned)bn_blocks(M, g, V, 2)), dim3(256), 0, s, dy, y, x, q.part,
+                       q.chunks, M, C, g.gc, g.groups, gamma, stats, dgamma, dbeta, (int)relu, dx, (int)acc_dx, dres,
+                       (int)acc_dres, mask);
+    return;
   }
+  if (pre_chunks) q = fold_sums(q, C, 256, partials + (size_t)pre_chunks * stat_pitch(C), s);
   hipLaunchKernelGGL((col_finalize_k<T, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
-                     src, chunks, M, C,
+                     q.part, q.chunks, M, C,
                      gamma, (const T*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
   const int64_t nvec = M * C / vec;
   bool fixc;
@@ -817,6 +1064,15 @@ void bn_apply_running(int dtype, const void* x, const void* res, bool relu, void
                               (const float*)beta, stats, relu_mask, s);
 }
 
+void bn_forward(int dtype, const void* x, const void* res, bool relu, void* y, const void* gamma, const void* beta, int64_t M, int C,
+                float* stats, float* partials, int pre_chunks, uint8_t* relu_mask, float* running, hipStream_t s) {
+  if (dtype == CD_BF16)
+    bn_forward_t<bf16_t>((const bf16_t*)x, (const bf16_t*)res, relu, (bf16_t*)y, (const bf16_t*)gamma, (const bf16_t*)beta, M, C, stats,
+                         partials, pre_chunks, relu_mask, running, s);
+  else
+    bn_forward_t<float>((const float*)x, (const float*)res, relu, (float*)y, (const float*)gamma, (const float*)beta, M, C, stats,
+                        partials, pre_chunks, relu_mask, running, s);
+}
 void bn_stats(int dtype, const void* x, const void* gamma, const void* beta, int64_t M, int C, float* stats,
               float* partials, int pre_chunks, float* scratch, hipStream_t s) {
   if (dtype == CD_BF16)
@@ -835,7 +1091,7 @@ void bn_relu_pool_backward(const bf16_t* dpool, const uint8_t* argmax, const bf1
                            const float* stats, bf16_t* dx, float* dgamma, float* dbeta, float* coef, float* partials,
                            const uint8_t* relu_mask, int64_t B, int H, int W, int C, hipStream_t s) {
   const int64_t M = B * H * W;
-  ReducePlan p = reduce_plan(M, C, 8);
+  ReducePlan p = reduce_plan(M, C, 8, 8);
   // the gathers leave a thread one row in flight at a time: four times the usual number of blocks keeps
   // the memory system busy instead
   const int64_t cap = (int64_t)(kPartialsBytes / ((size_t)stat_pitch(C) * 4));
@@ -847,13 +1103,6 @@ void bn_relu_pool_backward(const bf16_t* dpool, const uint8_t* argmax, const bf1
                      gamma, (const bf16_t*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
   hipLaunchKernelGGL(bn_pool_bwd_apply_k, dim3((unsigned)cdiv(M * (C / 8), 256)), dim3(256), 0, s, dpool, argmax, x, coef,
                      relu_mask, dx, B, H, W, C);
-}
-void bn_apply(int dtype, const void* x, const void* res, bool relu, void* y, int64_t M, int C, const float* stats,
-              uint8_t* relu_mask, hipStream_t s) {
-  if (dtype == CD_BF16)
-    bn_apply_t<bf16_t>((const bf16_t*)x, (const bf16_t*)res, relu, (bf16_t*)y, M, C, stats, relu_mask, s);
-  else
-    bn_apply_t<float>((const float*)x, (const float*)res, relu, (float*)y, M, C, stats, relu_mask, s);
 }
 void bn_backward(int dtype, const void* dy, const void* y, const void* x, const void* gamma, const float* stats,
                  bool relu, void* dx, bool acc_dx, void* dres, bool acc_dres, float* dgamma, float* dbeta, float* coef,

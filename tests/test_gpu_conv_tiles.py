@@ -113,6 +113,21 @@ def test_timer_counts_only_launches_that_are_made():
     assert n["norm"] == 2
 
 
+@pytest.mark.parametrize("name,dtype", [("groups_of_channels", "bf16"), ("groups_of_channels", "f32"), ("one_group", "bf16"), ("one_group", "f32"),
+                                        ("sums_in_a_kernel", "bf16")])
+def test_batchnorm_column_sums(name, dtype):
+    """The elementwise passes that add up their channels' partial sums themselves, and the ones behind a kernel that does: 136
+    and 200 channels (three groups of 48 at the most, four of 56 and a last one of 32), 8 (one vector a row), 24; rows that end inside a trip; 30 MB
+    of 40 channels, whose sums are folded."""
+    kw, mk, batch, res = {
+        "groups_of_channels": (dict(kind=1, widths=[136, 200], blocks=[1, 1], stem_width=136), lambda: nets.resnet20(widths=(136, 200), blocks=(1, 1)), 3, 11),
+        "one_group": (dict(kind=1, widths=[8, 24], blocks=[1, 1], stem_width=8), lambda: nets.resnet20(widths=(8, 24), blocks=(1, 1)), 5, 19),
+        "sums_in_a_kernel": (dict(kind=1, widths=[40], blocks=[1], stem_width=40), lambda: nets.resnet20(widths=(40,), blocks=(1,)), 90, 64),
+    }[name]
+    c = Case(kw, mk(), dtype, batch, res, 10)
+    check_layers(c, c.gpu())
+
+
 EVAL_SHAPES = {   # architecture, batch, resolution: the tiles, column counts and dtypes an evaluation-mode convolution can take
     "small_tiles": (dict(kind=2, widths=[72], blocks=[2], stem_width=64), "bf16", 3, 40),            # 288 columns, 300 rows
     "narrow_columns": (dict(kind=1, widths=[16, 40], blocks=[1, 1], stem_width=16), "bf16", 143, 31),  # 32- and 64-column tiles
