@@ -250,8 +250,10 @@ void attention_backward(const bf16_t* q, int64_t ldq, const bf16_t* k, const bf1
 void embed_forward(int dtype, const int32_t* tok, int64_t tok_pitch, int col0, int len, const void* table, int vocab, int d,
                    void* y, int64_t rows, const int32_t* pos, hipStream_t s);
 // dtable[tok] += sqrt(d) * dy[row], added onto a gradient that already holds the other uses of the table; one writer per
-// table row, additions in position order (bit-reproducible)
-void embed_backward(int dtype, const int32_t* tok, int64_t tok_pitch, int col0, int len, const void* dy, int vocab, int d,
-                    float* dtable, int64_t rows, hipStream_t s);
+// table row, additions in position order (bit-reproducible).  d: a multiple of 8, dy and dtable 16-byte aligned, fewer than
+// 2^31 - 512 rows; scratch: embed_backward_scratch bytes.
+size_t embed_backward_scratch(int64_t rows, int vocab);
+void embed_backward(const int32_t* tok, int64_t tok_pitch, int col0, int len, const bf16_t* dy, int vocab, int d, float* dtable,
+                    int64_t rows, int32_t* scratch, hipStream_t s);
 
 }  // namespace cd

@@ -51,7 +51,8 @@ struct Plan {
   std::vector<size_t> grad;   // byte offset of every tensor's gradient (save only)
   std::vector<size_t> aux;    // per op (save only): max-pool argmax bytes, ReLU sign bits of a BatchNorm,
                               // per-row mean and rstd of a LayerNorm, per (sentence, head, query) log-sum-exp
-                              // and dO.O of an attention; 0 = none
+                              // and dO.O of an attention, ids and counters of an embedding's backward pass; 0 = none
+  std::vector<size_t> ln_partials;   // per LayerNorm (save only): the column sums of its backward pass
   size_t bn_stats = 0;        // per BN slot: mean[C], invstd[C], scale[C], shift[C] fp32
   size_t bn_coef = 0;         // backward coefficients c1,c2,c3 [3][Cmax] fp32
   size_t partials = 0;        // reduction partials / split-K partials

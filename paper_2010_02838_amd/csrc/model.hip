@@ -501,6 +501,8 @@ Plan make_plan(const cd_model* m, int64_t B, bool save) {
         p.aux[i] = alloc((size_t)B * m->tensors[o.y].per_sample() / 8);
       if (o.kind == OP_LN) p.aux[i] = alloc((size_t)B * m->tensors[o.y].h * m->tensors[o.y].w * 2 * sizeof(float));
       if (o.kind == OP_ATTN) p.aux[i] = alloc((size_t)B * o.heads * m->tensors[o.y].h * 2 * sizeof(float));
+      if (o.kind == OP_LN) p.ln_partials[i] = alloc(ln_partials_bytes(B * m->tensors[o.y].h * m->tensors[o.y].w, m->tensors[o.y].c));
+      if (o.kind == OP_EMBED) p.aux[i] = alloc(embed_backward_scratch(B * m->tensors[o.y].h, m->arch.classes));
     }
   }
   p.total = off;
@@ -1196,8 +1198,8 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
         // gradient of the tied output projection (the first op of this pass)
         const TensorDesc& ty = m->tensors[o.y];
         ProfScope pr(CD_K_GLUE, c.s, 0, (double)batch * ty.per_sample() * (m->esize() + 8.0));
-        embed_backward(dt, static_cast<const int32_t*>(x), m->tensors[0].w, o.a0, o.a1, dy, m->arch.classes, ty.c, G(o.pw),
-                       batch * ty.h, c.s);
+        embed_backward(static_cast<const int32_t*>(x), m->tensors[0].w, o.a0, o.a1, static_cast<const bf16_t*>(dy), m->arch.classes,
+                       ty.c, G(o.pw), batch * ty.h, reinterpret_cast<int32_t*>(c.ws + c.plan.aux[i]), c.s);
         break;
       }
       case OP_ATTN: {

@@ -56,6 +56,16 @@ def test_attention_tile_edges_bf16_layers(Ts, Tt, d, ragged):
     check_layers(c, c.gpu(alpha=0.5, label_smoothing=0.1))
 
 
+@pytest.mark.parametrize("S,Ts,Tt,d,heads,vocab,ragged", [(5, 263, 9, 16, 2, 4, False), (5, 263, 9, 16, 2, 10, True),
+                                                          (1, 1, 1, 520, 65, 2000, False), (2, 512, 513, 16, 2, 700, False)])
+def test_embedding_gradient_of_repeated_tokens(S, Ts, Tt, d, heads, vocab, ragged):
+    """Positions of one id in one and in several of the 512-id pieces that a wave scans, more of them than are requested at
+    once, none at all; rows that are no multiple of the block's four, widths above one wave's 512 columns, padded positions."""
+    ref = nets.transformer(S, Ts, Tt, d=d, heads=heads, d_ff=16, vocab=vocab, enc_layers=1, dec_layers=1)
+    c = Case(dict(kind=4, widths=[d, 16, heads], blocks=[1, 1]), ref, "bf16", S, 0, vocab, jitter=0.1, tokens=(Ts, Tt), ragged=ragged)
+    check_layers(c, c.gpu(alpha=0.5, label_smoothing=0.1))
+
+
 def make_packed(name, multiple=16, slack_sentences=3):
     """The ragged batch of make(name, ragged=True), handed to the library without its padding."""
     S, Ts, Tt, d, heads, ff, vocab, ne, nd = CASES[name]
