@@ -103,11 +103,14 @@ void bn_backward(int dtype, const void* dy, const void* y, const void* x, const 
 void ln_forward(int dtype, const void* a, const void* r, const void* gamma, const void* beta, void* y, float* stats,
                 int64_t rows, int d, hipStream_t s);
 // dx = rstd * (g - mean(g) - xhat * mean(g * xhat)) with g = dy * gamma goes to da and dr (each nullable,
-// each added to its old contents if its acc flag is set); dgamma = sum dy * xhat, dbeta = sum dy.
-// partials: room for 1024 * 2 * d floats.
-void ln_backward(int dtype, const void* dy, const void* a, const void* r, const void* gamma, const float* stats, void* da,
-                 bool acc_a, void* dr, bool acc_r, float* dgamma, float* dbeta, float* partials, int64_t rows, int d,
-                 hipStream_t s);
+// each added to its old contents if its acc flag is set).  Returns the number of partial sums of dgamma = sum dy * xhat and
+// dbeta = sum dy left in partials (room for ln_partials_bytes), which ln_finalize adds up for several LayerNorms at once.
+size_t ln_partials_bytes(int64_t rows, int d);
+int ln_backward(int dtype, const void* dy, const void* a, const void* r, const void* gamma, const float* stats, void* da,
+                bool acc_a, void* dr, bool acc_r, float* partials, int64_t rows, int d, hipStream_t s);
+struct LnFinalizeJob { const float* partials; int chunks, d; float* dgamma; float* dbeta; };
+constexpr int kLnFinalizeJobs = 48;   // in a launch: they travel in the kernel arguments
+void ln_finalize(const LnFinalizeJob* jobs, int n, hipStream_t s);
 
 // argmax: optional [B][Ho][Wo][C] bytes, the window tap (r*k+s) of the first maximum; written by the
 // forward pass and, when given, used by the backward pass instead of rescanning the windows

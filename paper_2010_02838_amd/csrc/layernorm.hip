@@ -10,6 +10,7 @@
 // columns over the rows it visits (rows are dealt round-robin), a block writes them once, and a second
 // kernel adds the blocks' partials in a fixed order (deterministic, no atomics).
 #include "kernels.h"
+#include <algorithm>
 
 namespace cd {
 
@@ -109,19 +110,22 @@ template <typename T, int NV> struct LnBwdRow {
 // dx goes to da (added to what is there if acc_a) and to dr (the residual input, likewise).
 // partials: [blocks][2][d] = the block's sums of dy (dbeta) and dy * xhat (dgamma).
 // A wave's rows are a serial chain of loads, two reductions and stores: the next row is requested before the current one is
-// reduced.  The four waves of a block add their column sums in LDS, so that ln_finalize_k reads a quarter as many.
-// 8192 rows of 512 bf16 (average over a Transformer step): 21.2 -> 15.7 us.
-template <typename T, int NV>
-__global__ void __launch_bounds__(256) ln_bwd_k(const T* __restrict__ dy, const T* __restrict__ a,
+// reduced.  There are at most 256 blocks, whose waves add their column sums in LDS, so that few partials are left.  Two waves per
+// SIMD, one for rows of two vectors per lane: a base Transformer step of 8192 rows of 512 takes 10.01 ms so and 10.05 with one,
+// one layer each with 3840 rows of 1024 1.70 and 1.68.  More, fastest where nothing else runs (512 columns: 15.8 us with one, 11.1 with
+// four), wait for room beside the weight gradients of the second stream: 10.12 ms.
+template <typename T, int NV, int W>
+__global__ void __launch_bounds__(64 * W) ln_bwd_k(const T* __restrict__ dy, const T* __restrict__ a,
                                                 const T* __restrict__ r, const T* __restrict__ gamma,
                                                 const float* __restrict__ stats, T* __restrict__ da, int acc_a,
                                                 T* __restrict__ dr, int acc_r, float* __restrict__ partials,
                                                 int64_t rows, int d) {
   constexpr int V = LnVec<T>::N;
   typedef typename LnVec<T>::Raw Raw;
-  __shared__ float sums[4][2][64 * NV * V];
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = (int64_t)gridDim.x * 4;
+  constexpr int PLANE = 64 * NV + 64 / V;   // column c lies at (c % V) * PLANE + c / V: no two lanes on one bank, written or read
+  __shared__ float sums[W / 2][2][V * PLANE];
+  const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+  const int64_t wave = (int64_t)blockIdx.x * W + wib, nwaves = (int64_t)gridDim.x * W;
   const int nvec = d / V;
   const float inv_d = 1.f / (float)d;
   float g[NV][V], sb[NV][V], sg[NV][V];
@@ -205,17 +209,26 @@ __global__ void __launch_bounds__(256) ln_bwd_k(const T* __restrict__ dy, const 
     }
     cur = next;
   }
+  auto each_sum = [&](auto&& f) {
+    float (&mine)[2][V * PLANE] = sums[wib & (W / 2 - 1)];
 #pragma unroll
-  for (int j = 0; j < NV; j++)
+    for (int j = 0; j < NV; j++)
 #pragma unroll
-    for (int k = 0; k < V; k++) {
-      sums[threadIdx.x >> 6][0][(lane + 64 * j) * V + k] = sb[j][k];
-      sums[threadIdx.x >> 6][1][(lane + 64 * j) * V + k] = sg[j][k];
-    }
+      for (int k = 0; k < V; k++) {
+        f(mine[0][k * PLANE + lane + 64 * j], sb[j][k]);
+        f(mine[1][k * PLANE + lane + 64 * j], sg[j][k]);
+      }
+  };
+  if (wib >= W / 2) each_sum([](float& m, float v) { m = v; });
   __syncthreads();
-  for (int i = threadIdx.x; i < 2 * d; i += 256) {
-    const int q = i >= d, c = i - q * d;
-    partials[((int64_t)blockIdx.x * 2 + q) * d + c] = (sums[0][q][c] + sums[1][q][c]) + (sums[2][q][c] + sums[3][q][c]);
+  if (wib < W / 2) each_sum([](float& m, float v) { m += v; });
+  __syncthreads();
+  for (int i = threadIdx.x; i < 2 * d; i += 64 * W) {
+    const int q = i >= d, c = i - q * d, at = c % V * PLANE + c / V;
+    float t = sums[0][q][at];
+#pragma unroll
+    for (int w = 1; w < W / 2; w++) t += sums[w][q][at];
+    partials[((int64_t)blockIdx.x * 2 + q) * d + c] = t;
   }
 }
 
@@ -289,11 +302,18 @@ __global__ void __launch_bounds__(256) ln_colsum_generic_k(const T* __restrict__
   partials[((int64_t)blockIdx.y * 2 + 1) * d + c] = sg;
 }
 
-// Adds the partials in a fixed order: block = 16 columns x 64 lanes, every lane adds every 64th partial, the 64 lanes of a
-// column are combined in LDS.  (Sixteen columns are one 64-byte piece of a row; 64 to a block left 8 blocks for 512 columns.)  256 partials of 512 columns
-// 4.7 us; 1024 partials with 64 columns to a block 8.1 us.
-__global__ void __launch_bounds__(1024) ln_finalize_k(const float* __restrict__ partials, int chunks, int d,
-                                                      float* __restrict__ dgamma, float* __restrict__ dbeta) {
+// Adds the partials in a fixed order, for all LayerNorms of a backward pass in one launch (blockIdx.y: the LayerNorm): block =
+// 16 columns x 64 lanes, every lane adds every 64th partial, the 64 lanes of a column are combined in LDS.  (Sixteen columns are one
+// 64-byte piece of a row.)  256 partials of 512 columns took 6.4 us between the kernels of the pass, 30 times in a base Transformer
+// step; 17 us for the 30 together.
+struct LnFinalizeJobs { LnFinalizeJob job[kLnFinalizeJobs]; };
+__global__ void __launch_bounds__(1024) ln_finalize_k(LnFinalizeJobs jobs) {
+  const LnFinalizeJob& jb = jobs.job[blockIdx.y];
+  const float* __restrict__ partials = jb.partials;
+  const int chunks = jb.chunks, d = jb.d;
+  float* __restrict__ dgamma = jb.dgamma;
+  float* __restrict__ dbeta = jb.dbeta;
+  if ((int)blockIdx.x * 16 >= d) return;
   __shared__ float sm[2][64][17];
   const int cl = threadIdx.x & 15, lane = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + cl;
@@ -319,12 +339,13 @@ __global__ void __launch_bounds__(1024) ln_finalize_k(const float* __restrict__ 
   dgamma[c] = sm[1][0][cl];
 }
 
-// waves to launch.  Backward: enough to fill the chip, few enough that the per-wave partials stay
-// small.  Forward: a wave per row up to 64 Ki waves (a row's load, reductions and store are serial).
-static int ln_blocks(int64_t rows, int64_t max_waves = 1024) {
+// Forward: a wave per row up to 64 Ki waves (a row's load, reductions and store are serial).
+static int ln_blocks(int64_t rows, int64_t max_waves) {
   int64_t waves = rows < max_waves ? rows : max_waves;
   return (int)cdiv(waves, 4);
 }
+// Backward: blocks of `waves` waves, at most one per compute unit (each leaves a partial sum of every column).
+static int ln_bwd_blocks(int64_t rows, int waves) { return (int)std::min<int64_t>(256, cdiv(rows, waves)); }
 
 template <typename T>
 static void ln_forward_t(const T* a, const T* r, const T* gamma, const T* beta, T* y, float* stats, int64_t rows, int d,
@@ -344,30 +365,29 @@ static void ln_forward_t(const T* a, const T* r, const T* gamma, const T* beta, 
 }
 
 template <typename T>
-static void ln_backward_t(const T* dy, const T* a, const T* r, const T* gamma, const float* stats, T* da, bool acc_a,
-                          T* dr, bool acc_r, float* dgamma, float* dbeta, float* partials, int64_t rows, int d,
-                          hipStream_t s) {
+static int ln_backward_t(const T* dy, const T* a, const T* r, const T* gamma, const float* stats, T* da, bool acc_a,
+                         T* dr, bool acc_r, float* partials, int64_t rows, int d, hipStream_t s) {
   constexpr int V = LnVec<T>::N;
   const bool vec = d % V == 0 && aligned16(dy) && aligned16(a) && aligned16(r) && aligned16(gamma) && aligned16(da) &&
                    aligned16(dr) && d <= 64 * 2 * V;   // (the row, its gradient and the running sums stay in registers)
-  const int blocks = ln_blocks(rows);
-  int chunks;
   if (vec) {
-    const int nv = (int)cdiv(d / V, 64);
-    chunks = blocks;
-#define CD_LN_BWD(NV)                                                                                          \
-  hipLaunchKernelGGL((ln_bwd_k<T, NV>), dim3(blocks), dim3(256), 0, s, dy, a, r, gamma, stats, da, (int)acc_a, dr, \
-                     (int)acc_r, partials, rows, d)
-    if (nv <= 1) CD_LN_BWD(1); else CD_LN_BWD(2);
-#undef CD_LN_BWD
-  } else {
-    hipLaunchKernelGGL((ln_bwd_generic_k<T>), dim3(blocks), dim3(256), 0, s, dy, a, r, gamma, stats, da, (int)acc_a, dr,
-                       (int)acc_r, rows, d);
-    chunks = rows < 64 ? (int)rows : 64;
-    hipLaunchKernelGGL((ln_colsum_generic_k<T>), dim3((unsigned)cdiv(d, 256), chunks), dim3(256), 0, s, dy, a, r, stats,
-                       partials, rows, d);
+#define CD_LN_BWD(NV, W)                                                                                          \
+  {                                                                                                               \
+    const int blocks = ln_bwd_blocks(rows, W);                                                                    \
+    hipLaunchKernelGGL((ln_bwd_k<T, NV, W>), dim3(blocks), dim3(64 * W), 0, s, dy, a, r, gamma, stats, da, (int)acc_a, dr, \
+                       (int)acc_r, partials, rows, d);                                                            \
+    return blocks;                                                                                                \
   }
-  hipLaunchKernelGGL(ln_finalize_k, dim3((unsigned)cdiv(d, 16)), dim3(1024), 0, s, partials, chunks, d, dgamma, dbeta);
+    if (cdiv(d / V, 64) <= 1) CD_LN_BWD(1, 8)
+    CD_LN_BWD(2, 4)
+#undef CD_LN_BWD
+  }
+  const int chunks = rows < 64 ? (int)rows : 64;
+  hipLaunchKernelGGL((ln_bwd_generic_k<T>), dim3(ln_blocks(rows, 1024)), dim3(256), 0, s, dy, a, r, gamma, stats, da, (int)acc_a, dr,
+                     (int)acc_r, rows, d);
+  hipLaunchKernelGGL((ln_colsum_generic_k<T>), dim3((unsigned)cdiv(d, 256), chunks), dim3(256), 0, s, dy, a, r, stats,
+                     partials, rows, d);
+  return chunks;
 }
 
 void ln_forward(int dtype, const void* a, const void* r, const void* gamma, const void* beta, void* y, float* stats,
@@ -380,15 +400,28 @@ void ln_forward(int dtype, const void* a, const void* r, const void* gamma, cons
                         d, s);
 }
 
-void ln_backward(int dtype, const void* dy, const void* a, const void* r, const void* gamma, const float* stats, void* da,
-                 bool acc_a, void* dr, bool acc_r, float* dgamma, float* dbeta, float* partials, int64_t rows, int d,
-                 hipStream_t s) {
+size_t ln_partials_bytes(int64_t rows, int d) { return (size_t)std::min<int64_t>(256, rows) * 2 * d * sizeof(float); }
+
+int ln_backward(int dtype, const void* dy, const void* a, const void* r, const void* gamma, const float* stats, void* da,
+                bool acc_a, void* dr, bool acc_r, float* partials, int64_t rows, int d, hipStream_t s) {
   if (dtype == CD_BF16)
-    ln_backward_t<bf16_t>((const bf16_t*)dy, (const bf16_t*)a, (const bf16_t*)r, (const bf16_t*)gamma, stats, (bf16_t*)da,
-                          acc_a, (bf16_t*)dr, acc_r, dgamma, dbeta, partials, rows, d, s);
-  else
-    ln_backward_t<float>((const float*)dy, (const float*)a, (const float*)r, (const float*)gamma, stats, (float*)da, acc_a,
-                         (float*)dr, acc_r, dgamma, dbeta, partials, rows, d, s);
+    return ln_backward_t<bf16_t>((const bf16_t*)dy, (const bf16_t*)a, (const bf16_t*)r, (const bf16_t*)gamma, stats, (bf16_t*)da,
+                                 acc_a, (bf16_t*)dr, acc_r, partials, rows, d, s);
+  return ln_backward_t<float>((const float*)dy, (const float*)a, (const float*)r, (const float*)gamma, stats, (float*)da, acc_a,
+                              (float*)dr, acc_r, partials, rows, d, s);
+}
+
+void ln_finalize(const LnFinalizeJob* jobs, int n, hipStream_t s) {
+  for (int i0 = 0; i0 < n; i0 += kLnFinalizeJobs) {
+    LnFinalizeJobs t = {};
+    const int m = std::min(kLnFinalizeJobs, n - i0);
+    int d = 0;
+    for (int i = 0; i < m; i++) {
+      t.job[i] = jobs[i0 + i];
+      d = std::max(d, t.job[i].d);
+    }
+    hipLaunchKernelGGL(ln_finalize_k, dim3((unsigned)cdiv(d, 16), m), dim3(1024), 0, s, t);
+  }
 }
 
 }  // namespace cd

@@ -457,6 +457,7 @@ Plan make_plan(const cd_model* m, int64_t B, bool save) {
     p.lin_dz = alloc((size_t)B * m->tensors[m->ops.back().y].per_sample() * 2);
   }
   p.aux.assign(m->ops.size(), 0);
+  p.ln_partials.assign(m->ops.size(), 0);
   p.gx.assign(m->ops.size(), 0);
   {
     size_t tmax = 0, wdmax = 0;
@@ -500,9 +501,9 @@ Plan make_plan(const cd_model* m, int64_t B, bool save) {
       if (o.kind == OP_BN && o.relu && m->dtype == CD_BF16 && m->tensors[o.y].c % 8 == 0)
         p.aux[i] = alloc((size_t)B * m->tensors[o.y].per_sample() / 8);
       if (o.kind == OP_LN) p.aux[i] = alloc((size_t)B * m->tensors[o.y].h * m->tensors[o.y].w * 2 * sizeof(float));
-      if (o.kind == OP_ATTN) p.aux[i] = alloc((size_t)B * o.heads * m->tensors[o.y].h * 2 * sizeof(float));
       if (o.kind == OP_LN) p.ln_partials[i] = alloc(ln_partials_bytes(B * m->tensors[o.y].h * m->tensors[o.y].w, m->tensors[o.y].c));
       if (o.kind == OP_EMBED) p.aux[i] = alloc(embed_backward_scratch(B * m->tensors[o.y].h, m->arch.classes));
+      if (o.kind == OP_ATTN) p.aux[i] = alloc((size_t)B * o.heads * m->tensors[o.y].h * 2 * sizeof(float));
     }
   }
   p.total = off;
@@ -1152,6 +1153,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     if (m->ops[j].res >= 0 && m->ops[j].res != m->ops[j].x) readers[m->ops[j].res]++;
   }
   std::vector<char> relu_done(m->tensors.size(), 0);
+  std::vector<LnFinalizeJob> ln_sums;   // column sums of the LayerNorms so far
   // frozen front end (the ops before first_trainable_op): no gradient reaches it; its parameters' gradients are zeros
   for (int i = 0; i < m->first_trainable_op; i++) {
     const Op& o = m->ops[i];
@@ -1280,8 +1282,10 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
         void* dres = o.res > 0 ? c.grad(o.res) : nullptr;   // the input batch takes no gradient
         const bool acc_res = o.res > 0 && written[o.res];
         ProfScope pr(CD_K_NORM, c.s, 0, (double)rows * tx.c * m->esize() * (3 + (res ? 1 : 0) + (dres ? 1 : 0)));
-        ln_backward(dt, dy, in, res, c.P(o.pw), reinterpret_cast<const float*>(c.ws + c.plan.aux[i]), dx, acc, dres,
-                    acc_res, G(o.pw), G(o.pb), c.partials(), rows, tx.c, c.s);
+        float* partials = reinterpret_cast<float*>(c.ws + c.plan.ln_partials[i]);   // (its own: added up at the end of the pass)
+        const int chunks = ln_backward(dt, dy, in, res, c.P(o.pw), reinterpret_cast<const float*>(c.ws + c.plan.aux[i]), dx, acc,
+                                       dres, acc_res, partials, rows, tx.c, c.s);
+        ln_sums.push_back(LnFinalizeJob{partials, chunks, tx.c, G(o.pw), G(o.pb)});
         if (o.res > 0) written[o.res] = 1;
         break;
       }
@@ -1416,6 +1420,10 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     if (o.x != 0) written[o.x] = 1;
   }
   for (PendingWgrads& q : pending) run_wgrads(q);
+  if (!ln_sums.empty()) {
+    ProfScope pr(CD_K_NORM, c.s, 0, 0);
+    ln_finalize(ln_sums.data(), (int)ln_sums.size(), c.s);
+  }
   if (forks > 0) {  // join: the caller's stream continues after the last weight gradient
     hipEvent_t ev = side_event(forks);
     if (!ev || hipEventRecord(ev, side) != hipSuccess || hipStreamWaitEvent(c.s, ev, 0) != hipSuccess) {
