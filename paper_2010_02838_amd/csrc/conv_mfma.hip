@@ -778,6 +778,17 @@ static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
     if (a.Cs == 64) return launch_tile<MODE, 256, 64, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
     return launch_tile<MODE, 256, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
   }
+  if (a.N <= 64) {
+    // N <= 64 over few rows (conv_rows_rule): 128x32, and 128x64 or 64x64
+    const int rows = conv_rows_rule(a.M, a.N, a.K, STATS != 0);
+    if (rows < 256 && a.N <= 32) return launch_tile<MODE, 128, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
+    if constexpr (NWRAP == 1) {
+      if (rows == 64 && a.Cs >= 64) return launch_tile<MODE, 64, 64, 2, 2, STATS, 1, REMAP, EPI, 64, 4>(a, s);
+      if (rows == 128 && a.Cs >= 64) return launch_tile<MODE, 128, 64, 2, 2, STATS, 1, REMAP, EPI, 64, 3>(a, s);
+    }
+    if (rows == 64) return launch_tile<MODE, 64, 64, 2, 2, STATS, NWRAP, REMAP, EPI, 32, 4>(a, s);
+    if (rows == 128) return launch_tile<MODE, 128, 64, 2, 2, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
+  }
   if (a.N <= 32) {
     // few channels, few steps (3 to 9): with more workgroups than two per compute unit, two stages (40 KB, three workgroups per
     // unit, one tile of loads less in front of the first step) against three stages: evaluation of ResNet-20 at
@@ -846,7 +857,7 @@ void linear_fwd_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, float
     if (bias) launch_linear<256, 128, 1, true, 32, 3>(a, s); else launch_linear<256, 128, 0, true, 32, 3>(a, s);
   } else if (group && F >= 64) {
     if (bias) launch_linear<128, 128, 1, true, 64, 2>(a, s); else launch_linear<128, 128, 0, true, 64, 2>(a, s);
-  } else if (tile == TILE_SMALL) {   // few rows or few classes: as igemm_tile says (256 x 1000 x 2048 18 -> 11 us)
+  } else if (tile == TILE_SMALL || (C <= 64 && F >= 64 && B <= 64 * 256)) {   // few rows or few classes: as igemm_tile says (256 x 1000 x 2048 18 -> 11 us)
     if (bias) launch_linear<64, 64, 1, false, 64, 4>(a, s); else launch_linear<64, 64, 0, false, 64, 4>(a, s);
   } else if (F >= 64) {
     if (bias) launch_linear<128, 128, 1, false, 64, 2>(a, s); else launch_linear<128, 128, 0, false, 64, 2>(a, s);
@@ -1469,13 +1480,15 @@ void sum_splits(const float* part, float* out, int64_t n, int splits, hipStream_
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)cdiv(n, 64)), dim3(256), 0, s, part, out, n, splits);
 }
 
-// The splits of a batch: 256 outputs (four a thread) x 4 split lanes per block, in the order of wgrad_reduce_kernel; behind a job's
-// outputs a block per 256 channels adds the bias sums.
+// The splits of a batch: 256 outputs (four a thread) x 4 split lanes per block, in the order of wgrad_reduce_kernel; of more than 64
+// splits (few weights, that is few blocks, and 16 loads and more in a lane's chain) 64 outputs x 16 split lanes: 2304 weights in 512 splits
+// 13.0 -> 4.1 us.  Behind a job's outputs a block per 256 channels adds the bias sums.
 struct WgradSum { const float* part; float* out; const double* bias_part; float* bias_out; uint32_t n4; int splits, N; uint32_t first, bias_first; };
+__host__ __device__ inline unsigned wgrad_sum_lanes(int splits) { return splits > 64 ? 16u : 4u; }
 template <int NJ> struct WgradSums { WgradSum j[NJ]; int n; };
 template <int NJ>
 __global__ void __launch_bounds__(256) wgrad_sum_kernel(WgradSums<NJ> b) {
-  __shared__ float4 sm[4][64];
+  __shared__ float4 sm[256];
   int k = 0;
   if (NJ > 1)
     while (k + 1 < b.n && b.j[k + 1].first <= blockIdx.x) k++;
@@ -1488,23 +1501,28 @@ __global__ void __launch_bounds__(256) wgrad_sum_kernel(WgradSums<NJ> b) {
     q.bias_out[c] = (float)s;
     return;
   }
-  const int ol = threadIdx.x & 63, lane = threadIdx.x >> 6;
-  const uint32_t i = (blockIdx.x - q.first) * 64u + (uint32_t)ol;
+  const unsigned lanes = wgrad_sum_lanes(q.splits), outs = 256u / lanes;
+  const unsigned ol = threadIdx.x & (outs - 1u), lane = threadIdx.x / outs;
+  const uint32_t i = (blockIdx.x - q.first) * outs + ol;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (i < q.n4) {
     const float4* p = reinterpret_cast<const float4*>(q.part) + i;
-#pragma unroll 4
-    for (int j = lane; j < q.splits; j += 4) {
+#pragma unroll 8
+    for (int j = (int)lane; j < q.splits; j += (int)lanes) {
       const float4 v = p[(int64_t)j * q.n4];
       s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
   }
-  sm[lane][ol] = s;
+  sm[threadIdx.x] = s;
   __syncthreads();
   if (lane == 0 && i < q.n4) {
-    const float4 t0 = sm[0][ol], t1 = sm[1][ol], t2 = sm[2][ol], t3 = sm[3][ol];
-    reinterpret_cast<float4*>(q.out)[i] = make_float4((t0.x + t1.x) + (t2.x + t3.x), (t0.y + t1.y) + (t2.y + t3.y),
-                                                      (t0.z + t1.z) + (t2.z + t3.z), (t0.w + t1.w) + (t2.w + t3.w));
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (unsigned l = 0; l < lanes; l += 4) {
+      const float4 t0 = sm[l * outs + ol], t1 = sm[(l + 1) * outs + ol], t2 = sm[(l + 2) * outs + ol], t3 = sm[(l + 3) * outs + ol];
+      t.x += (t0.x + t1.x) + (t2.x + t3.x); t.y += (t0.y + t1.y) + (t2.y + t3.y);
+      t.z += (t0.z + t1.z) + (t2.z + t3.z); t.w += (t0.w + t1.w) + (t2.w + t3.w);
+    }
+    reinterpret_cast<float4*>(q.out)[i] = t;
   }
 }
 
@@ -1572,7 +1590,7 @@ static void wgrad_run(const WgradProblem* p, int n, int pitch, float* partials, 
       WgradSum& q = sums.j[sums.n++];
       q.part = a.out; q.out = p[k].dw; q.n4 = (uint32_t)(h.weights() / 4); q.splits = splits; q.N = h.N;
       q.first = sum_blocks;
-      sum_blocks += (unsigned)cdiv(q.n4, 64);
+      sum_blocks += (unsigned)cdiv(q.n4, 256 / wgrad_sum_lanes(splits));
       q.bias_first = sum_blocks;
       q.bias_part = nullptr; q.bias_out = p[k].db;
       if (p[k].db) {

@@ -50,6 +50,18 @@ inline int conv_tile_rule(int64_t M, int N, int K, bool small_tiles, bool sums) 
   return small < narrow && small < square ? TILE_SMALL : narrow < square ? TILE_NARROW : TILE_SQUARE;
 }
 
+// Rows of a tile where there are at most 64 columns (one column tile): 256, but 128 or 64 (64 only from 33 columns on) while those leave
+// compute units without a tile.  A launch with column sums takes as many row tiles as the BatchNorm behind it adds up by itself
+// (kSumBytes below: 64 KB, 8 bytes a column and tile).  ResNet-20 at batch 128, 256 rows before and now: 8192 x 64 x 576 (32 tiles) 10.1 ->
+// 6.3 us, its data gradient with sums 13.7 -> 8.5, 32768 x 32 x 288 (128 tiles) 7.9 -> 6.1 and 10.2 -> 8.3.  A contraction of four 32-wide
+// steps or fewer is all prologue and epilogue: 5.6 us either way (8192 x 16 x 32, 2048 x 64 x 32).
+inline int conv_rows_rule(int64_t M, int N, int K, bool sums) {
+  if (K <= 128) return 256;
+  const int64_t most = sums ? (64 << 10) / (8 * (N <= 32 ? 32 : 64)) : 256;
+  if (N > 32 && (M + 63) / 64 <= most) return 64;
+  return (M + 127) / 128 <= most ? 128 : 256;
+}
+
 // Row tiles, i.e. partial sums, of a launch over M rows that takes column sums, at the most: 64-row tiles are chosen only where
 // there are at most 256 tiles of 128x128.
 inline int64_t conv_stat_chunks_max(int64_t M) { return M <= 256 * 128 ? (M + 63) / 64 : (M + 127) / 128; }

@@ -119,6 +119,29 @@ def test_tile_of_a_convolution(tile, shape, want):
     assert tile(*shape) == want
 
 
+@pytest.fixture(scope="module")
+def rows_rule(tmp_path_factory):
+    """rows of a tile, and whether the sums it leaves are at most as many as the check for their room counts and 64 KB"""
+    run = compiled(tmp_path_factory.mktemp("rows"), """
+int main(int, char** v) {
+  const long long M = atoll(v[1]);
+  const int N = atoi(v[2]), sums = atoi(v[3]), rows = conv_rows_rule(M, N, atoi(v[4]), sums != 0);
+  const long long tiles = (M + rows - 1) / rows;
+  printf("%d %d", rows, (int)(tiles <= conv_stat_chunks_max(M) && (rows == 256 || tiles * N * 8 <= kSumBytes)));
+}
+""")
+    return lambda *a: tuple(int(t) for t in run(*a).split())
+
+
+@pytest.mark.parametrize("M,N,sums,rows", [(1, 64, 1, 64), (8192, 64, 1, 64), (8193, 64, 1, 128), (16384, 33, 1, 128), (16385, 64, 1, 256),
+                                           (16384, 64, 0, 64), (16385, 64, 0, 128), (32769, 64, 0, 256), (1, 32, 1, 128), (32768, 32, 1, 128),
+                                           (32769, 32, 1, 256), (32768, 8, 0, 128), (32769, 8, 0, 256)])
+def test_rows_of_a_narrow_tile(rows_rule, M, N, sums, rows):
+    got, room = rows_rule(M, N, sums, 129)
+    assert got == rows and (room or not sums)
+    assert rows_rule(M, N, sums, 128)[0] == 256
+
+
 @pytest.mark.parametrize("rows,cols,vec4,want", [
     (66309, 12, 1, (1, 1)), (66309, 20, 1, (2, 1)), (66309, 36, 1, (4, 1)), (33635, 68, 1, (4, 1)),   # test_gpu_generic_conv.py
     (17664, 20, 1, (2, 0)), (66309, 12, 0, (1, 0)), (65408, 16, 1, (1, 0)), (65409, 16, 1, (1, 1)),

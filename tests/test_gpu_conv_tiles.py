@@ -32,6 +32,12 @@ SHAPES = {
     # 16 and 4 pixels: less than a step; 64-column and 64-row tiles beside 128 (bottleneck: 1x1 and 3x3, stride 2, a shortcut each)
     "few_pixels": (dict(kind=2, widths=[24, 72], blocks=[2, 2], stem_width=64),
                    lambda: nets.resnet50(classes=10, widths=(24, 72), blocks=(2, 2), stem=64), 1, 16),
+    # at most 64 columns over few rows: 63 tiles of 128x32, 32 of 64x64 (the last ones ragged), stride 2 between them
+    "rows_32_64": (dict(kind=1, widths=[32, 64], blocks=[2, 1], stem_width=32), lambda: nets.resnet20(widths=(32, 64), blocks=(2, 1)), 20, 20),
+    # 12493 rows of 64 columns: 128x64 with column sums, 64x64 without; 16 channels gathered for 64
+    "rows_16_64": (dict(kind=1, widths=[16, 64], blocks=[1, 2], stem_width=16), lambda: nets.resnet20(widths=(16, 64), blocks=(1, 2)), 13, 62),
+    # 8410 and 2250 rows of 40 columns, 40 channels: 32-wide steps
+    "columns_40": (dict(kind=1, widths=[40, 40], blocks=[1, 1], stem_width=40), lambda: nets.resnet20(widths=(40, 40), blocks=(1, 1)), 10, 29),
     # 520 tiles with column sums: 128x128 still (without the sums 256x128: the test below)
     "rows_per_sum": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), lambda: nets.resnet20(widths=(128,), blocks=(1,)), 260, 16),
 }
