@@ -140,10 +140,12 @@ inline bool wgrad_alone(const WgradShape& h, int64_t operand_bytes) {
   return r.splits == 1 || 4 * (2 * h.partials(r.splits)) <= operand_bytes;
 }
 // Whether the layers collected so far are a launch: tiles enough without a split, or enough work for every compute unit to be busy
-// some 20 us (96 steps in each of 512 workgroups), or as much as the pass still has to collect and worth a launch: launches run beside
-// the data gradients of the layers in front, and what is launched last runs beside nothing.
+// some 20 us (96 steps in each of 512 workgroups), or as much as the pass still has to collect and worth a launch, or all of them:
+// launches run beside the data gradients of the layers in front, and what is launched at the end of the pass runs beside nothing (two
+// bottleneck blocks on 43 images of 64x96: 774 us a pass with the last launches at its end, 721 with each as soon as its class is
+// complete, 743 with a launch per layer; basic blocks at 160x161 698, 664 and 713).
 inline bool wgrad_batch_full(int64_t tiles, int64_t work, int jobs, int64_t work_left) {
-  return jobs >= kWgradJobs || tiles >= kWgradBlocks || work >= (int64_t)kWgradBlocks * 96 ||
+  return jobs >= kWgradJobs || tiles >= kWgradBlocks || work >= (int64_t)kWgradBlocks * 96 || work_left == 0 ||
          (work >= work_left && work >= (int64_t)kWgradBlocks * 16);
 }
 
