@@ -59,6 +59,25 @@ def test_loss_parity_shapes(rows, cols, mode):
     check(z, [zp], t, 0.5, 0.0, mode)
 
 
+@pytest.mark.parametrize("rows,cols", [(1, 7), (64, 1024), (1024, 1024), (1025, 1024), (2047, 511), (2048, 12), (2049, 12)])
+@pytest.mark.parametrize("mode,temperature", [("mse", 1.0), ("kl", 1.0), ("kl", 2.0)])
+def test_valid_rows_are_counted(rows, cols, mode, temperature):
+    """Around the sizes up to which every wave counts the valid rows itself: some ignored, and one target out of range (a status
+    bit, its row left out); the row kernel and (temperature 2) the one with several passes."""
+    z, zp = synth.logits(rows, cols, 3.0, seed=rows), synth.logits(rows, cols, 3.0, seed=rows + 1)
+    t = synth.labels(rows, cols, seed=7)
+    t[1::3] = -1
+    check(z, [zp], t, 0.5, 0.1, mode, temperature=temperature)
+    if rows > 1:
+        bad = t.copy()
+        bad[0], t[0] = cols, -1
+        l, status, dz = run_gpu(z, [zp], bad, 0.5, 0.1, mode, temperature=temperature)
+        want, ok, dz_want = run_gpu(z, [zp], t, 0.5, 0.1, mode, temperature=temperature)
+        assert status == 1 and ok == 0
+        np.testing.assert_array_equal(l, want)
+        np.testing.assert_array_equal(dz, dz_want)
+
+
 @pytest.mark.parametrize("cols", [1, 2, 3, 5, 255, 257, 1023, 1025, 4095, 4097, 8191, 8193, 10007, 16381, 16385, 32766, 32767, 32769])
 @pytest.mark.parametrize("mode,peers", [("mse", 0), ("mse", 1), ("mse", 3), ("kl", 1), ("mse_centered_rows", 1)])
 def test_ragged_rows(cols, mode, peers):
