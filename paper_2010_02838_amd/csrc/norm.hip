@@ -220,30 +220,30 @@ __global__ void __launch_bounds__(256) col_reduce_k(const T* __restrict__ a0, co
 }
 
 // FIN 0: BatchNorm statistics.  FIN 1: BatchNorm backward sums.  FIN 2: plain column sum.
-// Block = 16 channels x 16 chunk lanes: every lane adds every 16th chunk, the 16 lanes of a channel are
+// Block = 16 channels x 64 chunk lanes: every lane adds every 64th chunk, the 64 lanes of a channel are
 // combined in LDS in a fixed order.  What bounds it is the rate at which one compute unit reads past its
 // L2, so the channels go to as many blocks as 64-byte pieces of a partial row allow.  Backward sums of the ResNeXt
-// blocks (up to 1024 chunks): 10.0 -> 7.2 us; of ResNet-50 6.2 -> 5.5; 64 channels to a block with as many
+// blocks (up to 1024 chunks): 10.0 -> 7.2 us with 16 lanes, 6.2 with 64; 64 channels to a block with as many
 // loads in flight: no faster than one load at a time.
-constexpr int kFinalizeCols = 16, kFinalizeLoads = 8;   // (loads past the last chunk re-read a real one, count as zero)
+constexpr int kFinalizeCols = 16, kFinalizeLanes = 64, kFinalizeLoads = 8;   // (loads past the last chunk re-read a real one, count as zero)
 template <typename T, int FIN>
-__global__ void __launch_bounds__(256) col_finalize_k(const float* __restrict__ partials, int chunks, int64_t M, int C,
+__global__ void __launch_bounds__(kFinalizeCols * kFinalizeLanes) col_finalize_k(const float* __restrict__ partials, int chunks, int64_t M, int C,
                                                        const T* __restrict__ gamma, const T* __restrict__ beta,
                                                        float* __restrict__ stats, float* __restrict__ out0,
                                                        float* __restrict__ out1, float* __restrict__ coef) {
-  __shared__ double sm[2][16][kFinalizeCols];
+  __shared__ double sm[2][kFinalizeLanes][kFinalizeCols];
   const int cl = threadIdx.x % kFinalizeCols, lane = threadIdx.x / kFinalizeCols;
   const int c = blockIdx.x * kFinalizeCols + cl;
   double a0 = 0.0, a1 = 0.0;
   if (c < C) {
     const float* p = partials + c;
     const int64_t pitch = stat_pitch(C);
-    for (int j = lane; j < chunks; j += 16 * kFinalizeLoads) {
+    for (int j = lane; j < chunks; j += kFinalizeLanes * kFinalizeLoads) {
       float v0[kFinalizeLoads], v1[kFinalizeLoads];
 #pragma unroll
       for (int u = 0; u < kFinalizeLoads; u++) {
-        const bool in = j + 16 * u < chunks;
-        const int64_t at = (in ? j + 16 * u : j) * pitch;
+        const bool in = j + kFinalizeLanes * u < chunks;
+        const int64_t at = (in ? j + kFinalizeLanes * u : j) * pitch;
         v0[u] = p[at];
         v1[u] = FIN != 2 ? p[at + C] : 0.f;
         if (!in) { v0[u] = 0.f; v1[u] = 0.f; }
@@ -258,10 +258,18 @@ __global__ void __launch_bounds__(256) col_finalize_k(const float* __restrict__ 
   sm[0][lane][cl] = a0;
   sm[1][lane][cl] = a1;
   __syncthreads();
+  if (lane < 8) {   // 8 lanes a channel (all in the first two waves), then one
+    double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+    for (int j = 0; j < kFinalizeLanes / 8; j++) { t0 += sm[0][lane + 8 * j][cl]; t1 += sm[1][lane + 8 * j][cl]; }
+    sm[0][lane][cl] = t0;   // (row `lane` is read by this thread alone)
+    sm[1][lane][cl] = t1;
+  }
+  __syncthreads();
   if (lane != 0 || c >= C) return;
   double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-  for (int j = 0; j < 16; j++) { s0 += sm[0][j][cl]; s1 += sm[1][j][cl]; }
+  for (int j = 0; j < 8; j++) { s0 += sm[0][j][cl]; s1 += sm[1][j][cl]; }
   if (FIN == 0) {
     const double mean = s0 / (double)M;
     double var = s1 / (double)M - mean * mean;
@@ -876,7 +884,10 @@ static ReducePlan launch_reduce(const T* a0, const T* a1, const T* a2, const flo
 
 // Where the column sums of M rows lie, and in how many chunks: from the convolution in front (pre_chunks > 0, in partials), or reduced here.
 struct ColSums { const float* part; int chunks; };
-// Folds them into kFoldChunks in scratch where they are more than `most`
+// Folds them into kFoldChunks in scratch where they are more than `most`.  Up to 2048 chunks the launch of the fold, 5 us and a gap,
+// costs more than it saves (a pass of two ResNeXt blocks 1464 us with a limit of 256, 1452 with 1024, 1454 with 2048; ResNet-50 step
+// 25.90, 25.86 and 25.78 ms).
+constexpr int kFinalizeChunks = 2048;
 static ColSums fold_sums(ColSums q, int C, int most, float* scratch, hipStream_t s) {
   if (q.chunks <= most) return q;
   hipLaunchKernelGGL(col_fold_k, dim3((unsigned)cdiv(C, 64), kFoldChunks), dim3(1024), 0, s, q.part, q.chunks, C, scratch);
@@ -895,8 +906,8 @@ static void bn_stats_t(const T* x, const T* gamma, const T* beta, int64_t M, int
     q.chunks = (vec > 1 ? launch_reduce<T, V, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)
                         : launch_reduce<T, 1, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)).chunks;
   else
-    q = fold_sums(q, C, 256, scratch, s);
-  hipLaunchKernelGGL((col_finalize_k<T, 0>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
+    q = fold_sums(q, C, kFinalizeChunks, scratch, s);
+  hipLaunchKernelGGL((col_finalize_k<T, 0>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      q.part, q.chunks, M, C, gamma, beta, stats, (float*)nullptr, (float*)nullptr, (float*)nullptr);
 }
 
@@ -963,8 +974,8 @@ static void bn_backward_t(const T* dy, const T* y, const T* x, const T* gamma, c
                        (int)acc_dres, mask);
     return;
   }
-  if (pre_chunks) q = fold_sums(q, C, 256, partials + (size_t)pre_chunks * stat_pitch(C), s);
-  hipLaunchKernelGGL((col_finalize_k<T, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
+  if (pre_chunks) q = fold_sums(q, C, kFinalizeChunks, partials + (size_t)pre_chunks * stat_pitch(C), s);
+  hipLaunchKernelGGL((col_finalize_k<T, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      q.part, q.chunks, M, C,
                      gamma, (const T*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
   const int64_t nvec = M * C / vec;
@@ -984,7 +995,7 @@ static void colsum_t(const T* a, int64_t M, int C, float* out, float* partials, 
   constexpr int V = sizeof(T) == 2 ? 8 : 4;
   ReducePlan p = vec > 1 ? launch_reduce<T, V, 2>(a, nullptr, nullptr, nullptr, false, M, C, partials, s)
                          : launch_reduce<T, 1, 2>(a, nullptr, nullptr, nullptr, false, M, C, partials, s);
-  hipLaunchKernelGGL((col_finalize_k<T, 2>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
+  hipLaunchKernelGGL((col_finalize_k<T, 2>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      partials, p.chunks, M, C,
                      (const T*)nullptr, (const T*)nullptr, (float*)nullptr, out, (float*)nullptr, (float*)nullptr);
 }
@@ -1098,7 +1109,7 @@ void bn_relu_pool_backward(const bf16_t* dpool, const uint8_t* argmax, const bf1
   p.chunks = (int)(p.chunks * 4 < cap ? p.chunks * 4 : cap);
   hipLaunchKernelGGL(bn_pool_bwd_reduce_k, dim3(p.chunks, p.cgroups), dim3(256), 0, s, dpool, argmax, x, stats, relu_mask, B,
                      H, W, C, partials);
-  hipLaunchKernelGGL((col_finalize_k<bf16_t, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(16 * kFinalizeCols), 0, s,
+  hipLaunchKernelGGL((col_finalize_k<bf16_t, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      partials, p.chunks, M, C,
                      gamma, (const bf16_t*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
   hipLaunchKernelGGL(bn_pool_bwd_apply_k, dim3((unsigned)cdiv(M * (C / 8), 256)), dim3(256), 0, s, dpool, argmax, x, coef,
