@@ -158,7 +158,7 @@ def test_transformer_base_size_packed_layers():
 
 
 def test_transformer_step_is_bit_reproducible():
-    """Two runs of the same step give identical bits (no atomics anywhere: the embedding gradient has one writer per
+    """Two runs of the same step give identical bits (no atomics but on integers: the embedding gradient has one writer per
     table row and a fixed order of additions); tokens repeat many times at this vocabulary size."""
     import torch
     from paper_2010_02838_amd.runner import pack_flat, unpack_flat
