@@ -884,9 +884,8 @@ static ReducePlan launch_reduce(const T* a0, const T* a1, const T* a2, const flo
 
 // Where the column sums of M rows lie, and in how many chunks: from the convolution in front (pre_chunks > 0, in partials), or reduced here.
 struct ColSums { const float* part; int chunks; };
-// Folds them into kFoldChunks in scratch where they are more than `most`.  Up to 2048 chunks the launch of the fold, 5 us and a gap,
-// costs more than it saves (a pass of two ResNeXt blocks 1464 us with a limit of 256, 1452 with 1024, 1454 with 2048; ResNet-50 step
-// 25.90, 25.86 and 25.78 ms).
+// Folds them into kFoldChunks in scratch where they are more than `most`.  In the backward pass up to 2048 chunks the launch of the fold, 5 us and a gap,
+// costs more than it saves.
 constexpr int kFinalizeChunks = 2048;
 static ColSums fold_sums(ColSums q, int C, int most, float* scratch, hipStream_t s) {
   if (q.chunks <= most) return q;
@@ -906,7 +905,7 @@ static void bn_stats_t(const T* x, const T* gamma, const T* beta, int64_t M, int
     q.chunks = (vec > 1 ? launch_reduce<T, V, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)
                         : launch_reduce<T, 1, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)).chunks;
   else
-    q = fold_sums(q, C, kFinalizeChunks, scratch, s);
+    q = fold_sums(q, C, 256, scratch, s);   // (the statistics keep the order of their sums: logits and loss stay what they were)
   hipLaunchKernelGGL((col_finalize_k<T, 0>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      q.part, q.chunks, M, C, gamma, beta, stats, (float*)nullptr, (float*)nullptr, (float*)nullptr);
 }
