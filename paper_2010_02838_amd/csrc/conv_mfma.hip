@@ -1233,7 +1233,7 @@ constexpr int WG_MS = 32;   // pixels per main-loop step
 
 // PW: 1x1 filters, stride 1, no padding: row m of x belongs to row m of dy
 template <int BN, int BKK, bool PW, int NJ>
-__global__ void __launch_bounds__(256) wgrad_kernel(WgradBatch<NJ> batch) {
+__global__ void __launch_bounds__(256, NJ > 1 ? 2 : 1) wgrad_kernel(WgradBatch<NJ> batch) {
   constexpr int NS = kWgradStages;
   constexpr int NVR = BN / 8, KVR = BKK / 8;   // 16-byte vectors per tile row
   constexpr int DV = WG_MS * NVR / 256, XV = WG_MS * KVR / 256;  // vectors per thread per step
@@ -1385,6 +1385,23 @@ __global__ void __launch_bounds__(256) wgrad_kernel(WgradBatch<NJ> batch) {
     if (half) s += (double)(bhalf + t); else bhalf = t;
   };
 
+  // FOLD: every wgrad_fold steps the accumulators are added to a second set of fp32 sums, and what that addition rounds away stays behind
+  // in the accumulator (compensated summation).  A launch of several layers cuts the rows into few splits or none, and one chain of
+  // fp32 additions over all of them was further from the float64 result than the splits it took the place of.  2-norm of the error
+  // over that of dw, a layer by itself in splits / one chain / folded: 512 x 512 over 8192 rows 6.7e-8 / 2.8e-7 / 5.7e-8, 640 x 320 over
+  // 6144 2.8e-7 / 8.6e-7 / 2.7e-7, 64 x 576 over 8192 2.3e-7 / 4.1e-7 / 2.0e-7.  One chain and folded: Wide-ResNet step 7.71 -> 7.77 ms,
+  // one-layer Transformer pass 1568 -> 1581 us, packed Transformer step 9.81 -> 9.77 ms.  (The bound of two waves per SIMD in the
+  // kernel's attributes keeps the accumulators in ordinary registers: moved in and out of the others for each fold, 1707 us.)
+  constexpr bool FOLD = NJ > 1;
+  f32x16_t sum[FOLD ? TN : 1][FOLD ? TK : 1];
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int j = 0; j < TK; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) sum[i][j][v] = 0.f;
+  }
   const int steps = (mend - mbeg + WG_MS - 1) / WG_MS;
   uint32_t cur = 0, nxt = STAGE_BYTES;
 #pragma unroll
@@ -1428,6 +1445,30 @@ __global__ void __launch_bounds__(256) wgrad_kernel(WgradBatch<NJ> batch) {
     }
     cur = nxt;
     nxt = nxt + STAGE_BYTES == NS * STAGE_BYTES ? 0u : nxt + STAGE_BYTES;
+    if constexpr (FOLD) {
+      if (st % wgrad_fold(BN, BKK) == wgrad_fold(BN, BKK) - 1) {
+#pragma unroll
+        for (int i = 0; i < TN; i++)
+#pragma unroll
+          for (int j = 0; j < TK; j++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) {
+              const float b = acc[i][j][v], t = sum[i][j][v] + b;
+              // (of an infinite sum the difference is NaN or infinite: a finite remainder leaves the sum as it is.  A real one is at most
+              // half a last place, 2^103)
+              acc[i][j][v] = __builtin_amdgcn_fmed3f(b - (t - sum[i][j][v]), -0x1p104f, 0x1p104f);
+              sum[i][j][v] = t;
+            }
+      }
+    }
+  }
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int j = 0; j < TK; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[i][j][v] += sum[i][j][v];
   }
 
   float* out = a.out + ((int64_t)split * a.slices + sl) * a.N * a.K;   // N*K*4 bytes < 2^33: 32-bit element offsets inside

@@ -73,6 +73,9 @@ inline bool conv_sums_fit(int64_t M, int64_t pitch, size_t bytes) {
 // ---- weight gradients of the matrix-core path (conv_mfma.hip) -----------------------------------------------------------------
 constexpr int kWgradJobs = 16;     // layers in a launch: their table travels in the kernel arguments
 constexpr int kWgradStages = 3;
+// Steps of 32 pixels that one accumulator runs over in a launch of several layers, at the most: as many rows as the shortest splits that
+// layers by themselves are cut into (256 rows of 128x128 tiles, 128 of smaller ones, which have fewer sums to fold)
+constexpr int wgrad_fold(int bn, int bk) { return bn == 128 && bk == 128 ? 8 : 4; }
 constexpr int kWgradBlocks = 512;  // workgroups a launch of several layers aims for: two a compute unit
 struct WgradShape {
   int64_t M;      // pixels (rows)
