@@ -1581,8 +1581,9 @@ static void launch_wgrad(const WgradJob* jobs, int n, unsigned blocks, hipStream
   }
 }
 
-WgradShape conv_wgrad_shape(const ConvGeom& g, int slices) {
+WgradShape conv_wgrad_shape(const ConvGeom& g, int slices, bool bias) {
   WgradShape h;
+  h.bias = bias;
   h.M = g.M(); h.N = g.Cout; h.K = g.K(); h.slices = slices;
   h.taps = g.kh * g.kw;
   h.pointwise = g.kh == 1 && g.kw == 1 && g.stride == 1 && g.pad == 0;
@@ -1595,8 +1596,7 @@ static void wgrad_run(const WgradProblem* p, int n, int pitch, float* partials, 
   WgradShape shapes[kWgradJobs];
   WgradSplit plan[kWgradJobs];
   for (int k = 0; k < n; k++) {
-    shapes[k] = conv_wgrad_shape(p[k].g, p[k].slices);
-    shapes[k].bias = p[k].db != nullptr;
+    shapes[k] = conv_wgrad_shape(p[k].g, p[k].slices, p[k].db != nullptr);
   }
   wgrad_plan(shapes, n, partials_bytes, g_tune_co, plan);
   WgradSums<kWgradJobs> sums;

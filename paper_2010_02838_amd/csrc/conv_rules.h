@@ -78,10 +78,10 @@ constexpr int kWgradStages = 3;
 constexpr int wgrad_fold(int bn, int bk) { return bn == 128 && bk == 128 ? 8 : 4; }
 constexpr int kWgradBlocks = 512;  // workgroups a launch of several layers aims for: two a compute unit
 struct WgradShape {
-  int64_t M;      // pixels (rows)
-  int N, K;       // dw [N][K], per slice
-  int taps, slices;
-  bool pointwise, bias;
+  int64_t M = 0;        // pixels (rows)
+  int N = 0, K = 0;     // dw [N][K], per slice
+  int taps = 0, slices = 0;
+  bool pointwise = false, bias = false;   // bias: the bias gradient comes with it
   int bn() const { return N > 64 ? 128 : 64; }
   int bk() const { return K > 64 ? 128 : 64; }
   int tile_class() const { return (bn() == 128 ? 4 : 0) + (bk() == 128 ? 2 : 0) + (pointwise ? 1 : 0); }

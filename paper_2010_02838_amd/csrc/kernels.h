@@ -181,7 +181,7 @@ void conv_wgrad_mfma(const bf16_t* x, const bf16_t* dy, float* dw, const ConvGeo
 struct WgradProblem { const bf16_t* x; const bf16_t* dy; float* dw; float* db; ConvGeom g; int slices; };
 void conv_wgrad_batch(const WgradProblem* p, int n, float* partials, size_t partials_bytes, hipStream_t s);
 struct WgradShape;
-WgradShape conv_wgrad_shape(const ConvGeom& g, int slices);
+WgradShape conv_wgrad_shape(const ConvGeom& g, int slices, bool bias);
 // Grouped convolutions (Cin = Cout = C, groups of C / groups channels) on the same kernels, reading and writing the
 // row-major tensors in place: slices of grouped_mfma_slice(C, groups) = 32 or 64 channels (0: this shape is not taken;
 // the slice must hold whole groups and divide C).  w is the grouped filter [C][kh][kw][C / groups]; wd is scratch for

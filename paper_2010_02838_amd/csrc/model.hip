@@ -1107,7 +1107,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
   for (size_t i = (size_t)m->first_trainable_op; i < m->ops.size(); i++) {
     if (m->ops[i].kind != OP_CONV || grouped_sliced(m, m->ops[i], batch) || m->ops[i].groups > 1) continue;
     const ConvGeom g = conv_geom(m, m->ops[i], batch), gp = packed_geom(g);
-    const WgradShape h = conv_wgrad_shape(gp, 1);
+    const WgradShape h = conv_wgrad_shape(gp, 1, m->ops[i].pb >= 0);
     if (use_mfma(m, g) && waits(gp, h)) pending[h.tile_class()].work_left += h.tiles() * h.steps();
   }
   int late_rc = CD_OK;   // a launch-time failure of the fork / join machinery: reported after the join was attempted
@@ -1353,7 +1353,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
             w.x = c.xpack();
             w.dw = reinterpret_cast<float*>(c.wpack());
           }
-          const WgradShape h = conv_wgrad_shape(gp, 1);
+          const WgradShape h = conv_wgrad_shape(gp, 1, o.pb >= 0);
           PendingWgrads one;
           const bool wait = waits(gp, h);
           PendingWgrads& q = wait ? pending[h.tile_class()] : one;

@@ -237,3 +237,38 @@ def test_weight_gradient_splits_take_every_row_once(wgrad_splits, layers, scratc
     assert bytes_ <= scratch
     if len(layers) > 1:   # a launch of several layers stays within two workgroups a compute unit where it splits at all
         assert blocks <= 512 or all(s == 1 for s in splits)
+
+
+def test_weight_gradient_shape_starts_from_defined_values(tmp_path):
+    """Every field, also in memory that held something else: the decisions below are made from shapes that the caller fills in part."""
+    out = compiled(tmp_path, """
+#include <cstring>
+#include <new>
+int main() {
+  for (int fill = 0; fill < 256; fill += 255) {
+    alignas(WgradShape) unsigned char mem[sizeof(WgradShape)];
+    memset(mem, fill, sizeof mem);
+    const WgradShape* s = new (mem) WgradShape;
+    unsigned char bools[2];
+    memcpy(bools, &s->pointwise, 1);
+    memcpy(bools + 1, &s->bias, 1);
+    printf("%lld %d %d %d %d %d %d ", (long long)s->M, s->N, s->K, s->taps, s->slices, bools[0], bools[1]);
+  }
+}
+""")().split()
+    assert out == ["0"] * 14
+
+
+@pytest.mark.parametrize("M,N,K,with_bias,without", [
+    (8192, 2048, 32, 0, 1), (65536, 32, 32, 0, 1),      # the bias sums of the splits are what tips them
+    (8192, 512, 512, 0, 0), (8192, 32768, 512, 1, 1), (802816, 64, 64, 1, 1)])
+def test_weight_gradient_by_itself(tmp_path, M, N, K, with_bias, without):
+    """Pointwise layers whose partial sums, with those of the bias gradient, are a quarter of what the operands move or less go by themselves."""
+    run = compiled(tmp_path, """
+int main(int, char** v) {
+  WgradShape s;
+  s.M = atoll(v[1]); s.N = atoi(v[2]); s.K = atoi(v[3]); s.pointwise = true; s.taps = s.slices = 1; s.bias = atoi(v[4]) != 0;
+  printf("%d", (int)wgrad_alone(s, 2 * s.M * ((int64_t)s.N + s.K)));
+}
+""")
+    assert (int(run(M, N, K, 1)), int(run(M, N, K, 0))) == (with_bias, without)
