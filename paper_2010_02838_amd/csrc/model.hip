@@ -1072,7 +1072,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
   // The side stream and its events belong to the library and are shared by every caller of this process: the lock
   // is held from here to the join, so that two host threads never interleave forks on it.  Everything the forks
   // need (the stream, one event per convolution and one for the join) exists before the first launch; if the
-  // runtime refuses any of it the call runs on the caller's stream alone.
+  // runtime refuses any of it the call runs on the caller's stream alone, and a launch whose fork it refuses later on does.
   std::unique_lock<std::mutex> side_lock(side_mutex(), std::defer_lock);
   hipStream_t side = nullptr;
   if (!timer_enabled() && !force_serial()) {
@@ -1110,23 +1110,26 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     const WgradShape h = conv_wgrad_shape(gp, 1, m->ops[i].pb >= 0);
     if (use_mfma(m, g) && waits(gp, h)) pending[h.tile_class()].work_left += h.tiles() * h.steps();
   }
-  int late_rc = CD_OK;   // a launch-time failure of the fork / join machinery: reported after the join was attempted
-  hipStream_t wgrad_stream = side ? side : c.s;
+  // Launches them, on the second stream behind what the caller's stream holds so far; where the runtime refuses the event or the wait,
+  // on the caller's stream (whose partials area is free between two ops).  Returns the stream.
   auto run_wgrads = [&](PendingWgrads& q) {
-    if (q.p.empty()) return;
+    hipStream_t s = c.s;
+    if (q.p.empty()) return s;
     if (side) {
       hipEvent_t ev = side_event(forks);
-      if (!ev || hipEventRecord(ev, c.s) != hipSuccess || hipStreamWaitEvent(side, ev, 0) != hipSuccess) {
+      if (ev && hipEventRecord(ev, c.s) == hipSuccess && hipStreamWaitEvent(side, ev, 0) == hipSuccess) {
+        s = side;
+        forks++;
+      } else {
         (void)hipGetLastError();
-        late_rc = set_error(CD_ERR_HIP, "backward: could not fork onto the weight-gradient stream (event record / wait failed)");
       }
-      forks++;
     }
-    ProfScope pr(CD_K_CONV_WGRAD, wgrad_stream, q.flops, q.bytes);
-    conv_wgrad_batch(q.p.data(), (int)q.p.size(), c.partials_side(), c.plan.partials_bytes, wgrad_stream);
+    ProfScope pr(CD_K_CONV_WGRAD, s, q.flops, q.bytes);
+    conv_wgrad_batch(q.p.data(), (int)q.p.size(), s == c.s ? c.partials() : c.partials_side(), c.plan.partials_bytes, s);
     q.p.clear();
     q.tiles = q.work = 0;
     q.flops = q.bytes = 0.0;
+    return s;
   };
   std::vector<char> written(m->tensors.size(), 0);
   // gradients of residual inputs that are handed on as "dy and a bit mask" instead of being written
@@ -1363,9 +1366,11 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
           q.flops += 2.0 * g.M() * g.Cout * g.K();
           q.bytes += conv_bytes(m, g) + 2.0 * g.Cout * g.K();
           if (wait) q.work_left -= h.tiles() * h.steps();
-          if (!wait || wgrad_batch_full(q.tiles, q.work, (int)q.p.size(), q.work_left)) run_wgrads(q);
-          if (s2d_form(g)) s2d_unpack_dw(w.dw, G(o.pw), g.Cout, g.kh, gp.kh, 2 * gp.pad - g.pad, wgrad_stream);
-          else if (g.Cin == 3) unpad_c8_to_c3(w.dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, wgrad_stream);
+          if (!wait || wgrad_batch_full(q.tiles, q.work, (int)q.p.size(), q.work_left)) {
+            const hipStream_t ws = run_wgrads(q);   // (a 3-channel image's layer never waits: its dw is unpacked behind it)
+            if (s2d_form(g)) s2d_unpack_dw(w.dw, G(o.pw), g.Cout, g.kh, gp.kh, 2 * gp.pad - g.pad, ws);
+            else if (g.Cin == 3) unpad_c8_to_c3(w.dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, ws);
+          }
         } else {
           if (o.pb >= 0) {
             ProfScope pr(CD_K_GLUE, c.s, 0, (double)g.M() * g.Cout * m->esize());
@@ -1428,10 +1433,9 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     hipEvent_t ev = side_event(forks);
     if (!ev || hipEventRecord(ev, side) != hipSuccess || hipStreamWaitEvent(c.s, ev, 0) != hipSuccess) {
       (void)hipGetLastError();
-      late_rc = set_error(CD_ERR_HIP, "backward: could not join the weight-gradient stream (event record / wait failed); "
-                                      "synchronise the device before reading or freeing the buffers of this call");
+      return set_error(CD_ERR_HIP, "backward: could not join the weight-gradient stream (event record / wait failed); "
+                                   "synchronise the device before reading or freeing the buffers of this call");
     }
   }
-  if (late_rc) return late_rc;
   return check_launch("backward");
 }

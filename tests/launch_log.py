@@ -1,0 +1,28 @@
+"""What the library enqueues, in order, without a GPU: `python launch_log.py FAKE_LIBRARY REQUEST` (a JSON object: kind, dtype, arch,
+batch, and optionally fail = [function, n-th call in the backward pass]) prints the log of one codistill_backward call as JSON.
+
+A process of its own: the stand-in for the HIP runtime (fake_hip.cpp) has to be loaded before anything else that uses HIP.  The
+pointers that it hands over are never read, on the host or anywhere else."""
+import ctypes
+import json
+import os
+import sys
+import types
+
+if __name__ == "__main__":
+    fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+    fake.fake_hip_log.restype = ctypes.c_char_p
+    sys.modules["torch"] = types.SimpleNamespace(bfloat16="bf16", float32="f32")   # (the binding needs it for device memory and streams only)
+    sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    from paper_2010_02838_amd import binding as B
+
+    req = json.loads(sys.argv[2])
+    m = B.Model(B.arch_preset(req["kind"], **req["arch"]), B.CD_BF16 if req["dtype"] == "bf16" else B.CD_F32)
+    at = lambda k: ctypes.c_void_p(k << 32)   # noqa: E731
+    fake.fake_hip_reset()
+    if req.get("fail"):
+        fake.fake_hip_fail(req["fail"][0].encode(), ctypes.c_long(req["fail"][1]))
+    rc = B.lib.codistill_backward(m._h, at(1), at(2), req["batch"], at(3), m.workspace_bytes(req["batch"], True), at(4), at(5), at(6))
+    log = [line.split(" ") for line in fake.fake_hip_log().decode().splitlines()]
+    json.dump(dict(rc=rc, error=B.lib.codistill_last_error().decode(), main="%x" % (6 << 32),
+                   log=[[what, stream, name, int(code)] for what, stream, name, code in log]), sys.stdout)

@@ -1,0 +1,86 @@
+"""The order of the backward pass's launches on its two streams, and what happens where the runtime refuses one of its forks: looked at
+on the host, with a stand-in for the HIP runtime that enqueues nothing (fake_hip.cpp)."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2010_02838_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+MODELS = {
+    "basic": dict(kind=B.CD_ARCH_RESNET_BASIC, dtype="bf16", batch=16, arch=dict(in_h=32, in_w=32, widths=[32, 64], blocks=[2, 2])),
+    "big_stem": dict(kind=B.CD_ARCH_RESNET_BOTTLENECK, dtype="bf16", batch=4, arch=dict(in_h=64, in_w=64, widths=[64, 128], blocks=[1, 1])),
+    "transformer": dict(kind=B.CD_ARCH_TRANSFORMER, dtype="bf16", batch=8, arch=dict(in_h=64, in_w=64, classes=512, widths=[256, 1024, 4], blocks=[1, 1])),
+}
+
+
+@pytest.fixture(scope="module")
+def backward(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"), "-o", lib], check=True)
+
+    def run(name, fail=None, **env):
+        out = subprocess.run([sys.executable, os.path.join(HERE, "launch_log.py"), lib, json.dumps(dict(MODELS[name], fail=fail))],
+                             check=True, capture_output=True, text=True, env=dict(os.environ, **env)).stdout
+        return json.loads(out)
+    return run
+
+
+def _kernels(r, stream=None):
+    return sorted(name for what, s, name, _ in r["log"] if what == "launch" and (stream is None or (s == r["main"]) == stream))
+
+
+def _forks(r):
+    """Checks that every run of launches on the second stream stands right behind a record on the caller's stream and a wait for it
+    that both went well, and that the caller's stream waits for the last of them; returns the number of runs."""
+    main, log, runs = r["main"], r["log"], 0
+    last_side = -1
+    for k, (what, s, name, code) in enumerate(log):
+        if what != "launch" or s == main:
+            continue
+        last_side = k
+        if log[k - 1][0] == "launch" and log[k - 1][1] == s:
+            continue
+        runs += 1
+        (w0, s0, e0, c0), (w1, s1, e1, c1) = log[k - 2], log[k - 1]
+        assert (w0, s0, c0, w1, s1, c1) == ("record", main, 0, "wait", s, 0) and e0 == e1, log[k - 3:k + 1]
+    if runs:
+        behind = [x for x in log[last_side + 1:] if x[0] != "launch"]
+        assert [(x[0], x[1] == main) for x in behind[-2:]] == [("record", False), ("wait", True)] and behind[-2][2] == behind[-1][2]
+    return runs
+
+
+@pytest.mark.parametrize("name", list(MODELS))
+def test_weight_gradients_run_on_the_second_stream(backward, name):
+    r = backward(name)
+    assert r["rc"] == 0 and _forks(r) >= 1
+    assert any("wgrad_kernel" in k for k in _kernels(r, False))
+    assert all("wgrad" in k or "unpack" in k or "unpad" in k for k in _kernels(r, False))
+    serial = backward(name, CODISTILL_SERIAL="1")
+    assert serial["rc"] == 0 and not _kernels(serial, False)
+    assert _kernels(serial) == _kernels(r)
+
+
+@pytest.mark.parametrize("name", list(MODELS))
+@pytest.mark.parametrize("call", ["hipEventRecord", "hipStreamWaitEvent"])
+def test_refused_fork_runs_on_the_callers_stream(backward, name, call):
+    """The launches of a fork whose event cannot be recorded, or waited for, go to the caller's stream (with what belongs to them, the
+    unpacking of a stem's gradient); the call succeeds, the other forks stay, and the same kernels run."""
+    whole = backward(name)
+    forks = _forks(whole)
+    for n in range(1, forks + 1):
+        r = backward(name, fail=[call, n])
+        assert r["rc"] == 0, r["error"]
+        assert sum(code != 0 for _, _, _, code in r["log"]) == 1
+        assert _forks(r) == forks - 1
+        assert _kernels(r) == _kernels(whole)
+        assert any("wgrad_kernel" in k for k in _kernels(r, True))
+
+
+def test_refused_join_is_reported(backward):
+    forks = _forks(backward("basic"))
+    r = backward("basic", fail=["hipEventRecord", forks + 1])
+    assert r["rc"] == B.CD_ERR_HIP and "join" in r["error"]
