@@ -292,6 +292,7 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
 #pragma unroll
       for (int q = 0; q < 4; q++) {
         const int n = n0 + i * 16 + fk + q;
+        nsc[i][q] = nsh[i][q] = 0.f;   // (channels behind the last one are computed and not stored)
         if (n < a.N)
           running_scale_shift(a.norm.running, static_cast<const T*>(a.norm.gamma), static_cast<const T*>(a.norm.beta), a.N, n,
                               &nsc[i][q], &nsh[i][q]);
@@ -307,25 +308,29 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
       if (n >= a.N) continue;
       T* o = out + ((unsigned)m * (unsigned)a.N + (unsigned)n);
       const int nv = a.N - n < 4 ? a.N - n : 4;
-      float v[4];
+      // All four elements are computed without a condition of their own (of a fourth channel that is not there: zeros, not stored).
+      // Where each was changed inside `q < nv`, clang of ROCm 7.2 copied the accumulators' four registers from condition to condition and
+      // wrote element 0 over 1 and 2 (v_accvgpr_write_b32 a1, v0; a2, v0) in eight of the eighteen normalising kernels, whether or not nsc and
+      // nsh of the missing channels were defined.
+      float v[4], old[4] = {0.f, 0.f, 0.f, 0.f};   // old: the gradient so far, or the residual
+      const T* add = NORM ? nullptr : MODE == 1 && a.accumulate ? o : nullptr;
+      if constexpr (NORM) {
+        if (a.norm.res) add = static_cast<const T*>(a.norm.res) + ((unsigned)m * (unsigned)a.N + (unsigned)n);
+      }
+      if (add) {
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+          if (q < nv) old[q] = Cvt<T>::ld(add[q]);
+      }
 #pragma unroll
       for (int q = 0; q < 4; q++) {
         v[q] = acc[i][j][q];
-        if (q < nv) {
-          if (MODE == 1 && a.accumulate) v[q] += Cvt<T>::ld(o[q]);
-          if (MODE == 0 && a.relu) v[q] = fmaxf(v[q], 0.f);
+        if constexpr (NORM) {
+          v[q] = gen_norm<T>(a, v[q], nsc[i][q], nsh[i][q], old[q]);
+        } else {
+          if (MODE == 1) v[q] = a.accumulate ? v[q] + old[q] : v[q];
+          if (MODE == 0) v[q] = a.relu ? fmaxf(v[q], 0.f) : v[q];
         }
-      }
-      if constexpr (NORM) {   // (all four, straight: inside the condition above the compiler mixed up the lanes' values)
-        float r[4] = {0.f, 0.f, 0.f, 0.f};
-        if (a.norm.res) {
-          const T* p = static_cast<const T*>(a.norm.res) + ((unsigned)m * (unsigned)a.N + (unsigned)n);
-#pragma unroll
-          for (int q = 0; q < 4; q++)
-            if (q < nv) r[q] = Cvt<T>::ld(p[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; q++) v[q] = gen_norm<T>(a, v[q], nsc[i][q], nsh[i][q], r[q]);
       }
       if ((a.N & 3) == 0) {   // four channels of a pixel at a 4-element boundary
         if (sizeof(T) == 4) {
