@@ -884,9 +884,10 @@ static ReducePlan launch_reduce(const T* a0, const T* a1, const T* a2, const flo
 
 // Where the column sums of M rows lie, and in how many chunks: from the convolution in front (pre_chunks > 0, in partials), or reduced here.
 struct ColSums { const float* part; int chunks; };
-// Folds them into kFoldChunks in scratch where they are more than `most`.  In the backward pass up to 2048 chunks the launch of the fold, 5 us and a gap,
-// costs more than it saves.
-constexpr int kFinalizeChunks = 2048;
+// Folds them into kFoldChunks in scratch where they are more than `most`.  In the backward pass the fold, 5 us and a gap in front of a finalize
+// of 5, pays from about 1600 chunks on: 72, 136 and 256 channels, from the first launch to the end of the last, with it and without:
+// 1024 chunks 10 us and 5.8 to 7.4, 1536 chunks 10 and 8.5 to 10, 2048 chunks 10 and 11.3 to 12.7, 4096 chunks 10 and 21 to 23.
+constexpr int kFinalizeChunks = 1600;
 static ColSums fold_sums(ColSums q, int C, int most, float* scratch, hipStream_t s) {
   if (q.chunks <= most) return q;
   hipLaunchKernelGGL(col_fold_k, dim3((unsigned)cdiv(C, 64), kFoldChunks), dim3(1024), 0, s, q.part, q.chunks, C, scratch);
@@ -905,7 +906,9 @@ static void bn_stats_t(const T* x, const T* gamma, const T* beta, int64_t M, int
     q.chunks = (vec > 1 ? launch_reduce<T, V, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)
                         : launch_reduce<T, 1, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)).chunks;
   else
-    q = fold_sums(q, C, 256, scratch, s);   // (the statistics keep the order of their sums: logits and loss stay what they were)
+    // (more than 256 of a convolution's partial sums are folded first, here, although up to kFinalizeChunks the fold is the longer way in the
+    // forward pass too: in another order the statistics differ in the last place and all roundings behind them move)
+    q = fold_sums(q, C, 256, scratch, s);
   hipLaunchKernelGGL((col_finalize_k<T, 0>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      q.part, q.chunks, M, C, gamma, beta, stats, (float*)nullptr, (float*)nullptr, (float*)nullptr);
 }

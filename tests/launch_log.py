@@ -1,5 +1,6 @@
 """What the library enqueues, in order, without a GPU: `python launch_log.py FAKE_LIBRARY REQUEST` (a JSON object: kind, dtype, arch,
-batch, and optionally fail = [function, n-th call in the backward pass]) prints the log of one codistill_backward call as JSON.
+batch, and optionally call = "forward" (saving for a backward pass) and fail = [function, n-th call]) prints the log of one
+codistill_backward or codistill_forward call as JSON.
 
 A process of its own: the stand-in for the HIP runtime (fake_hip.cpp) has to be loaded before anything else that uses HIP.  The
 pointers that it hands over are never read, on the host or anywhere else."""
@@ -22,7 +23,11 @@ if __name__ == "__main__":
     fake.fake_hip_reset()
     if req.get("fail"):
         fake.fake_hip_fail(req["fail"][0].encode(), ctypes.c_long(req["fail"][1]))
-    rc = B.lib.codistill_backward(m._h, at(1), at(2), req["batch"], at(3), m.workspace_bytes(req["batch"], True), at(4), at(5), at(6))
+    ws = at(3), m.workspace_bytes(req["batch"], True)
+    if req.get("call") == "forward":
+        rc = B.lib.codistill_forward(m._h, at(1), at(2), req["batch"], 1, B.CD_BN_BATCH_STATS, None, *ws, at(4), at(6))
+    else:
+        rc = B.lib.codistill_backward(m._h, at(1), at(2), req["batch"], *ws, at(4), at(5), at(6))
     log = [line.split(" ") for line in fake.fake_hip_log().decode().splitlines()]
     json.dump(dict(rc=rc, error=B.lib.codistill_last_error().decode(), main="%x" % (6 << 32),
                    log=[[what, stream, name, int(code)] for what, stream, name, code in log]), sys.stdout)

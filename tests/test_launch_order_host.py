@@ -1,5 +1,6 @@
-"""The order of the backward pass's launches on its two streams, and what happens where the runtime refuses one of its forks: looked at
-on the host, with a stand-in for the HIP runtime that enqueues nothing (fake_hip.cpp)."""
+"""The order of the backward pass's launches on its two streams, what happens where the runtime refuses one of its forks, and which
+kernels a call takes on either side of a rule's line: looked at on the host, with a stand-in for the HIP runtime that enqueues nothing
+(fake_hip.cpp)."""
 import json
 import os
 import subprocess
@@ -22,8 +23,9 @@ def backward(tmp_path_factory):
     lib = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"), "-o", lib], check=True)
 
-    def run(name, fail=None, **env):
-        out = subprocess.run([sys.executable, os.path.join(HERE, "launch_log.py"), lib, json.dumps(dict(MODELS[name], fail=fail))],
+    def run(model, fail=None, call="backward", **env):
+        req = dict(MODELS[model] if isinstance(model, str) else model, fail=fail, call=call)
+        out = subprocess.run([sys.executable, os.path.join(HERE, "launch_log.py"), lib, json.dumps(req)],
                              check=True, capture_output=True, text=True, env=dict(os.environ, **env)).stdout
         return json.loads(out)
     return run
@@ -84,3 +86,11 @@ def test_refused_join_is_reported(backward):
     forks = _forks(backward("basic"))
     r = backward("basic", fail=["hipEventRecord", forks + 1])
     assert r["rc"] == B.CD_ERR_HIP and "join" in r["error"]
+
+
+@pytest.mark.parametrize("batch,folds", [(200, 0), (201, 2)])
+def test_fold_of_many_backward_sums(backward, batch, folds):
+    """A data gradient of 128-row tiles leaves 8 partial sums an image: 1600 of them are added up as they are, 1608 folded
+    first (two BatchNorms with a convolution right behind them)."""
+    r = backward(dict(kind=B.CD_ARCH_RESNET_BASIC, dtype="bf16", batch=batch, arch=dict(in_h=32, in_w=32, widths=[72], blocks=[1], stem_width=72)))
+    assert r["rc"] == 0 and sum("col_fold_k" in k for k in _kernels(r)) == folds
