@@ -851,13 +851,19 @@ void linear_fwd_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, float
   // (8192 x 32768 x 512 inside a training step: 471 us on 128x128 tiles, 459 so; non-temporal stores of the logits, faster when
   // the launch is repeated alone, 368 us, cost it 70 us there)
   const bool group = (int64_t)C * F * 2 > (4 << 20) && C >= 2048;
+  // otherwise 64x64 tiles for few rows as igemm_tile says (256 x 1000 x 2048 18 -> 11 us), and for at most 64 classes up to 16384 rows, a
+  // tile for every compute unit: the busiest unit has the same number of tiles of either shape there and a 64x64 one is the shorter
+  // chain.  128x128 and 64x64 tiles, 10 classes: 128 rows of 64 8.0 and 3.8 us, of 2048 25.9 and 10.0; 16384 rows of 64 9.2 and 4.5, of 2048
+  // 26.1 and 12.9; 64 classes 16384 x 512 9.6 and 5.7.  (Beyond the line 64x64 tiles win less, and lose in places: 32768 rows of 2048
+  // onto 64 classes 43 and 34, 65536 of 64 7.9 and 8.2.)
+  const bool narrow = C <= 64 && F >= 64 && B <= 64 * 256;
   const int tile = igemm_tile(B, C, F, F >= 64, false);
   if (group && F <= 512 && cdiv(B, 256) * cdiv(C, 128) >= 512) {
     a.group_m = 4;
     if (bias) launch_linear<256, 128, 1, true, 32, 3>(a, s); else launch_linear<256, 128, 0, true, 32, 3>(a, s);
   } else if (group && F >= 64) {
     if (bias) launch_linear<128, 128, 1, true, 64, 2>(a, s); else launch_linear<128, 128, 0, true, 64, 2>(a, s);
-  } else if (tile == TILE_SMALL || (C <= 64 && F >= 64 && B <= 64 * 256)) {   // few rows or few classes: as igemm_tile says (256 x 1000 x 2048 18 -> 11 us)
+  } else if (tile == TILE_SMALL || narrow) {
     if (bias) launch_linear<64, 64, 1, false, 64, 4>(a, s); else launch_linear<64, 64, 0, false, 64, 4>(a, s);
   } else if (F >= 64) {
     if (bias) launch_linear<128, 128, 1, false, 64, 2>(a, s); else launch_linear<128, 128, 0, false, 64, 2>(a, s);

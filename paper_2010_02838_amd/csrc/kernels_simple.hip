@@ -463,8 +463,10 @@ __global__ void __launch_bounds__(256) linear_dx_k(const float* __restrict__ dy,
   dx[idx] = Cvt<T>::st(acc);
 }
 // dw[c][f] = sum_b dy[b][c] x[b][f], db[c] = sum_b dy[b][c] (the column f = F, x = 1).  Block = 64 features x G row groups
-// for 4 classes; the groups are added in LDS in a fixed order.  A group's rows are a chain of loads: 16 groups where the blocks do not
-// fill the chip anyway (10 classes of 64 features over 128 rows, 6 blocks: 19.9 us with 4 groups, 11.8 with 16).
+// for 4 classes; the groups are added in LDS in a fixed order.  A group's rows are a chain of loads: 16 groups for up to 256 blocks, where
+// every block has a compute unit to itself, otherwise 4.  fp32, 4 and 16 groups: 64 features over 128 rows, 6 blocks 11.9 and 5.5 us, 256
+// blocks 11.6 and 5.2, over 1024 rows 79 and 27; from there on it depends on the rows: 2048 blocks over 32 rows 7.2 and 10.2, over 128
+// 17.8 and 21.0, over 1024 232 and 227.
 template <typename T, int G>
 __global__ void __launch_bounds__(64 * G) linear_dw_k(const float* __restrict__ dy, const T* __restrict__ x,
                                                    float* __restrict__ dw, float* __restrict__ db, int64_t B, int F,

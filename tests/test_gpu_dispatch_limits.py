@@ -58,3 +58,24 @@ def test_backward_sums_of_a_batchnorm(batch):
             assert bool(((got - terms.sum(0)).abs() <= (128 + 51 + 4) * U * terms.abs().sum(0)).all())
         seen += 1
     assert seen == 2
+
+
+@pytest.mark.parametrize("rows,features,classes", [(16384, 64, 64), (16385, 64, 64), (16321, 64, 3), (16384, 56, 64), (16384, 200, 61), (1, 64, 1)])
+def test_logits_of_a_classifier(rows, features, classes):
+    """64x64 and 128x128 tiles on both sides of the line, ragged last rows, columns and steps: products of bf16 are exact, at most one rounding
+    for each of the `features` additions."""
+    from paper_2010_02838_amd import binding as B
+    m, ops, read, _, z, _, _, param = _pass(B.CD_ARCH_TRANSFORMER_HEAD, "bf16", rows, False, widths=[features, 64], classes=classes)
+    x, w = read(ops[-1]["x"]), param(ops[-1]["param_w"])
+    assert bool(((z.double() - x @ w.t()).abs() <= features * U * (x.abs() @ w.abs().t())).all())
+
+
+@pytest.mark.parametrize("rows", [1, 15, 16, 70])
+@pytest.mark.parametrize("features,classes", [(64, 512), (64, 513), (63, 1024), (5, 3)])
+def test_dense_weight_gradient(rows, features, classes):
+    """16 and 4 row groups (256 and 258 blocks), fewer rows than groups, no whole columns or classes: a product and an addition a row, and the sum
+    of the groups."""
+    from paper_2010_02838_amd import binding as B
+    m, ops, read, _, _, dz, grad, _ = _pass(B.CD_ARCH_TRANSFORMER_HEAD, "f32", rows, widths=[features, 8], classes=classes)
+    x, d = read(ops[-1]["x"]), dz.double()
+    assert bool(((grad(ops[-1]["param_w"]) - d.t() @ x).abs() <= (2 * rows + 16) * U * (d.abs().t() @ x.abs())).all())

@@ -94,3 +94,21 @@ def test_fold_of_many_backward_sums(backward, batch, folds):
     first (two BatchNorms with a convolution right behind them)."""
     r = backward(dict(kind=B.CD_ARCH_RESNET_BASIC, dtype="bf16", batch=batch, arch=dict(in_h=32, in_w=32, widths=[72], blocks=[1], stem_width=72)))
     assert r["rc"] == 0 and sum("col_fold_k" in k for k in _kernels(r)) == folds
+
+
+@pytest.mark.parametrize("rows,features,classes,small", [
+    (16384, 64, 64, 1), (16385, 64, 64, 0), (16384, 56, 64, 0), (16384, 64, 65, 1), (16385, 64, 65, 0)])
+def test_tiles_of_a_classifier(backward, rows, features, classes, small):
+    """At most 64 classes: 64x64 tiles up to 16384 rows, if the features fill a 64-wide step (65 classes: two columns of 64x64 tiles for each of
+    128x128, up to the same number of rows)."""
+    r = backward(dict(kind=B.CD_ARCH_TRANSFORMER_HEAD, dtype="bf16", batch=rows, arch=dict(widths=[features, 64], classes=classes)), call="forward")
+    logits = [k for k in _kernels(r) if "igemm_kernel" in k and "ELb1ELi0ELi1ELb0" in k]   # fp32 output
+    assert r["rc"] == 0 and len(logits) == 1 and ("ILi0ELi64ELi64E" in logits[0]) == bool(small), logits
+
+
+@pytest.mark.parametrize("classes,groups", [(512, 16), (513, 4)])
+def test_row_groups_of_a_dense_weight_gradient(backward, classes, groups):
+    """256 and 258 blocks of 64 features and 4 classes."""
+    r = backward(dict(kind=B.CD_ARCH_TRANSFORMER_HEAD, dtype="f32", batch=70, arch=dict(widths=[64, 8], classes=classes)))
+    dw = [k for k in _kernels(r) if "linear_dw_k" in k]
+    assert r["rc"] == 0 and len(dw) == 1 and "IfLi%dEE" % groups in dw[0], dw
