@@ -101,20 +101,9 @@ __device__ inline float tile_diagonal(f32x16_t d, int c) {
   return b4 ? x1 : x0;
 }
 
-// 16-byte load through a raw buffer descriptor: an offset at or beyond the buffer size returns
-// zeros, so a masked-out vector costs one select instead of a branch around the load.
-typedef int v4i32_t __attribute__((ext_vector_type(4)));
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-__device__ inline uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
-  const v4i32_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, 0);
-  return make_uint4((uint32_t)v.x, (uint32_t)v.y, (uint32_t)v.z, (uint32_t)v.w);
-}
-
 // 16 bytes per lane from a buffer straight into LDS: lane l of the wave writes its vector at
-// lds_addr + 16*l (lds_addr is uniform over the wave and travels in M0); an offset outside the
-// buffer writes zeros.  The compiler does not see these loads: the kernel waits for them itself
+// lds_addr + 16*l (lds_addr is uniform over the wave and travels in M0); an offset at or beyond the buffer's size
+// writes zeros, so that a masked-out vector costs one select instead of a branch around the load.  The compiler does not see these loads: the kernel waits for them itself
 // (wait_vmem) before a barrier publishes the tile.
 typedef int rsrc_words_t __attribute__((ext_vector_type(4)));
 // the four descriptor words of a raw buffer (stride 0): base address, size in bytes, data format
