@@ -103,8 +103,8 @@ __device__ inline float tile_diagonal(f32x16_t d, int c) {
 
 // 16 bytes per lane from a buffer straight into LDS: lane l of the wave writes its vector at
 // lds_addr + 16*l (lds_addr is uniform over the wave and travels in M0); an offset at or beyond the buffer's size
-// writes zeros, so that a masked-out vector costs one select instead of a branch around the load.  The compiler does not see these loads: the kernel waits for them itself
-// (wait_vmem) before a barrier publishes the tile.
+// writes zeros, so that a masked-out vector costs one select instead of a branch around the load.  The compiler does
+// not see these loads: the kernel waits for them itself (wait_vmem) before a barrier publishes the tile.
 typedef int rsrc_words_t __attribute__((ext_vector_type(4)));
 // the four descriptor words of a raw buffer (stride 0): base address, size in bytes, data format
 __device__ inline rsrc_words_t make_rsrc_words(const void* p, uint32_t bytes) {

@@ -997,7 +997,8 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
         const int64_t rows = batch * tx.h * tx.w;
         ProfScope pr(CD_K_LINEAR, c.s, 2.0 * rows * F * C,
                      (double)m->esize() * ((double)rows * F + (double)F * C) + 4.0 * rows * C);
-        if (dt == CD_BF16 && !force_simple() && F % 8 == 0 && (int64_t)F * C * 2 < (1LL << 31))
+        // (32-bit element offsets into the input, byte offsets into the weights)
+        if (dt == CD_BF16 && !force_simple() && F % 8 == 0 && rows * F < (1LL << 31) && (int64_t)F * C * 2 < (1LL << 31))
           linear_fwd_mfma(static_cast<const bf16_t*>(in), static_cast<const bf16_t*>(c.P(o.pw)),
                           static_cast<const bf16_t*>(c.P(o.pb)), static_cast<float*>(out), rows, F, C, c.s);
         else

@@ -112,3 +112,13 @@ def test_row_groups_of_a_dense_weight_gradient(backward, classes, groups):
     r = backward(dict(kind=B.CD_ARCH_TRANSFORMER_HEAD, dtype="f32", batch=70, arch=dict(widths=[64, 8], classes=classes)))
     dw = [k for k in _kernels(r) if "linear_dw_k" in k]
     assert r["rc"] == 0 and len(dw) == 1 and "IfLi%dEE" % groups in dw[0], dw
+
+
+@pytest.mark.parametrize("features,matrix", [(2040, 1), (2048, 0)])
+def test_dense_layer_on_very_many_inputs(backward, features, matrix):
+    """2^20 rows: the matrix-core kernel takes inputs of fewer than 2^31 elements (its offsets are 32 bits wide: of 2^31 and more it read
+    zeros, or other rows), the plain kernel the rest."""
+    r = backward(dict(kind=B.CD_ARCH_TRANSFORMER_HEAD, dtype="bf16", batch=1 << 20, arch=dict(widths=[features, 8], classes=8)), call="forward")
+    assert r["rc"] == 0
+    assert sum("igemm_kernel" in k and "ELb1ELi0ELi1ELb0" in k for k in _kernels(r)) == matrix
+    assert sum("linear_fwd_k" in k for k in _kernels(r)) == 1 - matrix
