@@ -1212,6 +1212,7 @@ struct WgradJob {
   double* bias_part;  // column sums of dy, the bias gradient: [splits][N] (more than one split) or null
   float* bias_out;    // [N] (one split) or null
   int M, m_per_split;
+  int fold;           // (launches of several layers) steps that one chain of additions covers at the most
   int N, K;
   int H, W, Cin, Ho, Wo, kw, stride, pad;
   int ktiles, tiles_per_slice, tiles;   // tiles along K; of a slice of dw; of dw in all
@@ -1380,13 +1381,15 @@ __global__ void __launch_bounds__(256, NJ > 1 ? 2 : 1) wgrad_kernel(WgradBatch<N
     if (half) s += (double)(bhalf + t); else bhalf = t;
   };
 
-  // FOLD: every wgrad_fold steps the accumulators are added to a second set of fp32 sums, and what that addition rounds away stays behind
+  // FOLD: every a.fold steps the accumulators are added to a second set of fp32 sums, and what that addition rounds away stays behind
   // in the accumulator (compensated summation).  A launch of several layers cuts the rows into few splits or none, and one chain of
-  // fp32 additions over all of them was further from the float64 result than the splits it took the place of.  2-norm of the error
-  // over that of dw, a layer by itself in splits / one chain / folded: 512 x 512 over 8192 rows 6.7e-8 / 2.8e-7 / 5.7e-8, 640 x 320 over
-  // 6144 2.8e-7 / 8.6e-7 / 2.7e-7, 64 x 576 over 8192 2.3e-7 / 4.1e-7 / 2.0e-7.  One chain and folded: Wide-ResNet step 7.71 -> 7.77 ms,
-  // one-layer Transformer pass 1568 -> 1581 us, packed Transformer step 9.81 -> 9.77 ms.  (The bound of two waves per SIMD in the
-  // kernel's attributes keeps the accumulators in ordinary registers: moved in and out of the others for each fold, 1707 us.)
+  // fp32 additions over all of them was further from the float64 result than the splits it took the place of: a chain now covers the rows
+  // of one of those (wgrad_own_rows).  2-norm of the error over that of dw, a layer by itself in splits / one chain / folded:
+  // 512 x 512 over 8192 rows 6.7e-8 / 2.8e-7 / 5.7e-8, 640 x 320 over 6144 2.8e-7 / 8.6e-7 / 2.5e-7, 64 x 576 over 8192 2.3e-7 / 4.1e-7 /
+  // 2.0e-7.  One encoder layer's four layers alone 83 -> 90 us, steps and passes within 0.2 % of the time with one chain (with a fold every 256
+  // rows whatever the layer 95 us, and the one-layer Transformer pass 1581 us where it is 1566).
+  // (The bound of two waves per SIMD in the kernel's attributes keeps the accumulators in ordinary registers: moved in and out of the
+  // others for each fold, the one-layer Transformer pass took 1707 us.)
   constexpr bool FOLD = NJ > 1;
   f32x16_t sum[FOLD ? TN : 1][FOLD ? TK : 1];
   if constexpr (FOLD) {
@@ -1397,6 +1400,7 @@ __global__ void __launch_bounds__(256, NJ > 1 ? 2 : 1) wgrad_kernel(WgradBatch<N
 #pragma unroll
         for (int v = 0; v < 16; v++) sum[i][j][v] = 0.f;
   }
+  int until_fold = FOLD ? a.fold : 0;
   const int steps = (mend - mbeg + WG_MS - 1) / WG_MS;
   uint32_t cur = 0, nxt = STAGE_BYTES;
 #pragma unroll
@@ -1441,7 +1445,8 @@ __global__ void __launch_bounds__(256, NJ > 1 ? 2 : 1) wgrad_kernel(WgradBatch<N
     cur = nxt;
     nxt = nxt + STAGE_BYTES == NS * STAGE_BYTES ? 0u : nxt + STAGE_BYTES;
     if constexpr (FOLD) {
-      if (st % wgrad_fold(BN, BKK) == wgrad_fold(BN, BKK) - 1) {
+      if (--until_fold == 0) {
+        until_fold = a.fold;
 #pragma unroll
         for (int i = 0; i < TN; i++)
 #pragma unroll
@@ -1614,6 +1619,7 @@ static void wgrad_run(const WgradProblem* p, int n, int pitch, float* partials, 
     a.tiles_per_slice = (int)(h.tiles() / h.slices);
     a.tiles = (int)h.tiles();
     a.m_per_split = (int)plan[k].m_per_split;
+    a.fold = (int)(wgrad_own_rows(h, partials_bytes) / 32);
     a.first = blocks;
     a.out = p[k].dw;
     a.bias_part = nullptr;

@@ -73,9 +73,6 @@ inline bool conv_sums_fit(int64_t M, int64_t pitch, size_t bytes) {
 // ---- weight gradients of the matrix-core path (conv_mfma.hip) -----------------------------------------------------------------
 constexpr int kWgradJobs = 16;     // layers in a launch: their table travels in the kernel arguments
 constexpr int kWgradStages = 3;
-// Steps of 32 pixels that one accumulator runs over in a launch of several layers, at the most: as many rows as the shortest splits that
-// layers by themselves are cut into (256 rows of 128x128 tiles, 128 of smaller ones, which have fewer sums to fold)
-constexpr int wgrad_fold(int bn, int bk) { return bn == 128 && bk == 128 ? 8 : 4; }
 constexpr int kWgradBlocks = 512;  // workgroups a launch of several layers aims for: two a compute unit
 struct WgradShape {
   int64_t M = 0;        // pixels (rows)
@@ -135,6 +132,12 @@ inline void wgrad_plan(const WgradShape* s, int n, size_t partials_bytes, int tu
     }
     if (whole || (blocks <= target && bytes <= (int64_t)partials_bytes)) return;
   }
+}
+// Rows (whole steps) of a split of this layer by itself, whatever launch it is in.
+inline int64_t wgrad_own_rows(const WgradShape& h, size_t partials_bytes) {
+  WgradSplit r;
+  wgrad_plan(&h, 1, partials_bytes, 0, &r);
+  return r.m_per_split;
 }
 // Whether a layer by itself loses little: its splits' partial sums, written and read again, are a small part of what its operands move.
 inline bool wgrad_alone(const WgradShape& h, int64_t operand_bytes) {
