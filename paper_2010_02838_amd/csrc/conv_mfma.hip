@@ -1199,8 +1199,8 @@ void conv_grouped_dgrad_mfma(const bf16_t* dy, const bf16_t* w, bf16_t* wd, bf16
 // a late ResNet stage has 16 to 144 tiles, which fill the chip only if its pixels are cut into many splits, and each split is
 // an fp32 copy of dw to be written and added up again; side by side the layers fill it with few splits or none.  (The rule: wgrad_plan in
 // conv_rules.h.)  Splits are added by a second kernel in a fixed order.
-// One encoder layer (8192 tokens, 512 columns, 2048 inside): its four layers one after the other 146 us with registers in front of the
-// LDS and two stages, 114 with this loop, 69 in one launch, 78 with the bias gradients (41 launch by launch before); 32768 x 512 over 8192 rows
+// One encoder layer (8192 tokens, 512 columns, 2048 inside), sums of the splits included: its four layers one after the other 138 us with
+// registers in front of the LDS and two stages, 190 with the bias gradients; one launch 84 and 88, with the folds below 90 and 95; 32768 x 512 over 8192 rows
 // 363 -> 308, 256 x 2304 over 50176 99 -> 90.  More stages or 64-pixel steps cost workgroups per compute unit and were no faster.
 //
 // Main loop: as igemm_kernel's, steps of 32 pixels, NS stages in LDS filled by direct loads NS - 1 steps ahead, one barrier a
@@ -1523,8 +1523,11 @@ void sum_splits(const float* part, float* out, int64_t n, int splits, hipStream_
 
 // The splits of a batch: 256 outputs (four a thread) x 4 split lanes per block, in the order of wgrad_reduce_kernel; of more than 64
 // splits (few weights, that is few blocks, and 16 loads and more in a lane's chain) 64 outputs x 16 split lanes: 2304 weights in 512 splits
-// 13.0 -> 4.1 us.  Behind a job's outputs a block per 256 channels adds the bias sums.
+// 13.0 -> 4.1 us.  Behind a job's outputs a block per 16 channels adds the bias sums, every 16th split to a lane: a layer with a bias and
+// few weights has hundreds of splits, and a thread a channel walked them alone (32 channels of 30784 pixels, 240 splits: the launch
+// 55.8 -> 5.4 us; step of a two-layer network on 26 images of 37x32 264 -> 219).
 struct WgradSum { const float* part; float* out; const double* bias_part; float* bias_out; uint32_t n4; int splits, N; uint32_t first, bias_first; };
+constexpr int kBiasCols = 16;
 __host__ __device__ inline unsigned wgrad_sum_lanes(int splits) { return splits > 64 ? 16u : 4u; }
 template <int NJ> struct WgradSums { WgradSum j[NJ]; int n; };
 template <int NJ>
@@ -1535,11 +1538,19 @@ __global__ void __launch_bounds__(256) wgrad_sum_kernel(WgradSums<NJ> b) {
     while (k + 1 < b.n && b.j[k + 1].first <= blockIdx.x) k++;
   const WgradSum& q = b.j[k];
   if (blockIdx.x >= q.bias_first) {
-    const int c = (int)(blockIdx.x - q.bias_first) * 256 + (int)threadIdx.x;
-    if (c >= q.N) return;
+    double* bs = reinterpret_cast<double*>(sm);   // [16 lanes][16 channels]
+    const int c = (int)(blockIdx.x - q.bias_first) * kBiasCols + (int)threadIdx.x % kBiasCols, lane = (int)threadIdx.x / kBiasCols;
     double s = 0.0;
-    for (int j = 0; j < q.splits; j++) s += q.bias_part[(int64_t)j * q.N + c];
-    q.bias_out[c] = (float)s;
+    if (c < q.N) {
+#pragma unroll 8
+      for (int j = lane; j < q.splits; j += 256 / kBiasCols) s += q.bias_part[(int64_t)j * q.N + c];
+    }
+    bs[threadIdx.x] = s;
+    __syncthreads();
+    if (lane == 0 && c < q.N) {
+      for (int l = 1; l < 256 / kBiasCols; l++) s += bs[l * kBiasCols + (int)threadIdx.x];
+      q.bias_out[c] = (float)s;
+    }
     return;
   }
   const unsigned lanes = wgrad_sum_lanes(q.splits), outs = 256u / lanes;
@@ -1640,7 +1651,7 @@ static void wgrad_run(const WgradProblem* p, int n, int pitch, float* partials, 
         room += align_up((size_t)h.N * splits * sizeof(double), 256);
         a.bias_out = nullptr;
         q.bias_part = a.bias_part;
-        sum_blocks += (unsigned)cdiv(h.N, 256);
+        sum_blocks += (unsigned)cdiv(h.N, kBiasCols);
       } else {
         q.bias_first = 0xffffffffu;
       }

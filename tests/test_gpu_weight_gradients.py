@@ -127,3 +127,27 @@ def test_infinite_operands():
             want[:, col] = sum(dy[r] * v for r, v in rows)
         assert bool(torch.isinf(want[:, c]).any()) and bool(torch.isnan(want[:, c + 2]).any())
         assert torch.equal(torch.nan_to_num(got, nan=1.5), torch.nan_to_num(want, nan=1.5)), "op %d" % i
+
+
+@pytest.mark.parametrize("batch,h,w", [(1, 8, 16), (2, 8, 16), (16, 8, 16), (17, 8, 16), (26, 37, 32)])
+def test_bias_gradients(batch, h, w):
+    """1, 2, 16, 17 and 240 splits of 40 channels (three blocks of 16, the last one partial), a layer that goes by itself: sums of bf16 in
+    fp32 over eight pixels, in fp64 over the rest."""
+    from paper_2010_02838_amd import binding as B
+    m = B.Model(B.arch_preset(B.CD_ARCH_TINY_CNN, in_h=h, in_w=w, widths=[16, 40]), B.CD_BF16)
+    dev, g = "cuda:0", torch.Generator().manual_seed(3)
+    params = to_device(pack_flat(m, synth.he_init(m.param_table(), 1, 0.1)), torch.bfloat16)
+    x = torch.randn(batch, h, w, 3, generator=g).to(dev, torch.bfloat16)
+    ws = torch.empty(m.workspace_bytes(batch, True), dtype=torch.uint8, device=dev)
+    z, grads = torch.empty(batch, 10, device=dev), torch.empty(m.n_elements, device=dev)
+    B.codistill_forward(m, params, x, ws, z, True)
+    B.codistill_backward(m, params, x, ws, torch.randn(batch, 10, generator=g).to(dev), grads)
+    torch.cuda.synchronize()
+    ops, ts = m.graph(batch)
+    for o in ops:
+        if o["kind"] == "conv":
+            t, p = ts[o["y"]], m.params[o["param_b"]]
+            n = 2 * batch * h * w * t["c"]
+            dy = ws[t["grad_offset"]:t["grad_offset"] + n].view(torch.bfloat16).view(-1, t["c"]).double()
+            got = grads[p["offset"]:p["offset"] + p["size"]].double()
+            assert bool(((got - dy.sum(0)).abs() <= 8 * 2.0 ** -24 * dy.abs().sum(0)).all())
