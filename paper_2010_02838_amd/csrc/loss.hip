@@ -124,10 +124,12 @@ __device__ inline bool row_target(const LossArgs& a, int64_t row, int& t) {
 }
 
 // Number of valid rows, where no launch in front has counted them: for few short rows every wave goes through the targets itself, at
-// most 32 loads a lane that arrive behind the row's own.  Exact in fp32 (and in any order).  128 rows of 10 columns 14.9 -> 11.4 us a
-// loss, 256 x 1000 15.0 -> 11.8, 1024 x 1000 13.8 -> 11.1; beyond 2^20 logits, and where a row is a whole block's, the count is longer
-// than the launch: 2048 x 1000 14.6 -> 15.8, 1021 x 10007 with three peers 59.8 -> 61.2.
-static bool own_count(int64_t rows, int64_t cols) { return rows <= 2048 && cols <= 1024 && rows * cols <= 1 << 20; }
+// most 16 loads a lane that arrive behind the row's own.  Exact in fp32 (and in any order).  A launch in front against the count, KL:
+// calls issued one by one (bound by the launches) 128 rows of 10 columns 13.2 -> 10.9 us, 1024 x 1000 13.2 -> 10.9, two peers 1024 x 511
+// 13.7 -> 13.2; replayed from a graph, 128 rows 4 to 7 % shorter, 512 rows level, 1024 x 1000 9.4 -> 10.2, two peers 1 to 5 % shorter up to
+// 1024 rows.  Above, the count outgrows the launch: replayed, 2048 x 100 9.0 -> 12.3 and two peers 6 to 8 % longer; one by one, two peers
+// 1283 x 749 16.0 -> 16.9 (one peer 2048 x 511 13.1 -> 14.1).
+static bool own_count(int64_t rows, int64_t cols) { return rows <= 1024 && cols <= 1024; }
 template <int TPR>
 __device__ inline int valid_rows(const LossArgs& a, float* smem) {
   float n[1] = {0.f};
@@ -421,15 +423,12 @@ __global__ void __launch_bounds__(256) loss_row_generic_kernel(LossArgs a) {
 // ---- step 3: deterministic sum of the per-row terms ------------------------------------------
 __global__ void __launch_bounds__(1024) loss_finalize_kernel(LossArgs a, float* loss_out) {
   __shared__ double s_t[1024], s_d[1024];
-  int n = 0, bad = 0;   // (meta is nullptr: up to 2048 rows)
-  if (!a.meta) {
-    for (int64_t r0 = 0; r0 < a.rows; r0 += 1024) {
-      const int64_t r = r0 + threadIdx.x;
-      const int t = r < a.rows ? a.targets[r] : a.ignore_index;
-      const bool off = t != a.ignore_index && (t < 0 || t >= a.cols);
-      n += __syncthreads_count(t != a.ignore_index && !off);
-      bad |= __syncthreads_or(off);
-    }
+  int n = 0, bad = 0;
+  if (!a.meta) {   // (at most 1024 rows: one a thread)
+    const int t = threadIdx.x < a.rows ? a.targets[threadIdx.x] : a.ignore_index;
+    const bool off = t != a.ignore_index && (t < 0 || t >= a.cols);
+    n = __syncthreads_count(t != a.ignore_index && !off);
+    bad = __syncthreads_or(off);
   }
   // every thread adds its rows in a fixed order, four independent loads in flight at a time
   double st[4] = {0.0, 0.0, 0.0, 0.0}, sd[4] = {0.0, 0.0, 0.0, 0.0};

@@ -122,3 +122,13 @@ def test_dense_layer_on_very_many_inputs(backward, features, matrix):
     assert r["rc"] == 0
     assert sum("igemm_kernel" in k and "ELb1ELi0ELi1ELb0" in k for k in _kernels(r)) == matrix
     assert sum("linear_fwd_k" in k for k in _kernels(r)) == 1 - matrix
+
+
+@pytest.mark.parametrize("peers", [1, 2])
+@pytest.mark.parametrize("rows,cols,counted", [(1024, 1024, 0), (1025, 12, 1), (1283, 749, 1), (64, 1025, 1)])
+def test_launch_that_counts_the_valid_rows_of_a_loss(backward, peers, rows, cols, counted):
+    """Up to 1024 rows of 1024 columns the row kernel counts for itself; above that a launch in front is the shorter way."""
+    r = backward(dict(loss=[rows, cols, peers]))
+    assert r["rc"] == 0
+    assert sum("loss_prep_kernel" in k for k in _kernels(r)) == counted
+    assert sum("loss_row_generic_kernel" in k for k in _kernels(r)) == peers - 1
