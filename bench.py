@@ -34,12 +34,12 @@ PEAK_HBM_GBS = 8000.0
 # this script, FETCH_SIZE then WRITE_SIZE, each scaled by what the same counter read for the 1 GiB copy of
 # --copy-calibration).  Valid only for the kernels the counters were taken on: set to None when one changes.
 TRAFFIC_SOURCE = "profiles/resnet50_bs256_step_hbm_counters.md"
-ROOFLINE_TRAFFIC_BYTES = 260.2e6        # bn_apply_k<bf16,8,true,false>: FETCH_SIZE 76167.4 KiB x 2.000 + WRITE_SIZE 101792.6 KiB x 1.000
-ROOFLINE_CONV_TRAFFIC_BYTES = 221.7e6   # igemm_kernel<0,128,256,...>: FETCH_SIZE 41324.3 KiB x 2.000 + WRITE_SIZE 133859.5 KiB x 1.000
+ROOFLINE_TRAFFIC_BYTES = 260.2e6        # bn_apply_k<bf16,8,true,false>: FETCH_SIZE 76163.8 KiB x 2.000 + WRITE_SIZE 101792.6 KiB x 1.000
+ROOFLINE_CONV_TRAFFIC_BYTES = 221.7e6   # igemm_kernel<0,128,256,...>: FETCH_SIZE 41317.8 KiB x 2.000 + WRITE_SIZE 133859.5 KiB x 1.000
 # Matrix-pipe busy share of that convolution kernel from hardware counters (SQ_VALU_MFMA_BUSY_CYCLES over
 # GRBM_GUI_ACTIVE x 1024 SIMDs, mean over its dispatches); None when the kernel changes.
 MFMA_COUNTER_SOURCE = "profiles/resnet50_bs256_step_mfma_counters.md"
-ROOFLINE_CONV_MFMA_BUSY = 0.238
+ROOFLINE_CONV_MFMA_BUSY = 0.236
 
 
 def roofline_of(flops, nbytes, ms, launches, kernel, traffic, event_overhead_us=None):
