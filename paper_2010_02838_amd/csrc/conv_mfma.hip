@@ -148,6 +148,15 @@ __device__ inline void wait_step() {
 // apart and share their swz.
 template <int BKT> __device__ inline int lds_swz(int row) { return BKT == 32 ? (row >> 2) & 3 : (row >> 1) & 7; }
 
+// Waves per SIMD that a kernel's registers must leave room for: as many workgroups per compute unit as the LDS allows, up to three
+// (128x128 tiles in three 32-wide stages) or two.
+constexpr int igemm_waves(int BM, int BN, int WAVES_M, int WAVES_N, int BKT, int NS, int WK) {
+  const int tiles = (BM / WAVES_M / 32) * (BN / WAVES_N / 32), stages = NS * (BM + BN) * BKT * 2, waves = WAVES_M * WAVES_N * WK;
+  if (waves == 8) return 2;
+  if (stages > 80 * 1024) return 1;
+  return tiles >= 8 ? 2 : BM == 128 && BN == 128 && NS == 3 ? 3 : 1;
+}
+
 // MODE 0: fprop gather, hs = hd*stride - pad + r.
 // MODE 1: dgrad gather for stride 1, hs = hd + pad - r.
 // (The dgrad of a stride-2 convolution is run as four MODE 0 problems, one per parity of the output
@@ -169,29 +178,36 @@ template <int BKT> __device__ inline int lds_swz(int row) { return BKT == 32 ? (
 // EPI: 0 plain output, 1 per-column bias added, 2 bias and ReLU, 3 the evaluation-mode BatchNorm that follows (its pass over the
 // tensor, a read and a write of it, was a third of an evaluation: ResNet-50 at batch 50 1719 us with it, 1353 without).  GROUP: grouped tile order (wide outputs).
 // Both are compile-time: the plain kernels pay nothing for them.
+// WK: groups of waves that share a tile's places and take equal parts of every step's contraction (1 or 2).
 template <int MODE, int BM, int BN, int WAVES_M, int WAVES_N, bool F32OUT = false, int STATS = 0, int NWRAP = 1,
-          bool REMAP = false, int EPI = 0, bool GROUP = false, int BKT = 32, int NS = 3>
-__global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32) >= 8 ? 2 : BM == 128 && BN == 128 && NS == 3 ? 3 : 1)) igemm_kernel(IgemmArgs a) {
+          bool REMAP = false, int EPI = 0, bool GROUP = false, int BKT = 32, int NS = 3, int WK = 1>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, BN, WAVES_M, WAVES_N, BKT, NS, WK)) igemm_kernel(IgemmArgs a) {
   // (as many waves per SIMD, i.e. workgroups per compute unit, as the LDS allows: two for the tiles whose accumulators take 128
   // registers, three for 128x128 tiles in three 32-wide stages; the bound keeps the other registers within what that leaves)
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int SL = BKT / 8, RPP_L = 256 / SL;  // 16-byte slots per LDS row, rows per load pass of the block
+  constexpr int WAVES = WAVES_M * WAVES_N * WK, NT = 64 * WAVES;
+  constexpr int EM = WM / WK, TE = TM / WK;    // rows and 32-row tiles of a wave in the epilogue
+  static_assert(TM % WK == 0 && (BKT / 16) % WK == 0, "the groups share the sub-steps of a step and the row tiles of the epilogue");
+  constexpr int SL = BKT / 8, RPP_L = NT / SL;  // 16-byte slots per LDS row, rows per load pass of the block
   constexpr int AV = BM / RPP_L;                // activation vectors per thread per step
-  constexpr int BN_PAD = BN < RPP_L ? RPP_L : BN;   // filter rows in LDS (whole load passes)
+  constexpr int BN_PAD = (BN + RPP_L - 1) / RPP_L * RPP_L;   // filter rows in LDS (whole load passes)
   constexpr int BV = BN_PAD / RPP_L;            // filter vectors per thread per step
   constexpr int STAGE = (BM + BN_PAD) * BKT;    // elements per stage: activation rows, then filter rows
   static_assert(BKT == 32 || (BKT == 64 && NWRAP == 1), "64-wide steps need at least 64 channels per tap");
   constexpr int MAIN_BYTES = NS * STAGE * 2;
-  constexpr int EROWS = WM < 64 ? WM : 64;     // rows staged per epilogue pass
+  constexpr int EROWS = EM < 64 ? EM : 64;     // rows staged per epilogue pass
   constexpr int EPITCH = WN + 8;
-  constexpr int EPI_BYTES = 4 * EROWS * EPITCH * 2;
-  constexpr int SMEM = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
+  constexpr int EPI_BYTES = WAVES * EROWS * EPITCH * 2;
+  constexpr int RED_BYTES = STATS ? WAVES_M * WK * 2 * BN * 4 : 0;   // column sums behind the staging rows
+  constexpr int SMEM = MAIN_BYTES > EPI_BYTES + RED_BYTES ? MAIN_BYTES : EPI_BYTES + RED_BYTES;
   __shared__ __attribute__((aligned(16))) char smem[SMEM];
   // smem: [NS stages][BM + BN_PAD rows][BKT elements], later the epilogue's staging rows
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave % WAVES_M) * WM, wn0 = (wave / WAVES_M) * WN;
+  const int wmn = wave % (WAVES_M * WAVES_N), kg = wave / (WAVES_M * WAVES_N);   // place in the tile, group along the contraction
+  const int wm0 = (wmn % WAVES_M) * WM, wn0 = (wmn / WAVES_M) * WN;
+  const int em0 = wm0 + kg * EM;   // first row of this wave in the epilogue
   const unsigned tile = xcd_remap(blockIdx.x, gridDim.x);
   // row and element indices fit 32 bits: every operand is smaller than 2 GiB (conv_mfma_supported)
   unsigned tm = tile / (unsigned)a.ntiles, tn = tile % (unsigned)a.ntiles;
@@ -318,14 +334,15 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   // loop: sixteen registers through the loop would spill (128x256) or cost the third workgroup per compute unit (128x128).
   // (The input's vectors leave the two 128-accumulator tiles short of 6 (256x128) and 2 (128x256) registers: those are stored to
   // scratch memory in front of the loop and loaded behind it.)
-  constexpr int BS_LPR = WN / 8, BS_RPP = 64 / BS_LPR, BS_EROWS = WM < 64 ? WM : 64;
-  constexpr int BS_NV = STATS == 2 ? (WM / BS_EROWS) * (BS_EROWS / BS_RPP) : 1;
+  constexpr int BS_LPR = WN / 8, BS_RPP = 64 / BS_LPR, BS_EROWS = EM < 64 ? EM : 64;
+  constexpr int BS_NV = STATS == 2 ? (EM / BS_EROWS) * ((BS_EROWS + BS_RPP - 1) / BS_RPP) : 1;
   uint4 bs_x[BS_NV];
   uint32_t bs_bits[BS_NV];
   auto bs_index = [&](int v, bool& ok) {   // element index of vector v in an [M][N] tensor
-    const int pass = v / (BS_EROWS / BS_RPP), pp = v % (BS_EROWS / BS_RPP);
-    const int m = m0 + wm0 + pass * BS_EROWS + pp * BS_RPP + lane / BS_LPR, n = n0 + wn0 + (lane % BS_LPR) * 8;
-    ok = m < M && n < a.N;
+    constexpr int PP = (BS_EROWS + BS_RPP - 1) / BS_RPP;
+    const int pass = v / PP, row = v % PP * BS_RPP + lane / BS_LPR;
+    const int m = m0 + em0 + pass * BS_EROWS + row, n = n0 + wn0 + (lane % BS_LPR) * 8;
+    ok = m < M && n < a.N && row < BS_EROWS && lane < BS_RPP * BS_LPR;
     return (unsigned)m * (unsigned)a.N + (unsigned)n;
   };
   if (STATS == 2) {
@@ -393,13 +410,14 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   // (Not for the 128-accumulator tiles that also hold the backward sums' operands through the loop: no registers are left for
   // a second fragment buffer, they read a sub-step's fragments and use them.)
   constexpr bool AHEAD = !(STATS == 2 && TN * TM >= 8);
-  constexpr int KK = BKT / 16, TT = TN * TM, FB = AHEAD ? 2 : 1;
+  constexpr int KK = BKT / 16 / WK, TT = TN * TM, FB = AHEAD ? 2 : 1;   // (sub-steps of this wave's group)
   bf16x8_t wf[FB][TN], xf[FB][TM];  // [buffer][tile]
   // byte offset of this lane's fragment of sub-step kk inside a tile row block (swz depends on the lane's row only: tile
   // rows are multiples of 32 apart)
   uint32_t fcol[KK];
 #pragma unroll
-  for (int kk = 0; kk < KK; kk++) fcol[kk] = (uint32_t)(frow * BKT + (((kk * 2 + fcv) ^ lds_swz<BKT>(frow)) << 3)) * 2u;
+  for (int kk = 0; kk < KK; kk++)
+    fcol[kk] = (uint32_t)(frow * BKT + ((((kg * KK + kk) * 2 + fcv) ^ lds_swz<BKT>(frow)) << 3)) * 2u;
   const uint32_t xbase = (uint32_t)(wm0 * BKT) * 2u, wbase = (uint32_t)((BM + wn0) * BKT) * 2u;
   auto read_frags = [&](int buf, uint32_t stage_b, int kk) {
     const char* xp = smem + (stage_b + xbase + fcol[kk]);
@@ -432,7 +450,15 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
         acc[i / TM][i % TM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & (FB - 1)][i / TM], xf[kk & (FB - 1)][i % TM],
                                                                       acc[i / TM][i % TM], 0, 0, 0);
         // in the MFMA's shadow: a share of the next offsets, in the last sub-step of the loads
-        if (kk < KK - 1) {
+        if (KK == 1) {   // one sub-step a step: an offset in front of its load
+#pragma unroll
+          for (int v = 0; v < AV + BV; v++)
+            if (v * TT / (AV + BV) == i) {
+              prep_piece(kt + NS, v);
+              issue(cur, v);
+            }
+          if (i == TT - 1) prep_piece(kt + NS, NPIECE - 1);
+        } else if (kk < KK - 1) {
           constexpr int SLOTS = (KK - 1) * TT;
           const int slot = kk * TT + i;
 #pragma unroll
@@ -462,6 +488,41 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
 
   // accumulator layout: lane holds pixel column (lane % 32); register v holds channel
   // 8*(v/4) + 4*(lane/32) + v%4 of the 32x32 tile
+  if constexpr (WK == 2) {
+    // Each of the two waves of a place hands the other one half of its row tiles and adds what it gets (the first group's sum
+    // plus the second's, whichever wave adds): 16-byte vectors in lane order.
+    constexpr int HALF = TN * TE * 16 * 64;   // floats a wave hands over
+    static_assert(WAVES * HALF * 4 <= SMEM, "room for the sums that change hands");
+    float* mine = reinterpret_cast<float*>(smem) + wave * HALF + lane * 4;
+    const float* theirs = reinterpret_cast<const float*>(smem) + (kg ? wave - WAVES / 2 : wave + WAVES / 2) * HALF + lane * 4;
+    __syncthreads();   // the main loop's tiles are no longer read
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int j = 0; j < TE; j++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          float4 v;
+          v.x = kg ? acc[i][j][4 * g] : acc[i][TE + j][4 * g];
+          v.y = kg ? acc[i][j][4 * g + 1] : acc[i][TE + j][4 * g + 1];
+          v.z = kg ? acc[i][j][4 * g + 2] : acc[i][TE + j][4 * g + 2];
+          v.w = kg ? acc[i][j][4 * g + 3] : acc[i][TE + j][4 * g + 3];
+          *reinterpret_cast<float4*>(mine + ((i * TE + j) * 4 + g) * 256) = v;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int j = 0; j < TE; j++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          const float4 v = *reinterpret_cast<const float4*>(theirs + ((i * TE + j) * 4 + g) * 256);
+          acc[i][j][4 * g] = (kg ? acc[i][TE + j][4 * g] : acc[i][j][4 * g]) + v.x;
+          acc[i][j][4 * g + 1] = (kg ? acc[i][TE + j][4 * g + 1] : acc[i][j][4 * g + 1]) + v.y;
+          acc[i][j][4 * g + 2] = (kg ? acc[i][TE + j][4 * g + 2] : acc[i][j][4 * g + 2]) + v.z;
+          acc[i][j][4 * g + 3] = (kg ? acc[i][TE + j][4 * g + 3] : acc[i][j][4 * g + 3]) + v.w;
+        }
+  }
   if (BIAS) {
 #pragma unroll
     for (int i = 0; i < TN; i++)
@@ -470,7 +531,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
         const float bv[4] = {__uint_as_float(bias4[i][g].x << 16), __uint_as_float(bias4[i][g].x & 0xffff0000u),
                              __uint_as_float(bias4[i][g].y << 16), __uint_as_float(bias4[i][g].y & 0xffff0000u)};
 #pragma unroll
-        for (int j = 0; j < TM; j++)
+        for (int j = 0; j < TE; j++)
 #pragma unroll
           for (int q = 0; q < 4; q++) acc[i][j][4 * g + q] += bv[q];
       }
@@ -478,7 +539,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   if (F32OUT) {
     // one 32-row tile row of the wave at a time: [32][WN] floats (+4 of padding) per wave
     constexpr int FP = WN + 4;
-    static_assert(4 * 32 * FP * 4 <= SMEM, "fp32 staging fits the tile memory");
+    static_assert(!F32OUT || WAVES * 32 * FP * 4 <= SMEM, "fp32 staging fits the tile memory");
     float* fst = reinterpret_cast<float*>(smem) + wave * 32 * FP;
     float* dst = reinterpret_cast<float*>(a.dst);
     constexpr int FLPR = WN / 4;       // lanes per output row (16-byte vectors)
@@ -486,7 +547,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
     const int fr = lane / FLPR, fc = (lane % FLPR) * 4;
     __syncthreads();  // the main loop's tiles are no longer read
 #pragma unroll
-    for (int j = 0; j < TM; j++) {
+    for (int j = 0; j < TE; j++) {
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int i = 0; i < TN; i++)
@@ -498,7 +559,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
 #pragma unroll
       for (int p = 0; p < 32 / FRPP; p++) {
         const int row = p * FRPP + fr;
-        const int m = m0 + wm0 + j * 32 + row;
+        const int m = m0 + em0 + j * 32 + row;
         const int n = n0 + wn0 + fc;
         if (m < M && n < a.N) {
           const float4 v = *reinterpret_cast<const float4*>(fst + row * FP + fc);
@@ -518,7 +579,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
 #pragma unroll
     for (int i = 0; i < TN; i++)
 #pragma unroll
-      for (int j = 0; j < TM; j++)
+      for (int j = 0; j < TE; j++)
 #pragma unroll
         for (int v = 0; v < 16; v++) acc[i][j][v] = fmaxf(acc[i][j][v], 0.f);
   }
@@ -526,10 +587,11 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   bf16_t* stage = reinterpret_cast<bf16_t*>(smem) + wave * EROWS * EPITCH;
   constexpr int LPR = WN / 8;        // lanes per output row
   constexpr int RPP = 64 / LPR;      // rows per pass
+  constexpr int PASSES = (EROWS + RPP - 1) / RPP;
   constexpr int TPG = EROWS / 32;    // 32-row tiles per staging pass
+  const bool lane_ok = lane < RPP * LPR;   // (all of them where a row's vectors divide 64)
   const int er = lane / LPR, ec = (lane % LPR) * 8;
-  // STATS: per-wave column sums [WAVES_M][2][BN], behind the staging rows
-  static_assert(STATS == 0 || EPI_BYTES + WAVES_M * 2 * BN * 4 <= SMEM, "no room for the column sums behind the staging rows");
+  // STATS: per-wave column sums [WAVES_M * WK][2][BN], behind the staging rows
   static_assert(STATS != 2 || !REMAP, "the backward sums are taken where the rows are stored in order");
   // STATS 2: running sums of dz and of dz * x over this lane's 8 channels (the same in every pass); the mean and the
   // scale of xhat = (x - mean) * invstd are applied to the tile's sums at the end (the sums are linear in x)
@@ -552,15 +614,15 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
   float* red = reinterpret_cast<float*>(smem + EPI_BYTES);
   __syncthreads();  // the main loop's tiles are no longer read: the staging rows alias them
 #pragma unroll
-  for (int g0 = 0; g0 < TM; g0 += TPG) {
+  for (int g0 = 0; g0 < TE; g0 += TPG) {
     // The staging rows belong to this wave alone, and a wave's LDS accesses execute in program order:
     // no block barrier between its writes, its reads and the next pass's writes.
-    uint4 nres[EPI == 3 ? EROWS / RPP : 1];   // EPI 3: the residual rows of this pass, requested in front of the staging
+    uint4 nres[EPI == 3 ? PASSES : 1];   // EPI 3: the residual rows of this pass, requested in front of the staging
     if (EPI == 3 && a.norm_res) {
 #pragma unroll
-      for (int p = 0; p < EROWS / RPP; p++) {
-        const int m = m0 + wm0 + g0 * 32 + p * RPP + er, n = n0 + wn0 + ec;
-        if (m < M && n < a.N) nres[p] = *reinterpret_cast<const uint4*>(a.norm_res + ((unsigned)m * (unsigned)a.N + (unsigned)n));
+      for (int p = 0; p < PASSES; p++) {
+        const int m = m0 + em0 + g0 * 32 + p * RPP + er, n = n0 + wn0 + ec;
+        if (m < M && n < a.N && lane_ok && p * RPP + er < EROWS) nres[p] = *reinterpret_cast<const uint4*>(a.norm_res + ((unsigned)m * (unsigned)a.N + (unsigned)n));
       }
     }
     __builtin_amdgcn_wave_barrier();
@@ -586,7 +648,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
       const int tr_m = 8 * (grp >> 1) + (li >> 2), tr_c = 16 * (grp & 1) + 4 * (li & 3);
       const __bf16 one = (__bf16)1.0f;
       const bf16x8_t ones = {one, one, one, one, one, one, one, one};
-      const int wmi = wave % WAVES_M, c = lane & 31;
+      const int wmi = (wmn % WAVES_M) * WK + kg, c = lane & 31;
 #pragma unroll 1
       for (int i = 0; i < TN; i++) {   // one 32-column block at a time: two accumulator tiles live
         f32x16_t ds, dq;
@@ -612,11 +674,11 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
       }
     }
 #pragma unroll
-    for (int p = 0; p < EROWS / RPP; p++) {
+    for (int p = 0; p < PASSES; p++) {
       const int row = p * RPP + er;
-      int m = m0 + wm0 + g0 * 32 + row;
+      int m = m0 + em0 + g0 * 32 + row;
       const int n = n0 + wn0 + ec;
-      if (m < M && n < a.N) {
+      if (m < M && n < a.N && lane_ok && row < EROWS) {
         uint4 v = *reinterpret_cast<const uint4*>(stage + row * EPITCH + ec);
         if (REMAP) {  // strided placement of the rows (parity class of a stride-2 dgrad)
           const unsigned q = (unsigned)m / (unsigned)a.Wd;
@@ -667,8 +729,8 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
           v = make_uint4(o[0], o[1], o[2], o[3]);
         }
         if (STATS == 2) {   // the stored values feed the sums of the BatchNorm's backward pass
-          const uint4 xr = bs_x[(g0 / TPG) * (EROWS / RPP) + p];
-          const uint32_t bits = bs_bits[(g0 / TPG) * (EROWS / RPP) + p];
+          const uint4 xr = bs_x[(g0 / TPG) * PASSES + p];
+          const uint32_t bits = bs_bits[(g0 / TPG) * PASSES + p];
           const uint32_t gv[4] = {v.x, v.y, v.z, v.w}, xv[4] = {xr.x, xr.y, xr.z, xr.w};
 #pragma unroll
           for (int q = 0; q < 4; q++) {
@@ -688,14 +750,25 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
     // lanes that share their 8 channels (one per row of a pass) add up, the first of them hands the wave's sums over
 #pragma unroll
     for (int k = 0; k < 8; k++) {
+      if constexpr (64 % LPR == 0) {
 #pragma unroll
-      for (int off = LPR; off < 64; off <<= 1) {
-        bs0[k] += __shfl_xor(bs0[k], off, 64);
-        bs1[k] += __shfl_xor(bs1[k], off, 64);
+        for (int off = LPR; off < 64; off <<= 1) {
+          bs0[k] += __shfl_xor(bs0[k], off, 64);
+          bs1[k] += __shfl_xor(bs1[k], off, 64);
+        }
+      } else {   // (the first LPR lanes hold the sums)
+        float t0 = bs0[k], t1 = bs1[k];
+#pragma unroll
+        for (int r = 1; r < RPP; r++) {
+          t0 += __shfl(bs0[k], (lane + r * LPR) & 63, 64);
+          t1 += __shfl(bs1[k], (lane + r * LPR) & 63, 64);
+        }
+        bs0[k] = t0;
+        bs1[k] = t1;
       }
     }
     if (lane < LPR) {
-      const int wmi = wave % WAVES_M;
+      const int wmi = (wmn % WAVES_M) * WK + kg;
 #pragma unroll
       for (int k = 0; k < 8; k++) {
         red[(wmi * 2 + 0) * BN + wn0 + ec + k] = bs0[k];
@@ -709,7 +782,7 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
     if (tid < BN && n0 + tid < a.N) {
       float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-      for (int w = 0; w < WAVES_M; w++) { s0 += red[(w * 2 + 0) * BN + tid]; s1 += red[(w * 2 + 1) * BN + tid]; }
+      for (int w = 0; w < WAVES_M * WK; w++) { s0 += red[(w * 2 + 0) * BN + tid]; s1 += red[(w * 2 + 1) * BN + tid]; }
       if (STATS == 2) s1 = (s1 - a.bn_stats[n0 + tid] * s0) * a.bn_stats[a.N + n0 + tid];   // sum dz x -> sum dz xhat
       const int64_t mt = tm;
       a.stat_partials[mt * stat_pitch(a.N) + n0 + tid] = s0;
@@ -724,7 +797,11 @@ __global__ void __launch_bounds__(256, ((BM / WAVES_M / 32) * (BN / WAVES_N / 32
 // from L2 into LDS move 31 B per cycle and compute unit in 64-byte row segments and 52 in 128-byte ones (a line at a time is
 // looked up), so 64-wide steps feed the matrix cores where 32-wide ones cannot: 530 against 315 cycles per 16 KB.  A
 // workgroup alone on its compute unit takes 1200 cycles a step, two together 860 each.
-//  - one workgroup per compute unit or less (at most 256): four stages of 64-wide steps (128 KB), loads three steps ahead;
+//  - one workgroup per compute unit or less (at most 256): four stages of 64-wide steps (128 KB), loads three steps ahead, and eight
+//    waves, four for the first and four for the second half of every step's contraction (WK): a SIMD's two waves read fragments and
+//    multiply in turns, the halves are added in front of the epilogue.  With four waves 6144 x 640 x 5760 49 to 58 us (two cards), now 41 to
+//    51, 9800 x 256 x 2304 21.6 -> 18.1, 8192 x 320 x 2880 26.6 -> 22.1, 4096 x 640 x 5760 44.5 -> 35.9; 3840 x 1024 x 4096 and 8192 x 512 x
+//    2048, whose rows come from memory once, 42 -> 40.5 and 25.2 -> 24.6 (loads alone: 23.4);
 //  - otherwise two stages (64 KB, two workgroups per unit);
 //  - many tiles of a short contraction (more than 1024, K <= 512) live on their prologues and epilogues overlapping: three
 //    workgroups per unit with 32-wide steps (200704 x 128 x 512: 45 us, 51 with two).
@@ -748,12 +825,12 @@ int conv_fprop_tile_class(const ConvGeom& g, bool bias, bool sums) {
   return t == TILE_SQUARE || (t == TILE_TALL && bias) ? 0 : (t == TILE_WIDE ? 1 : 2);   // (no 256x128 kernel with a bias)
 }
 
-template <int MODE, int BM, int BN, int WM, int WN, int STATS, int NWRAP, bool REMAP, int EPI, int BKT, int NS>
+template <int MODE, int BM, int BN, int WM, int WN, int STATS, int NWRAP, bool REMAP, int EPI, int BKT, int NS, int WK = 1>
 static int launch_tile(IgemmArgs& a, hipStream_t s) {
   a.ntiles = (int)cdiv(a.N, BN);
   const int mt = (int)cdiv(a.M, BM);
-  hipLaunchKernelGGL((igemm_kernel<MODE, BM, BN, WM, WN, false, STATS, NWRAP, REMAP, EPI, false, BKT, NS>),
-                     dim3((unsigned)((int64_t)mt * a.ntiles)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((igemm_kernel<MODE, BM, BN, WM, WN, false, STATS, NWRAP, REMAP, EPI, false, BKT, NS, WK>),
+                     dim3((unsigned)((int64_t)mt * a.ntiles)), dim3(64 * WM * WN * WK), 0, s, a);
   return mt;
 }
 
@@ -798,7 +875,7 @@ static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
       if (tile == TILE_SMALL) return launch_tile<MODE, 64, 64, 2, 2, STATS, 1, REMAP, EPI, 64, 4>(a, s);
       if (tile == TILE_NARROW) return launch_tile<MODE, 128, 64, 2, 2, STATS, 1, REMAP, EPI, 64, 3>(a, s);
       const int64_t wgs = cdiv(a.M, 128) * cdiv(a.N, 128);
-      if (wgs <= 256) return launch_tile<MODE, 128, 128, 2, 2, STATS, 1, REMAP, EPI, 64, 4>(a, s);
+      if (wgs <= 256) return launch_tile<MODE, 128, 128, 2, 2, STATS, 1, REMAP, EPI, 64, 4, 2>(a, s);
       if (wgs <= 1024 || a.K > 512) return launch_tile<MODE, 128, 128, 2, 2, STATS, 1, REMAP, EPI, 64, 2>(a, s);
     }
   }
