@@ -816,6 +816,8 @@ static int igemm_tile(int64_t M, int N, int K, bool small_tiles, bool sums) {
   if (g_tune_tile == 4) return N % 256 == 0 ? TILE_WIDE : TILE_SQUARE;
   if (g_tune_tile == 5) return TILE_NARROW;
   if (g_tune_tile == 6) return TILE_SMALL;
+  if (g_tune_tile == 7 && small_tiles) return TILE_160;
+  if (conv_cols160_rule(M, N, K, small_tiles)) return TILE_160;
   return conv_tile_rule(M, N, K, small_tiles, sums);
 }
 int conv_fprop_tile_class(const ConvGeom& g, bool bias, bool sums) {
@@ -872,6 +874,7 @@ static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
       if (tile == TILE_WIDE) return launch_tile<MODE, 128, 256, 2, 2, STATS, 1, false, EPI, 32, 3>(a, s);
     }
     if (w64) {
+      if (tile == TILE_160) return launch_tile<MODE, 128, 160, 4, 1, STATS, 1, REMAP, EPI, 64, 2>(a, s);
       if (tile == TILE_SMALL) return launch_tile<MODE, 64, 64, 2, 2, STATS, 1, REMAP, EPI, 64, 4>(a, s);
       if (tile == TILE_NARROW) return launch_tile<MODE, 128, 64, 2, 2, STATS, 1, REMAP, EPI, 64, 3>(a, s);
       const int64_t wgs = cdiv(a.M, 128) * cdiv(a.N, 128);

@@ -23,7 +23,7 @@ namespace cd {
 //    a tile shape is the number of workgroups on the busiest unit times what one costs there (128x64 0.7 of a 128x128
 //    one, 64x64 half), but no less than what one takes alone (1.4, 1.08 and 0.75): 2450 x 512 x 4608 (80 tiles of 128x128)
 //    49 -> 26 on 312 of 64x64, 24576 x 320 x 2880 74 -> 66 on 128x64 (five columns of 64 instead of three of 128).
-enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2, TILE_NARROW = 3, TILE_SMALL = 4 };   // 128x128 256x128 128x256 128x64 64x64
+enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2, TILE_NARROW = 3, TILE_SMALL = 4, TILE_160 = 5 };   // 128x128 256x128 128x256 128x64 64x64 128x160
 // M rows, N > 64 columns, contraction K; small_tiles: the 64-wide steps that the last two need fit; sums: takes column sums
 inline int conv_tile_rule(int64_t M, int N, int K, bool small_tiles, bool sums) {
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
@@ -48,6 +48,23 @@ inline int conv_tile_rule(int64_t M, int N, int K, bool small_tiles, bool sums) 
     return t128 > 512 && e256 >= e128 ? TILE_TALL : TILE_SQUARE;
   }
   return small < narrow && small < square ? TILE_SMALL : narrow < square ? TILE_NARROW : TILE_SQUARE;
+}
+
+// Whether a width that 160 divides takes 128x160 tiles instead (asked before conv_tile_rule).  160 columns are two of 128, 37 % of them
+// padding, and 320 two and a half; a 128x160 tile also moves a tenth fewer bytes per product than a 128x128 one and two fifths fewer than a
+// 128x64 one.  In units of a 128x128 tile a pair of them on a compute unit costs 2.6 and one 1.9; of the narrow ones a
+// last round on a fifth of the units does not count.  us, without and with: 98304 x 160 x 1440 74 -> 62, 131072 x 160 x 1440 94 -> 69, 32768 x 160 x 1440 26.7 -> 23, 24576 x 320 x 2880
+// 55 -> 48, 32768 x 320 x 2880 64 -> 51, 65536 x 480 x 480 64 -> 56; on the other side of the line 16384 x 160 x 1440 16.1 and 20.8, 12288 x
+// 320 x 2880 27.9 and 32, 20480 x 320 x 2880 (narrow tiles, 3.1 a unit) 38 and 46, 6144 x 640 x 5760 43 and 61.  (256x160 tiles of eight
+// waves 47 for 24576 x 320 x 2880, 61 for 98304 x 160 x 1440, and behind on fewer rows; a partial sum keeps its 128 rows so.)
+inline bool conv_cols160_rule(int64_t M, int N, int K, bool wide_steps) {   // wide_steps: the 64-wide steps that the tile needs fit
+  auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  if (N % 160 || !wide_steps) return false;
+  const int64_t per = cdiv(cdiv(M, 128) * (N / 160), 256);   // on the busiest compute unit
+  const double each = 2.6 * (double)(per / 2) + 1.9 * (double)(per % 2);
+  const double square = std::max(1.4, (double)cdiv(cdiv(M, 128) * cdiv(N, 128), 256));
+  const double narrow = std::max(1.08, (K <= 1024 ? 0.68 : 0.72) * (double)cdiv(cdiv(M, 128) * cdiv(N, 64) - 51, 256));
+  return each < 0.98 * std::min(square, narrow);
 }
 
 // Rows of a tile where there are at most 64 columns (one column tile): 256, but 128 or 64 (64 only from 33 columns on) while those leave

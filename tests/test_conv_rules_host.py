@@ -119,6 +119,19 @@ def test_tile_of_a_convolution(tile, shape, want):
     assert tile(*shape) == want
 
 
+@pytest.mark.parametrize("shape,want", [
+    # (rows, columns, contraction, 64 channels or more per tap): either side of each line, and widths that 160 does not divide
+    ((98304, 160, 1440, 1), 1), ((98304, 160, 1440, 0), 0), ((32768, 160, 1440, 1), 1), ((16384, 160, 1440, 1), 0), ((24576, 320, 2880, 1), 1),
+    ((12288, 320, 2880, 1), 0), ((20480, 320, 2880, 1), 0), ((6144, 640, 5760, 1), 0), ((65536, 480, 480, 1), 1), ((8192, 480, 480, 1), 0),
+    ((98304, 128, 1440, 1), 0), ((98304, 168, 1440, 1), 0),
+    ((26010, 160, 1440, 1), 1), ((26010, 320, 1440, 1), 1), ((26010, 320, 64, 1), 1),   # the launches of test_gpu_conv_tiles.py, "columns_160" and "columns_320"
+])
+def test_columns_in_tiles_of_160(tmp_path_factory, shape, want):
+    run = compiled(tmp_path_factory.mktemp("cols160"),
+                   "int main(int, char** v) { printf(\"%d\", (int)conv_cols160_rule(atoll(v[1]), atoi(v[2]), atoi(v[3]), atoi(v[4]) != 0)); }")
+    assert int(run(*shape)) == want
+
+
 @pytest.fixture(scope="module")
 def rows_rule(tmp_path_factory):
     """rows of a tile, and whether the sums it leaves are at most as many as the check for their room counts and 64 KB"""

@@ -38,6 +38,10 @@ SHAPES = {
     "rows_16_64": (dict(kind=1, widths=[16, 64], blocks=[1, 2], stem_width=16), lambda: nets.resnet20(widths=(16, 64), blocks=(1, 2)), 13, 62),
     # 8410 and 2250 rows of 40 columns, 40 channels: 32-wide steps
     "columns_40": (dict(kind=1, widths=[40, 40], blocks=[1, 1], stem_width=40), lambda: nets.resnet20(widths=(40, 40), blocks=(1, 1)), 10, 29),
+    # 128x160 tiles, the last row tile ragged: 104040 rows of 160 columns, the parity classes of a stride-2 data gradient onto 160 (26010
+    # rows), and two columns of tiles (320) over 26010 rows
+    "columns_160": (dict(kind=1, widths=[160, 64], blocks=[1, 1], stem_width=160), lambda: nets.resnet20(widths=(160, 64), blocks=(1, 1)), 90, 34),
+    "columns_320": (dict(kind=1, widths=[320], blocks=[1], stem_width=320), lambda: nets.resnet20(widths=(320,), blocks=(1,)), 90, 17),
     # 520 tiles with column sums: 128x128 still (without the sums 256x128: the test below)
     "rows_per_sum": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), lambda: nets.resnet20(widths=(128,), blocks=(1,)), 260, 16),
 }
@@ -138,6 +142,7 @@ EVAL_SHAPES = {   # architecture, batch, resolution: the tiles, column counts an
     "small_tiles": (dict(kind=2, widths=[72], blocks=[2], stem_width=64), "bf16", 3, 40),            # 288 columns, 300 rows
     "narrow_columns": (dict(kind=1, widths=[16, 40], blocks=[1, 1], stem_width=16), "bf16", 143, 31),  # 32- and 64-column tiles
     "wide_and_tall": (dict(kind=2, widths=[128], blocks=[1], stem_width=64), "bf16", 130, 65),         # 128x256; odd image: no fused pool
+    "columns_160": (dict(kind=1, widths=[160], blocks=[1], stem_width=160), "bf16", 90, 17),           # 128x160
     "tall": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), "bf16", 231, 17),                 # 256x128
     "grouped": (dict(kind=5, widths=[128, 256], out_widths=[128, 256], blocks=[2, 1], stem_width=64, groups=32), "bf16", 5, 48),
     "odd_channels": (dict(kind=1, widths=[18, 22], blocks=[1, 1], stem_width=18), "bf16", 7, 13),
