@@ -91,3 +91,32 @@ def test_adam_constant_gradient_closed_form():
     for t in range(1, 5):
         B.codistill_adam_step(w, m, v, g, None, 0.25, t)
     np.testing.assert_allclose(w.cpu().numpy(), -4 * 0.25 * np.sign(g.cpu().numpy()), rtol=2e-6)
+
+
+@pytest.mark.parametrize("adam,lowp,line", [(False, True, (512 << 20) // 22), (False, False, (512 << 20) // 20),
+                                            (True, True, (512 << 20) // 30), (True, False, (512 << 20) // 28)])
+def test_update_beyond_the_cache_equals_its_parts(adam, lowp, line):
+    """A pass of more than 512 MB bypasses the caches; the same elements in two shorter passes do not: every tensor agrees bit for bit
+    (one element per thread, no sum).  Just above the line, with a ragged tail, and the part below it of the line's own length."""
+    from paper_2010_02838_amd import binding as B
+    n, cut = line + 11, line // 8 * 8
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    w, v, g = (torch.randn(n, generator=gen, device="cuda:0") for _ in range(3))
+    m = torch.randn(n, generator=gen, device="cuda:0") * 0.1
+    v = v.abs() if adam else v
+    out = []
+    for parts in ([(0, n)], [(0, cut), (cut, n)]):
+        t = [x.clone() for x in (w, m, v, g)]
+        lp = torch.zeros(n, dtype=torch.bfloat16, device="cuda:0") if lowp else None
+        for a, b in parts:
+            p = [x[a:b] for x in t]
+            l = None if lp is None else lp[a:b]
+            if adam:
+                B.codistill_adam_step(p[0], p[1], p[2], p[3], l, 1e-3, 2, 0.9, 0.98, 1e-8, 1e-4)
+            else:
+                B.codistill_sgd_step(p[0], p[2], p[3], l, 0.1, 0.9, 1e-4)
+        out.append(t + ([lp] if lowp else []))
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    assert not torch.equal(out[0][0], w)
