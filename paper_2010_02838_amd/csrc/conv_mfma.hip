@@ -1581,27 +1581,7 @@ __global__ void __launch_bounds__(256, NJ > 1 ? 2 : 1) wgrad_kernel(WgradBatch<N
   }
 }
 
-// 64 outputs x 4 split lanes per block; every lane adds every 4th split, fixed-order combine in LDS
-__global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* __restrict__ part, float* __restrict__ out,
-                                                           int64_t n, int splits) {
-  __shared__ float sm[4][64];
-  const int ol = threadIdx.x & 63, lane = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 64 + ol;
-  float s = 0.f;
-  if (i < n) {
-#pragma unroll 8
-    for (int j = lane; j < splits; j += 4) s += part[(int64_t)j * n + i];
-  }
-  sm[lane][ol] = s;
-  __syncthreads();
-  if (lane == 0 && i < n) out[i] = (sm[0][ol] + sm[1][ol]) + (sm[2][ol] + sm[3][ol]);
-}
-
-void sum_splits(const float* part, float* out, int64_t n, int splits, hipStream_t s) {
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)cdiv(n, 64)), dim3(256), 0, s, part, out, n, splits);
-}
-
-// The splits of a batch: 256 outputs (four a thread) x 4 split lanes per block, in the order of wgrad_reduce_kernel; of more than 64
+// The splits of a batch: 256 outputs (four a thread) x 4 split lanes per block, every lane adds every 4th split; of more than 64
 // splits (few weights, that is few blocks, and 16 loads and more in a lane's chain) 64 outputs x 16 split lanes: 2304 weights in 512 splits
 // 13.0 -> 4.1 us.  Behind a job's outputs a block per 16 channels adds the bias sums, every 16th split to a lane: a layer with a bias and
 // few weights has hundreds of splits, and a thread a channel walked them alone (32 channels of 30784 pixels, 240 splits: the launch

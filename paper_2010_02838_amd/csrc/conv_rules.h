@@ -228,6 +228,12 @@ inline GenericWgradPlan generic_wgrad_plan(int64_t M, int N, int K, bool v4, siz
   p.splits = up(M, p.m_per_split);
   return p;
 }
+// bytes of the partial sums of dw and of the bias gradient, on 256-byte boundaries (none without a split)
+struct GenericWgradRoom { size_t dw, bias; };
+inline GenericWgradRoom generic_wgrad_room(const GenericWgradPlan& p, int64_t weights, int N, bool bias) {
+  if (p.splits < 2) return {0, 0};
+  return {(size_t)((weights * p.splits * 4 + 255) / 256 * 256), bias ? (size_t)((N * p.splits * 8 + 255) / 256 * 256) : 0};
+}
 // first pixel behind the split that starts at mbeg < M (the splits overshoot M by up to 64 pixels each: mbeg + m_per_split need
 // not fit 32 bits)
 constexpr int generic_split_end(int M, int mbeg, int m_per_split) {

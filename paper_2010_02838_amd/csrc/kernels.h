@@ -49,11 +49,10 @@ bool conv_generic_supported(const ConvGeom& g);
 void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
                         hipStream_t s, const EvalNorm* norm = nullptr);
 void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, const ConvGeom& g, bool accumulate, hipStream_t s);
-// partials: scratch for the split sums (as many fp32 copies of dw as splits; without room for two the launch is not split)
-void conv_wgrad_generic(int dtype, const void* x, const void* dy, float* dw, const ConvGeom& g, float* partials,
-                        size_t partials_bytes, hipStream_t s);
-// out[i] = sum over j of part[j * n + i], in a fixed order
-void sum_splits(const float* part, float* out, int64_t n, int splits, hipStream_t s);
+// The weight gradients of several layers, and the bias gradients db (nullable, [Cout]) with them, in a launch per 16 layers and one that
+// adds up their splits.  partials: scratch for the split sums (as many fp32 copies of dw as splits; without room for two a layer is not split)
+struct GenericWgradProblem { const void* x; const void* dy; float* dw; float* db; ConvGeom g; };
+void conv_wgrad_generic_batch(int dtype, const GenericWgradProblem* p, int n, float* partials, size_t partials_bytes, hipStream_t s);
 void relu_bwd_inplace(int dtype, void* dy, const void* y, int64_t n, hipStream_t s);
 void colsum(int dtype, const void* a, int64_t M, int C, float* out, float* partials, hipStream_t s);
 

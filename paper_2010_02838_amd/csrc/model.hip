@@ -1132,6 +1132,9 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     q.flops = q.bytes = 0.0;
     return s;
   };
+  // those of the fp32 matrix instruction's convolutions, until the end of the pass
+  std::vector<GenericWgradProblem> generic_wgrads;
+  double generic_flops = 0, generic_bytes = 0;
   std::vector<char> written(m->tensors.size(), 0);
   // gradients of residual inputs that are handed on as "dy and a bit mask" instead of being written
   // (see residual_grad_route)
@@ -1373,15 +1376,19 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
             else if (g.Cin == 3) unpad_c8_to_c3(w.dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, ws);
           }
         } else {
-          if (o.pb >= 0) {
-            ProfScope pr(CD_K_GLUE, c.s, 0, (double)g.M() * g.Cout * m->esize());
-            colsum(dt, dy, g.M(), g.Cout, G(o.pb), c.partials(), c.s);
-          }
-          ProfScope pr(CD_K_CONV_WGRAD, c.s, 2.0 * g.M() * g.Cout * g.K(), conv_bytes(m, g) + 2.0 * g.Cout * g.K());
-          if (use_generic(g) && generic_wgrad_pays(g.M(), (int64_t)g.Cout * g.K()))
-            conv_wgrad_generic(dt, in, dy, G(o.pw), g, c.partials(), c.plan.partials_bytes, c.s);
-          else
+          const double flops = 2.0 * g.M() * g.Cout * g.K(), bytes = conv_bytes(m, g) + 2.0 * g.Cout * g.K();
+          if (use_generic(g) && generic_wgrad_pays(g.M(), (int64_t)g.Cout * g.K())) {   // (at the end of the pass, all of them)
+            generic_wgrads.push_back({in, dy, G(o.pw), o.pb >= 0 ? G(o.pb) : nullptr, g});
+            generic_flops += flops;
+            generic_bytes += bytes;
+          } else {
+            if (o.pb >= 0) {
+              ProfScope pr(CD_K_GLUE, c.s, 0, (double)g.M() * g.Cout * m->esize());
+              colsum(dt, dy, g.M(), g.Cout, G(o.pb), c.partials(), c.s);
+            }
+            ProfScope pr(CD_K_CONV_WGRAD, c.s, flops, bytes);
             conv_wgrad_simple(dt, in, dy, G(o.pw), g, c.s);
+          }
         }
         if (o.x != 0) {
           ProfScope pr(CD_K_CONV_DGRAD, c.s, 2.0 * g.M() * g.Cout * g.K(), conv_bytes(m, g));
@@ -1426,6 +1433,10 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     if (o.x != 0) written[o.x] = 1;
   }
   for (PendingWgrads& q : pending) run_wgrads(q);
+  if (!generic_wgrads.empty()) {
+    ProfScope pr(CD_K_CONV_WGRAD, c.s, generic_flops, generic_bytes);
+    conv_wgrad_generic_batch(dt, generic_wgrads.data(), (int)generic_wgrads.size(), c.partials(), c.plan.partials_bytes, c.s);
+  }
   if (!ln_sums.empty()) {
     ProfScope pr(CD_K_NORM, c.s, 0, 0);
     ln_finalize(ln_sums.data(), (int)ln_sums.size(), c.s);

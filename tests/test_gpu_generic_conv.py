@@ -1,6 +1,7 @@
 """Convolutions on the fp32 matrix instruction (any channel count, fp32 and bf16 storage), layer by layer against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import nets
 from paper_2010_02838_amd import synth
@@ -146,3 +147,38 @@ def test_infinite_filter_elements_in_a_strided_data_gradient(monkeypatch, dtype,
         return [c.read(strided[0]["x"], "grad_offset")]
     for a, b in _both_forms(monkeypatch, run):
         _same(a, b, tol, "input gradient")
+
+
+def test_more_layers_than_a_weight_gradient_launch_takes():
+    """17 layers (the six of at most 1024 weights go to the plain kernel): weight gradients in launches of 16 and 1, four channels per load and
+    one, 507, 147 and 48 pixels (several splits and one, the last step ragged)."""
+    c = Case(dict(kind=1, widths=[20, 36, 9], blocks=[4, 4, 2], stem_width=20), nets.resnet20(widths=(20, 36, 9), blocks=(4, 4, 2)), "f32", 3, 13, 10)
+    check_layers(c, c.gpu())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("widths", [(16, 40), (5, 35)])
+@pytest.mark.parametrize("batch,h,w", [(1, 8, 16), (2, 13, 16), (26, 37, 32)])
+def test_bias_gradients_with_the_weight_gradients(dtype, widths, batch, h, w):
+    """One split, four and some hundred, channel counts that end inside a tile and inside a block of the splits' sum, against the float64 sums of
+    the dy that the pass left.  A lane adds at most 8 values in fp32 and the rest in fp64: 8 half places of the sum of magnitudes, and one to round."""
+    from paper_2010_02838_amd import binding as B
+    if dtype == "bf16" and widths == (16, 40):
+        pytest.skip("on the bf16 matrix cores")
+    m = B.Model(B.arch_preset(B.CD_ARCH_TINY_CNN, in_h=h, in_w=w, widths=list(widths)), B.CD_F32 if dtype == "f32" else B.CD_BF16)
+    dev, gen, dt = "cuda:0", torch.Generator().manual_seed(3), m.torch_dtype
+    params = to_device(pack_flat(m, synth.he_init(m.param_table(), 1, 0.1)), dt)
+    x = torch.randn(batch, h, w, 3, generator=gen).to(dev, dt)
+    ws = torch.empty(m.workspace_bytes(batch, True), dtype=torch.uint8, device=dev)
+    z, grads = torch.empty(batch, 10, device=dev), torch.full((m.n_elements,), 7.0, device=dev)
+    B.codistill_forward(m, params, x, ws, z, True)
+    B.codistill_backward(m, params, x, ws, torch.randn(batch, 10, generator=gen).to(dev), grads)
+    torch.cuda.synchronize()
+    ops, ts = m.graph(batch)
+    for o in ops:
+        if o["kind"] == "conv":
+            t, p = ts[o["y"]], m.params[o["param_b"]]
+            n = dt.itemsize * batch * h * w * t["c"]
+            dy = ws[t["grad_offset"]:t["grad_offset"] + n].view(dt).view(-1, t["c"]).double()
+            got = grads[p["offset"]:p["offset"] + p["size"]].double()
+            assert bool(((got - dy.sum(0)).abs() <= 9 * 2.0 ** -24 * dy.abs().sum(0)).all())
