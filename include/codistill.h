@@ -300,6 +300,15 @@ int codistill_backward(const cd_model* m, const void* params, const void* x, int
                        void* workspace, size_t workspace_bytes, const float* dlogits,
                        float* grads_out, void* stream);
 
+/* The same call; `streams` says where the weight gradients run.  CD_STREAMS_TWO: on the second stream, as codistill_backward runs
+ * them.  CD_STREAMS_AUTO: there too, but at the end of the pass on the caller's stream where the network is so small that forking
+ * costs more than it hides (their sums may then be cut into other splits; the last places of a gradient differ).  Any other
+ * value -> CD_ERR_INVALID_ARG. */
+enum { CD_STREAMS_TWO = 0, CD_STREAMS_AUTO = 1 };
+int codistill_backward_streams(const cd_model* m, const void* params, const void* x, int64_t batch,
+                               void* workspace, size_t workspace_bytes, const float* dlogits,
+                               float* grads_out, int32_t streams, void* stream);
+
 /*
  * Momentum-SGD update, in place (Algorithm 1: theta <- theta - eta * gradient; momentum form of
  * the large-minibatch recipe the paper follows, Section 4.1):

@@ -18,6 +18,7 @@ CD_F32, CD_BF16 = 0, 1
 CD_DIST_MSE_LOGITS, CD_DIST_KL, CD_DIST_MSE_CENTERED = 0, 1, 2
 CD_MEAN_ALL, CD_MEAN_ROWS = 0, 1
 CD_BN_BATCH_STATS, CD_BN_RUNNING = 0, 1
+CD_STREAMS_TWO, CD_STREAMS_AUTO = 0, 1
 CD_ARCH_TINY_CNN, CD_ARCH_RESNET_BASIC, CD_ARCH_RESNET_BOTTLENECK, CD_ARCH_TRANSFORMER_HEAD = 0, 1, 2, 3
 CD_ARCH_TRANSFORMER = 4
 CD_ARCH_RESNET_BASIC_IMAGENET = 5
@@ -84,6 +85,7 @@ _SIGS = {
     "codistill_loss_grad": [_vp, ctypes.POINTER(_vp), _vp, _i64, _i64, ctypes.POINTER(LossCfg), _vp, _vp, _vp, _sz, _vp],
     "codistill_loss_grad_static": [_vp, ctypes.POINTER(_vp), _vp, _i64, _i64, ctypes.POINTER(LossCfg), _vp, _vp, _vp],
     "codistill_backward": [_vp, _vp, _vp, _i64, _vp, _sz, _vp, _vp, _vp],
+    "codistill_backward_streams": [_vp, _vp, _vp, _i64, _vp, _sz, _vp, _vp, _i32, _vp],
     "codistill_sgd_step": [_vp, _vp, _vp, _vp, _i64, _f32, _f32, _f32, _i32, _vp],
     "codistill_adam_step": [_vp, _vp, _vp, _vp, _vp, _i64, _f32, _f32, _f32, _f32, _f32, _i64, _vp],
     "codistill_profile_enable": [_i32],
@@ -236,9 +238,9 @@ def codistill_loss_grad_static(z_local, z_peers, targets, loss_out, dz_out, alph
 
 
 def codistill_backward(model, params, x, workspace, dlogits, grads_out):
-    _check(lib.codistill_backward(model._h, _ptr(params), _ptr(x), x.shape[0], _ptr(workspace),
-                                  workspace.numel() * workspace.element_size(), _ptr(dlogits), _ptr(grads_out),
-                                  _stream()))
+    _check(lib.codistill_backward_streams(model._h, _ptr(params), _ptr(x), x.shape[0], _ptr(workspace),
+                                          workspace.numel() * workspace.element_size(), _ptr(dlogits), _ptr(grads_out),
+                                          CD_STREAMS_AUTO, _stream()))
 
 
 def codistill_sgd_step(master_w, momentum_v, grad, lowp_w_out, lr, momentum, weight_decay=0.0, nesterov=False):

@@ -162,6 +162,22 @@ inline bool wgrad_alone(const WgradShape& h, int64_t operand_bytes) {
   wgrad_plan(&h, 1, ~(size_t)0 >> 1, 0, &r);
   return r.splits == 1 || 4 * (2 * h.partials(r.splits)) <= operand_bytes;
 }
+// Whether a layer by itself would be over before it has begun: 16 steps a workgroup or fewer, so that most of its time goes into the first
+// loads, the stores and the splits' sums.  (ResNet-20's step at batch 128, whose 16-channel layers are 8 steps by themselves: 177 launches and
+// ten forks -> 161 and four, 976 -> 905 us replayed from a graph.)
+inline bool wgrad_short(const WgradShape& h) {
+  WgradSplit r;
+  wgrad_plan(&h, 1, ~(size_t)0 >> 1, 0, &r);
+  return r.m_per_split <= 16 * 32;
+}
+// Whether a pass's waiting layers are so little work altogether (their tiles' steps: 128 in each of 512 workgroups, some 30 us) that they go at
+// its end, on the caller's stream.  Beside the rest of a small pass they take the compute units that its short launches wait for, and an
+// event and a wait are 15 us of the host's time and a gap on the device.  us a pass, with forks and without, by work (512 tile steps): two basic
+// blocks of 16 and 32 channels on 80 images of 28x35 (26) 307 and 286, two bottleneck blocks on 30 images of 112x113 (25) 618 and 608, ResNeXt's
+// on 19 of 160x161 (42) 905 and 882 and on 45 of 160x160 (96) 1448 and 1422, two Wide-ResNet blocks on 28 images (90) 782 and 744,
+// bottleneck blocks on 70 of 96x96 (115) 1036 and 1020; above the line ResNet-20's step at batch 128 (146) 873 and 926, bottleneck blocks on 34
+// images of 192x192 (205) 1564 and 1612.  (Behind one fork, when all or half of them have come: slower than either.)
+inline bool wgrad_together(int64_t work) { return work < (int64_t)kWgradBlocks * 128; }
 // Whether the layers collected so far are a launch: tiles enough without a split, or enough work for every compute unit to be busy
 // some 20 us (96 steps in each of 512 workgroups), or as much as the pass still has to collect and worth a launch, or all of them:
 // launches run beside the data gradients of the layers in front, and what is launched at the end of the pass runs beside nothing (two

@@ -1037,8 +1037,8 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
 }
 
 // --------------------------------------------------------------------------------- backward
-extern "C" int codistill_backward(const cd_model* m, const void* params, const void* x, int64_t batch, void* workspace,
-                                  size_t workspace_bytes, const float* dlogits, float* grads_out, void* stream) {
+static int backward_run(const cd_model* m, const void* params, const void* x, int64_t batch, void* workspace, size_t workspace_bytes,
+                        const float* dlogits, float* grads_out, int32_t streams, void* stream) {
   int rc = check_common("backward", m, params, x, batch, workspace);
   if (rc) return rc;
   CD_REQUIRE(dlogits && grads_out && aligned16(dlogits) && aligned16(grads_out),
@@ -1099,24 +1099,29 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     }
   }
   int forks = 0;
-  // The weight gradients of the matrix-core convolutions wait here, by tile class, until they are a launch (wgrad_batch_full): each
-  // needs its dy and its input only, which nothing after this point of the pass writes to.  They have a partials area of their own.
+  // The weight gradients of the matrix-core convolutions wait here, by tile class, until they are a launch (wgrad_batch_full), or, of a
+  // small network, for the end of the pass (wgrad_together): each needs its dy and its input only, which nothing after this point of the
+  // pass writes to.  They have a partials area of their own.
   struct PendingWgrads { std::vector<WgradProblem> p; int64_t tiles = 0, work = 0, work_left = 0; double flops = 0, bytes = 0; };
   PendingWgrads pending[8];
   auto operand_bytes = [](const ConvGeom& g) { return 2 * (g.B * g.H * g.W * (int64_t)g.Cin + g.M() * (int64_t)g.Cout); };
-  auto waits = [&](const ConvGeom& g, const WgradShape& h) { return g.Cin > 16 && !wgrad_alone(h, operand_bytes(g)); };   // (not a packed stem)
+  auto waits = [&](const ConvGeom& g, const WgradShape& h) { return g.Cin != 3 && (!wgrad_alone(h, operand_bytes(g)) || wgrad_short(h)); };   // (not a packed stem)
   for (size_t i = (size_t)m->first_trainable_op; i < m->ops.size(); i++) {
     if (m->ops[i].kind != OP_CONV || grouped_sliced(m, m->ops[i], batch) || m->ops[i].groups > 1) continue;
     const ConvGeom g = conv_geom(m, m->ops[i], batch), gp = packed_geom(g);
     const WgradShape h = conv_wgrad_shape(gp, 1, m->ops[i].pb >= 0);
-    if (use_mfma(m, g) && waits(gp, h)) pending[h.tile_class()].work_left += h.tiles() * h.steps();
+    if (use_mfma(m, g) && waits(g, h)) pending[h.tile_class()].work_left += h.tiles() * h.steps();
   }
+  int64_t waiting = 0;
+  for (const PendingWgrads& q : pending) waiting += q.work_left;
+  const bool together = streams == CD_STREAMS_AUTO && wgrad_together(waiting);
   // Launches them, on the second stream behind what the caller's stream holds so far; where the runtime refuses the event or the wait,
-  // on the caller's stream (whose partials area is free between two ops).  Returns the stream.
-  auto run_wgrads = [&](PendingWgrads& q) {
+  // and at the end of the pass (`last`: nothing is left that they could run beside), on the caller's stream (whose partials area is free
+  // between two ops).  Returns the stream.
+  auto run_wgrads = [&](PendingWgrads& q, bool last) {
     hipStream_t s = c.s;
     if (q.p.empty()) return s;
-    if (side) {
+    if (side && !last) {
       hipEvent_t ev = side_event(forks);
       if (ev && hipEventRecord(ev, c.s) == hipSuccess && hipStreamWaitEvent(side, ev, 0) == hipSuccess) {
         s = side;
@@ -1362,7 +1367,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
           }
           const WgradShape h = conv_wgrad_shape(gp, 1, o.pb >= 0);
           PendingWgrads one;
-          const bool wait = waits(gp, h);
+          const bool wait = waits(g, h);
           PendingWgrads& q = wait ? pending[h.tile_class()] : one;
           q.p.push_back(w);
           q.tiles += h.tiles();
@@ -1370,8 +1375,9 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
           q.flops += 2.0 * g.M() * g.Cout * g.K();
           q.bytes += conv_bytes(m, g) + 2.0 * g.Cout * g.K();
           if (wait) q.work_left -= h.tiles() * h.steps();
-          if (!wait || wgrad_batch_full(q.tiles, q.work, (int)q.p.size(), q.work_left)) {
-            const hipStream_t ws = run_wgrads(q);   // (a 3-channel image's layer never waits: its dw is unpacked behind it)
+          if (!wait || (together ? (int)q.p.size() >= kWgradJobs : wgrad_batch_full(q.tiles, q.work, (int)q.p.size(), q.work_left))) {
+            // (the network's first layer, which has no data gradient, is the last of the pass)
+            const hipStream_t ws = run_wgrads(q, o.x == 0 || (wait && together));   // (a 3-channel image's layer never waits: its dw is unpacked behind it)
             if (s2d_form(g)) s2d_unpack_dw(w.dw, G(o.pw), g.Cout, g.kh, gp.kh, 2 * gp.pad - g.pad, ws);
             else if (g.Cin == 3) unpad_c8_to_c3(w.dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, ws);
           }
@@ -1432,7 +1438,7 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     }
     if (o.x != 0) written[o.x] = 1;
   }
-  for (PendingWgrads& q : pending) run_wgrads(q);
+  for (PendingWgrads& q : pending) run_wgrads(q, true);
   if (!generic_wgrads.empty()) {
     ProfScope pr(CD_K_CONV_WGRAD, c.s, generic_flops, generic_bytes);
     conv_wgrad_generic_batch(dt, generic_wgrads.data(), (int)generic_wgrads.size(), c.partials(), c.plan.partials_bytes, c.s);
@@ -1450,4 +1456,15 @@ extern "C" int codistill_backward(const cd_model* m, const void* params, const v
     }
   }
   return check_launch("backward");
+}
+
+extern "C" int codistill_backward(const cd_model* m, const void* params, const void* x, int64_t batch, void* workspace,
+                                  size_t workspace_bytes, const float* dlogits, float* grads_out, void* stream) {
+  return backward_run(m, params, x, batch, workspace, workspace_bytes, dlogits, grads_out, CD_STREAMS_TWO, stream);
+}
+
+extern "C" int codistill_backward_streams(const cd_model* m, const void* params, const void* x, int64_t batch, void* workspace,
+                                          size_t workspace_bytes, const float* dlogits, float* grads_out, int32_t streams, void* stream) {
+  CD_REQUIRE(streams == CD_STREAMS_TWO || streams == CD_STREAMS_AUTO, "backward: unknown streams %d", streams);
+  return backward_run(m, params, x, batch, workspace, workspace_bytes, dlogits, grads_out, streams, stream);
 }

@@ -1,5 +1,5 @@
 """What the library enqueues, in order, without a GPU: `python launch_log.py FAKE_LIBRARY REQUEST` (a JSON object: kind, dtype, arch,
-batch, and optionally call = "forward" (saving for a backward pass) and fail = [function, n-th call]) prints the log of one
+batch, and optionally call = "forward" (saving for a backward pass) or "backward_auto" and fail = [function, n-th call]) prints the log of one
 codistill_backward or codistill_forward call as JSON; loss = [rows, columns, peers] in its place that of a codistill_loss_grad.
 
 A process of its own: the stand-in for the HIP runtime (fake_hip.cpp) has to be loaded before anything else that uses HIP.  The
@@ -30,6 +30,9 @@ if __name__ == "__main__":
                                        ctypes.byref(cfg), at(4), at(5), at(3), 1 << 30, at(6))
     elif req.get("call") == "forward":
         rc = B.lib.codistill_forward(m._h, at(1), at(2), req["batch"], 1, B.CD_BN_BATCH_STATS, None, at(3), m.workspace_bytes(req["batch"], True), at(4), at(6))
+    elif req.get("call") == "backward_auto":
+        rc = B.lib.codistill_backward_streams(m._h, at(1), at(2), req["batch"], at(3), m.workspace_bytes(req["batch"], True), at(4), at(5),
+                                              B.CD_STREAMS_AUTO, at(6))
     else:
         rc = B.lib.codistill_backward(m._h, at(1), at(2), req["batch"], at(3), m.workspace_bytes(req["batch"], True), at(4), at(5), at(6))
     log = [line.split(" ") for line in fake.fake_hip_log().decode().splitlines()]

@@ -132,3 +132,28 @@ def test_launch_that_counts_the_valid_rows_of_a_loss(backward, peers, rows, cols
     assert r["rc"] == 0
     assert sum("loss_prep_kernel" in k for k in _kernels(r)) == counted
     assert sum("loss_row_generic_kernel" in k for k in _kernels(r)) == peers - 1
+
+
+@pytest.mark.parametrize("batch,apart", [(16, 0), (80, 0), (200, 1)])
+def test_weight_gradients_of_a_small_network_at_the_end_of_the_pass(backward, batch, apart):
+    """With CD_STREAMS_AUTO the layers of a small network (less than 65536 tile steps in all) go at the end, on the caller's stream, a class to a
+    launch and nothing forked; a larger one forks as CD_STREAMS_TWO does."""
+    model = dict(MODELS["basic"], batch=batch)
+    auto, two = backward(model, call="backward_auto"), backward(model)
+    assert auto["rc"] == two["rc"] == 0 and _forks(two) >= 1
+    assert (_forks(auto) >= 1) == bool(apart)
+    names = [n for what, _, n, _ in auto["log"] if what == "launch"]
+    if apart:
+        assert auto["log"] == two["log"]
+    else:
+        assert not any(what in ("record", "wait") for what, _, _, _ in auto["log"])
+        waiting = [k for k, n in enumerate(names) if "wgrad_kernel" in n and "Li16EE" in n]
+        assert waiting and min(waiting) > max(k for k, n in enumerate(names) if "igemm_kernel" in n)
+    assert sum("wgrad_kernel" in n for n in names) <= sum("wgrad_kernel" in k for k in _kernels(two))
+
+
+def test_streams_argument_is_checked():
+    m = B.Model(B.arch_preset(B.CD_ARCH_TINY_CNN), B.CD_F32)
+    at = [k << 32 for k in range(1, 7)]
+    for streams in (-1, 2):
+        assert B.lib.codistill_backward_streams(m._h, at[0], at[1], 2, at[2], 1 << 40, at[3], at[4], streams, None) == B.CD_ERR_INVALID_ARG
