@@ -45,7 +45,7 @@ class StepRunner:
         # priority) beside the local forward, so that one model's memory-bound kernels and partly
         # filled launches share the chip with the other's.
         self.overlap_peers = overlap_peers
-        self.side = torch.cuda.Stream(device=device) if overlap_peers else None
+        self.side = torch.cuda.Stream(device=device) if overlap_peers and self._overlap_pays() else None
         n, C = model.n_elements, model.classes
         f32 = dict(dtype=torch.float32, device=device)
         self.master = torch.zeros(n, **f32)
@@ -64,6 +64,18 @@ class StepRunner:
         self.dz = torch.empty(rows, C, **f32)
         self.loss = torch.zeros(4, **f32)
         self.scratch = torch.empty(B.loss_scratch_bytes(rows, C), dtype=torch.uint8, device=device)
+
+    def _overlap_pays(self):
+        """Whether a peer's forward pass is worth a second stream.  The two waits that order it are 20 us of the host's time each; what
+        they can hide is a pass.  Two-layer network, step with and without (us): fp32, 8 images 173 and 85, 50 images (10 MB of activations)
+        172 and 121, 100 (21 MB) 180 and 186; bf16, 8 images 196 and 109, 100 (10 MB) 200 and 157, 200 (21 MB) 200 and 191, 800 of
+        40x40 549 and 590.  ResNet-20 with two streams 871, one after the other 1169."""
+        for pm in self.peers:
+            ops, tensors = pm.graph(self.batch)
+            moved = sum(self.batch * t["h"] * t["w"] * t["c"] for t in tensors) * pm.torch_dtype.itemsize
+            if len(ops) > 8 or moved > 16 << 20:
+                return True
+        return False
 
     def params(self):
         return self.lowp if self.lowp is not None else self.master
@@ -110,7 +122,7 @@ class StepRunner:
         """x: [B,H,W,3] device tensor in the model dtype (the Transformer: int32 [B, source + target tokens]);
         y: int32 device tensor, one target per row of logits.  adam = (beta1, beta2, eps) replaces the momentum-SGD
         update by Adam (momentum and nesterov are then unused)."""
-        if self.overlap_peers and self.peers:
+        if self.overlap_peers and self.side is not None and self.peers:
             main = torch.cuda.current_stream()
             self.side.wait_stream(main)           # x, the peer parameters and the last step's reads are in order
             with torch.cuda.stream(self.side):
