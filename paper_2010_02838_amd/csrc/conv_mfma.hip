@@ -54,6 +54,7 @@ struct IgemmArgs {
   uint32_t src_bytes, wt_bytes;
   const bf16_t* bias;  // per-column bias added to the output (kernels with EPI >= 1)
   float* stat_partials;  // STATS kernels: [m-tiles][stat_pitch(N)] per-tile column sums and sums of squares
+  int sum_parts = 1;     // 256x256 tiles: one partial sum for the 256 rows, or one for every 128 (2)
   // STATS == 2 (a data gradient that completes the gradient of a BatchNorm's output): the sums that BatchNorm's
   // backward pass reduces over the rows, taken from the values as they are stored: dz = the output, gated by the
   // BatchNorm's ReLU bit mask (bn_mask, nullable: no ReLU), and dz * xhat with xhat = (bn_x - mean) * invstd,
@@ -335,25 +336,36 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
   // (The input's vectors leave the two 128-accumulator tiles short of 6 (256x128) and 2 (128x256) registers: those are stored to
   // scratch memory in front of the loop and loaded behind it.)
   constexpr int BS_LPR = WN / 8, BS_RPP = 64 / BS_LPR, BS_EROWS = EM < 64 ? EM : 64;
-  constexpr int BS_NV = STATS == 2 ? (EM / BS_EROWS) * ((BS_EROWS + BS_RPP - 1) / BS_RPP) : 1;
+  // (256x256 tiles, whose vectors are 64 registers, request them pass by pass in the epilogue)
+  constexpr bool BS_LATE = BM == 256 && BN == 256;
+  constexpr int BS_PP = (BS_EROWS + BS_RPP - 1) / BS_RPP, BS_NV = STATS == 2 ? (BS_LATE ? 1 : EM / BS_EROWS) * BS_PP : 1;
   uint4 bs_x[BS_NV];
   uint32_t bs_bits[BS_NV];
   auto bs_index = [&](int v, bool& ok) {   // element index of vector v in an [M][N] tensor
-    constexpr int PP = (BS_EROWS + BS_RPP - 1) / BS_RPP;
-    const int pass = v / PP, row = v % PP * BS_RPP + lane / BS_LPR;
+    const int pass = v / BS_PP, row = v % BS_PP * BS_RPP + lane / BS_LPR;
     const int m = m0 + em0 + pass * BS_EROWS + row, n = n0 + wn0 + (lane % BS_LPR) * 8;
     ok = m < M && n < a.N && row < BS_EROWS && lane < BS_RPP * BS_LPR;
     return (unsigned)m * (unsigned)a.N + (unsigned)n;
   };
-  if (STATS == 2) {
+  auto bs_request_x = [&](int pass) {
 #pragma unroll
     for (int v = 0; v < BS_NV; v++) {
       bool ok;
-      const unsigned idx = bs_index(v, ok);
+      const unsigned idx = bs_index(pass * BS_PP + v, ok);
       bs_x[v] = make_uint4(0, 0, 0, 0);
       if (ok) bs_x[v] = *reinterpret_cast<const uint4*>(a.bn_x + idx);
     }
-  }
+  };
+  auto bs_request_bits = [&](int pass) {
+#pragma unroll
+    for (int v = 0; v < BS_NV; v++) {
+      bool ok;
+      const unsigned idx = bs_index(pass * BS_PP + v, ok);
+      bs_bits[v] = 0u;
+      if (ok) bs_bits[v] = a.bn_mask ? a.bn_mask[idx >> 3] : 0xffu;
+    }
+  };
+  if (STATS == 2 && !BS_LATE) bs_request_x(0);
   // EPI: the bias of this lane's channels, requested here so that its latency passes under the main loop (read behind it, element
   // by element, it cost 3 us a tile: 8192 x 2048 x 512 26 us, now 23).  Register v of tile i belongs to channel
   // n0 + wn0 + 32 i + 8 (v / 4) + 4 (lane / 32) + v % 4: four consecutive channels at a time, on 8-byte boundaries.
@@ -409,7 +421,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
   // kt; the loads of tile kt+NS go there.  Their offsets were computed in the shadow of the earlier sub-steps' MFMAs.
   // (Not for the 128-accumulator tiles that also hold the backward sums' operands through the loop: no registers are left for
   // a second fragment buffer, they read a sub-step's fragments and use them.)
-  constexpr bool AHEAD = !(STATS == 2 && TN * TM >= 8);
+  constexpr bool AHEAD = !(STATS == 2 && TN * TM >= 8 && !BS_LATE);
   constexpr int KK = BKT / 16 / WK, TT = TN * TM, FB = AHEAD ? 2 : 1;   // (sub-steps of this wave's group)
   bf16x8_t wf[FB][TN], xf[FB][TM];  // [buffer][tile]
   // byte offset of this lane's fragment of sub-step kk inside a tile row block (swz depends on the lane's row only: tile
@@ -475,15 +487,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
     cur = nxt;
     nxt = nxt + STAGE * 2u == NS * STAGE * 2u ? 0 : nxt + STAGE * 2u;
   }
-  if (STATS == 2) {
-#pragma unroll
-    for (int v = 0; v < BS_NV; v++) {
-      bool ok;
-      const unsigned idx = bs_index(v, ok);
-      bs_bits[v] = 0u;
-      if (ok) bs_bits[v] = a.bn_mask ? a.bn_mask[idx >> 3] : 0xffu;
-    }
-  }
+  if (STATS == 2 && !BS_LATE) bs_request_bits(0);
   wait_vmem<0>();  // the masked loads past the end still write (zeros) into the stages the epilogue reuses
 
   // accumulator layout: lane holds pixel column (lane % 32); register v holds channel
@@ -625,6 +629,10 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
         if (m < M && n < a.N && lane_ok && p * RPP + er < EROWS) nres[p] = *reinterpret_cast<const uint4*>(a.norm_res + ((unsigned)m * (unsigned)a.N + (unsigned)n));
       }
     }
+    if (STATS == 2 && BS_LATE) {
+      bs_request_x(g0 / TPG);
+      bs_request_bits(g0 / TPG);
+    }
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int i = 0; i < TN; i++)
@@ -729,8 +737,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
           v = make_uint4(o[0], o[1], o[2], o[3]);
         }
         if (STATS == 2) {   // the stored values feed the sums of the BatchNorm's backward pass
-          const uint4 xr = bs_x[(g0 / TPG) * PASSES + p];
-          const uint32_t bits = bs_bits[(g0 / TPG) * PASSES + p];
+          const uint4 xr = bs_x[(BS_LATE ? 0 : g0 / TPG) * PASSES + p];
+          const uint32_t bits = bs_bits[(BS_LATE ? 0 : g0 / TPG) * PASSES + p];
           const uint32_t gv[4] = {v.x, v.y, v.z, v.w}, xv[4] = {xr.x, xr.y, xr.z, xr.w};
 #pragma unroll
           for (int q = 0; q < 4; q++) {
@@ -779,14 +787,24 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
   if (STATS) {
     // fold the waves of a column
     __syncthreads();
-    if (tid < BN && n0 + tid < a.N) {
+    constexpr int PARTS = BM == 256 && BN == 256 ? 2 : 1, WPP = WAVES_M * WK / PARTS;   // partial sums of the tile at the most, waves to each
+    const int parts = PARTS == 1 ? 1 : a.sum_parts, part = PARTS == 1 ? 0 : tid / BN, col = PARTS == 1 ? tid : tid % BN;
+    static_assert(PARTS * BN <= NT, "a thread for each of them");
+    if (part < parts && tid < PARTS * BN && n0 + col < a.N && m0 + part * (BM / PARTS) < M) {
       float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-      for (int w = 0; w < WAVES_M * WK; w++) { s0 += red[(w * 2 + 0) * BN + tid]; s1 += red[(w * 2 + 1) * BN + tid]; }
-      if (STATS == 2) s1 = (s1 - a.bn_stats[n0 + tid] * s0) * a.bn_stats[a.N + n0 + tid];   // sum dz x -> sum dz xhat
-      const int64_t mt = tm;
-      a.stat_partials[mt * stat_pitch(a.N) + n0 + tid] = s0;
-      a.stat_partials[mt * stat_pitch(a.N) + a.N + n0 + tid] = s1;
+      for (int w = 0; w < WPP; w++) {
+        s0 += red[((part * WPP + w) * 2 + 0) * BN + col];
+        s1 += red[((part * WPP + w) * 2 + 1) * BN + col];
+      }
+      if (parts < PARTS) {
+#pragma unroll
+        for (int w = WPP; w < WPP * PARTS; w++) { s0 += red[(w * 2 + 0) * BN + col]; s1 += red[(w * 2 + 1) * BN + col]; }
+      }
+      if (STATS == 2) s1 = (s1 - a.bn_stats[n0 + col] * s0) * a.bn_stats[a.N + n0 + col];   // sum dz x -> sum dz xhat
+      const int64_t mt = (int64_t)tm * parts + part;
+      a.stat_partials[mt * stat_pitch(a.N) + n0 + col] = s0;
+      a.stat_partials[mt * stat_pitch(a.N) + a.N + n0 + col] = s1;
     }
   }
 }
@@ -809,7 +827,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
 // 4608 76 -> 67 us, 6144 x 640 x 5760 63 -> 52, 8192 x 512 x 2048 28 -> 23, 200704 x 128 x 1152 83 -> 76; the large layers of
 // ResNet-50 at batch 256 are bound by memory and by the clock under full matrix load and gain 1 to 3 %.
 // (Which tile: conv_tile_rule in conv_rules.h.)
-static int igemm_tile(int64_t M, int N, int K, bool small_tiles, bool sums) {
+// eight: the eight-wave tiles may be chosen (launches that store their rows in order)
+static int igemm_tile(int64_t M, int N, int K, bool small_tiles, bool sums, bool eight) {
   if (N <= 64) return TILE_SQUARE;
   if (g_tune_tile == 2) return TILE_SQUARE;
   if (g_tune_tile == 3) return TILE_TALL;
@@ -817,13 +836,16 @@ static int igemm_tile(int64_t M, int N, int K, bool small_tiles, bool sums) {
   if (g_tune_tile == 5) return TILE_NARROW;
   if (g_tune_tile == 6) return TILE_SMALL;
   if (g_tune_tile == 7 && small_tiles) return TILE_160;
+  if (g_tune_tile == 8) eight = false;
+  if (eight)
+    if (const int t = conv_eight_waves_rule(M, N, K, small_tiles)) return t;
   if (conv_cols160_rule(M, N, K, small_tiles)) return TILE_160;
   return conv_tile_rule(M, N, K, small_tiles, sums);
 }
 int conv_fprop_tile_class(const ConvGeom& g, bool bias, bool sums) {
   if (g.Cout <= 64) return 2;
   if (g.Cin < BK) return 0;
-  const int t = igemm_tile(g.M(), g.Cout, (int)g.K(), g.Cin >= 64, sums);
+  const int t = igemm_tile(g.M(), g.Cout, (int)g.K(), g.Cin >= 64, sums, true);
   return t == TILE_SQUARE || (t == TILE_TALL && bias) ? 0 : (t == TILE_WIDE ? 1 : 2);   // (no 256x128 kernel with a bias)
 }
 
@@ -833,7 +855,7 @@ static int launch_tile(IgemmArgs& a, hipStream_t s) {
   const int mt = (int)cdiv(a.M, BM);
   hipLaunchKernelGGL((igemm_kernel<MODE, BM, BN, WM, WN, false, STATS, NWRAP, REMAP, EPI, false, BKT, NS, WK>),
                      dim3((unsigned)((int64_t)mt * a.ntiles)), dim3(64 * WM * WN * WK), 0, s, a);
-  return mt;
+  return BM == 256 && BN == 256 && a.sum_parts == 2 ? (int)cdiv(a.M, 128) : mt;
 }
 
 // returns the number of m-tiles (= statistics chunks when STATS; conv_stat_chunks_max bounds it)
@@ -868,10 +890,15 @@ static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
   if (a.N <= 64 || g_tune_tile == 1) return launch_tile<MODE, 256, 64, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
   if constexpr (NWRAP == 1) {
     const bool w64 = a.Cs >= 64;
-    const int tile = igemm_tile(a.M, a.N, a.K, w64, STATS != 0);
+    const int tile = igemm_tile(a.M, a.N, a.K, w64, STATS != 0, !REMAP);
     if constexpr (!REMAP) {
       if ((EPI == 0 || EPI == 3) && tile == TILE_TALL) return launch_tile<MODE, 256, 128, 2, 2, STATS, 1, false, EPI, 32, 3>(a, s);
       if (tile == TILE_WIDE) return launch_tile<MODE, 128, 256, 2, 2, STATS, 1, false, EPI, 32, 3>(a, s);
+      if (tile == TILE_256) {   // (a partial sum keeps the rows it had in the tiles that these take the place of)
+        a.sum_parts = conv_tile_rule(a.M, a.N, a.K, true, true) == TILE_TALL ? 1 : 2;
+        return launch_tile<MODE, 256, 256, 2, 4, STATS, 1, false, EPI, 64, 2>(a, s);
+      }
+      if (tile == TILE_WIDE8) return launch_tile<MODE, 128, 256, 2, 4, STATS, 1, false, EPI, 64, 3>(a, s);
     }
     if (w64) {
       if (tile == TILE_160) return launch_tile<MODE, 128, 160, 4, 1, STATS, 1, REMAP, EPI, 64, 2>(a, s);
@@ -918,7 +945,8 @@ void linear_fwd_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, float
   a.wt_bytes = (uint32_t)((int64_t)C * F * 2);
   // a filter matrix beyond an L2's 4 MiB under a wide output: grouped tile order, with a short contraction on 256x128 tiles
   // (8192 x 32768 x 512 inside a training step: 471 us on 128x128 tiles, 459 so; non-temporal stores of the logits, faster when
-  // the launch is repeated alone, 368 us, cost it 70 us there)
+  // the launch is repeated alone, 368 us, cost it 70 us there; 256x256 tiles of eight waves: the step 0.7 % faster, where the launch runs beside a
+  // peer's, but passes of one model 1 to 3 % slower)
   const bool group = (int64_t)C * F * 2 > (4 << 20) && C >= 2048;
   // otherwise 64x64 tiles for few rows as igemm_tile says (256 x 1000 x 2048 18 -> 11 us), and for at most 64 classes up to 16384 rows, a
   // tile for every compute unit: the busiest unit has the same number of tiles of either shape there and a 64x64 one is the shorter
@@ -926,7 +954,7 @@ void linear_fwd_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, float
   // 26.1 and 12.9; 64 classes 16384 x 512 9.6 and 5.7.  (Beyond the line 64x64 tiles win less, and lose in places: 32768 rows of 2048
   // onto 64 classes 43 and 34, 65536 of 64 7.9 and 8.2.)
   const bool narrow = C <= 64 && F >= 64 && B <= 64 * 256;
-  const int tile = igemm_tile(B, C, F, F >= 64, false);
+  const int tile = igemm_tile(B, C, F, F >= 64, false, false);
   if (group && F <= 512 && cdiv(B, 256) * cdiv(C, 128) >= 512) {
     a.group_m = 4;
     if (bias) launch_linear<256, 128, 1, true, 32, 3>(a, s); else launch_linear<256, 128, 0, true, 32, 3>(a, s);

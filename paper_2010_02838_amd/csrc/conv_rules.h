@@ -23,7 +23,7 @@ namespace cd {
 //    a tile shape is the number of workgroups on the busiest unit times what one costs there (128x64 0.7 of a 128x128
 //    one, 64x64 half), but no less than what one takes alone (1.4, 1.08 and 0.75): 2450 x 512 x 4608 (80 tiles of 128x128)
 //    49 -> 26 on 312 of 64x64, 24576 x 320 x 2880 74 -> 66 on 128x64 (five columns of 64 instead of three of 128).
-enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2, TILE_NARROW = 3, TILE_SMALL = 4, TILE_160 = 5 };   // 128x128 256x128 128x256 128x64 64x64 128x160
+enum { TILE_SQUARE = 0, TILE_TALL = 1, TILE_WIDE = 2, TILE_NARROW = 3, TILE_SMALL = 4, TILE_160 = 5, TILE_256 = 6, TILE_WIDE8 = 7 };   // 128x128 256x128 128x256 128x64 64x64 128x160 256x256 128x256
 // M rows, N > 64 columns, contraction K; small_tiles: the 64-wide steps that the last two need fit; sums: takes column sums
 inline int conv_tile_rule(int64_t M, int N, int K, bool small_tiles, bool sums) {
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
@@ -48,6 +48,22 @@ inline int conv_tile_rule(int64_t M, int N, int K, bool small_tiles, bool sums) 
     return t128 > 512 && e256 >= e128 ? TILE_TALL : TILE_SQUARE;
   }
   return small < narrow && small < square ? TILE_SMALL : narrow < square ? TILE_NARROW : TILE_SQUARE;
+}
+
+// Tiles of eight waves on a compute unit of their own, 64-wide steps: 128x256 in three stages or 256x256 in two (0: neither; asked first).
+// A 32-wide step reads rows in 64-byte segments, 31 B a cycle and compute unit against 52 in 128-byte ones, which two workgroups of 128x256
+// tiles wait for (8192 x 2048 x 512: 25000 cycles of loads, 16000 of matrix instructions; 256x256 tiles 10000).  They pay where they fill most
+// of a round of 256 compute units: 144 tiles and more of one, or seven eighths of two.  us, without and with, 128x256: 10240 x 512 x 2048 (160) 39
+// -> 31, 12544 x 512 x 2048 (196) 41 -> 33, 9408 x 512 x 4608 (148) 54 -> 49, 7168 x 1024 x 1024 (224) 20.1 -> 17.5, 2560 x 2048 x 512
+// (160) 12.8 -> 11.5, outside 4096 x 1024 x 1024 (128) 13.4 and 15.7, 5120 x 2048 x 512 (320) 19.5 and 20.2; 256x256: 3840 x 4096 x
+// 1024 (240) 38 -> 30, 50176 x 256 x 2304 (196) 75 -> 62, 8192 x 2048 x 512 (256) 27 -> 23.5, 6144 x 1536 x 512 (144) 19.3 -> 16.8, 16384
+// x 2048 x 512 (512) 48 -> 41, outside 4096 x 2048 x 512 (128) 14.6 and 17.0, 12288 x 2048 x 512 (384) 37 and 39, 75264 x 256 x 512
+// (294) 40 and 46.  Contractions below 256 live on the overlap of several workgroups (802816 x 256 x 64 101 and 122).
+inline int conv_eight_waves_rule(int64_t M, int N, int K, bool wide_steps) {   // wide_steps: 64-wide steps fit
+  if (N % 256 || K < 256 || !wide_steps) return 0;
+  const int64_t half = (M + 127) / 128 * (N / 256), full = (M + 255) / 256 * (N / 256);
+  if (half >= 144 && half <= 256) return TILE_WIDE8;
+  return (full >= 144 && full <= 256) || (full >= 448 && full <= 512) ? TILE_256 : 0;
 }
 
 // Whether a width that 160 divides takes 128x160 tiles instead (asked before conv_tile_rule).  160 columns are two of 128, 37 % of them

@@ -119,6 +119,30 @@ def test_tile_of_a_convolution(tile, shape, want):
     assert tile(*shape) == want
 
 
+TILE_256, WIDE8 = 6, 7
+
+
+@pytest.mark.parametrize("shape,want", [
+    # (rows, columns, contraction, 64 channels or more per tap): either side of each line
+    ((10240, 512, 2048, 1), WIDE8), ((8192, 512, 2048, 1), 0), ((9153, 512, 2048, 1), WIDE8), ((9088, 512, 2048, 1), 0), ((16384, 512, 2048, 1), WIDE8),
+    ((16385, 512, 2048, 1), 0), ((18176, 512, 2048, 1), 0), ((18177, 512, 2048, 1), TILE_256), ((8192, 2048, 512, 1), TILE_256),
+    ((8193, 2048, 512, 1), 0), ((12288, 2048, 512, 1), 0), ((14336, 2048, 512, 1), TILE_256), ((16384, 2048, 512, 1), TILE_256),
+    ((16385, 2048, 512, 1), 0), ((8192, 2048, 256, 1), TILE_256), ((8192, 2048, 192, 1), 0), ((8192, 2048, 512, 0), 0), ((8192, 2176, 512, 1), 0),
+    # the launches of test_gpu_conv_tiles.py: "eight_waves_tall", "eight_waves_256", "eight_waves_128", dense layers
+    ((50286, 256, 2304, 1), TILE_256), ((9537, 1024, 256, 1), TILE_256), ((4624, 1024, 256, 1), WIDE8), ((4700, 2304, 256, 1), TILE_256),
+    ((4700, 1024, 256, 1), WIDE8),
+])
+def test_tiles_of_eight_waves(tmp_path_factory, shape, want):
+    run = compiled(tmp_path_factory.mktemp("eight"),
+                   "int main(int, char** v) { printf(\"%d\", conv_eight_waves_rule(atoll(v[1]), atoi(v[2]), atoi(v[3]), atoi(v[4]) != 0)); }")
+    assert int(run(*shape)) == want
+
+
+def test_partial_sums_of_the_tiles_that_256_rows_take_the_place_of(tile):
+    """256x256 tiles leave one partial sum for their rows where 256x128 tiles would, two elsewhere."""
+    assert tile(50286, 256, 2304, 1, 1) == TALL and tile(9537, 1024, 256, 1, 1) == WIDE
+
+
 @pytest.mark.parametrize("shape,want", [
     # (rows, columns, contraction, 64 channels or more per tap): either side of each line, and widths that 160 does not divide
     ((98304, 160, 1440, 1), 1), ((98304, 160, 1440, 0), 0), ((32768, 160, 1440, 1), 1), ((16384, 160, 1440, 1), 0), ((24576, 320, 2880, 1), 1),

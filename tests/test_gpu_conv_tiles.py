@@ -38,6 +38,11 @@ SHAPES = {
     "rows_16_64": (dict(kind=1, widths=[16, 64], blocks=[1, 2], stem_width=16), lambda: nets.resnet20(widths=(16, 64), blocks=(1, 2)), 13, 62),
     # 8410 and 2250 rows of 40 columns, 40 channels: 32-wide steps
     "columns_40": (dict(kind=1, widths=[40, 40], blocks=[1, 1], stem_width=40), lambda: nets.resnet20(widths=(40, 40), blocks=(1, 1)), 10, 29),
+    # tiles of eight waves: 256x256 with one partial sum for their 256 rows (50286 rows, 197 tiles, the last one 110 rows), with two (9537 rows
+    # onto 1024 columns, the last tile 65 rows: one of its two), 128x256 (4624 rows onto 1024 columns)
+    "eight_waves_tall": (dict(kind=1, widths=[256], blocks=[1], stem_width=256), lambda: nets.resnet20(widths=(256,), blocks=(1,)), 174, 17),
+    "eight_waves_256": (dict(kind=2, widths=[256], blocks=[1], stem_width=64), lambda: nets.resnet50(classes=10, widths=(256,), blocks=(1,), stem=64), 33, 68),
+    "eight_waves_128": (dict(kind=2, widths=[256], blocks=[1], stem_width=64), lambda: nets.resnet50(classes=10, widths=(256,), blocks=(1,), stem=64), 16, 68),
     # 128x160 tiles, the last row tile ragged: 104040 rows of 160 columns, the parity classes of a stride-2 data gradient onto 160 (26010
     # rows), and two columns of tiles (320) over 26010 rows
     "columns_160": (dict(kind=1, widths=[160, 64], blocks=[1, 1], stem_width=160), lambda: nets.resnet20(widths=(160, 64), blocks=(1, 1)), 90, 34),
@@ -78,6 +83,8 @@ def test_tall_tiles_without_column_sums(monkeypatch):
 @pytest.mark.parametrize("shape", [(2100, 512, 2048, 264),    # 128x256 tiles with bias and ReLU, 64x64 with bias
                                    (70, 72, 200, 1000),       # few rows: 64x64 tiles, fp32 logits too
                                    (300, 520, 72, 4104),      # logits of a filter beyond 4 MiB: grouped tile order, 64-wide steps
+                                   (4700, 256, 2304, 264),    # 256x256 tiles, 18 row tiles and a ragged one; bias and ReLU, data gradient
+                                   (4700, 256, 1024, 264),    # 128x256 tiles of eight waves
                                    (8200, 64, 128, 4104)])    # 64-wide steps with a single step; ragged logits
 def test_dense_layer_tiles_bf16_layers(shape):
     c = head_case("bf16", *shape)
@@ -143,6 +150,8 @@ EVAL_SHAPES = {   # architecture, batch, resolution: the tiles, column counts an
     "narrow_columns": (dict(kind=1, widths=[16, 40], blocks=[1, 1], stem_width=16), "bf16", 143, 31),  # 32- and 64-column tiles
     "wide_and_tall": (dict(kind=2, widths=[128], blocks=[1], stem_width=64), "bf16", 130, 65),         # 128x256; odd image: no fused pool
     "columns_160": (dict(kind=1, widths=[160], blocks=[1], stem_width=160), "bf16", 90, 17),           # 128x160
+    "eight_waves_256": (dict(kind=2, widths=[256], blocks=[2], stem_width=64), "bf16", 33, 68),        # 256x256, with a residual
+    "eight_waves_128": (dict(kind=2, widths=[256], blocks=[1], stem_width=64), "bf16", 16, 68),        # 128x256 of eight waves
     "tall": (dict(kind=1, widths=[128], blocks=[1], stem_width=128), "bf16", 231, 17),                 # 256x128
     "grouped": (dict(kind=5, widths=[128, 256], out_widths=[128, 256], blocks=[2, 1], stem_width=64, groups=32), "bf16", 5, 48),
     "odd_channels": (dict(kind=1, widths=[18, 22], blocks=[1, 1], stem_width=18), "bf16", 7, 13),
