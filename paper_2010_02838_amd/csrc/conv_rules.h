@@ -192,8 +192,10 @@ inline bool wgrad_short(const WgradShape& h) {
 // blocks of 16 and 32 channels on 80 images of 28x35 (26) 307 and 286, two bottleneck blocks on 30 images of 112x113 (25) 618 and 608, ResNeXt's
 // on 19 of 160x161 (42) 905 and 882 and on 45 of 160x160 (96) 1448 and 1422, two Wide-ResNet blocks on 28 images (90) 782 and 744,
 // bottleneck blocks on 70 of 96x96 (115) 1036 and 1020; above the line ResNet-20's step at batch 128 (146) 873 and 926, bottleneck blocks on 34
-// images of 192x192 (205) 1564 and 1612.  (Behind one fork, when all or half of them have come: slower than either.)
-inline bool wgrad_together(int64_t work) { return work < (int64_t)kWgradBlocks * 128; }
+// images of 192x192 (205) 1564 and 1612.  Layers of at most 64 output channels count 1.4: the other launches of their pass leave part of the chip
+// idle; basic blocks of 16 and 32 channels on 226 images of 32x32 (98, almost all narrow) 525 and 554, of 64 and 128 on 36 images of 224x225 (96, of
+// which 70) 778 and 744.  (Behind one fork, when all or half of them have come: slower than either.)
+inline bool wgrad_together(int64_t work, int64_t narrow) { return work + narrow * 2 / 5 < (int64_t)kWgradBlocks * 128; }
 // Whether the layers collected so far are a launch: tiles enough without a split, or enough work for every compute unit to be busy
 // some 20 us (96 steps in each of 512 workgroups), or as much as the pass still has to collect and worth a launch, or all of them:
 // launches run beside the data gradients of the layers in front, and what is launched at the end of the pass runs beside nothing (two

@@ -1112,9 +1112,10 @@ static int backward_run(const cd_model* m, const void* params, const void* x, in
     const WgradShape h = conv_wgrad_shape(gp, 1, m->ops[i].pb >= 0);
     if (use_mfma(m, g) && waits(g, h)) pending[h.tile_class()].work_left += h.tiles() * h.steps();
   }
-  int64_t waiting = 0;
+  int64_t waiting = 0, narrow = 0;
   for (const PendingWgrads& q : pending) waiting += q.work_left;
-  const bool together = streams == CD_STREAMS_AUTO && wgrad_together(waiting);
+  for (int k = 0; k < 4; k++) narrow += pending[k].work_left;   // (WgradShape::tile_class: 64 rows of dw to a tile)
+  const bool together = streams == CD_STREAMS_AUTO && wgrad_together(waiting, narrow);
   // Launches them, on the second stream behind what the caller's stream holds so far; where the runtime refuses the event or the wait,
   // and at the end of the pass (`last`: nothing is left that they could run beside), on the caller's stream (whose partials area is free
   // between two ops).  Returns the stream.
