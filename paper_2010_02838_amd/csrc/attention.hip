@@ -430,8 +430,10 @@ template <int DH> struct RowStage {
 // One wave: 32 queries on the lanes.  Per chunk of 64 keys: S^T = K Q^T (two 32-key tiles), online softmax per
 // lane (the two half-waves of a query exchange their maxima; their partial sums are added at the end),
 // O^T += V^T P^T with P rounded to bf16.
+// (Three workgroups per compute unit, registers held to 168: 912 workgroups of a packed step were two rounds of 512 with 192, 18.4 -> 16.9 us
+// a launch; four, held to 128, 17.7 and on padded sentences slower than with two.)
 template <int DH>
-__global__ void __launch_bounds__(256) attn_fwd_mfma_k(AttArgs a) {
+__global__ void __launch_bounds__(256, 3) attn_fwd_mfma_k(AttArgs a) {
   constexpr int KS = DH / 16, DT = DH / 32;
   __shared__ __attribute__((aligned(16))) bf16_t Ks[MF_ROWS * MF_PITCH];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[MF_ROWS * MF_PITCH];
