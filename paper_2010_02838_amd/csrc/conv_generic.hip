@@ -52,6 +52,7 @@ struct GenArgs {
   int H, W, Cin, Ho, Wo, Cout, kh, kw, stride, pad;
   int relu, accumulate;
   int m_per_split, ktiles, tiles;   // wgrad
+  float* sums;       // fprop, nullable: column sums and sums of squares of the stored values, a row block each: [blocks][stat_pitch(N)]
 };
 struct GenNormArgs : GenArgs { EvalNorm norm; };   // fprop with the evaluation-mode BatchNorm that follows
 
@@ -112,12 +113,25 @@ template <typename T> __device__ inline float gen_wgrad_element(const GenArgs& a
   return acc;
 }
 
+// the sum over the sixteen lanes of a row, in every one of them
+template <int CTRL> __device__ inline float dpp_add(float v) {
+  return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ inline float sum16(float v) {
+  v = dpp_add<0xB1>(v);    // quad_perm [1,0,3,2]
+  v = dpp_add<0x4E>(v);    // quad_perm [2,3,0,1]
+  v = dpp_add<0x141>(v);   // row_half_mirror
+  return dpp_add<0x140>(v);   // row_mirror
+}
+
 // MODE 0: fprop, MODE 1: dgrad.  Block = 4 waves down the rows, each 16 TM rows x 16 TN columns; 32 contraction elements
 // per step, two LDS buffers, the next step's elements travel in registers while the matrix cores work on this one.  The
 // filter is the MFMA "A" operand, so a lane's four accumulators are four consecutive channels of one pixel.  A lane reads
 // its four k of a 16-element chunk as one 16-byte LDS load; element k of a chunk lies at place 4 (k % 4) + k / 4, so that
 // instruction j takes k = 4 j + lane / 16: the sums run over k in ascending order, tap by tap, as the definition and the
 // plain kernels add them.  Rows are 36 floats apart: 16 rows start in 16 different 16-byte bank groups.
+// A BatchNorm behind the convolution gets its column sums here (GenArgs::sums): a pass of its own over the tensor was 4 to 8 us and a launch
+// (two-block fp32 network on 32 images of 32x32: six of them, 231 -> 218 us a pass; the sums add 0.5 us to a convolution).
 // VEC: channels per load (4 where both channel counts allow it).  NORM (fprop): the evaluation-mode BatchNorm behind it is applied
 // to the values as they are stored.
 template <typename T, int MODE, int VEC, int TM, int TN, bool NORM>
@@ -298,6 +312,14 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
                               &nsc[i][q], &nsh[i][q]);
       }
   }
+  constexpr bool SUMS = MODE == 0 && !NORM;
+  float cs0[SUMS ? TN : 1][4], cs1[SUMS ? TN : 1][4];   // this lane's channels, summed over its rows
+  if (SUMS) {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) { cs0[i][q] = 0.f; cs1[i][q] = 0.f; }
+  }
 #pragma unroll
   for (int j = 0; j < TM; j++) {
     const int m = m0 + (wave * TM + j) * 16 + fr;
@@ -332,6 +354,14 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
           if (MODE == 0) v[q] = a.relu ? fmaxf(v[q], 0.f) : v[q];
         }
       }
+      if constexpr (SUMS) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          const float t = Cvt<T>::ld(Cvt<T>::st(v[q]));   // (a channel behind the last one is a sum of zeros)
+          cs0[i][q] += t;
+          cs1[i][q] = fmaf(t, t, cs1[i][q]);
+        }
+      }
       if ((a.N & 3) == 0) {   // four channels of a pixel at a 4-element boundary
         if (sizeof(T) == 4) {
           *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
@@ -346,6 +376,7 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
       }
     }
   }
+  const int again_any = again != 0;
   if (__builtin_expect(__any(again != 0), 0)) {
     while (again) {
       const int e = __ffs(again) - 1;
@@ -363,6 +394,41 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
         v = gen_norm<T>(a, v, sc, sh, r);
       }
       *o = Cvt<T>::st(v);
+    }
+  }
+  if constexpr (SUMS) {
+    if (a.sums) {   // uniform over the launch
+      // the sixteen lanes of a channel, then the four waves, in a fixed order
+      float* red = &As[0][0];   // [wave][2][BN]; (the main loop ends with a barrier)
+#pragma unroll
+      for (int i = 0; i < TN; i++)
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          const float t0 = sum16(cs0[i][q]), t1 = sum16(cs1[i][q]);
+          if (fr == 0) {
+            red[(wave * 2 + 0) * BN + i * 16 + fk + q] = t0;
+            red[(wave * 2 + 1) * BN + i * 16 + fk + q] = t1;
+          }
+        }
+      const bool recomputed = __syncthreads_or(again_any);
+      if (__builtin_expect(recomputed, 0)) __syncthreads();   // (and what was stored is there)
+      if (tid < BN && n0 + tid < a.N) {
+        float t0 = 0.f, t1 = 0.f;
+        if (__builtin_expect(recomputed, 0)) {   // elements were computed again behind the sums: take them from what was stored
+          const int end = a.M - m0 < BM ? a.M - m0 : BM;
+          for (int r = 0; r < end; r++) {
+            const float t = Cvt<T>::ld(out[(unsigned)(m0 + r) * (unsigned)a.N + (unsigned)(n0 + tid)]);
+            t0 += t;
+            t1 = fmaf(t, t, t1);
+          }
+        } else {
+#pragma unroll
+          for (int w = 0; w < 4; w++) { t0 += red[(w * 2 + 0) * BN + tid]; t1 += red[(w * 2 + 1) * BN + tid]; }
+        }
+        float* o = a.sums + (int64_t)blockIdx.x * stat_pitch(a.N) + n0 + tid;
+        o[0] = t0;
+        o[a.N] = t1;
+      }
     }
   }
 }
@@ -638,8 +704,8 @@ static void fprop_generic_t(const std::conditional_t<NORM, GenNormArgs, GenArgs>
   if (v4) launch_generic<T, 0, 4, NORM>(a, s); else launch_generic<T, 0, 1, NORM>(a, s);
 }
 
-void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
-                        hipStream_t s, const EvalNorm* norm) {
+int conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
+                       hipStream_t s, const EvalNorm* norm, float* stat_partials, size_t stat_bytes) {
   GenNormArgs a = {gen_args(g), {}};
   a.src = x; a.w = w; a.bias = bias; a.out = y; a.relu = relu;
   a.M = (int)g.M(); a.N = g.Cout; a.K = g.K();
@@ -647,9 +713,12 @@ void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bia
   if (norm) {
     a.norm = *norm;
     if (dtype == CD_BF16) fprop_generic_t<bf16_t, true>(a, v4, s); else fprop_generic_t<float, true>(a, v4, s);
-  } else {
-    if (dtype == CD_BF16) fprop_generic_t<bf16_t, false>(a, v4, s); else fprop_generic_t<float, false>(a, v4, s);
+    return 0;
   }
+  const int64_t chunks = cdiv(a.M, generic_tall_tiles(a.M, a.N, v4) ? 128 : 64);
+  if (stat_partials && (size_t)(chunks + kFoldChunks) * stat_pitch(a.N) * sizeof(float) <= stat_bytes) a.sums = stat_partials;
+  if (dtype == CD_BF16) fprop_generic_t<bf16_t, false>(a, v4, s); else fprop_generic_t<float, false>(a, v4, s);
+  return a.sums ? (int)chunks : 0;
 }
 
 void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, const ConvGeom& g, bool accumulate, hipStream_t s) {

@@ -46,8 +46,8 @@ void conv_wgrad_simple(int dtype, const void* x, const void* dy, float* dw, cons
 // kernels above remain for CODISTILL_FORCE_SIMPLE, for tensors of 2^31 elements or 2^30 pixels and more (generic_conv_fits) and
 // for weight gradients of few weights over few pixels (generic_wgrad_pays).
 bool conv_generic_supported(const ConvGeom& g);
-void conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
-                        hipStream_t s, const EvalNorm* norm = nullptr);
+int conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias, void* y, const ConvGeom& g, bool relu,
+                       hipStream_t s, const EvalNorm* norm = nullptr, float* stat_partials = nullptr, size_t stat_bytes = 0);
 void conv_dgrad_generic(int dtype, const void* dy, const void* w, void* dx, const ConvGeom& g, bool accumulate, hipStream_t s);
 // The weight gradients of several layers, and the bias gradients db (nullable, [Cout]) with them, in a launch per 16 layers and one that
 // adds up their splits.  partials: scratch for the split sums (as many fp32 copies of dw as splits; without room for two a layer is not split)

@@ -926,7 +926,10 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
           if (use_generic(g)) {
             const bool normed = eval_norm(oi, &norm);
             if (normed) out = c.act(m->ops[oi + 1].y);
-            conv_fprop_generic(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s, normed ? &norm : nullptr);
+            const bool fuse = bn_mode == CD_BN_BATCH_STATS && oi + 1 < m->ops.size() && m->ops[oi + 1].kind == OP_BN && m->ops[oi + 1].x == o.y;
+            stat_chunks = conv_fprop_generic(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s, normed ? &norm : nullptr,
+                                             fuse ? c.partials() : nullptr, c.plan.partials_bytes);
+            stat_tensor = stat_chunks ? o.y : -1;
             if (normed) oi++;
           } else conv_fprop_simple(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s);
         }

@@ -182,3 +182,30 @@ def test_bias_gradients_with_the_weight_gradients(dtype, widths, batch, h, w):
             dy = ws[t["grad_offset"]:t["grad_offset"] + n].view(dt).view(-1, t["c"]).double()
             got = grads[p["offset"]:p["offset"] + p["size"]].double()
             assert bool(((got - dy.sum(0)).abs() <= 9 * 2.0 ** -24 * dy.abs().sum(0)).all())
+
+
+@pytest.mark.parametrize("dtype,tol", [("f32", 1e-4), ("bf16", 3e-2)])
+@pytest.mark.parametrize("width,batch,hw", [(12, 69, 31), (36, 5, 17), (5, 3, 13)])
+@pytest.mark.parametrize("odd", [False, True])
+def test_statistics_from_the_convolution(dtype, tol, width, batch, hw, odd):
+    """The first BatchNorm's mean and 1 / sqrt(var + eps) from the column sums that the convolution left (128- and 64-row blocks, ragged last ones, one
+    and four channels per load) against float64 sums of what it stored; odd: an infinite pixel, whose channels' elements are computed again from
+    their definition behind the sums."""
+    n = _Net(dtype, batch, hw, hw, kind=1, widths=[width], blocks=[1], stem_width=width)
+    if odd:
+        n.x[batch - 1, 1, 2, 0] = float("inf")
+    n.pass_(n.flat)
+    conv, bn = n.ops[0], n.ops[1]
+    assert conv["kind"] == "conv" and bn["kind"] == "bn"
+    x, y = n.read(conv["y"], "act_offset"), n.read(bn["y"], "act_offset")
+    with np.errstate(all="ignore"):
+        mean, var = x.mean((0, 1, 2)), x.var((0, 1, 2))
+        g, b = n.param(n.flat, bn["param_w"]), n.param(n.flat, bn["param_b"])
+        want = np.maximum((x - mean) / np.sqrt(var + 1e-5) * g + b, 0)
+    if not odd:
+        assert np.isfinite(want).all() and rel(y, want) <= tol
+    else:   # a channel that sees the pixel has no finite statistics
+        bad = ~np.isfinite(x).all((0, 1, 2))
+        assert bad.any()
+        assert not (np.isfinite(y).all((0, 1, 2)) & (y.std((0, 1, 2)) > 0))[bad].any()
+        assert bad.all() or rel(y[..., ~bad], want[..., ~bad]) <= tol
