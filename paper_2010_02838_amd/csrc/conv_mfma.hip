@@ -49,6 +49,7 @@ struct IgemmArgs {
   int src_pitch = 0;   // 0: Cs (an ordinary convolution)
   int sliced = 0;
   int pointwise;  // kh = kw = 1, stride 1, no padding (set by the launcher)
+  FastDiv div_w = {0, 0}, div_h = {0, 0};   // by Wd and Hd (set by the launcher)
   int group_m;    // GROUP kernels: tile order in groups of this many row tiles
   int ntiles;
   uint32_t src_bytes, wt_bytes;
@@ -79,6 +80,9 @@ __device__ inline unsigned xcd_remap(unsigned bid, unsigned nblocks) {
   const unsigned per = nblocks >> 3, rem = nblocks & 7u;
   return xcd * per + (xcd < rem ? xcd : rem) + idx;
 }
+
+// n / d for n < 2^31 (fast_div)
+__device__ inline unsigned div_by(unsigned n, FastDiv f) { return __umulhi(n << 1, f.mul) >> f.shift; }
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -250,23 +254,19 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
       continue;
     }
     const unsigned mm = rowok ? (unsigned)m : 0u;
-    const unsigned q = mm / (unsigned)a.Wd;
+    const unsigned q = div_by(mm, a.div_w);
     const int wd = (int)(mm - q * (unsigned)a.Wd);
-    const int b = (int)(q / (unsigned)a.Hd);
+    const int b = (int)div_by(q, a.div_h);
     const int hd = (int)(q - (unsigned)b * (unsigned)a.Hd);
     const int hh = MODE == 0 ? hd * a.stride - a.pad : hd + a.pad;
     const int ww = MODE == 0 ? wd * a.stride - a.pad_w : wd + a.pad_w;
-    uint32_t hm = 0, wm = 0;
-    for (int r = 0; r < a.kh; r++) {
-      const int hs = MODE == 0 ? hh + r : hh - r;
-      if (hs >= 0 && hs < a.Hs) hm |= 1u << r;
-    }
-    for (int t = 0; t < a.kw; t++) {
-      const int ws = MODE == 0 ? ww + t : ww - t;
-      if (ws >= 0 && ws < a.Ws) wm |= 1u << t;
-    }
-    hmask[j] = rowok ? hm : 0u;
-    wmask[j] = wm;
+    // taps that read inside: bits lo .. hi - 1 (0 <= h + r < n forwards, 0 <= h - r < n backwards; at most 7 taps)
+    auto taps = [](int h, int n, int k) {
+      const int lo = min(max(MODE == 0 ? -h : h - n + 1, 0), 31), hi = min(max(MODE == 0 ? n - h : h + 1, 0), k);
+      return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+    };
+    hmask[j] = rowok ? taps(hh, a.Hs, a.kh) : 0u;
+    wmask[j] = taps(ww, a.Ws, a.kw);
     rowoff[j] = ((b * a.Hs + hh) * a.Ws + ww) * P + cs0;
   }
   // byte offset of this thread's filter row (+ its 16-byte column); rows past N start beyond every buffer's end (operands
@@ -689,9 +689,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
       if (m < M && n < a.N && lane_ok && row < EROWS) {
         uint4 v = *reinterpret_cast<const uint4*>(stage + row * EPITCH + ec);
         if (REMAP) {  // strided placement of the rows (parity class of a stride-2 dgrad)
-          const unsigned q = (unsigned)m / (unsigned)a.Wd;
+          const unsigned q = div_by((unsigned)m, a.div_w);
           const int wd = m - (int)(q * (unsigned)a.Wd);
-          const int b = (int)(q / (unsigned)a.Hd);
+          const int b = (int)div_by(q, a.div_h);
           const int hd = (int)q - b * a.Hd;
           m = (b * a.Ho + hd * a.omul + a.ooff_h) * a.Wo + wd * a.omul + a.ooff_w;
         }
@@ -864,6 +864,8 @@ static int launch_igemm_w(IgemmArgs a, hipStream_t s) {
   a.pointwise = (a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.pad_w == 0 && a.Hs == a.Hd &&
                  a.Ws == a.Wd) ? 1 : 0;
   a.group_m = 1;
+  a.div_w = fast_div((uint32_t)a.Wd);
+  a.div_h = fast_div((uint32_t)a.Hd);
   if (a.sliced) {   // grouped convolution: one column tile per slice of Cs = 32 or 64 channels
     if (a.Cs == 64) return launch_tile<MODE, 256, 64, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);
     return launch_tile<MODE, 256, 32, 4, 1, STATS, NWRAP, REMAP, EPI, 32, 3>(a, s);

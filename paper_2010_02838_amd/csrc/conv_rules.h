@@ -7,6 +7,17 @@
 
 namespace cd {
 
+// ---- division by a number that is the same for a whole launch -----------------------------------------------------------------
+// n / d for n < 2^31, d >= 1 as (2 n mul / 2^32) >> shift: with 2^shift >= d > 2^(shift - 1) and mul = ceil(2^(31 + shift) / d) < 2^32 the
+// excess mul d - 2^(31 + shift) is less than d <= 2^shift, so n times it stays below 2^(31 + shift).
+struct FastDiv { uint32_t mul, shift; };
+inline FastDiv fast_div(uint32_t d) {
+  FastDiv f = {0, 0};
+  while ((1ull << f.shift) < d) f.shift++;
+  f.mul = (uint32_t)(((1ull << (31 + f.shift)) + d - 1) / d);
+  return f;
+}
+
 // ---- output tile of the matrix-core convolutions (conv_mfma.hip) ------------------------------------------------------------
 // Tiles, measured with random operands that come from memory (constant ones leave the matrix cores a higher clock), on the
 // layer shapes of ResNet-50 at batch 256 and 50, Wide-ResNet at 96 and the Transformer (us):

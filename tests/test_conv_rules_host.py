@@ -82,6 +82,28 @@ def test_generic_convolutions_stay_within_the_launch_limits(generic_fits, geom, 
         assert threads < 2 ** 32 and blocks_y <= 65535
 
 
+def test_division_by_a_launch_constant(tmp_path):
+    """Quotients below, at and above multiples, at the largest dividend, for small, odd, two's-power and very large divisors."""
+    assert compiled(tmp_path, """
+int main() {
+  auto div = [](unsigned n, FastDiv f) { return (unsigned)(((unsigned long long)(n << 1) * f.mul) >> 32) >> f.shift; };
+  for (unsigned d = 1; d < 4000; d++) {
+    const FastDiv f = fast_div(d);
+    for (unsigned k : {0u, 1u, 2u, 7u, 1000u, 2147483647u / d - 1, 2147483647u / d})
+      for (int e = -1; e <= 1; e++) {
+        const long long n = (long long)k * d + e;
+        if (n >= 0 && n < (1ll << 31) && div((unsigned)n, f) != (unsigned)n / d) { printf("%u %lld", d, n); return 0; }
+      }
+    if (div(2147483647u, f) != 2147483647u / d) { printf("%u", d); return 0; }
+  }
+  for (unsigned d : {65535u, 65536u, 65537u, 1000003u, 1073741823u, 1073741824u, 1073741825u, 2147483647u, 2147483648u})
+    for (unsigned n : {0u, 1u, d - 1, d, 2147483647u, 1073741824u})
+      if (n < (1u << 31) && div(n, fast_div(d)) != n / d) { printf("%u %u", d, n); return 0; }
+  printf("ok");
+}
+""")() == "ok"
+
+
 SQUARE, TALL, WIDE, NARROW, SMALL = range(5)
 
 
