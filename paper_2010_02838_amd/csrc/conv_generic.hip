@@ -52,6 +52,7 @@ struct GenArgs {
   int H, W, Cin, Ho, Wo, Cout, kh, kw, stride, pad;
   int relu, accumulate;
   int m_per_split, ktiles, tiles;   // wgrad
+  FastDiv by_cin, by_cout, by_kw, by_stride, by_w, by_h, by_wo, by_ho;
   float* sums;       // fprop, nullable: column sums and sums of squares of the stored values, a row block each: [blocks][stat_pitch(N)]
 };
 struct GenNormArgs : GenArgs { EvalNorm norm; };   // fprop with the evaluation-mode BatchNorm that follows
@@ -155,9 +156,9 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
   for (int j = 0; j < AP; j++) {
     const int m = m0 + ar + j * RPP;
     const unsigned mm = m < a.M ? (unsigned)m : 0u;
-    const unsigned q = mm / (unsigned)WD;
+    const unsigned q = div_by(mm, MODE == 0 ? a.by_wo : a.by_w);
     const int x = (int)(mm - q * (unsigned)WD);
-    const unsigned b = q / (unsigned)HD;
+    const unsigned b = div_by(q, MODE == 0 ? a.by_ho : a.by_h);
     const int y = (int)(q - b * (unsigned)HD);
     pb[j] = (int)b * HS;
     ph[j] = MODE == 0 ? y * a.stride - a.pad : y + a.pad;
@@ -169,8 +170,8 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
   auto gload = [&](int kt) {
     {
       const int k = kt * BK + kv * VEC;
-      const unsigned tap = (unsigned)k / (unsigned)CS;
-      const int c = k - (int)tap * CS, r = (int)(tap / (unsigned)a.kw), s = (int)tap - r * a.kw;
+      const unsigned tap = div_by((unsigned)k, MODE == 0 ? a.by_cin : a.by_cout);
+      const int c = k - (int)tap * CS, r = (int)div_by(tap, a.by_kw), s = (int)tap - r * a.kw;
 #pragma unroll
       for (int j = 0; j < AP; j++) {
         int h, w;
@@ -182,7 +183,7 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
           h = ph[j] - r; w = pw[j] - s;
           ok = ok && h >= 0 && w >= 0;
           if (a.stride != 1) {
-            const int hq = h / a.stride, wq = w / a.stride;
+            const int hq = (int)div_by((unsigned)h, a.by_stride), wq = (int)div_by((unsigned)w, a.by_stride);   // (negative ones are out already)
             ok = ok && hq * a.stride == h && wq * a.stride == w;
             h = hq; w = wq;
           }
@@ -207,7 +208,7 @@ __global__ void __launch_bounds__(256) conv_generic_k(std::conditional_t<NORM, G
 #pragma unroll
       for (int j = 0; j < FP; j++) {
         const int kr = tid / CV + j * FRPP, k = kt * BK + kr;
-        const unsigned tap = (unsigned)k / (unsigned)CS;
+        const unsigned tap = div_by((unsigned)k, a.by_cout);
         const int n = k - (int)tap * CS;
 #pragma unroll
         for (int i = 0; i < VEC; i++) rb[j][i] = 0.f;
@@ -452,6 +453,7 @@ struct GenWgradJob : GenArgs {
 };
 constexpr int kGenWgradJobs = 16;
 struct GenWgradBatch { GenWgradJob j[kGenWgradJobs]; int n; };
+static_assert(sizeof(GenWgradBatch) <= 4096, "the table travels in the kernel arguments");
 // LDS floats of a tile shape
 template <int TN, int TK> constexpr int gen_wgrad_floats() {
   constexpr int BN = 16 * TN, BKK = 16 * TK, PN = TN == 1 ? 16 : BN + 16, PK = TK == 1 ? 16 : BKK + 16;
@@ -478,15 +480,15 @@ __device__ inline void gen_wgrad_tile(const GenWgradJob& a, const unsigned wg, f
   const int xv = tid % KVN, xr = tid / KVN;
   const int k = k0 + xv * VEC;
   const bool kok = k < a.K;
-  const int tap = kok ? k / a.Cin : 0;
-  const int kc = k - tap * a.Cin, kr = tap / a.kw, ks = tap - kr * a.kw;
+  const int tap = kok ? (int)div_by((unsigned)k, a.by_cin) : 0;
+  const int kc = k - tap * a.Cin, kr = (int)div_by((unsigned)tap, a.by_kw), ks = tap - kr * a.kw;
   int pb[XP], ph[XP], pw[XP];
 #pragma unroll
   for (int j = 0; j < XP; j++) {
     const unsigned m = (unsigned)(mbeg + xr + j * XR);
-    const unsigned q = m / (unsigned)a.Wo;
+    const unsigned q = div_by(m, a.by_wo);
     pw[j] = (int)(m - q * (unsigned)a.Wo);
-    pb[j] = (int)(q / (unsigned)a.Ho);
+    pb[j] = (int)div_by(q, a.by_ho);
     ph[j] = (int)(q - (unsigned)pb[j] * (unsigned)a.Ho);
   }
   // one step moves every row MS pixels on: whole images, then whole rows, then columns
@@ -672,6 +674,9 @@ static GenArgs gen_args(const ConvGeom& g) {
   GenArgs a = {};
   a.H = g.H; a.W = g.W; a.Cin = g.Cin; a.Ho = g.Ho; a.Wo = g.Wo; a.Cout = g.Cout;
   a.kh = g.kh; a.kw = g.kw; a.stride = g.stride; a.pad = g.pad;
+  a.by_cin = fast_div((uint32_t)g.Cin); a.by_cout = fast_div((uint32_t)g.Cout); a.by_kw = fast_div((uint32_t)g.kw);
+  a.by_stride = fast_div((uint32_t)g.stride);
+  a.by_w = fast_div((uint32_t)g.W); a.by_h = fast_div((uint32_t)g.H); a.by_wo = fast_div((uint32_t)g.Wo); a.by_ho = fast_div((uint32_t)g.Ho);
   return a;
 }
 

@@ -81,9 +81,6 @@ __device__ inline unsigned xcd_remap(unsigned bid, unsigned nblocks) {
   return xcd * per + (xcd < rem ? xcd : rem) + idx;
 }
 
-// n / d for n < 2^31 (fast_div)
-__device__ inline unsigned div_by(unsigned n, FastDiv f) { return __umulhi(n << 1, f.mul) >> f.shift; }
-
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 // two floats -> two bf16 (round to nearest even) in one instruction
@@ -1330,6 +1327,7 @@ struct WgradJob {
   // dy and [s * Cin, (s + 1) * Cin) of x, both row-major with `pitch` channels per pixel (N = Cin = the slice width).
   // An ordinary convolution: one slice, x_pitch = Cin, dy_pitch = N.
   int slices, x_pitch, dy_pitch;
+  FastDiv div_wo, div_ho, div_cin, div_kw;
   uint32_t x_bytes, dy_bytes;
   uint32_t first;     // workgroups of the jobs in front of this one
 };
@@ -1387,17 +1385,17 @@ __global__ void __launch_bounds__(256, NJ > 1 ? 2 : 1) wgrad_kernel(WgradBatch<N
   // PW: byte offset of vector 0.  Otherwise: the tap and channel of this thread's column, and each row's pixel
   uint32_t xoff = ((uint32_t)xm * (uint32_t)a.x_pitch + (uint32_t)(xc0 + k)) * 2u;
   const uint32_t xstep = (uint32_t)WG_MS * (uint32_t)a.x_pitch * 2u, xrstep = (uint32_t)XROWS * (uint32_t)a.x_pitch * 2u;
-  const int tap = PW || xnot ? 0 : k / a.Cin;
-  const int kc = k - tap * a.Cin, kr = PW ? 0 : tap / a.kw, ks = tap - kr * (PW ? 0 : a.kw);
+  const int tap = PW || xnot ? 0 : (int)div_by((unsigned)k, a.div_cin);
+  const int kc = k - tap * a.Cin, kr = PW ? 0 : (int)div_by((unsigned)tap, a.div_kw), ks = tap - kr * (PW ? 0 : a.kw);
   int pb[PW ? 1 : XV], ph[PW ? 1 : XV], pw[PW ? 1 : XV];
   int adv_b = 0, adv_h = 0, adv_w = 0;
   if (!PW) {
 #pragma unroll
     for (int j = 0; j < XV; j++) {
       const unsigned m = (unsigned)(xm + XROWS * j);
-      const unsigned q = m / (unsigned)a.Wo;
+      const unsigned q = div_by(m, a.div_wo);
       pw[j] = (int)(m - q * (unsigned)a.Wo);
-      pb[j] = (int)(q / (unsigned)a.Ho);
+      pb[j] = (int)div_by(q, a.div_ho);
       ph[j] = (int)(q - (unsigned)pb[j] * (unsigned)a.Ho);
     }
     // one step moves every row WG_MS pixels on: whole images, then whole rows, then columns
@@ -1711,6 +1709,8 @@ static void wgrad_run(const WgradProblem* p, int n, int pitch, float* partials, 
     a.x = p[k].x; a.dy = p[k].dy;
     a.M = (int)h.M; a.N = h.N; a.K = h.K;
     a.H = g.H; a.W = g.W; a.Cin = g.Cin; a.Ho = g.Ho; a.Wo = g.Wo; a.kw = g.kw; a.stride = g.stride; a.pad = g.pad;
+    a.div_wo = fast_div((uint32_t)g.Wo); a.div_ho = fast_div((uint32_t)g.Ho);
+    a.div_cin = fast_div((uint32_t)g.Cin); a.div_kw = fast_div((uint32_t)g.kw);
     a.slices = h.slices;
     a.x_pitch = h.slices > 1 ? pitch : g.Cin;
     a.dy_pitch = h.slices > 1 ? pitch : g.Cout;

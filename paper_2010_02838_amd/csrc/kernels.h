@@ -3,9 +3,13 @@
 // are always fp32.  Nothing here allocates or synchronises.
 #pragma once
 #include "common.h"
+#include "conv_rules.h"
 #include <vector>
 
 namespace cd {
+
+// n / d for n < 2^31, f = fast_div(d)
+__device__ inline unsigned div_by(unsigned n, FastDiv f) { return __umulhi(n << 1, f.mul) >> f.shift; }
 
 struct ConvGeom {
   int64_t B;
