@@ -132,7 +132,11 @@ __device__ inline float sum16(float v) {
 // instruction j takes k = 4 j + lane / 16: the sums run over k in ascending order, tap by tap, as the definition and the
 // plain kernels add them.  Rows are 36 floats apart: 16 rows start in 16 different 16-byte bank groups.
 // A BatchNorm behind the convolution gets its column sums here (GenArgs::sums): a pass of its own over the tensor was 4 to 8 us and a launch
-// (two-block fp32 network on 32 images of 32x32: six of them, 231 -> 218 us a pass; the sums add 0.5 us to a convolution).
+// (two-block fp32 network on 32 images of 32x32: six of them, 231 -> 218 us a pass; the sums add 0.5 us to a convolution).  What is left is
+// added up in fp64, as the reduction pass's sums are: by the BatchNorm's own pass (bn_own_sums) or by a finalize launch, of more than
+// kFinalizeChunks partial sums behind a fold.  (Folded in fp32 from 256 on, images of 250 +- 2 had a variance off by 2e-4 on 33 of 32x32.)  That
+// network on 33, 65 and 128 images 285 -> 225 us, 365 -> 294, 463 -> 405
+// (generic_sums_pay).
 // VEC: channels per load (4 where both channel counts allow it).  NORM (fprop): the evaluation-mode BatchNorm behind it is applied
 // to the values as they are stored.
 template <typename T, int MODE, int VEC, int TM, int TN, bool NORM>
@@ -721,7 +725,9 @@ int conv_fprop_generic(int dtype, const void* x, const void* w, const void* bias
     return 0;
   }
   const int64_t chunks = cdiv(a.M, generic_tall_tiles(a.M, a.N, v4) ? 128 : 64);
-  if (stat_partials && (size_t)(chunks + kFoldChunks) * stat_pitch(a.N) * sizeof(float) <= stat_bytes) a.sums = stat_partials;
+  if (stat_partials && generic_sums_pay(a.M, a.N, dtype == CD_BF16 ? 2 : 4, chunks) &&
+      (size_t)(chunks + 2 * kFoldChunks) * stat_pitch(a.N) * sizeof(float) <= stat_bytes)
+    a.sums = stat_partials;
   if (dtype == CD_BF16) fprop_generic_t<bf16_t, false>(a, v4, s); else fprop_generic_t<float, false>(a, v4, s);
   return a.sums ? (int)chunks : 0;
 }

@@ -288,6 +288,10 @@ constexpr int generic_split_end(int M, int mbeg, int m_per_split) {
 // ---- elementwise passes of the BatchNorms (norm.hip) --------------------------------------------------------------------------
 // Channels are cut into groups of at most 64, a block takes one of them for all of its rows.
 constexpr int kFoldChunks = 32;   // chunks that long lists of partial sums are folded into
+// Lists that col_finalize_k adds up (in fp64) without a fold in front.  In the backward pass the fold, 5 us and a gap in front of a finalize
+// of 5, pays from about 1600 chunks on: 72, 136 and 256 channels, from the first launch to the end of the last, with it and without:
+// 1024 chunks 10 us and 5.8 to 7.4, 1536 chunks 10 and 8.5 to 10, 2048 chunks 10 and 11.3 to 12.7, 4096 chunks 10 and 21 to 23.
+constexpr int kFinalizeChunks = 1600;
 // Small tensors' blocks add up the partial sums of their channels themselves, 64 KB at the most, 16 loads a thread.  ResNet-20 at
 // batch 128 (0.5 to 4 MB): 240 -> 178 launches, 1330 -> 1192 us a step (1214 with up to 32 KB); a two-block fp32 network (2 MB) 318 -> 309.
 // Larger ones lose: 2048 blocks of several trips in ResNet-50 at batch 256, the sums folded to 16 KB for each: forward passes 41 -> 53 us,
@@ -305,6 +309,11 @@ constexpr int64_t kSumTensor = 8 << 20;
 inline bool bn_own_sums(int64_t M, int C, int esize, BnGroups g, int chunks) {
   return (int64_t)chunks * g.gc * 8 <= kSumBytes && M * C * esize <= kSumTensor;
 }
+// Whether a generic convolution leaves that many partial sums for the BatchNorm behind it.  More than a finalize takes need a fold, and where the
+// elementwise pass adds up a reduction's sums by itself (kSumTensor) that is a launch more than the reduction: one layer of 16 channels on 128 images
+// of 32x32 (2048 chunks, 8 MB).  Larger tensors have a finalize either way, and the fold is shorter than reading them: two-block fp32 network on
+// 400 images, three such layers, 909 us with the reduction, 904 with the fold.
+inline bool generic_sums_pay(int64_t M, int C, int esize, int64_t chunks) { return chunks <= kFinalizeChunks || M * C * esize > kSumTensor; }
 // blocks over M rows: a trip of `unroll` rows a thread
 inline int64_t bn_blocks(int64_t M, BnGroups g, int vec, int unroll) {
   const int64_t rows = (int64_t)(256 / (g.gc / vec)) * unroll;

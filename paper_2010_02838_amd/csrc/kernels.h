@@ -66,13 +66,14 @@ void colsum(int dtype, const void* a, int64_t M, int C, float* out, float* parti
 // forward pass writes it, the backward pass reads it instead of y (an eighth of a byte per element
 // instead of two bytes, in both of its passes).
 // pre_chunks > 0: the column sums of x are already in partials ([pre_chunks][stat_pitch(C)], from the producing convolution, with
-// room for 32 * stat_pitch(C) floats behind them); pre_chunks == 0: x is reduced first (partials is scratch).
+// room for 32 * stat_pitch(C) floats behind them); pre_chunks == 0: x is reduced first (partials is scratch).  exact: the sums are added up
+// in fp64 however many they are (those of conv_fprop_generic; room for 64 rows behind them).
 // running (nullable): the running averages, updated with momentum 0.1.
 void bn_forward(int dtype, const void* x, const void* res, bool relu, void* y, const void* gamma, const void* beta, int64_t M, int C,
-                float* stats, float* partials, int pre_chunks, uint8_t* relu_mask, float* running, hipStream_t s);
+                float* stats, float* partials, int pre_chunks, bool exact, uint8_t* relu_mask, float* running, hipStream_t s);
 // The statistics alone, into stats (in front of bn_relu_pool); scratch: the room behind the sums.
 void bn_stats(int dtype, const void* x, const void* gamma, const void* beta, int64_t M, int C, float* stats,
-              float* partials, int pre_chunks, float* scratch, hipStream_t s);
+              float* partials, int pre_chunks, bool exact, float* scratch, hipStream_t s);
 // Running averages [mean[C] | var[C]] (fp32) for the evaluation mode: updated from the statistics of a training-mode
 // pass over M rows (momentum 0.1, unbiased variance), or turned into stats in place of the batch's.
 void bn_running_update(const float* stats, float* running, int64_t M, int C, float momentum, hipStream_t s);

@@ -819,6 +819,7 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
     sentence_tables(tok + m->arch.in_h, c.positions() + m->arch.in_h, m->arch.in_w, m->arch.max_sentences, c.table(1), c.s);
   }
   int stat_chunks = 0, stat_tensor = -1;  // statistics a convolution left in the partials area for its BatchNorm
+  bool stat_exact = false;                // (they are added up in fp64 only)
   // Evaluation: the BatchNorm right behind a convolution, the tensor's only reader, is applied by the convolution as it stores; the
   // convolution's own output is then not written.  (With the per-launch timer on they stay two launches, so that each class's time
   // is its own.)
@@ -930,6 +931,7 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
             stat_chunks = conv_fprop_generic(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s, normed ? &norm : nullptr,
                                              fuse ? c.partials() : nullptr, c.plan.partials_bytes);
             stat_tensor = stat_chunks ? o.y : -1;
+            stat_exact = true;
             if (normed) oi++;
           } else conv_fprop_simple(dt, in, c.P(o.pw), c.P(o.pb), out, g, o.relu, c.s);
         }
@@ -949,7 +951,7 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
             if (bn_mode == CD_BN_RUNNING) {
               bn_stats_from_running(dt, running, c.P(o.pw), c.P(o.pb), c.stats(o), tx.c, c.s);
             } else {
-              bn_stats(dt, in, c.P(o.pw), c.P(o.pb), M, tx.c, c.stats(o), c.partials(), fused ? stat_chunks : 0,
+              bn_stats(dt, in, c.P(o.pw), c.P(o.pb), M, tx.c, c.stats(o), c.partials(), fused ? stat_chunks : 0, stat_exact,
                        fused ? c.partials() + (size_t)stat_chunks * stat_pitch(tx.c) : nullptr, c.s);
               if (running) bn_running_update(c.stats(o), running, M, tx.c, 0.1f, c.s);
             }
@@ -963,10 +965,11 @@ extern "C" int codistill_forward(const cd_model* m, const void* params, const vo
                        (double)M * tx.c * (m->esize() * (2 + (res ? 1 : 0)) + (o.relu && mask ? 0.125 : 0.0)));
           bn_apply_running(dt, in, res, o.relu, out, M, tx.c, running, c.P(o.pw), c.P(o.pb), c.stats(o), mask, c.s);
         } else {
-          bn_forward(dt, in, res, o.relu, out, c.P(o.pw), c.P(o.pb), M, tx.c, c.stats(o), c.partials(), fused ? stat_chunks : 0, mask,
-                     running, c.s);
+          bn_forward(dt, in, res, o.relu, out, c.P(o.pw), c.P(o.pb), M, tx.c, c.stats(o), c.partials(), fused ? stat_chunks : 0, stat_exact,
+                     mask, running, c.s);
         }
         stat_tensor = -1;
+        stat_exact = false;
         break;
       }
       case OP_LN: {

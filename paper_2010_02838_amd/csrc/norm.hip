@@ -301,31 +301,40 @@ __global__ void __launch_bounds__(kFinalizeCols * kFinalizeLanes) col_finalize_k
 // registers; each thread has UNROLL independent vectors in flight.
 constexpr int kEltUnroll = 4;
 
-// Fold many chunks of partial sums into 32: block = 64 channels x 16 lanes, grid.y = 32 slices.
+// Fold many chunks of partial sums into 32: block = 64 channels x 16 lanes, grid.y = 32 slices.  EXACT: added in fp64 and left as two fp32
+// parts, 32 chunks apart, which the finalize adds up like any other chunks.
+template <bool EXACT>
 __global__ void __launch_bounds__(1024) col_fold_k(const float* __restrict__ partials, int chunks, int C,
                                                    float* __restrict__ out) {
-  __shared__ float sm[2][16][64];
+  typedef std::conditional_t<EXACT, double, float> Sum;
+  __shared__ Sum sm[2][16][64];
   const int cl = threadIdx.x & 63, lane = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + cl;
   const int per = (chunks + gridDim.y - 1) / gridDim.y;
   const int j0 = blockIdx.y * per, j1 = j0 + per < chunks ? j0 + per : chunks;
-  float a0 = 0.f, a1 = 0.f;
+  Sum a0 = 0, a1 = 0;
   if (c < C) {
 #pragma unroll 4
     for (int j = j0 + lane; j < j1; j += 16) {
-      a0 += partials[(int64_t)j * stat_pitch(C) + c];
-      a1 += partials[(int64_t)j * stat_pitch(C) + C + c];
+      a0 += (Sum)partials[(int64_t)j * stat_pitch(C) + c];
+      a1 += (Sum)partials[(int64_t)j * stat_pitch(C) + C + c];
     }
   }
   sm[0][lane][cl] = a0;
   sm[1][lane][cl] = a1;
   __syncthreads();
   if (lane != 0 || c >= C) return;
-  float s0 = 0.f, s1 = 0.f;
+  Sum s0 = 0, s1 = 0;
 #pragma unroll
   for (int j = 0; j < 16; j++) { s0 += sm[0][j][cl]; s1 += sm[1][j][cl]; }
-  out[(int64_t)blockIdx.y * stat_pitch(C) + c] = s0;
-  out[(int64_t)blockIdx.y * stat_pitch(C) + C + c] = s1;
+  float* o = out + (int64_t)blockIdx.y * stat_pitch(C) + c;
+  o[0] = (float)s0;
+  o[C] = (float)s1;
+  if (EXACT) {   // (an infinite sum has no rest)
+    o += (int64_t)kFoldChunks * stat_pitch(C);
+    o[0] = isfinite(s0) ? (float)(s0 - (Sum)(float)s0) : 0.f;
+    o[C] = isfinite(s1) ? (float)(s1 - (Sum)(float)s1) : 0.f;
+  }
 }
 
 // mask (VEC 8 only, nullable): receives one byte per vector, bit k = (y[k] > 0), for the backward pass
@@ -884,21 +893,20 @@ static ReducePlan launch_reduce(const T* a0, const T* a1, const T* a2, const flo
 
 // Where the column sums of M rows lie, and in how many chunks: from the convolution in front (pre_chunks > 0, in partials), or reduced here.
 struct ColSums { const float* part; int chunks; };
-// Folds them into kFoldChunks in scratch where they are more than `most`.  In the backward pass the fold, 5 us and a gap in front of a finalize
-// of 5, pays from about 1600 chunks on: 72, 136 and 256 channels, from the first launch to the end of the last, with it and without:
-// 1024 chunks 10 us and 5.8 to 7.4, 1536 chunks 10 and 8.5 to 10, 2048 chunks 10 and 11.3 to 12.7, 4096 chunks 10 and 21 to 23.
-constexpr int kFinalizeChunks = 1600;
-static ColSums fold_sums(ColSums q, int C, int most, float* scratch, hipStream_t s) {
+// Folds them in scratch where they are more than `most`: into kFoldChunks, exact: into twice as many (col_fold_k).
+static ColSums fold_sums(ColSums q, int C, int most, bool exact, float* scratch, hipStream_t s) {
   if (q.chunks <= most) return q;
-  hipLaunchKernelGGL(col_fold_k, dim3((unsigned)cdiv(C, 64), kFoldChunks), dim3(1024), 0, s, q.part, q.chunks, C, scratch);
-  return {scratch, kFoldChunks};
+  const dim3 grid((unsigned)cdiv(C, 64), kFoldChunks);
+  if (exact) hipLaunchKernelGGL(col_fold_k<true>, grid, dim3(1024), 0, s, q.part, q.chunks, C, scratch);
+  else hipLaunchKernelGGL(col_fold_k<false>, grid, dim3(1024), 0, s, q.part, q.chunks, C, scratch);
+  return {scratch, exact ? 2 * kFoldChunks : kFoldChunks};
 }
 
 // Batch statistics -> stats.  pre_chunks > 0: the column sums are already in partials (written by the
-// producing convolution); otherwise x is reduced first.
+// producing convolution); otherwise x is reduced first.  exact: added up in fp64 throughout, as those of the reduction are.
 template <typename T>
 static void bn_stats_t(const T* x, const T* gamma, const T* beta, int64_t M, int C, float* stats, float* partials,
-                       int pre_chunks, float* scratch, hipStream_t s) {
+                       int pre_chunks, bool exact, float* scratch, hipStream_t s) {
   const int vec = pick_vec<T>(C, x, nullptr, nullptr, nullptr);
   constexpr int V = sizeof(T) == 2 ? 8 : 4;
   ColSums q = {partials, pre_chunks};
@@ -906,9 +914,9 @@ static void bn_stats_t(const T* x, const T* gamma, const T* beta, int64_t M, int
     q.chunks = (vec > 1 ? launch_reduce<T, V, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)
                         : launch_reduce<T, 1, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s)).chunks;
   else
-    // (more than 256 of a convolution's partial sums are folded first, here, although up to kFinalizeChunks the fold is the longer way in the
+    // (more than 256 of a bf16 matrix-core convolution's are folded first, here, although up to kFinalizeChunks the fold is the longer way in the
     // forward pass too: in another order the statistics differ in the last place and all roundings behind them move)
-    q = fold_sums(q, C, 256, scratch, s);
+    q = fold_sums(q, C, exact ? kFinalizeChunks : 256, exact, scratch, s);
   hipLaunchKernelGGL((col_finalize_k<T, 0>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      q.part, q.chunks, M, C, gamma, beta, stats, (float*)nullptr, (float*)nullptr, (float*)nullptr);
 }
@@ -932,7 +940,7 @@ static void bn_apply_t(const T* x, const T* res, bool relu, T* y, int64_t M, int
 
 template <typename T>
 static void bn_forward_t(const T* x, const T* res, bool relu, T* y, const T* gamma, const T* beta, int64_t M, int C, float* stats,
-                         float* partials, int pre_chunks, uint8_t* mask, float* running, hipStream_t s) {
+                         float* partials, int pre_chunks, bool exact, uint8_t* mask, float* running, hipStream_t s) {
   constexpr int V = sizeof(T) == 2 ? 8 : 4;
   const bool vec = pick_vec<T>(C, x, res, y, partials) > 1;
   const double bytes = (double)M * C * (sizeof(T) * (2 + (res ? 1 : 0)) + (relu && mask ? 0.125 : 0.0));
@@ -942,7 +950,7 @@ static void bn_forward_t(const T* x, const T* res, bool relu, T* y, const T* gam
   if (!own_sums || pre_chunks == 0) {
     ProfScope pr(CD_K_NORM, s, 0, pre_chunks ? 0.0 : (double)M * C * sizeof(T));
     if (own_sums) chunks = launch_reduce<T, V, 0>(x, nullptr, nullptr, nullptr, false, M, C, partials, s).chunks;
-    else bn_stats_t<T>(x, gamma, beta, M, C, stats, partials, pre_chunks, partials + (size_t)pre_chunks * stat_pitch(C), s);
+    else bn_stats_t<T>(x, gamma, beta, M, C, stats, partials, pre_chunks, exact, partials + (size_t)pre_chunks * stat_pitch(C), s);
   }
   {
     ProfScope pr(CD_K_BN_APPLY, s, 0, bytes);
@@ -976,7 +984,7 @@ static void bn_backward_t(const T* dy, const T* y, const T* x, const T* gamma, c
                        (int)acc_dres, mask);
     return;
   }
-  if (pre_chunks) q = fold_sums(q, C, kFinalizeChunks, partials + (size_t)pre_chunks * stat_pitch(C), s);
+  if (pre_chunks) q = fold_sums(q, C, kFinalizeChunks, false, partials + (size_t)pre_chunks * stat_pitch(C), s);
   hipLaunchKernelGGL((col_finalize_k<T, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      q.part, q.chunks, M, C,
                      gamma, (const T*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);
@@ -1078,21 +1086,21 @@ void bn_apply_running(int dtype, const void* x, const void* res, bool relu, void
 }
 
 void bn_forward(int dtype, const void* x, const void* res, bool relu, void* y, const void* gamma, const void* beta, int64_t M, int C,
-                float* stats, float* partials, int pre_chunks, uint8_t* relu_mask, float* running, hipStream_t s) {
+                float* stats, float* partials, int pre_chunks, bool exact, uint8_t* relu_mask, float* running, hipStream_t s) {
   if (dtype == CD_BF16)
     bn_forward_t<bf16_t>((const bf16_t*)x, (const bf16_t*)res, relu, (bf16_t*)y, (const bf16_t*)gamma, (const bf16_t*)beta, M, C, stats,
-                         partials, pre_chunks, relu_mask, running, s);
+                         partials, pre_chunks, exact, relu_mask, running, s);
   else
     bn_forward_t<float>((const float*)x, (const float*)res, relu, (float*)y, (const float*)gamma, (const float*)beta, M, C, stats,
-                        partials, pre_chunks, relu_mask, running, s);
+                        partials, pre_chunks, exact, relu_mask, running, s);
 }
 void bn_stats(int dtype, const void* x, const void* gamma, const void* beta, int64_t M, int C, float* stats,
-              float* partials, int pre_chunks, float* scratch, hipStream_t s) {
+              float* partials, int pre_chunks, bool exact, float* scratch, hipStream_t s) {
   if (dtype == CD_BF16)
     bn_stats_t<bf16_t>((const bf16_t*)x, (const bf16_t*)gamma, (const bf16_t*)beta, M, C, stats, partials, pre_chunks,
-                       scratch, s);
+                       exact, scratch, s);
   else
-    bn_stats_t<float>((const float*)x, (const float*)gamma, (const float*)beta, M, C, stats, partials, pre_chunks, scratch, s);
+    bn_stats_t<float>((const float*)x, (const float*)gamma, (const float*)beta, M, C, stats, partials, pre_chunks, exact, scratch, s);
 }
 void bn_relu_pool(const bf16_t* x, const float* stats, bf16_t* y, uint8_t* argmax, uint8_t* relu_mask, int64_t B, int H,
                   int W, int C, hipStream_t s) {

@@ -209,3 +209,30 @@ def test_statistics_from_the_convolution(dtype, tol, width, batch, hw, odd):
         assert bad.any()
         assert not (np.isfinite(y).all((0, 1, 2)) & (y.std((0, 1, 2)) > 0))[bad].any()
         assert bad.all() or rel(y[..., ~bad], want[..., ~bad]) <= tol
+
+
+@pytest.mark.parametrize("dtype,width,batch", [("f32", 16, 32), ("f32", 16, 33), ("f32", 20, 66), ("f32", 16, 105), ("f32", 20, 131), ("bf16", 20, 33), ("bf16", 36, 151)])
+def test_statistics_of_many_partial_sums_are_added_in_fp64(dtype, width, batch):
+    """Channels that copy an image of integers 250 - 3 .. 250 + 3: every sum over the rows of a block is exact in fp32 (128 x 253^2 < 2^24), those
+    over the tensor are not, and the variance is a 15000th of the mean square.  fp64 totals give it to the rounding of 1 / sqrt(var + eps) and of
+    the update, an fp32 total of 2^31 is off by up to 2^-25, 1e-3 of the variance.  512 partial sums (added up by the elementwise pass), more
+    (by the finalize), more than that takes (by a reduction pass) and more than 8 MB of them (folded in fp64 first)."""
+    c = _Net(dtype, batch, 32, 32, kind=1, widths=[width], blocks=[1], stem_width=width)
+    conv, bn = c.ops[0], c.ops[1]
+    assert conv["kind"] == "conv" and bn["kind"] == "bn"
+    gen = torch.Generator().manual_seed(5)
+    c.x = (250 + torch.randint(-3, 4, (batch, 32, 32, 3), generator=gen)).to("cuda:0", c.m.torch_dtype)
+    w = c.flat.copy()
+    filt = c.param(w, conv["param_w"])
+    filt[:] = 0
+    for k in range(width):
+        filt[k, 1, 1, k % 3] = 1
+    running = torch.zeros(c.m.bn_running_elements(), device="cuda:0")
+    c.B.codistill_forward(c.m, to_device(w, c.m.torch_dtype), c.x, c.ws, torch.empty(batch, 10, device="cuda:0"), True, c.B.CD_BN_BATCH_STATS, running)
+    got = running[:2 * width].double().cpu().numpy().reshape(2, width)
+    x = c.x.double().reshape(-1, 3)
+    mean, var = (v.cpu().numpy()[np.arange(width) % 3] for v in (x.mean(0), x.var(0, unbiased=False)))
+    M = batch * 1024
+    # mean and 0.1 mean; 1 / sqrt rounded (twice in its square), the square, its inverse, minus eps, times two factors rounded themselves
+    assert np.abs(got[0] / (0.1 * mean) - 1).max() <= 3 * 2.0 ** -24
+    assert np.abs(got[1] / (0.1 * var * M / (M - 1)) - 1).max() <= 10 * 2.0 ** -24

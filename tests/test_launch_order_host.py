@@ -152,6 +152,21 @@ def test_weight_gradients_of_a_small_network_at_the_end_of_the_pass(backward, ba
     assert sum("wgrad_kernel" in n for n in names) <= sum("wgrad_kernel" in k for k in _kernels(two))
 
 
+@pytest.mark.parametrize("batch,finalizes,reductions,folds", [(32, 0, 0, 0), (33, 3, 0, 0), (64, 1, 0, 0), (65, 6, 0, 0), (128, 5, 1, 0), (129, 6, 0, 1),
+                                                              (201, 6, 0, 3), (400, 6, 0, 3)])
+def test_launches_behind_the_column_sums_of_a_generic_convolution(backward, batch, finalizes, reductions, folds):
+    """A two-block fp32 network: the BatchNorm adds up what its convolution left by itself, or behind a finalize, or behind an fp64 fold and a finalize:
+    no more launches in front of any of its six elementwise passes than a reduction is (one where the tensor has at most 8 MB, else two)."""
+    model = dict(kind=B.CD_ARCH_RESNET_BASIC, dtype="f32", batch=batch, arch=dict(in_h=32, in_w=32, widths=[16, 32], blocks=[1, 1], stem_width=16))
+    r = backward(model, call="forward")
+    assert r["rc"] == 0
+    names = _kernels(r)
+    count = lambda part: sum(part in k for k in names)   # noqa: E731
+    assert count("conv_generic_k") == 6 and count("col_fold_kILb0EE") == 0
+    assert (count("col_finalize_k"), count("col_reduce_k"), count("col_fold_kILb1EE")) == (finalizes, reductions, folds)
+    assert len(names) == 14 + finalizes + reductions + folds <= (20 if batch <= 128 else 26)
+
+
 def test_streams_argument_is_checked():
     m = B.Model(B.arch_preset(B.CD_ARCH_TINY_CNN), B.CD_F32)
     at = [k << 32 for k in range(1, 7)]
