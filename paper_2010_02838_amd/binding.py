@@ -237,10 +237,10 @@ def codistill_loss_grad_static(z_local, z_peers, targets, loss_out, dz_out, alph
                                           ctypes.byref(cfg), _ptr(loss_out), _ptr(dz_out), _stream()))
 
 
-def codistill_backward(model, params, x, workspace, dlogits, grads_out):
+def codistill_backward(model, params, x, workspace, dlogits, grads_out, streams=CD_STREAMS_AUTO):
     _check(lib.codistill_backward_streams(model._h, _ptr(params), _ptr(x), x.shape[0], _ptr(workspace),
                                           workspace.numel() * workspace.element_size(), _ptr(dlogits), _ptr(grads_out),
-                                          CD_STREAMS_AUTO, _stream()))
+                                          streams, _stream()))
 
 
 def codistill_sgd_step(master_w, momentum_v, grad, lowp_w_out, lr, momentum, weight_decay=0.0, nesterov=False):

@@ -18,6 +18,7 @@ fp32 models are held to tight end-to-end tolerances.  For bf16 models two things
     common part, so storage rounding is amplified layer after layer; that deviation is a
     property of the workload, not of a kernel, and the first check is what pins the kernels.
 """
+import functools
 import json
 import os
 
@@ -666,15 +667,33 @@ def test_evaluation_mode_channel_counts(kind, width, batch, res, dtype_name):
 
 
 # ------------------------------------------------------------------- environment switches
-def test_serial_switch_is_bit_identical(monkeypatch):
+def _backward_on(monkeypatch, streams):
+    """Every backward pass of the binding, the step runner's too, with this choice of streams."""
+    from paper_2010_02838_amd import binding as B
+    monkeypatch.setattr(B, "codistill_backward", functools.partial(B.codistill_backward, streams=getattr(B, streams)))
+
+
+@pytest.mark.parametrize("streams", ["CD_STREAMS_AUTO", "CD_STREAMS_TWO"])
+def test_serial_switch_is_bit_identical(monkeypatch, streams):
     """CODISTILL_SERIAL=1 keeps the weight gradients on the caller's stream: same kernels, same fixed-order
-    reductions, so every result of the step is bit for bit that of the two-stream form."""
+    reductions, so every result of the step is bit for bit that of the two-stream form.  (A network as small as this one stays on the
+    caller's stream with CD_STREAMS_AUTO and forks with CD_STREAMS_TWO: test_launch_order_host.py.)"""
+    _backward_on(monkeypatch, streams)
     kw, mk, batch, res, classes = SMALL["bottleneck_mfma"]
     a = Case(kw, mk(), "bf16", batch, res, classes).gpu()
     monkeypatch.setenv("CODISTILL_SERIAL", "1")
     b = Case(kw, mk(), "bf16", batch, res, classes).gpu()
     for k in ("logits", "loss", "grad", "theta"):
         np.testing.assert_array_equal(a[k], b[k])
+
+
+@pytest.mark.parametrize("name", ["basic_mfma", "bottleneck_mfma", "resnext"])
+def test_two_streams_layers(monkeypatch, name):
+    """The per-layer oracle check with the weight gradients on the second stream, where these small networks have them on the caller's."""
+    _backward_on(monkeypatch, "CD_STREAMS_TWO")
+    kw, mk, batch, res, classes = SMALL[name]
+    c = Case(kw, mk(), "bf16", batch, res, classes)
+    check_layers(c, c.gpu())
 
 
 def test_separate_bn_reduction_switch_agrees(monkeypatch):

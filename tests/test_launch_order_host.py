@@ -167,6 +167,14 @@ def test_launches_behind_the_column_sums_of_a_generic_convolution(backward, batc
     assert len(names) == 14 + finalizes + reductions + folds <= (20 if batch <= 128 else 26)
 
 
+def test_small_networks_fork_with_two_streams_only(backward):
+    """The network whose two-stream pass test_gpu_step.py compares bit for bit with the one-stream pass: the first forks, AUTO does not."""
+    model = dict(kind=B.CD_ARCH_RESNET_BOTTLENECK, dtype="bf16", batch=5, arch=dict(in_h=72, in_w=72, classes=10, widths=[8, 16, 24, 32], blocks=[2, 1, 1, 1], stem_width=16))
+    two, auto, serial = backward(model), backward(model, call="backward_auto"), backward(model, CODISTILL_SERIAL="1")
+    assert _forks(two) >= 4 and _forks(auto) == _forks(serial) == 0
+    assert _kernels(two) == _kernels(serial)
+
+
 def test_streams_argument_is_checked():
     m = B.Model(B.arch_preset(B.CD_ARCH_TINY_CNN), B.CD_F32)
     at = [k << 32 for k in range(1, 7)]
