@@ -167,6 +167,15 @@ def test_launches_behind_the_column_sums_of_a_generic_convolution(backward, batc
     assert len(names) == 14 + finalizes + reductions + folds <= (20 if batch <= 128 else 26)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width,batch,h,w", [(12, 69, 31, 31), (36, 5, 17, 17), (5, 3, 13, 13), (12, 69, 1, 961), (36, 5, 1, 289), (5, 3, 1, 169)])
+def test_generic_convolutions_leave_column_sums(backward, dtype, width, batch, h, w):
+    """No reduction pass in front of the BatchNorms whose statistics test_gpu_generic_conv.py compares."""
+    r = backward(dict(kind=B.CD_ARCH_RESNET_BASIC, dtype=dtype, batch=batch, arch=dict(in_h=h, in_w=w, widths=[width], blocks=[1], stem_width=width)), call="forward")
+    assert r["rc"] == 0
+    assert sum("conv_generic_k" in k for k in _kernels(r)) == 3 and not any("col_reduce_k" in k for k in _kernels(r))
+
+
 def test_small_networks_fork_with_two_streams_only(backward):
     """The network whose two-stream pass test_gpu_step.py compares bit for bit with the one-stream pass: the first forks, AUTO does not."""
     model = dict(kind=B.CD_ARCH_RESNET_BOTTLENECK, dtype="bf16", batch=5, arch=dict(in_h=72, in_w=72, classes=10, widths=[8, 16, 24, 32], blocks=[2, 1, 1, 1], stem_width=16))
