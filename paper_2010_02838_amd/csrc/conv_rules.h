@@ -197,15 +197,16 @@ inline bool wgrad_short(const WgradShape& h) {
   wgrad_plan(&h, 1, ~(size_t)0 >> 1, 0, &r);
   return r.m_per_split <= 16 * 32;
 }
-// Whether a pass's waiting layers are so little work altogether (their tiles' steps: 128 in each of 512 workgroups, some 30 us) that they go at
-// its end, on the caller's stream.  Beside the rest of a small pass they take the compute units that its short launches wait for, and an
+// Whether a pass's layers, those that go by themselves included, are so little work altogether (their tiles' steps: 128 in each of 512
+// workgroups, some 30 us) that none of them forks: those that wait go at its end, all of them on the caller's stream.  Beside the rest of a small pass they take the compute units that its short launches wait for, and an
 // event and a wait are 15 us of the host's time and a gap on the device.  us a pass, with forks and without, by work (512 tile steps): two basic
 // blocks of 16 and 32 channels on 80 images of 28x35 (26) 307 and 286, two bottleneck blocks on 30 images of 112x113 (25) 618 and 608, ResNeXt's
 // on 19 of 160x161 (42) 905 and 882 and on 45 of 160x160 (96) 1448 and 1422, two Wide-ResNet blocks on 28 images (90) 782 and 744,
 // bottleneck blocks on 70 of 96x96 (115) 1036 and 1020; above the line ResNet-20's step at batch 128 (146) 873 and 926, bottleneck blocks on 34
 // images of 192x192 (205) 1564 and 1612.  Layers of at most 64 output channels count 1.4: the other launches of their pass leave part of the chip
 // idle; basic blocks of 16 and 32 channels on 226 images of 32x32 (98, almost all narrow) 525 and 554, of 64 and 128 on 36 images of 224x225 (96, of
-// which 70) 778 and 744.  (Behind one fork, when all or half of them have come: slower than either.)
+// which 70) 778 and 744.  Where only the waiting layers counted, large batches came back below the line with forks and a late launch: bottleneck blocks
+// on 50 images of 192x192 1254, now 1206, ResNeXt's on 90 of 160x160 2341 and 2315, basic ones on 800 of 32x32 795 and 778.  (Behind one fork, when all or half of them have come: slower than either.)
 inline bool wgrad_together(int64_t work, int64_t narrow) { return work + narrow * 2 / 5 < (int64_t)kWgradBlocks * 128; }
 // Whether the layers collected so far are a launch: tiles enough without a split, or enough work for every compute unit to be busy
 // some 20 us (96 steps in each of 512 workgroups), or as much as the pass still has to collect and worth a launch, or all of them:

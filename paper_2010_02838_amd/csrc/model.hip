@@ -1112,16 +1112,19 @@ static int backward_run(const cd_model* m, const void* params, const void* x, in
   PendingWgrads pending[8];
   auto operand_bytes = [](const ConvGeom& g) { return 2 * (g.B * g.H * g.W * (int64_t)g.Cin + g.M() * (int64_t)g.Cout); };
   auto waits = [&](const ConvGeom& g, const WgradShape& h) { return g.Cin != 3 && (!wgrad_alone(h, operand_bytes(g)) || wgrad_short(h)); };   // (not a packed stem)
+  int64_t all = 0, narrow = 0;
   for (size_t i = (size_t)m->first_trainable_op; i < m->ops.size(); i++) {
     if (m->ops[i].kind != OP_CONV || grouped_sliced(m, m->ops[i], batch) || m->ops[i].groups > 1) continue;
     const ConvGeom g = conv_geom(m, m->ops[i], batch), gp = packed_geom(g);
+    if (!use_mfma(m, g)) continue;
     const WgradShape h = conv_wgrad_shape(gp, 1, m->ops[i].pb >= 0);
-    if (use_mfma(m, g) && waits(g, h)) pending[h.tile_class()].work_left += h.tiles() * h.steps();
+    const int64_t work = h.tiles() * h.steps();
+    if (waits(g, h)) pending[h.tile_class()].work_left += work;
+    else if (m->ops[i].x == 0) continue;   // (the network's first layer by itself: on the caller's stream at the end of the pass either way)
+    all += work;
+    if (h.bn() == 64) narrow += work;
   }
-  int64_t waiting = 0, narrow = 0;
-  for (const PendingWgrads& q : pending) waiting += q.work_left;
-  for (int k = 0; k < 4; k++) narrow += pending[k].work_left;   // (WgradShape::tile_class: 64 rows of dw to a tile)
-  const bool together = streams == CD_STREAMS_AUTO && wgrad_together(waiting, narrow);
+  const bool together = streams == CD_STREAMS_AUTO && wgrad_together(all, narrow);
   // Launches them, on the second stream behind what the caller's stream holds so far; where the runtime refuses the event or the wait,
   // and at the end of the pass (`last`: nothing is left that they could run beside), on the caller's stream (whose partials area is free
   // between two ops).  Returns the stream.
@@ -1384,7 +1387,7 @@ static int backward_run(const cd_model* m, const void* params, const void* x, in
           if (wait) q.work_left -= h.tiles() * h.steps();
           if (!wait || (together ? (int)q.p.size() >= kWgradJobs : wgrad_batch_full(q.tiles, q.work, (int)q.p.size(), q.work_left))) {
             // (the network's first layer, which has no data gradient, is the last of the pass)
-            const hipStream_t ws = run_wgrads(q, o.x == 0 || (wait && together));   // (a 3-channel image's layer never waits: its dw is unpacked behind it)
+            const hipStream_t ws = run_wgrads(q, o.x == 0 || together);   // (a 3-channel image's layer never waits: its dw is unpacked behind it)
             if (s2d_form(g)) s2d_unpack_dw(w.dw, G(o.pw), g.Cout, g.kh, gp.kh, 2 * gp.pad - g.pad, ws);
             else if (g.Cin == 3) unpad_c8_to_c3(w.dw, G(o.pw), (int64_t)g.Cout * g.kh * g.kw, ws);
           }

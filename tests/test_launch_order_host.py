@@ -176,6 +176,25 @@ def test_generic_convolutions_leave_column_sums(backward, dtype, width, batch, h
     assert sum("conv_generic_k" in k for k in _kernels(r)) == 3 and not any("col_reduce_k" in k for k in _kernels(r))
 
 
+@pytest.mark.parametrize("arch", [dict(kind=B.CD_ARCH_RESNET_BASIC, arch=dict(in_h=32, in_w=32, widths=[16, 32], blocks=[1, 1], stem_width=16)),
+                                  dict(kind=B.CD_ARCH_RESNET_BOTTLENECK, arch=dict(in_h=96, in_w=96, widths=[64, 128], blocks=[1, 1])),
+                                  dict(kind=B.CD_ARCH_RESNET_BOTTLENECK, arch=dict(in_h=64, in_w=64, widths=[16], blocks=[1]))])
+def test_a_growing_batch_leaves_the_callers_stream_once(backward, arch):
+    """Layers go by themselves once a batch is large, and their work counts like that of the waiting ones: from some batch on the pass forks as
+    CD_STREAMS_TWO does, and below it has no event and no wait at all, layers by themselves included (the third network has one at its smallest sizes)."""
+    forked = []
+    for batch in (4, 32, 70, 120, 160, 226, 400, 512, 800, 1024, 2048):
+        model = dict(arch, dtype="bf16", batch=batch)
+        auto, two = backward(model, call="backward_auto"), backward(model)
+        assert auto["rc"] == two["rc"] == 0
+        forked.append(_forks(auto) >= 1)
+        if forked[-1]:
+            assert auto["log"] == two["log"]
+        else:
+            assert not any(what in ("record", "wait") for what, _, _, _ in auto["log"])
+    assert forked == sorted(forked) and forked[-1] and not forked[0]
+
+
 def test_small_networks_fork_with_two_streams_only(backward):
     """The network whose two-stream pass test_gpu_step.py compares bit for bit with the one-stream pass: the first forks, AUTO does not."""
     model = dict(kind=B.CD_ARCH_RESNET_BOTTLENECK, dtype="bf16", batch=5, arch=dict(in_h=72, in_w=72, classes=10, widths=[8, 16, 24, 32], blocks=[2, 1, 1, 1], stem_width=16))
