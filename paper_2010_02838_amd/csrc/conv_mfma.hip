@@ -420,6 +420,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
   // a second fragment buffer, they read a sub-step's fragments and use them.)
   constexpr bool AHEAD = !(STATS == 2 && TN * TM >= 8 && !BS_LATE);
   constexpr int KK = BKT / 16 / WK, TT = TN * TM, FB = AHEAD ? 2 : 1;   // (sub-steps of this wave's group)
+  static_assert(KK >= 2 && KK % 2 == 0, "a step ends on the fragment buffer that the next one begins with, and has a sub-step in front of its loads");
   bf16x8_t wf[FB][TN], xf[FB][TM];  // [buffer][tile]
   // byte offset of this lane's fragment of sub-step kk inside a tile row block (swz depends on the lane's row only: tile
   // rows are multiples of 32 apart)
@@ -459,15 +460,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
         acc[i / TM][i % TM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & (FB - 1)][i / TM], xf[kk & (FB - 1)][i % TM],
                                                                       acc[i / TM][i % TM], 0, 0, 0);
         // in the MFMA's shadow: a share of the next offsets, in the last sub-step of the loads
-        if (KK == 1) {   // one sub-step a step: an offset in front of its load
-#pragma unroll
-          for (int v = 0; v < AV + BV; v++)
-            if (v * TT / (AV + BV) == i) {
-              prep_piece(kt + NS, v);
-              issue(cur, v);
-            }
-          if (i == TT - 1) prep_piece(kt + NS, NPIECE - 1);
-        } else if (kk < KK - 1) {
+        if (kk < KK - 1) {
           constexpr int SLOTS = (KK - 1) * TT;
           const int slot = kk * TT + i;
 #pragma unroll
