@@ -330,8 +330,10 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
   // now and arrives during the main loop (vector memory operations retire in order: the main loop's first wait also waits for
   // these, and the compiler's own waits for them can only be too strict); its ReLU bits, a byte per vector, follow behind the
   // loop: sixteen registers through the loop would spill (128x256) or cost the third workgroup per compute unit (128x128).
-  // (The input's vectors leave the two 128-accumulator tiles short of 6 (256x128) and 2 (128x256) registers: those are stored to
-  // scratch memory in front of the loop and loaded behind it.)
+  // (The input's vectors leave the two 128-accumulator tiles of four waves short of 2 registers each: those are stored to scratch memory in
+  // front of the loop and loaded behind it.  It takes a request to a call and the row's check for ragged vectors alone, below: with a loop
+  // inside the request and the check everywhere they were 13 (256x128) and 9 (128x256), 248 and 239 us a launch of a ResNet-50 step at batch 256
+  // where they are 238 and 226 now.)
   constexpr int BS_LPR = WN / 8, BS_RPP = 64 / BS_LPR, BS_EROWS = EM < 64 ? EM : 64;
   // (256x256 tiles, whose vectors are 64 registers, request them pass by pass in the epilogue)
   constexpr bool BS_LATE = BM == 256 && BN == 256;
@@ -339,30 +341,28 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
   uint4 bs_x[BS_NV];
   uint32_t bs_bits[BS_NV];
   auto bs_index = [&](int v, bool& ok) {   // element index of vector v in an [M][N] tensor
-    const int pass = v / BS_PP, row = v % BS_PP * BS_RPP + lane / BS_LPR;
-    const int m = m0 + em0 + pass * BS_EROWS + row, n = n0 + wn0 + (lane % BS_LPR) * 8;
-    ok = m < M && n < a.N && row < BS_EROWS && lane < BS_RPP * BS_LPR;
+    const int pass = v / BS_PP, pp = v % BS_PP;
+    const int m = m0 + em0 + pass * BS_EROWS + pp * BS_RPP + lane / BS_LPR, n = n0 + wn0 + (lane % BS_LPR) * 8;
+    ok = m < M && n < a.N;
+    if constexpr (64 % BS_LPR != 0) ok = ok && pp * BS_RPP + lane / BS_LPR < BS_EROWS && lane < BS_RPP * BS_LPR;
     return (unsigned)m * (unsigned)a.N + (unsigned)n;
   };
-  auto bs_request_x = [&](int pass) {
-#pragma unroll
-    for (int v = 0; v < BS_NV; v++) {
-      bool ok;
-      const unsigned idx = bs_index(pass * BS_PP + v, ok);
-      bs_x[v] = make_uint4(0, 0, 0, 0);
-      if (ok) bs_x[v] = *reinterpret_cast<const uint4*>(a.bn_x + idx);
-    }
+  auto bs_request_x = [&](int v, int at) {   // vector `at` into place v
+    bool ok;
+    const unsigned idx = bs_index(at, ok);
+    bs_x[v] = make_uint4(0, 0, 0, 0);
+    if (ok) bs_x[v] = *reinterpret_cast<const uint4*>(a.bn_x + idx);
   };
-  auto bs_request_bits = [&](int pass) {
-#pragma unroll
-    for (int v = 0; v < BS_NV; v++) {
-      bool ok;
-      const unsigned idx = bs_index(pass * BS_PP + v, ok);
-      bs_bits[v] = 0u;
-      if (ok) bs_bits[v] = a.bn_mask ? a.bn_mask[idx >> 3] : 0xffu;
-    }
+  auto bs_request_bits = [&](int v, int at) {
+    bool ok;
+    const unsigned idx = bs_index(at, ok);
+    bs_bits[v] = 0u;
+    if (ok) bs_bits[v] = a.bn_mask ? a.bn_mask[idx >> 3] : 0xffu;
   };
-  if (STATS == 2 && !BS_LATE) bs_request_x(0);
+  if (STATS == 2 && !BS_LATE) {
+#pragma unroll
+    for (int v = 0; v < BS_NV; v++) bs_request_x(v, v);
+  }
   // EPI: the bias of this lane's channels, requested here so that its latency passes under the main loop (read behind it, element
   // by element, it cost 3 us a tile: 8192 x 2048 x 512 26 us, now 23).  Register v of tile i belongs to channel
   // n0 + wn0 + 32 i + 8 (v / 4) + 4 (lane / 32) + v % 4: four consecutive channels at a time, on 8-byte boundaries.
@@ -477,7 +477,10 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
     cur = nxt;
     nxt = nxt + STAGE * 2u == NS * STAGE * 2u ? 0 : nxt + STAGE * 2u;
   }
-  if (STATS == 2 && !BS_LATE) bs_request_bits(0);
+  if (STATS == 2 && !BS_LATE) {
+#pragma unroll
+    for (int v = 0; v < BS_NV; v++) bs_request_bits(v, v);
+  }
   wait_vmem<0>();  // the masked loads past the end still write (zeros) into the stages the epilogue reuses
 
   // accumulator layout: lane holds pixel column (lane % 32); register v holds channel
@@ -620,8 +623,10 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * WK, igemm_waves(BM, B
       }
     }
     if (STATS == 2 && BS_LATE) {
-      bs_request_x(g0 / TPG);
-      bs_request_bits(g0 / TPG);
+#pragma unroll
+      for (int v = 0; v < BS_NV; v++) bs_request_x(v, g0 / TPG * BS_PP + v);
+#pragma unroll
+      for (int v = 0; v < BS_NV; v++) bs_request_bits(v, g0 / TPG * BS_PP + v);
     }
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
