@@ -5,11 +5,28 @@ out, and calls the entry points in the order of the paper's Algorithm 1 / the
 checkpoint-exchange implementation of Section 3.  No arithmetic of the step
 lives here.
 """
+import threading
+
 import numpy as np
 import torch
 
 from . import binding as B
 from . import synth
+
+_streams = threading.local()
+
+
+def _peers_stream(device):
+    """The second stream beside this thread's current one, the same for all of its runners.  torch hands its streams out in turn and each gets
+    one of a few hardware queues; one that shares the caller's queue overlaps nothing (two of eleven runners of packed Transformer steps took 10.4 ms, the others 9.6),
+    and with a stream to a runner which of them that was depended on the runners before it."""
+    known = _streams.__dict__.setdefault("known", {})
+    key = (torch.device(device), torch.cuda.current_stream(device).cuda_stream)
+    if key not in known:
+        if len(known) >= 16:   # (torch keeps the streams themselves)
+            known.clear()
+        known[key] = torch.cuda.Stream(device=device)
+    return known[key]
 
 
 def pack_flat(model, dense):
@@ -45,13 +62,9 @@ class StepRunner:
         # priority) beside the local forward, so that one model's memory-bound kernels and partly
         # filled launches share the chip with the other's.
         self.overlap_peers = overlap_peers
-        # (A stream is taken from torch's pool and used once either way.  They are handed out in turn and get one of a few hardware queues at
-        # their first use; one that shares the caller's queue overlaps nothing, 9.4 -> 10.2 ms a Transformer step for one in nine, and which
-        # runner of a program that is should not depend on the sizes of the runners before it.)
-        side = torch.cuda.Stream(device=device) if overlap_peers else None
-        if side is not None:
-            side.wait_stream(torch.cuda.current_stream(device))
-        self.side = side if overlap_peers and self._overlap_pays() else None
+        self.overlap_pays = overlap_peers and self._overlap_pays()
+        if self.overlap_pays:
+            _peers_stream(device)   # (exists before a step is captured)
         n, C = model.n_elements, model.classes
         f32 = dict(dtype=torch.float32, device=device)
         self.master = torch.zeros(n, **f32)
@@ -75,7 +88,8 @@ class StepRunner:
         """Whether a peer's forward pass is worth a second stream.  The two waits that order it are 20 us of the host's time each; what
         they can hide is a pass.  Two-layer network, step with and without (us): fp32, 8 images 173 and 85, 50 images (10 MB of activations)
         172 and 121, 100 (21 MB) 180 and 186; bf16, 8 images 196 and 109, 100 (10 MB) 200 and 157, 200 (21 MB) 200 and 191, 800 of
-        40x40 549 and 590.  ResNet-20 with two streams 871, one after the other 1169."""
+        40x40 549 and 590.  ResNet-20 with two streams 871, one after the other 1169.  One peer at a time, not their sum: what several small ones
+        can hide behind is still one local pass (three peers, fp32, 75 images, 15 MB each, 231 and 217; bf16, 100 images 243 and 223)."""
         for pm in self.peers:
             ops, tensors = pm.graph(self.batch)
             moved = sum(self.batch * t["h"] * t["w"] * t["c"] for t in tensors) * pm.torch_dtype.itemsize
@@ -128,14 +142,14 @@ class StepRunner:
         """x: [B,H,W,3] device tensor in the model dtype (the Transformer: int32 [B, source + target tokens]);
         y: int32 device tensor, one target per row of logits.  adam = (beta1, beta2, eps) replaces the momentum-SGD
         update by Adam (momentum and nesterov are then unused)."""
-        if self.overlap_peers and self.side is not None and self.peers:
-            main = torch.cuda.current_stream()
-            self.side.wait_stream(main)           # x, the peer parameters and the last step's reads are in order
-            with torch.cuda.stream(self.side):
+        if self.overlap_peers and self.overlap_pays and self.peers:
+            main, side = torch.cuda.current_stream(), _peers_stream(self.dev)
+            side.wait_stream(main)                # x, the peer parameters and the last step's reads are in order
+            with torch.cuda.stream(side):
                 for pm, pp, pl in zip(self.peers, self.peer_params, self.peer_logits):
                     B.codistill_forward(pm, pp, x, self.ws_peer, pl, False)
             self.forward_local(x)
-            main.wait_stream(self.side)           # the loss needs every model's logits
+            main.wait_stream(side)                # the loss needs every model's logits
         else:
             self.forward_local(x)
             for pm, pp, pl in zip(self.peers, self.peer_params, self.peer_logits):

@@ -724,3 +724,43 @@ def test_plain_kernels_switch_bf16_layers(monkeypatch):
     got = c.gpu()
     check_layers(c, got)
     assert rel(got["logits"], ref["logits"].astype(np.float64)) <= STATED_TOL
+
+
+def test_runners_share_the_peers_stream():
+    """One second stream for the runners of a thread on one stream of the caller, none taken by a runner whose peers stay on the caller's; steps of two
+    runners in turn are bit for bit those of runners without it."""
+    import threading
+    import torch
+    from paper_2010_02838_amd import binding as B
+    from paper_2010_02838_amd import runner as R
+
+    def make(kind, overlap, **kw):
+        m = [B.Model(B.arch_preset(kind, in_h=16, in_w=16, **kw), B.CD_BF16) for _ in range(2)]
+        r = R.StepRunner(m[0], m[1:], 4, overlap_peers=overlap)
+        r.load(*[f(R.pack_flat(q, synth.he_init(q.param_table(), k, 0.1))) for f, q, k in ((lambda t: t, m[0], 1), (lambda t: [t], m[1], 2))])
+        return r
+
+    def steps(overlap):
+        runs = [make(B.CD_ARCH_RESNET_BASIC, overlap, widths=[w, 32], blocks=[1, 1], stem_width=w) for w in (16, 24)]
+        x, y = torch.randn(4, 16, 16, 3, generator=torch.Generator().manual_seed(1)).to("cuda:0", torch.bfloat16), torch.arange(4, device="cuda:0", dtype=torch.int32)
+        for _ in range(3):
+            for r in runs:
+                r.step(x, y, 1.0, 0.05, 0.9)
+        torch.cuda.synchronize()
+        return runs, [t.cpu() for r in runs for t in (r.master, r.logits, r.peer_logits[0])]
+
+    plain = steps(False)[1]
+    R._streams.__dict__.clear()
+    assert not make(B.CD_ARCH_TINY_CNN, True, widths=[16, 32]).overlap_pays and not R._streams.__dict__.get("known")
+    runs, out = steps(True)
+    assert all(r.overlap_pays for r in runs) and len(R._streams.known) == 1
+    for a, b in zip(plain, out):
+        assert torch.equal(a, b)
+    mine, other = R._peers_stream("cuda:0"), []
+    assert mine.cuda_stream != torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(torch.cuda.Stream()):
+        other.append(R._peers_stream("cuda:0"))
+    t = threading.Thread(target=lambda: other.append(R._peers_stream("cuda:0")))
+    t.start()
+    t.join()
+    assert len({s.cuda_stream for s in [mine] + other}) == 3 and R._peers_stream("cuda:0") is mine
