@@ -631,6 +631,7 @@ static int gen_wgrad_shape(bool v4, int tn, int tk) { return (v4 ? 4 : 0) + (tk 
 // job's outputs a block per 16 channels adds the bias sums.
 struct GenSum { const float* part; float* out; const double* bias_part; float* bias_out; uint32_t n; int splits, N; uint32_t first, bias_first; };
 struct GenSums { GenSum j[kGenWgradJobs]; int n; };
+static_assert(sizeof(GenSums) <= 4096, "the table travels in the kernel arguments");
 __host__ __device__ inline unsigned gen_sum_lanes(int splits) { return splits > 64 ? 16u : 4u; }
 __global__ void __launch_bounds__(256) gen_wgrad_sum_k(GenSums b) {
   __shared__ double bs[256];

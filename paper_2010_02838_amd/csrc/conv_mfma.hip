@@ -1008,6 +1008,7 @@ __global__ void __launch_bounds__(256) fill_zero16_k(uint4* p, int64_t n) {
 // ---- filter re-layouts of many data gradients in one launch ------------------------------------------------------
 constexpr int kLayoutJobs = 48;   // jobs per launch: the table travels in the kernel arguments
 struct LayoutBatch { WeightLayoutJob j[kLayoutJobs]; int n; int64_t total; };
+static_assert(sizeof(LayoutBatch) <= 4096, "the table travels in the kernel arguments");
 // A workgroup transposes one 64x64 tile (output x input channels) of one tap through LDS: 128-byte row segments are read and
 // written, where one thread per element read with a stride of the whole filter row (44 M filter elements of the Transformer:
 // 537 us, now 56; ResNet-50 256 -> 37).  Channel counts are multiples of 8 and every filter starts on a 16-byte boundary.
@@ -1330,6 +1331,7 @@ struct WgradJob {
   uint32_t first;     // workgroups of the jobs in front of this one
 };
 template <int NJ> struct WgradBatch { WgradJob j[NJ]; int n; };
+static_assert(sizeof(WgradBatch<kWgradJobs>) <= 4096, "the table travels in the kernel arguments");
 
 constexpr int WG_MS = 32;   // pixels per main-loop step
 
@@ -1616,6 +1618,7 @@ struct WgradSum { const float* part; float* out; const double* bias_part; float*
 constexpr int kBiasCols = 16;
 __host__ __device__ inline unsigned wgrad_sum_lanes(int splits) { return splits > 64 ? 16u : 4u; }
 template <int NJ> struct WgradSums { WgradSum j[NJ]; int n; };
+static_assert(sizeof(WgradSums<kWgradJobs>) <= 4096, "the table travels in the kernel arguments");
 template <int NJ>
 __global__ void __launch_bounds__(256) wgrad_sum_kernel(WgradSums<NJ> b) {
   __shared__ float4 sm[256];
