@@ -300,10 +300,12 @@ int codistill_backward(const cd_model* m, const void* params, const void* x, int
                        void* workspace, size_t workspace_bytes, const float* dlogits,
                        float* grads_out, void* stream);
 
-/* The same call; `streams` says where the weight gradients run.  CD_STREAMS_TWO: on the second stream, as codistill_backward runs
- * them.  CD_STREAMS_AUTO: there too, but at the end of the pass on the caller's stream where the network is so small that forking
- * costs more than it hides (their sums may then be cut into other splits; the last places of a gradient differ).  Any other
- * value -> CD_ERR_INVALID_ARG. */
+/* The same call; `streams` says where the weight gradients run.  CD_STREAMS_TWO: on the second stream.  CD_STREAMS_AUTO: there too, but
+ * on the caller's stream, most of them at the end of the pass, where all of them together are so little work that forking costs more than
+ * it hides (a small network on a small batch: up to a tenth of the pass).  Any other value -> CD_ERR_INVALID_ARG.
+ * codistill_backward is CD_STREAMS_TWO: the layers that share a launch at the end of a pass may be cut into other splits, so that the
+ * last places of a gradient differ, and a program built against codistill_backward keeps its bits.  New programs, and those that compare
+ * bits with the Python binding (which passes CD_STREAMS_AUTO), call this one. */
 enum { CD_STREAMS_TWO = 0, CD_STREAMS_AUTO = 1 };
 int codistill_backward_streams(const cd_model* m, const void* params, const void* x, int64_t batch,
                                void* workspace, size_t workspace_bytes, const float* dlogits,
@@ -388,10 +390,10 @@ enum {
   CD_K_CONV_DGRAD = 1, CD_K_CONV_WGRAD = 2,
   CD_K_NORM = 3,              /* normalisation launches other than CD_K_BN_APPLY */
   CD_K_GLUE = 4, CD_K_LINEAR = 5, CD_K_LOSS = 6, CD_K_SGD = 7,
-  CD_K_CONV_FPROP_NARROW = 8, /* every other fprop launch (other tile shapes, plain kernels) */
+  CD_K_CONV_FPROP_NARROW = 8, /* every other fprop launch (other tile shapes, 128x256 tiles of eight waves, plain kernels) */
   CD_K_BN_APPLY = 9,          /* BatchNorm forward: the elementwise normalise (+ residual, ReLU) kernel alone */
-  CD_K_CONV_FPROP_WIDE = 10,  /* bf16 MFMA fprop launches on 128x256 tiles (in training one kernel symbol,
-                                 in evaluation, without the column sums, another) */
+  CD_K_CONV_FPROP_WIDE = 10,  /* bf16 MFMA fprop launches on 128x256 tiles of four waves (in training one kernel
+                                 symbol, in evaluation, without the column sums, another) */
   CD_K_ATTN = 11,             /* attention forward and backward launches */
   CD_K_COUNT = 12
 };

@@ -149,7 +149,8 @@ bool conv_mfma_supported(const ConvGeom& g);
 // norm (nullable; without bias and stat_partials only): y is the normalised tensor instead.
 int conv_fprop_mfma(const bf16_t* x, const bf16_t* w, const bf16_t* bias, bool relu, bf16_t* y, const ConvGeom& g,
                     float* stat_partials, hipStream_t s, const EvalNorm* norm = nullptr);
-// which tiles conv_fprop_mfma runs this shape on, with a bias or with stat_partials (sums): 0 128x128, 1 128x256, 2 any other
+// which tiles conv_fprop_mfma runs this shape on, with a bias or with stat_partials (sums): 0 128x128, 1 128x256 of four waves, 2 any other
+// (a class of the timer is one kernel symbol in training: its roofline is that kernel's)
 int conv_fprop_tile_class(const ConvGeom& g, bool bias, bool sums);
 // dx[B*H*W][Cin] (+)= gather(dy)[.][taps*Cout] * wt[Cin][taps*Cout]^T.  w is the filter as stored; wt is
 // scratch of at least Cout*K + 32 elements that receives its re-laid-out copy (or copies, per parity
