@@ -67,7 +67,7 @@ void colsum(int dtype, const void* a, int64_t M, int C, float* out, float* parti
 // instead of two bytes, in both of its passes).
 // pre_chunks > 0: the column sums of x are already in partials ([pre_chunks][stat_pitch(C)], from the producing convolution, with
 // room for 32 * stat_pitch(C) floats behind them); pre_chunks == 0: x is reduced first (partials is scratch).  exact: the sums are added up
-// in fp64 however many they are (those of conv_fprop_generic; room for 64 rows behind them).
+// in fp64 however many they are (those of conv_fprop_generic; room for twice as many floats behind them).
 // running (nullable): the running averages, updated with momentum 0.1.
 void bn_forward(int dtype, const void* x, const void* res, bool relu, void* y, const void* gamma, const void* beta, int64_t M, int C,
                 float* stats, float* partials, int pre_chunks, bool exact, uint8_t* relu_mask, float* running, hipStream_t s);

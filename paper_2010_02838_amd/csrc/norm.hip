@@ -226,8 +226,8 @@ __global__ void __launch_bounds__(256) col_reduce_k(const T* __restrict__ a0, co
 // blocks (up to 1024 chunks): 10.0 -> 7.2 us with 16 lanes, 6.2 with 64; 64 channels to a block with as many
 // loads in flight: no faster than one load at a time.
 constexpr int kFinalizeCols = 16, kFinalizeLanes = 64, kFinalizeLoads = 8;   // (loads past the last chunk re-read a real one, count as zero)
-template <typename T, int FIN>
-__global__ void __launch_bounds__(kFinalizeCols * kFinalizeLanes) col_finalize_k(const float* __restrict__ partials, int chunks, int64_t M, int C,
+template <typename T, int FIN, typename Sum = float>   // Sum: of the partial sums
+__global__ void __launch_bounds__(kFinalizeCols * kFinalizeLanes) col_finalize_k(const Sum* __restrict__ partials, int chunks, int64_t M, int C,
                                                        const T* __restrict__ gamma, const T* __restrict__ beta,
                                                        float* __restrict__ stats, float* __restrict__ out0,
                                                        float* __restrict__ out1, float* __restrict__ coef) {
@@ -236,17 +236,17 @@ __global__ void __launch_bounds__(kFinalizeCols * kFinalizeLanes) col_finalize_k
   const int c = blockIdx.x * kFinalizeCols + cl;
   double a0 = 0.0, a1 = 0.0;
   if (c < C) {
-    const float* p = partials + c;
+    const Sum* p = partials + c;
     const int64_t pitch = stat_pitch(C);
     for (int j = lane; j < chunks; j += kFinalizeLanes * kFinalizeLoads) {
-      float v0[kFinalizeLoads], v1[kFinalizeLoads];
+      Sum v0[kFinalizeLoads], v1[kFinalizeLoads];
 #pragma unroll
       for (int u = 0; u < kFinalizeLoads; u++) {
         const bool in = j + kFinalizeLanes * u < chunks;
         const int64_t at = (in ? j + kFinalizeLanes * u : j) * pitch;
         v0[u] = p[at];
-        v1[u] = FIN != 2 ? p[at + C] : 0.f;
-        if (!in) { v0[u] = 0.f; v1[u] = 0.f; }
+        v1[u] = FIN != 2 ? p[at + C] : (Sum)0;
+        if (!in) { v0[u] = 0; v1[u] = 0; }
       }
 #pragma unroll
       for (int u = 0; u < kFinalizeLoads; u++) {
@@ -301,12 +301,10 @@ __global__ void __launch_bounds__(kFinalizeCols * kFinalizeLanes) col_finalize_k
 // registers; each thread has UNROLL independent vectors in flight.
 constexpr int kEltUnroll = 4;
 
-// Fold many chunks of partial sums into 32: block = 64 channels x 16 lanes, grid.y = 32 slices.  EXACT: added in fp64 and left as two fp32
-// parts, 32 chunks apart, which the finalize adds up like any other chunks.
-template <bool EXACT>
+// Fold many chunks of partial sums into 32, of type Sum: block = 64 channels x 16 lanes, grid.y = 32 slices.
+template <typename Sum>
 __global__ void __launch_bounds__(1024) col_fold_k(const float* __restrict__ partials, int chunks, int C,
-                                                   float* __restrict__ out) {
-  typedef std::conditional_t<EXACT, double, float> Sum;
+                                                   Sum* __restrict__ out) {
   __shared__ Sum sm[2][16][64];
   const int cl = threadIdx.x & 63, lane = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + cl;
@@ -327,14 +325,8 @@ __global__ void __launch_bounds__(1024) col_fold_k(const float* __restrict__ par
   Sum s0 = 0, s1 = 0;
 #pragma unroll
   for (int j = 0; j < 16; j++) { s0 += sm[0][j][cl]; s1 += sm[1][j][cl]; }
-  float* o = out + (int64_t)blockIdx.y * stat_pitch(C) + c;
-  o[0] = (float)s0;
-  o[C] = (float)s1;
-  if (EXACT) {   // (an infinite sum has no rest)
-    o += (int64_t)kFoldChunks * stat_pitch(C);
-    o[0] = isfinite(s0) ? (float)(s0 - (Sum)(float)s0) : 0.f;
-    o[C] = isfinite(s1) ? (float)(s1 - (Sum)(float)s1) : 0.f;
-  }
+  out[(int64_t)blockIdx.y * stat_pitch(C) + c] = s0;
+  out[(int64_t)blockIdx.y * stat_pitch(C) + C + c] = s1;
 }
 
 // mask (VEC 8 only, nullable): receives one byte per vector, bit k = (y[k] > 0), for the backward pass
@@ -893,13 +885,12 @@ static ReducePlan launch_reduce(const T* a0, const T* a1, const T* a2, const flo
 
 // Where the column sums of M rows lie, and in how many chunks: from the convolution in front (pre_chunks > 0, in partials), or reduced here.
 struct ColSums { const float* part; int chunks; };
-// Folds them in scratch where they are more than `most`: into kFoldChunks, exact: into twice as many (col_fold_k).
-static ColSums fold_sums(ColSums q, int C, int most, bool exact, float* scratch, hipStream_t s) {
+// Folds them into kFoldChunks in scratch where they are more than `most`.
+template <typename Sum = float>
+static ColSums fold_sums(ColSums q, int C, int most, float* scratch, hipStream_t s) {
   if (q.chunks <= most) return q;
-  const dim3 grid((unsigned)cdiv(C, 64), kFoldChunks);
-  if (exact) hipLaunchKernelGGL(col_fold_k<true>, grid, dim3(1024), 0, s, q.part, q.chunks, C, scratch);
-  else hipLaunchKernelGGL(col_fold_k<false>, grid, dim3(1024), 0, s, q.part, q.chunks, C, scratch);
-  return {scratch, exact ? 2 * kFoldChunks : kFoldChunks};
+  hipLaunchKernelGGL(col_fold_k<Sum>, dim3((unsigned)cdiv(C, 64), kFoldChunks), dim3(1024), 0, s, q.part, q.chunks, C, reinterpret_cast<Sum*>(scratch));
+  return {scratch, kFoldChunks};
 }
 
 // Batch statistics -> stats.  pre_chunks > 0: the column sums are already in partials (written by the
@@ -916,9 +907,14 @@ static void bn_stats_t(const T* x, const T* gamma, const T* beta, int64_t M, int
   else
     // (more than 256 of a bf16 matrix-core convolution's are folded first, here, although up to kFinalizeChunks the fold is the longer way in the
     // forward pass too: in another order the statistics differ in the last place and all roundings behind them move)
-    q = fold_sums(q, C, exact ? kFinalizeChunks : 256, exact, scratch, s);
-  hipLaunchKernelGGL((col_finalize_k<T, 0>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
-                     q.part, q.chunks, M, C, gamma, beta, stats, (float*)nullptr, (float*)nullptr, (float*)nullptr);
+    q = exact ? fold_sums<double>(q, C, kFinalizeChunks, scratch, s) : fold_sums(q, C, 256, scratch, s);
+  const dim3 grid((unsigned)cdiv(C, kFinalizeCols)), block(kFinalizeLanes * kFinalizeCols);
+  if (exact && q.part == scratch)
+    hipLaunchKernelGGL((col_finalize_k<T, 0, double>), grid, block, 0, s, reinterpret_cast<const double*>(q.part), q.chunks, M, C, gamma, beta, stats,
+                       (float*)nullptr, (float*)nullptr, (float*)nullptr);
+  else
+    hipLaunchKernelGGL((col_finalize_k<T, 0>), grid, block, 0, s, q.part, q.chunks, M, C, gamma, beta, stats, (float*)nullptr, (float*)nullptr,
+                       (float*)nullptr);
 }
 
 // y = relu?(scale * x + shift (+ res)) with the scale and shift that bn_stats_t left in stats
@@ -984,7 +980,7 @@ static void bn_backward_t(const T* dy, const T* y, const T* x, const T* gamma, c
                        (int)acc_dres, mask);
     return;
   }
-  if (pre_chunks) q = fold_sums(q, C, kFinalizeChunks, false, partials + (size_t)pre_chunks * stat_pitch(C), s);
+  if (pre_chunks) q = fold_sums(q, C, kFinalizeChunks, partials + (size_t)pre_chunks * stat_pitch(C), s);
   hipLaunchKernelGGL((col_finalize_k<T, 1>), dim3((unsigned)cdiv(C, kFinalizeCols)), dim3(kFinalizeLanes * kFinalizeCols), 0, s,
                      q.part, q.chunks, M, C,
                      gamma, (const T*)nullptr, const_cast<float*>(stats), dgamma, dbeta, coef);

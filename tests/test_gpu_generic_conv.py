@@ -212,9 +212,11 @@ def test_statistics_from_the_convolution(dtype, tol, width, batch, hw, odd):
         assert rel(y, np.maximum(want, 0)) <= tol
 
 
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** 51])
 @pytest.mark.parametrize("dtype,width,batch", [("f32", 16, 32), ("f32", 16, 33), ("f32", 20, 66), ("f32", 16, 105), ("f32", 20, 131), ("bf16", 20, 33), ("bf16", 36, 151)])
-def test_statistics_of_many_partial_sums_are_added_in_fp64(dtype, width, batch):
-    """Channels that copy an image of integers 250 - 3 .. 250 + 3: every sum over the rows of a block is exact in fp32 (128 x 253^2 < 2^24), those
+def test_statistics_of_many_partial_sums_are_added_in_fp64(dtype, width, batch, scale):
+    """Channels that copy an image of integers 250 - 3 .. 250 + 3 (times a power of two with which the squares of a block's rows have a finite
+    sum in fp32 and those of the tensor have not): every sum over the rows of a block is exact in fp32 (128 x 253^2 < 2^24), those
     over the tensor are not, and the variance is a 15000th of the mean square.  fp64 totals give it to the rounding of 1 / sqrt(var + eps) and of
     the update, an fp32 total of 2^31 is off by up to 2^-25, 1e-3 of the variance.  512 partial sums (added up by the elementwise pass), more
     (by the finalize), more than that takes (by a reduction pass) and more than 8 MB of them (folded in fp64 first)."""
@@ -222,7 +224,7 @@ def test_statistics_of_many_partial_sums_are_added_in_fp64(dtype, width, batch):
     conv, bn = c.ops[0], c.ops[1]
     assert conv["kind"] == "conv" and bn["kind"] == "bn"
     gen = torch.Generator().manual_seed(5)
-    c.x = (250 + torch.randint(-3, 4, (batch, 32, 32, 3), generator=gen)).to("cuda:0", c.m.torch_dtype)
+    c.x = (scale * (250 + torch.randint(-3, 4, (batch, 32, 32, 3), generator=gen))).to("cuda:0", c.m.torch_dtype)
     w = c.flat.copy()
     filt = c.param(w, conv["param_w"])
     filt[:] = 0

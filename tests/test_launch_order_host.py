@@ -162,8 +162,8 @@ def test_launches_behind_the_column_sums_of_a_generic_convolution(backward, batc
     assert r["rc"] == 0
     names = _kernels(r)
     count = lambda part: sum(part in k for k in names)   # noqa: E731
-    assert count("conv_generic_k") == 6 and count("col_fold_kILb0EE") == 0
-    assert (count("col_finalize_k"), count("col_reduce_k"), count("col_fold_kILb1EE")) == (finalizes, reductions, folds)
+    assert count("conv_generic_k") == 6 and count("col_fold_kIfE") == 0
+    assert (count("col_finalize_k"), count("col_reduce_k"), count("col_fold_kIdE")) == (finalizes, reductions, folds)
     assert len(names) == 14 + finalizes + reductions + folds <= (20 if batch <= 128 else 26)
 
 
